@@ -635,7 +635,8 @@ static hipError_t launch_gv_d(const GvArgs &a, dim3 grid, const GvPlan &d, bool 
 {
     constexpr int DM = gv_dmax(G, JT, MT, BITS);
     if (!bvec) {
-        if (d.ring) return launch_gv_t<BITS, JT, G, LG, MT, 2, true, false, QT>(a, grid, d.smem, st);
+        // (the plan's `ring` is about depths up to DM: with two slots, every third slab of a workgroup needs a refill)
+        if (d.per > 2) return launch_gv_t<BITS, JT, G, LG, MT, 2, true, false, QT>(a, grid, d.smem, st);
         return launch_gv_t<BITS, JT, G, LG, MT, 2, false, false, QT>(a, grid, d.smem, st);
     }
     if (d.ring) {

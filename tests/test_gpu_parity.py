@@ -168,6 +168,23 @@ def test_matmul_one_token_three_and_four_rank_tiles(gpu, bits, r, per):
     check_y(Y, want, "Y")
 
 
+@pytest.mark.parametrize("bits", [2, 3, 4])
+@pytest.mark.parametrize("M", [1, 2])
+@pytest.mark.parametrize("r,per", [(12, 3), (31, 4), (7, 8), (20, 9), (45, 6)])
+def test_matmul_one_token_ranks_not_a_multiple_of_eight(gpu, bits, M, r, per):
+    """Ranks whose rows of B are read entry by entry, with more slabs per workgroup than their two ring slots: every slab
+    beyond the second comes through a refilled slot, also where a deeper ring would have held them all."""
+    import paper_2601_22716_amd as L
+    if M == 2 and r > 32:
+        pytest.skip("two tokens take this kernel up to rank 32")
+    N = 4096 * per - 5
+    say(f"matmul one-token odd ranks: r={r} bits={bits} M={M} {per} slabs per workgroup N={N}")
+    cs = li.make_case("tiny", M=M, N=N, K=256, bits=bits, r=r, factor_dtype="bf16", seed=90 + per + r)
+    Y = gpu.DeviceCase(cs).matmul(path=L.LORDS_PATH_GEMV)
+    want = onp.matmul(cs.X_f32, cs.codes, cs.codebook, cs.B_f32, cs.A_f32, bits)
+    check_y(Y, want, "Y")
+
+
 @pytest.mark.parametrize("M", [1, 17, 40, 130, 300])
 def test_matmul_parity_ragged_tokens(gpu, M):
     import paper_2601_22716_amd as L
