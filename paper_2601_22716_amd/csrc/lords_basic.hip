@@ -5,7 +5,7 @@
 //
 // Both are streaming kernels bound by their output writes; the fused
 // lords_matmul kernels never call them.
-#include "lords_device.h"
+#include "lords_scale_f32.h"
 #include "lords_launch.h"
 
 namespace lords {
@@ -30,7 +30,73 @@ __global__ __launch_bounds__(256) void unpack_kernel(const uint8_t *__restrict__
     o[1] = u32x4{out[4], out[5], out[6], out[7]};
 }
 
-// One thread per group of 32 codes of one row.  The scale is summed over j in
+// Dequantisation, ranks up to 128: a wave takes 16 rows x 128 columns at a time, the scale comes off the matrix cores
+// (lords_scale_f32.h) and the level from an LDS table with one copy per lane.  Bound by the writes at ranks up to 32, by the
+// matrix instructions above.  The weights leave as whole 128-byte lines and past the caches (nobody here reads them again, and
+// 235 MB of them push everything else out of the last-level cache and stay dirty in it).
+// 14336 x 4096 at 4 bits, fp32 W: rank 32 276 -> 51 us (5.2 TB/s; 85 with half lines, 74 with ordinary stores of whole lines),
+// rank 64 474 -> 80, rank 128 878 -> 158, fp32 factors of rank 128 3329 -> 170 (the kernel below: one thread per 32 columns, a
+// fused multiply-add per rank entry and weight, stores 128 bytes apart); 500 x 512, rank 128: 56 -> 11.
+template <int BITS, int SG, bool F32FACT, bool F32OUT>
+__global__ __launch_bounds__(kSfThreads) void dequant_tile_kernel(const uint8_t *__restrict__ codes, const float *__restrict__ codebook,
+                                                                  const void *__restrict__ Bv, const void *__restrict__ Av,
+                                                                  void *__restrict__ Wv, int N, int K, int r, int per)
+{
+    constexpr int NL = 1 << BITS;
+    __shared__ __align__(16) float panel[SG * kSfCols * 16];
+    __shared__ float lut[NL * 64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, c = lane & 15, g = lane >> 4;
+    const int k0 = blockIdx.x * kSfCols, ngroups = K >> 5;
+    for (int i = tid; i < NL * 64; i += kSfThreads) lut[i] = codebook[i >> 6];
+    sf_stage_panel<SG, F32FACT>(panel, Av, r, K, k0, tid, kSfThreads);
+    __syncthreads();
+    const int nslabs = (N + 15) >> 4, s_end = min(nslabs, ((int)blockIdx.y + 1) * per);
+    for (int sl = blockIdx.y * per + wave; sl < s_end; sl += kSfWaves) {
+        const int n = min(sl * 16 + c, N - 1);
+        uint32_t gw[BITS], w[4];
+        load_group<BITS>(codes + ((size_t)n * ngroups + min((k0 >> 5) + g, ngroups - 1)) * (4 * BITS), gw);
+        float Bop[4 * SG];
+        sf_load_rows<SG, F32FACT>(Bop, Bv, n, r, g);
+        sf_unpack<BITS>(gw, w);
+        sf_transpose(w);
+        const int row0 = sl * 16 + (c & 7), row1 = row0 + 8;       // the rows this lane stores to (see sf_rows_to_lines)
+        u32x4 held = u32x4{0u, 0u, 0u, 0u};                        // bf16: the even sub-tile's piece
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if (k0 + 32 * q >= K) break;
+            float S[8], o[8];
+            sf_scales<SG>(panel, Bop, q, c, g, S);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) o[e] = lut[((w[q] >> (BITS * e)) & (NL - 1)) * 64 + lane] * S[e];
+            if (F32OUT) {
+                u32x4 p0, p1;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) { p0[e] = __builtin_bit_cast(uint32_t, o[e]); p1[e] = __builtin_bit_cast(uint32_t, o[4 + e]); }
+                sf_rows_to_lines(p0, p1);
+                float *dst = reinterpret_cast<float *>(Wv) + k0 + 32 * q + 8 * g + 4 * (c >> 3);
+                if (row0 < N) __builtin_nontemporal_store(p0, reinterpret_cast<u32x4 *>(dst + (size_t)row0 * K));
+                if (row1 < N) __builtin_nontemporal_store(p1, reinterpret_cast<u32x4 *>(dst + (size_t)row1 * K));
+            } else {
+                u32x4 v;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = (uint32_t)bf16_bits(o[2 * e]) | ((uint32_t)bf16_bits(o[2 * e + 1]) << 16);
+                // a line is two sub-tiles wide; the last sub-tile of an odd number of them goes out alone
+                if ((q & 1) == 0) held = v;
+                const bool pair = (q & 1) != 0, alone = !pair && k0 + 32 * (q + 1) >= K;
+                if (pair || alone) {
+                    u32x4 p0 = held, p1 = v;
+                    sf_rows_to_lines(p0, p1);
+                    uint16_t *dst = reinterpret_cast<uint16_t *>(Wv) + k0 + 32 * (q & ~1) + 32 * (c >> 3) + 8 * g;
+                    const bool mine = pair || c < 8;
+                    if (mine && row0 < N) __builtin_nontemporal_store(p0, reinterpret_cast<u32x4 *>(dst + (size_t)row0 * K));
+                    if (mine && row1 < N) __builtin_nontemporal_store(p1, reinterpret_cast<u32x4 *>(dst + (size_t)row1 * K));
+                }
+            }
+        }
+    }
+}
+
+// Larger ranks: one thread per group of 32 codes of one row.  The scale is summed over j in
 // increasing order with fp32 FMAs (exact products for bf16 factors).
 template <int BITS, bool F32FACT, bool F32OUT>
 __global__ __launch_bounds__(128) void dequant_kernel(const uint8_t *__restrict__ codes,
@@ -169,6 +235,17 @@ template <int BITS, bool F32FACT, bool F32OUT>
 static hipError_t launch_dequant_t(const void *codes, const float *codebook, const void *B, const void *A,
                                    void *W, int N, int K, int r, hipStream_t st)
 {
+    int per = 0;
+    const dim3 tiles = sf_grid(N, K, &per);
+    const int sg = tiles.y <= 65535u ? sf_groups(r) : 0;
+#define LORDS_DQCASE(S_)                                                                                               \
+    if (sg == S_) {                                                                                                    \
+        hipLaunchKernelGGL((dequant_tile_kernel<BITS, S_, F32FACT, F32OUT>), tiles, dim3(kSfThreads), 0, st,          \
+                           (const uint8_t *)codes, codebook, B, A, W, N, K, r, per);                                   \
+        return hipGetLastError();                                                                                      \
+    }
+    LORDS_DQCASE(2) LORDS_DQCASE(4) LORDS_DQCASE(8)
+#undef LORDS_DQCASE
     const long blocks_per_row = (K / 32 + 127) / 128;
     hipLaunchKernelGGL((dequant_kernel<BITS, F32FACT, F32OUT>), dim3((unsigned)(blocks_per_row * N)), dim3(128), 0, st,
                        (const uint8_t *)codes, codebook, B, A, W, N, K, r);

@@ -1,0 +1,193 @@
+// The scale S = B A in fp32, element by element, for the streaming kernels that need it to the bit
+// (lords_dequant, lords_quantize):
+//      S = fma(B[n][r-1], A[r-1][k], ... fma(B[n][0], A[0][k], 0) ...),     j increasing.
+// v_mfma_f32_16x16x4_f32 forms exactly that chain: its four products enter the accumulator one after the other, in
+// order of the contraction index, each with one rounding to nearest even (compared with fmaf chains on this chip over
+// 51,200 sums of 32 terms, bf16-exact and general operands: no bit differed).  So the r multiply-adds of a weight leave
+// the vector ALUs, where they cost 32 of about 112 lane operations per weight at rank 32.
+//
+// Tile of a wave: 16 rows (a slab) x 128 columns, in four sub-tiles of 32 columns.  MFMA (q, t) of sub-tile q computes
+// the scales of columns 32 q + 8 g' + 4 t + e (MFMA row 4 g' + e) of all 16 rows (MFMA column c), so that lane
+// (c = lane % 16, g = lane / 16) ends up with the eight consecutive columns 32 q + 8 g .. + 7 of row c: fp32 weights
+// of a sub-tile are 32 consecutive bytes per lane and one 128-byte line per row.
+#pragma once
+#include "lords_device.h"
+
+namespace lords {
+
+// A panel in LDS: fp32, 16 rank entries x 128 columns = 8 KB per rank block sg.  Entry (j, col) sits so that one 16-byte read of
+// lane (c, g) brings rank entries 16 sg + 4 i + g, i = 0..3, of its column; the four-lane-group slots are XOR-ed with the column's
+// eight-column block, which spreads the 16 lanes of a group over all banks.
+constexpr int kSfCols = 128;
+__host__ __device__ constexpr size_t sf_panel_bytes(int sgroups) { return (size_t)sgroups * kSfCols * 16 * sizeof(float); }
+__device__ __forceinline__ int sf_panel_at(int j, int col)
+{
+    return ((j >> 4) * kSfCols + col) * 16 + (((j & 3) ^ ((col >> 3) & 3)) << 2) + ((j >> 2) & 3);
+}
+
+// Stages columns k0 .. k0 + 127 of A (zero beyond the rank and beyond K) with `threads` threads.
+template <int SG, bool F32FACT>
+__device__ __forceinline__ void sf_stage_panel(float *panel, const void *Av, int r, int K, int k0, int tid, int threads)
+{
+    for (int id = tid; id < SG * 16 * (kSfCols / 8); id += threads) {
+        const int j = id / (kSfCols / 8), col = 8 * (id % (kSfCols / 8));
+        float v[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = 0.f;
+        if (j < r && k0 + col < K) {                       // (K is a multiple of 32: eight columns are in or out together)
+            if (F32FACT) {
+                const f32x4 *p = reinterpret_cast<const f32x4 *>(reinterpret_cast<const float *>(Av) + (size_t)j * K + k0 + col);
+                const f32x4 t0 = p[0], t1 = p[1];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) { v[e] = t0[e]; v[4 + e] = t1[e]; }
+            } else {
+                const u32x4 t = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const uint16_t *>(Av) + (size_t)j * K + k0 + col);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    v[2 * e] = __builtin_bit_cast(float, t[e] << 16);
+                    v[2 * e + 1] = __builtin_bit_cast(float, t[e] & 0xFFFF0000u);
+                }
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) panel[sf_panel_at(j, col + e)] = v[e];
+    }
+}
+
+// The lane's share of 16 rows of B: Bop[s] = B[n][4 s + g], zero beyond the rank.
+template <int SG, bool F32FACT>
+__device__ __forceinline__ void sf_load_rows(float (&Bop)[4 * SG], const void *Bv, int n, int r, int g)
+{
+    if (!F32FACT && (r & 7) == 0) {
+        const uint16_t *row = reinterpret_cast<const uint16_t *>(Bv) + (size_t)n * r;
+#pragma unroll
+        for (int h = 0; h < 2 * SG; ++h) {
+            u32x4 t = u32x4{0u, 0u, 0u, 0u};
+            if (8 * h < r) t = *reinterpret_cast<const u32x4 *>(row + 8 * h);
+            const uint32_t lo = (g & 2) ? t[1] : t[0], hi = (g & 2) ? t[3] : t[2];
+            Bop[2 * h] = __builtin_bit_cast(float, (g & 1) ? (lo & 0xFFFF0000u) : (lo << 16));
+            Bop[2 * h + 1] = __builtin_bit_cast(float, (g & 1) ? (hi & 0xFFFF0000u) : (hi << 16));
+        }
+    } else {
+#pragma unroll
+        for (int s = 0; s < 4 * SG; ++s) {
+            const int j = 4 * s + g;
+            float v = 0.f;
+            if (j < r) {
+                if (F32FACT) v = reinterpret_cast<const float *>(Bv)[(size_t)n * r + j];
+                else v = bf16_to_f32(reinterpret_cast<const uint16_t *>(Bv)[(size_t)n * r + j]);
+            }
+            Bop[s] = v;
+        }
+    }
+}
+
+// Scales of sub-tile q: S[4 t + e] belongs to column 32 q + 8 g + 4 t + e of row c.
+template <int SG>
+__device__ __forceinline__ void sf_scales(const float *panel, const float (&Bop)[4 * SG], int q, int c, int g, float (&S)[8])
+{
+    const float *p = panel + (32 * q + 8 * (c >> 2) + (c & 3)) * 16 + ((g ^ (c >> 2)) << 2);
+    f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+    for (int sg = 0; sg < SG; ++sg) {
+        const f32x4 a0 = *reinterpret_cast<const f32x4 *>(p + sg * (kSfCols * 16));
+        const f32x4 a1 = *reinterpret_cast<const f32x4 *>(p + sg * (kSfCols * 16) + 4 * 16);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0[i], Bop[4 * sg + i], acc[0], 0, 0, 0);
+            acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1[i], Bop[4 * sg + i], acc[1], 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) { S[e] = acc[0][e]; S[4 + e] = acc[1][e]; }
+}
+
+// 4 x 4 transposition between the words w[0..3] of a lane and the four lane groups g: afterwards w[i] of lane
+// group g is what w[g] was in lane group i.  (A sub-tile's eight codes per lane <-> the 32 consecutive codes of a
+// packed group per lane.)
+__device__ __forceinline__ void sf_transpose(uint32_t (&w)[4])
+{
+    auto s16 = [](uint32_t &a, uint32_t &b) {
+        const auto t = __builtin_amdgcn_permlane16_swap(a, b, false, false);   // odd lane groups of a <-> even lane groups of b
+        a = t[0];
+        b = t[1];
+    };
+    auto s32 = [](uint32_t &a, uint32_t &b) {
+        const auto t = __builtin_amdgcn_permlane32_swap(a, b, false, false);   // lane groups 2, 3 of a <-> lane groups 0, 1 of b
+        a = t[0];
+        b = t[1];
+    };
+    s16(w[0], w[1]);
+    s16(w[2], w[3]);
+    s32(w[0], w[2]);
+    s32(w[1], w[3]);
+}
+
+// Two 16-byte pieces of row c, 64 bytes of it over the four lane groups of each piece <-> one piece of row c % 8 and one of row
+// 8 + c % 8, in which the eight lanes of a row hold 128 consecutive bytes: lanes c < 8 the first piece, lanes c >= 8 the second.
+// A load or store of the exchanged pieces touches eight whole cache lines instead of sixteen halves.
+__device__ __forceinline__ void sf_rows_to_lines(u32x4 &p0, u32x4 &p1)
+{
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int a = (int)p0[e], b = (int)p1[e];
+        p0[e] = (uint32_t)__builtin_amdgcn_update_dpp(a, b, 0x128, 0xF, 0xC, false);    // lanes c >= 8: piece 1 of lane c - 8
+        p1[e] = (uint32_t)__builtin_amdgcn_update_dpp(b, a, 0x128, 0xF, 0x3, false);    // lanes c < 8: piece 0 of lane c + 8
+    }
+}
+// (the exchange is its own inverse)
+__device__ __forceinline__ void sf_lines_to_rows(u32x4 &l0, u32x4 &l1) { sf_rows_to_lines(l0, l1); }
+
+// Four words of eight codes each (BITS * 8 bits) <-> the BITS dwords of a 32-code group.
+template <int BITS>
+__device__ __forceinline__ void sf_pack(const uint32_t (&w)[4], uint32_t (&out)[BITS])
+{
+    if (BITS == 4) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) out[i % BITS] = w[i];
+    } else if (BITS == 3) {
+        out[0] = w[0] | (w[1] << 24);
+        out[1 % BITS] = (w[1] >> 8) | (w[2] << 16);
+        out[2 % BITS] = (w[2] >> 16) | (w[3] << 8);
+    } else {
+        out[0] = w[0] | (w[1] << 16);
+        out[1 % BITS] = w[2] | (w[3] << 16);
+    }
+}
+template <int BITS>
+__device__ __forceinline__ void sf_unpack(const uint32_t (&in)[BITS], uint32_t (&w)[4])
+{
+    if (BITS == 4) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) w[i] = in[i % BITS];
+    } else if (BITS == 3) {
+        w[0] = in[0];
+        w[1] = (in[0] >> 24) | (in[1 % BITS] << 8);
+        w[2] = (in[1 % BITS] >> 16) | (in[2 % BITS] << 16);
+        w[3] = in[2 % BITS] >> 8;                          // (bits beyond the 24 of a word are not looked at)
+    } else {
+        w[0] = in[0] & 0xFFFFu;
+        w[1] = in[0] >> 16;
+        w[2] = in[1 % BITS] & 0xFFFFu;
+        w[3] = in[1 % BITS] >> 16;
+    }
+}
+
+constexpr int kSfThreads = 256;                            // four waves share a panel of A
+constexpr int kSfWaves = kSfThreads / 64;
+constexpr int sf_groups(int r) { return r <= 32 ? 2 : r <= 64 ? 4 : r <= 128 ? 8 : 0; }   // rank blocks of 16; 0: not served
+
+// Launch shape: gridDim.x column tiles, gridDim.y runs of `per` slabs, dealt to the waves of a workgroup in turn.  About
+// four workgroups per CU, so that the panel (r x 128 of A, 16 KB at rank 32) is staged for as many rows as possible while every
+// CU keeps enough waves with loads in flight.
+inline dim3 sf_grid(int N, int K, int *per)
+{
+    const int ct = (K + kSfCols - 1) / kSfCols, slabs = (N + 15) / 16;
+    int runs = (1024 + ct - 1) / ct;
+    int p = (slabs + runs - 1) / runs;
+    p = (p + kSfWaves - 1) / kSfWaves * kSfWaves;          // whole rounds of the waves
+    *per = p;
+    return dim3((unsigned)ct, (unsigned)((slabs + p - 1) / p));
+}
+
+}  // namespace lords

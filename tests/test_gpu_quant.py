@@ -84,6 +84,30 @@ def test_quantize_matches_fp32_oracle_bit_for_bit(gpu, bits, wdt, fdt, N, K, r):
 
 
 @pytest.mark.parametrize("bits", [2, 3, 4])
+@pytest.mark.parametrize("fdt,odt,r", [("bf16", "f32", 32), ("f32", "bf16", 33), ("bf16", "bf16", 64), ("f32", "f32", 128), ("bf16", "f32", 129)])
+@pytest.mark.parametrize("N,K", [(1, 32), (37, 160), (2100, 1184)])
+def test_dequant_tiles(gpu, bits, fdt, odt, r, N, K):
+    """The dequantised weights at the edges of the 16-row x 128-column tiles and of the rank blocks.  Levels, factors and sums are fp32 and
+    in a stated order, so the only freedom against the fp64 oracle is the sum's rounding, r + 2 halves of an ulp of sum |B A| at most
+    (and one rounding to bf16 where the output is: half an ulp of an eight-bit significand, 2^-8)."""
+    say(f"dequant tiles bits={bits} factors={fdt} W={odt} N={N} K={K} r={r}")
+    cs = li.make_case("tiny", N=N, K=K, bits=bits, r=r, factor_dtype=fdt, seed=29, signed_factors=True)
+    t = gpu.torch
+    if fdt == "bf16":
+        Bt, At = gpu.L.bf16_from_bits(cs.B_bf16), gpu.L.bf16_from_bits(cs.A_bf16)
+    else:
+        Bt, At = t.from_numpy(cs.B_f32.copy()).cuda(), t.from_numpy(cs.A_f32.copy()).cuda()
+    W = t.full((N, K), float("nan"), dtype=t.float32 if odt == "f32" else t.bfloat16, device="cuda")
+    gpu.L.lords_dequant(t.from_numpy(cs.codes.copy()).cuda(), t.from_numpy(cs.codebook.copy()).cuda(), Bt, At, W, N, K, r, bits)
+    t.cuda.synchronize()
+    got = W.float().cpu().numpy().astype(np.float64)
+    want = onp.dequant(cs.codes, cs.codebook, cs.B_f32, cs.A_f32, bits)
+    mag = np.abs(cs.B_f32.astype(np.float64)) @ np.abs(cs.A_f32.astype(np.float64))
+    bound = mag * (r + 2) * 2.0 ** -24 + (np.abs(want) * 2.0 ** -8 if odt == "bf16" else 0.0) + 1e-30
+    assert np.isfinite(got).all() and (np.abs(got - want) <= bound).all()
+
+
+@pytest.mark.parametrize("bits", [2, 3, 4])
 def test_quantize_inverts_dequant(gpu, bits):
     """codes -> lords_dequant -> lords_quantize gives the codes back (distinct levels, non-zero scales)."""
     say(f"quantize(dequant(codes)) bits={bits}")
