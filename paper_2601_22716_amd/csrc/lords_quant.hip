@@ -12,12 +12,177 @@
 //   S    = fma(B[n][r-1], A[r-1][k], ... fma(B[n][0], A[0][k], 0) ...)      j increasing
 //   d_i  = fma(S, C[i], -W),  e_i = d_i * d_i,  q = the lowest i with minimal e_i
 //   block scale = max|W_block| / max_i |C[i]|
-#include "lords_device.h"
+#include "lords_scale_f32.h"
 #include "lords_launch.h"
 
 namespace lords {
 
-// One thread per group of 32 consecutive elements of one row: 32 scales, 32 searches, BITS dwords out.
+// ---- ranks up to 128: tiles of 16 rows x 128 columns per wave, the scale off the matrix cores (lords_scale_f32.h) ----
+//
+// The search.  For a table in increasing order d_i is monotone in i, rounding keeps it so, and e_i falls up to the level
+// nearest to t = W / S and rises after it.  The range of the table is cut into pieces 1/62 of it wide; where at most one mid-point
+// between neighbouring levels falls into a piece (widened by kQzMargin of its width on either side, which covers the rounding
+// of the reciprocal, the product and the fused multiply-add that find the piece), the nearest level is one of a pair i, i + 1
+// known beforehand, and the exact e_i, e_{i+1} decide.  The pair's answer is the lowest index with minimal e over the WHOLE table:
+//   * above: e rises after i + 1, and equal values there keep the lower index anyhow;
+//   * below: t lies a margin's width or more above the mid-point of i - 1 and i, so |d_{i-1}| exceeds |d_i| by |S| range / 1024 or
+//     more, which the bounds below keep 2^-22 of |d| or more and its square a normal number: e_{i-1} > e_i after rounding too.
+// The bounds: 2^-30 <= |S| <= 2^30, |W| <= 1000 |S| range, a range of 2^-10 .. 2^10 with gaps of range / 1024 or more, levels within
+// 1000 times the range.  Where they do not hold (S = 0 among them), or the table is not in increasing order or has two mid-points
+// in one piece, every level is searched, eight elements at a time.
+constexpr int kQzPieces = 64, kQzCopies = 8;
+constexpr float kQzMargin = 1.0f / 16.0f;
+constexpr float kQzScaleMin = 0x1p-30f, kQzScaleMax = 0x1p30f, kQzReach = 1000.f;
+constexpr float kQzBias = 0x1p23f;                             // added to a piece number, leaves it in the low bits of the significand
+
+typedef uint32_t u32x3 __attribute__((ext_vector_type(3), aligned(16)));
+// A piece's entry: address `base` + (low 24 bits of the biased piece number) * `stride`.
+__device__ __forceinline__ u32x3 load_piece(float u, uint32_t stride, uint32_t base)
+{
+    uint32_t at;
+    asm("v_mad_u32_u24 %0, %1, %2, %3" : "=v"(at) : "v"(u), "v"(stride), "v"(base));
+    return *reinterpret_cast<const __attribute__((address_space(3))) u32x3 *>((uintptr_t)at);
+}
+
+// Per weight: r / 128 of a matrix instruction, about 15 vector operations and one LDS read.  Bound by these (bf16 weights, half
+// the bytes, take 64 us where fp32 ones take 71).  14336 x 4096 at 4 bits, fp32 W: rank 32 256 -> 71 us (3.7 TB/s), rank 64
+// 442 -> 108, rank 128 849 -> 177, fp32 factors of rank 128 862 -> 197 (before: r fused multiply-adds and five operations per level
+// on every weight, the kernel further down); 1000 x 1024, rank 8: 8.4 -> 7.9; 500 x 512 at 2 bits, rank 128: 32 -> 12.
+template <int BITS, int SG, bool F32FACT, bool F32W>
+__global__ __launch_bounds__(kSfThreads) __attribute__((amdgpu_waves_per_eu(4))) void quantize_tile_kernel(const void *__restrict__ Wv, const float *__restrict__ codebook,
+                                                                   const void *__restrict__ Bv, const void *__restrict__ Av,
+                                                                   uint8_t *__restrict__ codes, int N, int K, int r, int per)
+{
+    constexpr int NL = 1 << BITS;
+    __shared__ __align__(16) float panel[SG * kSfCols * 16];
+    __shared__ __align__(16) f32x4 piece[kQzPieces * kQzCopies];       // {C[i], C[i+1], bits of i, -}, once per eight lanes
+    __shared__ float lut[NL];
+    __shared__ int table_ok;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, c = lane & 15, g = lane >> 4;
+    const int k0 = blockIdx.x * kSfCols, ngroups = K >> 5;
+    if (tid < NL) lut[tid] = codebook[tid];
+    __syncthreads();
+    // piece b holds the t with t inv + shift in b - 1/2 .. b + 1/2; the shift is a whole number, so that kQzBias + shift is exact
+    const float range = lut[NL - 1] - lut[0], inv = (float)(kQzPieces - 2) / range, shift = -rintf(lut[0] * inv);
+    if (wave == 0) {
+        static_assert(kQzPieces == 64, "one lane per piece");
+        const float lo = (float)lane - 0.5f - shift - kQzMargin, hi = (float)lane + 0.5f - shift + kQzMargin;
+        int below = 0, inside = 0;
+        bool good = range >= 0x1p-10f && range <= 0x1p10f && fmaxf(fabsf(lut[0]), fabsf(lut[NL - 1])) <= 1000.f * range;
+        for (int i = 0; i + 1 < NL; ++i) {
+            const float u = (0.5f * lut[i] + 0.5f * lut[i + 1]) * inv;
+            below += u < lo;
+            inside += u >= lo && u <= hi;
+            good = good && lut[i + 1] - lut[i] >= range * (1.0f / 1024.0f);
+        }
+        const int i = min(below, NL - 2);
+        const f32x4 p = f32x4{lut[i], lut[i + 1], __builtin_bit_cast(float, i), 0.f};
+        for (int q = 0; q < kQzCopies; ++q) piece[lane * kQzCopies + q] = p;
+        const bool all = __builtin_amdgcn_ballot_w64(good && inside <= 1) == ~0ull;
+        if (lane == 0) table_ok = all ? 1 : 0;
+    }
+    sf_stage_panel<SG, F32FACT>(panel, Av, r, K, k0, tid, kSfThreads);
+    __syncthreads();
+    const float reach = table_ok != 0 ? kQzReach * range : -1.f;    // (a table that is not good for the pairs: nothing is within reach)
+    const float bias = kQzBias + shift;
+    const uint32_t mypiece = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) f32x4 *)piece + (lane & (kQzCopies - 1)) * 16u;
+
+    const int nslabs = (N + 15) >> 4, s_end = min(nslabs, ((int)blockIdx.y + 1) * per);
+    for (int sl = blockIdx.y * per + wave; sl < s_end; sl += kSfWaves) {
+        const int n = min(sl * 16 + c, N - 1);                 // rows >= N: recomputed, never stored
+        // every load of the tile goes out before the first use: the weights (each load covers whole 128-byte lines of eight rows,
+        // see sf_rows_to_lines), then the rows of B
+        const int row0 = min(sl * 16 + (c & 7), N - 1), row1 = min(sl * 16 + 8 + (c & 7), N - 1);
+        constexpr int NP = F32W ? 8 : 4;                       // 16-byte pieces of a lane: one per four or eight columns of every sub-tile
+        u32x4 wp[NP];
+#pragma unroll
+        for (int i = 0; i < NP; i += 2) {
+            // (pieces beyond K: the last ones of the row, never used)
+            const int col = F32W ? 16 * i + 8 * g + 4 * (c >> 3) : 32 * (i + (c >> 3)) + 8 * g;
+            const size_t at = min(k0 + col, F32W ? K - 4 : K - 8);
+            const unsigned char *base = reinterpret_cast<const unsigned char *>(Wv);
+            wp[i] = *reinterpret_cast<const u32x4 *>(base + ((size_t)row0 * K + at) * (F32W ? 4 : 2));
+            wp[i + 1] = *reinterpret_cast<const u32x4 *>(base + ((size_t)row1 * K + at) * (F32W ? 4 : 2));
+        }
+        float Bop[4 * SG];
+        sf_load_rows<SG, F32FACT>(Bop, Bv, n, r, g);
+#pragma unroll
+        for (int i = 0; i < NP; i += 2) sf_lines_to_rows(wp[i], wp[i + 1]);
+        uint32_t word[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if (k0 + 32 * q >= K) break;
+            float w[8];
+            if (F32W) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const uint32_t lo = wp[(2 * q) % NP][e], hi = wp[(2 * q + 1) % NP][e];
+                    w[e] = __builtin_bit_cast(float, lo);
+                    w[4 + e] = __builtin_bit_cast(float, hi);
+                }
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    w[2 * e] = __builtin_bit_cast(float, wp[q][e] << 16);
+                    w[2 * e + 1] = __builtin_bit_cast(float, wp[q][e] & 0xFFFF0000u);
+                }
+            }
+            float S[8];
+            sf_scales<SG>(panel, Bop, q, c, g, S);
+            float smin = fabsf(S[0]), smax = fabsf(S[0]), wmax = fabsf(w[0]);
+#pragma unroll
+            for (int e = 1; e < 8; ++e) { smin = fminf(smin, fabsf(S[e])); smax = fmaxf(smax, fabsf(S[e])); wmax = fmaxf(wmax, fabsf(w[e])); }
+            const bool sure = smin >= kQzScaleMin && smax <= kQzScaleMax && wmax <= smin * reach;
+            // (all eight pieces are asked for before the first is used)
+            u32x3 p[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const float u = fminf(fmaxf(__builtin_fmaf(w[e] * __builtin_amdgcn_rcpf(S[e]), inv, bias), kQzBias), kQzBias + (float)(kQzPieces - 1));
+                p[e] = load_piece(u, kQzCopies * 16u, mypiece);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            uint32_t out = 0u;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const uint32_t c0 = p[e][0], c1 = p[e][1];             // (copied first: a bit cast of a vector's element takes element 0)
+                const float d0 = __builtin_fmaf(S[e], __builtin_bit_cast(float, c0), -w[e]), d1 = __builtin_fmaf(S[e], __builtin_bit_cast(float, c1), -w[e]);
+                uint32_t best = p[e][2] + (d1 * d1 < d0 * d0 ? 1u : 0u);
+                asm volatile("" : "+v"(best));                         // (made here: kept as a lane mask per element it fills the scalar registers)
+                out |= best << (BITS * e);
+            }
+            if (__builtin_amdgcn_ballot_w64(!sure) != 0) {
+                out = 0u;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    uint32_t best = 0u;
+                    const float d0 = __builtin_fmaf(S[e], lut[0], -w[e]);
+                    float ebest = d0 * d0;
+#pragma unroll 1
+                    for (int i = 1; i < NL; ++i) {
+                        const float d = __builtin_fmaf(S[e], lut[i], -w[e]);
+                        const float err = d * d;
+                        const bool better = err < ebest;               // strict: ties keep the lower index
+                        best = better ? (uint32_t)i : best;
+                        ebest = better ? err : ebest;
+                    }
+                    out |= best << (BITS * e);
+                }
+            }
+            word[q] = out;
+        }
+        sf_transpose(word);
+        uint32_t gw[BITS];
+        sf_pack<BITS>(word, gw);
+        const int grp = (k0 >> 5) + g;
+        if (sl * 16 + c < N && grp < ngroups) {
+            uint32_t *dst = reinterpret_cast<uint32_t *>(codes + ((size_t)n * ngroups + grp) * (4 * BITS));
+#pragma unroll
+            for (int d = 0; d < BITS; ++d) dst[d] = gw[d];
+        }
+    }
+}
+
+// Larger ranks: one thread per group of 32 consecutive elements of one row: 32 scales, 32 searches, BITS dwords out.
 // The 128 threads of a workgroup take the SAME 32 columns of 128 consecutive rows, so the A values
 // of a step of the j loop are the same for every lane (scalar loads, operands straight from scalar
 // registers) and only B is read per lane.
@@ -212,6 +377,19 @@ template <int BITS>
 static hipError_t launch_quantize_bits(const void *W, const float *codebook, const void *B, const void *A, void *codes,
                                        int N, int K, int r, bool f32w, bool f32fact, hipStream_t st)
 {
+    int per = 0;
+    const dim3 tiles = sf_grid(N, K, &per);
+    const int sg = tiles.y <= 65535u ? sf_groups(r) : 0;
+    if (sg != 0) {
+#define LORDS_QTCASE(S_, FF_, FW_)                                                                                      \
+    if (sg == S_ && f32fact == FF_ && f32w == FW_)                                                                     \
+        hipLaunchKernelGGL((quantize_tile_kernel<BITS, S_, FF_, FW_>), tiles, dim3(kSfThreads), 0, st, W, codebook, B, A, (uint8_t *)codes, N, K, r, per)
+        LORDS_QTCASE(2, false, false); LORDS_QTCASE(2, false, true); LORDS_QTCASE(2, true, false); LORDS_QTCASE(2, true, true);
+        LORDS_QTCASE(4, false, false); LORDS_QTCASE(4, false, true); LORDS_QTCASE(4, true, false); LORDS_QTCASE(4, true, true);
+        LORDS_QTCASE(8, false, false); LORDS_QTCASE(8, false, true); LORDS_QTCASE(8, true, false); LORDS_QTCASE(8, true, true);
+#undef LORDS_QTCASE
+        return hipGetLastError();
+    }
     const dim3 grid((unsigned)((N + 127) / 128), (unsigned)(K / 32)), block(128);
 #define LORDS_QCASE(FF_, FW_) \
     hipLaunchKernelGGL((quantize_kernel<BITS, FF_, FW_>), grid, block, 0, st, W, codebook, B, A, (uint8_t *)codes, N, K, r)

@@ -83,6 +83,56 @@ def test_quantize_matches_fp32_oracle_bit_for_bit(gpu, bits, wdt, fdt, N, K, r):
     assert np.all(err <= best + 1e-5 * (np.abs(S) * np.abs(C).max() + np.abs(W)) ** 2)
 
 
+def hard_table(kind, bits):
+    """Level tables at the edges of the search: evenly spaced integers (many exact ties), out of order, with equal
+    neighbours, two levels much closer than the rest, and a table far from zero."""
+    n = 1 << bits
+    t = li.nf_codebook(bits)
+    if kind == "int":
+        return li.int_codebook(bits)
+    if kind == "unordered":
+        return t[np.random.default_rng(5).permutation(n)].copy()
+    if kind == "equal":
+        t = t.copy()
+        t[n // 2] = t[n // 2 - 1]
+        return t
+    if kind == "close":
+        t = t.copy()
+        t[1] = t[0] + np.float32(1e-3)
+        return t
+    return (t * np.float32(1e-5) + np.float32(1.0)).astype(np.float32)      # "far"
+
+
+@pytest.mark.parametrize("bits", [2, 3, 4])
+@pytest.mark.parametrize("kind", ["int", "unordered", "equal", "close", "far"])
+@pytest.mark.parametrize("fdt,r", [("bf16", 33), ("f32", 64), ("bf16", 128), ("f32", 129)])
+def test_quantize_search_edges_bit_for_bit(gpu, bits, kind, fdt, r):
+    """Weights on mid-points between levels and far outside the table, scales of either sign, zero and at both ends of the fp32
+    range; ranks at the edges of the rank blocks and beyond the last one.  K is no multiple of the 128-column tile."""
+    N, K = 50, 416
+    say(f"quantize edges bits={bits} table={kind} factors={fdt} r={r}")
+    cs = li.make_case("tiny", N=N, K=K, bits=bits, r=r, factor_dtype=fdt, seed=23, signed_factors=True)
+    B, A = cs.B_f32.copy(), cs.A_f32.copy()
+    B[3] = 0.0                                              # S = 0 in a whole row
+    B[4] *= np.float32(2.0 ** -110)
+    B[5] *= np.float32(2.0 ** 110)
+    A[:, 7] = 0.0
+    table = hard_table(kind, bits)
+    S = onp.scale_matrix(B, A)
+    g = np.random.default_rng(11)
+    mids = 0.5 * (table[:-1].astype(np.float64) + table[1:])
+    W = (S * g.choice(np.concatenate([mids, table.astype(np.float64)]), size=(N, K))).astype(np.float32)
+    W[10:20] = (S[10:20] * g.uniform(-2.0, 2.0, (10, K)) * np.abs(table).max()).astype(np.float32)
+    W[20] *= np.float32(1e6)                                # every level rounds to the same distance
+    W[21] = 0.0
+    if fdt == "bf16":
+        Bt, At = gpu.L.bf16_from_bits(li.to_bf16(B)[0]), gpu.L.bf16_from_bits(li.to_bf16(A)[0])
+    else:
+        Bt, At = gpu.torch.from_numpy(B).cuda(), gpu.torch.from_numpy(A).cuda()
+    got = run_quantize(gpu, None, W, table, Bt, At, N, K, r, bits)
+    np.testing.assert_array_equal(got, onp.pack_codes(oc.quantize_f32(W, table, B, A, bits), bits))
+
+
 @pytest.mark.parametrize("bits", [2, 3, 4])
 @pytest.mark.parametrize("fdt,odt,r", [("bf16", "f32", 32), ("f32", "bf16", 33), ("bf16", "bf16", 64), ("f32", "f32", 128), ("bf16", "f32", 129)])
 @pytest.mark.parametrize("N,K", [(1, 32), (37, 160), (2100, 1184)])
