@@ -312,12 +312,32 @@ __global__ __launch_bounds__(256) void block_scale_kernel(const void *__restrict
 // The same for block sizes g that divide 256 (and are multiples of 4): W is read as one flat stream of
 // 4-element vectors, kU vectors per lane in flight; a block is g/4 neighbouring lanes of one vector row,
 // its maximum taken by cross-lane steps within that group.  Blocks are consecutive in the flat order
-// (K = r g), so block b is elements b g .. b g + g - 1 and its scale is entry b of B.
+// (K = r g), so block b is elements b g .. b g + g - 1 and its scale is entry b of B.  The workgroups after the first
+// `scale_blocks` write the indicator A: a launch of its own for its 0.3 MB took 4.8 us of 49 on 14336 x 4096, block size 128.
 constexpr int kBsU = 8;
 template <bool F32W, bool F32FACT>
 __global__ __launch_bounds__(256) void block_scale_vec_kernel(const void *__restrict__ Wv, const float *__restrict__ codebook,
-                                                              void *__restrict__ Bv, long nvec, int g, int nl)
+                                                              void *__restrict__ Bv, void *__restrict__ Av, long nvec, int g, int nl,
+                                                              int scale_blocks, int K, int r)
 {
+    if ((int)blockIdx.x >= scale_blocks) {
+        // the indicator A, eight entries per thread (K is a multiple of 32: all of one row)
+        const long id = ((long)(blockIdx.x - scale_blocks) * 256 + threadIdx.x) * 8;
+        if (id >= (long)r * K) return;
+        const int j = (int)(id / K), k = (int)(id - (long)j * K);
+        uint32_t in[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) in[e] = k + e >= j * g && k + e < (j + 1) * g ? (F32FACT ? 0x3F800000u : 0x3F80u) : 0u;
+        if (F32FACT) {
+            u32x4 *dst = reinterpret_cast<u32x4 *>(reinterpret_cast<float *>(Av) + id);
+            dst[0] = u32x4{in[0], in[1], in[2], in[3]};
+            dst[1] = u32x4{in[4], in[5], in[6], in[7]};
+        } else {
+            *reinterpret_cast<u32x4 *>(reinterpret_cast<uint16_t *>(Av) + id) =
+                u32x4{in[0] | (in[1] << 16), in[2] | (in[3] << 16), in[4] | (in[5] << 16), in[6] | (in[7] << 16)};
+        }
+        return;
+    }
     const int lane = threadIdx.x & 63;
     const long wave = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
     const long v0 = wave * (64 * kBsU) + lane;                       // this lane's first vector
@@ -418,12 +438,14 @@ hipError_t launch_block_init(const void *W, const float *codebook, void *B, void
     const int g = K / r;
     if ((g % 4) == 0 && (256 % g) == 0) {
         const long nvec = (long)N * K / 4;
-        const dim3 gv((unsigned)((nvec + 4 * 64 * kBsU - 1) / (4 * 64 * kBsU)));
+        const unsigned scale_blocks = (unsigned)((nvec + 4 * 64 * kBsU - 1) / (4 * 64 * kBsU));
+        const dim3 gv(scale_blocks + (unsigned)(((long)r * K + 2047) / 2048));
 #define LORDS_BCASE(FW_, FF_) \
-    hipLaunchKernelGGL((block_scale_vec_kernel<FW_, FF_>), gv, dim3(256), 0, st, W, codebook, B, nvec, g, nl)
+    hipLaunchKernelGGL((block_scale_vec_kernel<FW_, FF_>), gv, dim3(256), 0, st, W, codebook, B, A, nvec, g, nl, (int)scale_blocks, K, r)
         if (f32w) { if (f32fact) LORDS_BCASE(true, true); else LORDS_BCASE(true, false); }
         else { if (f32fact) LORDS_BCASE(false, true); else LORDS_BCASE(false, false); }
 #undef LORDS_BCASE
+        return hipGetLastError();
     } else if (f32w) {
         if (f32fact) hipLaunchKernelGGL((block_scale_kernel<true, true>), g1, dim3(256), 0, st, W, codebook, B, N, K, r, nl);
         else hipLaunchKernelGGL((block_scale_kernel<true, false>), g1, dim3(256), 0, st, W, codebook, B, N, K, r, nl);
