@@ -83,18 +83,57 @@ __global__ __launch_bounds__(256) void decode_kernel(DecodeArgs a)
             }
         }
     };
-    // Factors that cannot be read as 16-byte operands (fp32, or a rank that is not a multiple
-    // of 8) are gathered element by element at the point of use: the slow, general variant.
-    auto gather_B = [&](int i) {
-        const int row = (slab0 + i) * 16 + c;
+    // Factors that cannot be read as 16-byte operands (fp32, or a rank that is not a multiple of 8): the
+    // rows of B of this workgroup are one contiguous stretch of memory, fetched once with whole-line loads, laid
+    // out in LDS as operands (fp32: the parts [Bhi | Bhi | Blo] of lords_device.h) and read from there slab by slab.
+    // (Gathered entry by entry at the point of use every slab paid a memory latency; with the A tile below
+    // gathered the same way 512 x 256, 4 bits, fp32 rank 4, 4 tokens took 23.0 us, now 7;
+    // 4096 x 4096 rank 16, 1 / 4 tokens 69 / 98 -> 17.3 / 25.8 us.)
+    constexpr int RPB = 32 * SS, BST = RPB + 8;
+    uint16_t *Bs = reinterpret_cast<uint16_t *>(smem + R0 + 128);          // [16 * ns][BST]
+    auto stage_B = [&]() {
+        const int r = a.f.r, row0 = slab0 * 16, rows = min(ns * 16, N - row0);
+        const int total = rows * r;
+        for (int id = tid; id < ns * 16 * (RPB / 8); id += 256)            // entries beyond the rank, rows beyond N: zero
+            *reinterpret_cast<u32x4 *>(Bs + (id / (RPB / 8)) * BST + 8 * (id % (RPB / 8))) = u32x4{0u, 0u, 0u, 0u};
+        __syncthreads();
+        constexpr int FL = 8;                                               // loads in flight per thread
+        for (int base = 0; base < total; base += 256 * FL) {
+            if (a.f.f32) {
+                float x[FL];
 #pragma unroll
-        for (int s = 0; s < SS; ++s) {
-            typedef __attribute__((__vector_size__(8 * sizeof(short)))) short s16x8;
-            s16x8 t;
+                for (int q = 0; q < FL; ++q)
+                    x[q] = reinterpret_cast<const float *>(a.f.B)[(size_t)row0 * r + min(base + tid + 256 * q, total - 1)];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) t[e] = (short)factorB_bits(a.f, row, 32 * s + 8 * g + e);
-            Bop[i][s] = __builtin_bit_cast(bf16x8, t);
+                for (int q = 0; q < FL; ++q) {
+                    const int id = base + tid + 256 * q;
+                    if (id >= total) continue;
+                    const int row = (int)((unsigned)id / (unsigned)r), j = id - row * r;
+                    const uint16_t hi = bf16_bits(x[q]);
+                    uint16_t *d = Bs + row * BST + j;
+                    d[0] = hi;
+                    d[r] = hi;
+                    d[2 * r] = bf16_bits(x[q] - bf16_to_f32(hi));
+                }
+            } else {
+                uint16_t x[FL];
+#pragma unroll
+                for (int q = 0; q < FL; ++q)
+                    x[q] = reinterpret_cast<const uint16_t *>(a.f.B)[(size_t)row0 * r + min(base + tid + 256 * q, total - 1)];
+#pragma unroll
+                for (int q = 0; q < FL; ++q) {
+                    const int id = base + tid + 256 * q;
+                    if (id >= total) continue;
+                    const int row = (int)((unsigned)id / (unsigned)r);
+                    Bs[row * BST + (id - row * r)] = x[q];
+                }
+            }
         }
+    };
+    auto read_B = [&](int i) {
+#pragma unroll
+        for (int s = 0; s < SS; ++s)
+            Bop[i][s] = *reinterpret_cast<const bf16x8 *>(Bs + (i * 16 + c) * BST + 32 * s + 8 * g);
     };
 
     // ---- 0. first loads of the row stream go out before any set-up --------------------------
@@ -102,6 +141,7 @@ __global__ __launch_bounds__(256) void decode_kernel(DecodeArgs a)
     for (int i = 0; i < kDepth; ++i) issue(i);
 
     if (tid < NL) cb[tid] = a.codebook[tid];
+    if (!BVEC) stage_B();                          // (visible to all waves after the barriers below)
 
     // ---- 1. A columns of this wave's block -> a-operands of the scale MFMAs ------------------
     bf16x8 Aop[G][SS][8];
@@ -147,16 +187,40 @@ __global__ __launch_bounds__(256) void decode_kernel(DecodeArgs a)
                     *reinterpret_cast<u32x4 *>(Aw + jl * AST + 8 * kc) = o;
                 }
             } else {
-                for (int id = lane; id < 32 * KT; id += 64) {
-                    const int jl = id / KT, kk = id % KT;
-                    uint16_t v;
-                    if (M1) {
-                        const float x = (kb + kk < K) ? bf16_to_f32(a.X[kb + kk]) : 0.f;
-                        v = factorAx_bits(a.f, 32 * s + jl, kb + kk, x);
-                    } else {
-                        v = factorA_bits(a.f, 32 * s + jl, kb + kk);
+                // fp32 factors: 8 columns of a row at a time, split into the parts [Ahi ; Alo ; Ahi]; four rows in flight
+#pragma unroll
+                for (int q0 = 0; q0 < NCH; q0 += 4) {
+                    f32x4 t[4][2];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const int jj = 32 * s + (lane + 64 * (q0 + q)) / CPR;
+                        t[q][0] = t[q][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+                        if (jj < a.f.r_eff && k0 < K) {
+                            const int j = jj < a.f.r ? jj : jj < 2 * a.f.r ? jj - a.f.r : jj - 2 * a.f.r;
+                            const f32x4 *src = reinterpret_cast<const f32x4 *>(reinterpret_cast<const float *>(a.f.A) + (size_t)j * K + k0);
+                            t[q][0] = src[0];
+                            t[q][1] = src[1];
+                        }
                     }
-                    Aw[jl * AST + kk] = v;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const int jl = (lane + 64 * (q0 + q)) / CPR, jj = 32 * s + jl;
+                        const bool low = jj >= a.f.r && jj < 2 * a.f.r;
+                        u32x4 o;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            uint16_t h[2];
+#pragma unroll
+                            for (int d = 0; d < 2; ++d) {
+                                float x = t[q][e >> 1][2 * (e & 1) + d];
+                                if (M1) x = jj < a.f.r_eff ? x * xk[2 * e + d] : 0.f;     // (fp32 product, then split like a factor)
+                                h[d] = bf16_bits(x);
+                                if (low) h[d] = bf16_bits(x - bf16_to_f32(h[d]));
+                            }
+                            o[e] = (uint32_t)h[0] | ((uint32_t)h[1] << 16);
+                        }
+                        *reinterpret_cast<u32x4 *>(Aw + jl * AST + 8 * kc) = o;
+                    }
                 }
             }
             __syncthreads();
@@ -207,7 +271,7 @@ __global__ __launch_bounds__(256) void decode_kernel(DecodeArgs a)
         if (i < ns) {
             if (i + kDepth < kNS) issue(i + kDepth);
             __builtin_amdgcn_sched_barrier(0);     // keep the prefetch ahead of this slab's arithmetic
-            if (!BVEC) gather_B(i);
+            if (!BVEC) read_B(i);
             float p0 = 0.f, p1 = 0.f, p2 = 0.f, p3 = 0.f;
 #pragma unroll
             for (int v = 0; v < G; ++v) {
@@ -385,10 +449,12 @@ static hipError_t launch_decode_t(const DecodeArgs &a, dim3 grid, hipStream_t st
     constexpr size_t A_BYTES = 4 * 32 * AST * 2, LUT_BYTES = (size_t)(1 << (2 * BITS)) * 256, RED_BYTES = 4 * kNS * 64 * 16;
     constexpr size_t R0 = A_BYTES > LUT_BYTES ? (A_BYTES > RED_BYTES ? A_BYTES : RED_BYTES)
                                               : (LUT_BYTES > RED_BYTES ? LUT_BYTES : RED_BYTES);
-    const size_t smem = R0 + 128;
+    const size_t smem = R0 + 128 + (BVEC ? 0 : (size_t)a.ns * 16 * (32 * SS + 8) * 2);    // (rows of B that pass through LDS)
     static LdsOptIn lds_opt_in;
     if (smem > 48 * 1024) {
-        const hipError_t e = allow_dynamic_lds(lds_opt_in, reinterpret_cast<const void *>(&decode_kernel<BITS, SS, G, BVEC, M1>), smem);
+        // (asked for once per device: the most any launch of this instantiation takes)
+        const hipError_t e = allow_dynamic_lds(lds_opt_in, reinterpret_cast<const void *>(&decode_kernel<BITS, SS, G, BVEC, M1>),
+                                               R0 + 128 + (BVEC ? 0 : (size_t)kNS * 16 * (32 * SS + 8) * 2));
         if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL((decode_kernel<BITS, SS, G, BVEC, M1>), grid, dim3(256), smem, st, a);
