@@ -104,6 +104,10 @@ inline lords_path resolve_path(lords_path path, const lords::MatmulProblem &p)
     if (path != LORDS_PATH_AUTO) return path;
     if (p.M > 16) return LORDS_PATH_PREFILL;
     if (p.M >= 2 && p.r > 64 && lords::prefill_fast_supported(p)) return LORDS_PATH_PREFILL;
+    // fp32 factors (contraction 3 r, the same oldest few-token kernel): above 32 columns on layers above 32 M weights
+    // (us, few-token / large-M at 4 tokens: 14336 x 4096 rank 16 59.3 / 43.4, rank 40 82 / 67; 4096 x 4096
+    // rank 16 25.8 / 31.7, rank 40 34.7 / 41.6; at rank 4 34.5 / 41.3 and 22.7 / 28.7).
+    if (p.M >= 2 && p.f32fact && 3 * p.r > 32 && (long)p.N * p.K > (32L << 20) && lords::prefill_fast_supported(p)) return LORDS_PATH_PREFILL;
     return LORDS_PATH_DECODE;
 }
 
@@ -142,8 +146,15 @@ int launch_matmul(const lords::MatmulProblem &p, lords_path path, const WsView &
 // are left to the caller (*extra_ptr).
 int plan_workspace(const lords::MatmulProblem &p, lords_path path, size_t extra, void *stream, WsView *ws, void **extra_ptr)
 {
-    const size_t own = matmul_need(p, path);
-    const int rc = get_workspace(own + extra, stream, ws);
+    size_t own = matmul_need(p, path);
+    int rc = get_workspace(own + extra, stream, ws);
+    if (rc != LORDS_OK && p.f32fact && !is_decode(path) && own > kFront) {
+        // (no room for shared tiles, and none to be had, as under capture: whole tiles need no scratch.  With bf16
+        //  factors the call is refused instead: warm the shape up before capturing it.)
+        own = kFront;
+        rc = get_workspace(own + extra, stream, ws);
+        if (rc == LORDS_OK) ws->bytes = own;
+    }
     if (rc == LORDS_OK && extra_ptr) *extra_ptr = ws->base + own;
     return rc;
 }
@@ -355,8 +366,10 @@ int matmul_in(const void *X, const void *codes, const float *codebook, const voi
         const bool ok = is_decode(path) ? (use_gemv(p, path) || decode_kind(p) == kFew) : lords::prefill_fast_supported(p);
         if (!ok) return LORDS_ERR_UNSUPPORTED;
     }
-    // (a caller's workspace must have the size the query gives; the static one is used as far as it goes)
-    if (!ws.base || ws.bytes < matmul_need(p, path, ws_given ? kNoLimit : ws.bytes)) return LORDS_ERR_WORKSPACE;
+    // (a caller's workspace must have the size the query gives; the static one is used as far as it goes, and so is
+    //  a caller's for a large-M product with fp32 factors, whose whole-tile form needs the front only)
+    const bool elastic = !ws_given || (f32fact && !is_decode(path));
+    if (!ws.base || ws.bytes < matmul_need(p, path, elastic ? ws.bytes : kNoLimit)) return LORDS_ERR_WORKSPACE;
     return launch_matmul(p, path, ws, stream);
 }
 }  // namespace

@@ -45,10 +45,12 @@ struct PrefillArgs {
     const uint16_t *X;
     const uint8_t *codes;
     const float *codebook;
-    const uint16_t *B;     // N x r bf16
-    const uint16_t *A;     // r x K bf16
+    const void *B;         // N x rf, bf16 or fp32
+    const void *A;         // rf x K, bf16 or fp32
     void *Y;
-    int M, N, K, r;
+    int M, N, K;
+    int r;                 // contraction length of the scales: rf, or 3 rf for fp32 factors (hi/lo parts, see the kernel)
+    int rf;                // rank of the factors
     int y_f32;
     int row_bytes;
     int nt, mt;            // tiles along N and M
@@ -84,7 +86,14 @@ __device__ __forceinline__ uint32_t pair_index(const uint32_t (&w)[BITS], int p)
     return v & ((1u << (2 * BITS)) - 1u);
 }
 
-template <int BITS, int SS, int WM, int R, int WN = 4, int MB = 8>
+// F32: fp32 factors.  They are split x = hi + lo (two bf16) and the scale is the contraction of length
+// 3 rf of [Bhi | Bhi | Blo] with [Ahi ; Alo ; Ahi] (lords_device.h).  The A tile then comes through
+// registers: a thread requests 8 columns of a row with the codes of the next K tile, and splits them into
+// the three LDS rows (rank rows j, rf + j, 2 rf + j) after this tile's products: about 20 vector
+// instructions per thread and K tile at rank 16, no scratch and no launch of its own.
+// 4096 x 4096, 4 bits, rank 16, 500 tokens: 50 us (general kernel of lords_fused.hip: 361); 2048 tokens 100 (728);
+// 14336 x 4096, rank 40, 17 tokens 67 (608).
+template <int BITS, int SS, int WM, int R, int WN = 4, int MB = 8, bool F32 = false>
 __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(WN * WM / 4, WN * WM / 4))) void prefill_kernel(PrefillArgs a)
 {
     constexpr int BN = 16 * R * WN, BM = 16 * MB * WM, NT = 64 * WN * WM, RP = 32 * SS, NL = 1 << BITS, NE = 1 << (2 * BITS);
@@ -110,6 +119,7 @@ __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(WN
     const int unit_end = min(unit + a.per, total_units);
     if (unit >= unit_end) return;
     const int wn = wave % WN, wm = wave / WN;
+    const uint16_t *A16 = reinterpret_cast<const uint16_t *>(a.A), *B16 = reinterpret_cast<const uint16_t *>(a.B);   // (bf16 factors)
 
     // ---- level table --------------------------------------------------------------------------------
     for (int id = tid; id < NE * kPfCopies; id += NT) {
@@ -147,15 +157,27 @@ __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(WN
 #pragma unroll
             for (int e = 0; e < 8; ++e) t[e] = 0;
             if (n < N) {
-                if ((a.r & 7) == 0) {
-                    if (jj0 + 8 <= a.r) t = *reinterpret_cast<const s16x8 *>(a.B + (size_t)n * a.r + jj0);
+                if constexpr (F32) {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        const int jj = jj0 + e;
+                        if (jj < a.r) {
+                            const int j = jj < a.rf ? jj : jj < 2 * a.rf ? jj - a.rf : jj - 2 * a.rf;
+                            const float x = reinterpret_cast<const float *>(a.B)[(size_t)n * a.rf + j];
+                            const uint16_t hi = bf16_bits(x);
+                            t[e] = (short)(jj >= 2 * a.rf ? bf16_bits(x - bf16_to_f32(hi)) : hi);
+                        }
+                    }
+                } else if ((a.r & 7) == 0) {
+                    if (jj0 + 8 <= a.r) t = *reinterpret_cast<const s16x8 *>(B16 + (size_t)n * a.r + jj0);
                 } else {
 #pragma unroll
                     for (int e = 0; e < 8; ++e)
-                        if (jj0 + e < a.r) t[e] = (short)a.B[(size_t)n * a.r + jj0 + e];
+                        if (jj0 + e < a.r) t[e] = (short)B16[(size_t)n * a.r + jj0 + e];
                 }
             }
             Bop[rho][s] = __builtin_bit_cast(bf16x8, t);
+            if constexpr (F32) __builtin_amdgcn_sched_barrier(0);     // (eight gathered entries in flight, not all of them: registers)
         }
     }
 
@@ -171,7 +193,7 @@ __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(WN
     // A tile: row-major, 256 B per rank row, lane (wave, l) fetches chunk (l & 15) ^ (row & 15) of
     // row 4 wave + l / 16 (+ RPP per pass).  The byte offsets of a lane's chunks from the tile's
     // first element do not change along K and are kept in registers.
-    constexpr int AQ = (RP + RPP - 1) / RPP;
+    constexpr int AQ = F32 ? 0 : (RP + RPP - 1) / RPP;         // (fp32 factors: the A tile takes the other way, below)
     constexpr int TPP = 4 * WN * WM, XJ = BM / TPP;             // tokens per staging pass, passes
     static_assert(BM % TPP == 0, "a staging pass covers whole token groups");
     const int xm0 = 4 * wave + (lane >> 4);
@@ -179,7 +201,7 @@ __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(WN
     const int xt0 = 4 * wave + ((lane >> 3) & 3);             // the lane's token in pass 0 (then + TPP per pass)
     const int xv = (lane & 7) ^ (xt0 & 7);                    // (TPP is a multiple of 8: the same in every pass)
     const int xkcol = 32 * (xv & 3) + 8 * (xv >> 2) + 16 * (lane >> 5);
-    uint32_t xo[XJ], ao[AQ];
+    uint32_t xo[XJ], ao[AQ + 1];
 #pragma unroll
     for (int j = 0; j < XJ; ++j) {
         const int m = min(m_blk + xt0 + TPP * j, M - 1);       // rows >= M: a copy of the last row, never stored
@@ -197,7 +219,7 @@ __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(WN
             for (int j = 0; j < XJ; ++j) lds_direct_16(Xtile + kb, xo[j], xl0 + p * XBUF + j * (TPP * 256));
 #pragma unroll
             for (int q = 0; q < AQ; ++q)
-                if (xm0 + RPP * q < a.r) lds_direct_16(a.A + kb, ao[q], al0 + p * ABUF + q * (RPP * 256));
+                if (xm0 + RPP * q < a.r) lds_direct_16(A16 + kb, ao[q], al0 + p * ABUF + q * (RPP * 256));
         } else {
             // ragged last tile: X chunks beyond K are fetched from further left (any finite data will
             // do: their weights are zero), A columns beyond K of a live rank row must read as zero
@@ -210,7 +232,7 @@ __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(WN
 #pragma unroll
             for (int q = 0; q < AQ; ++q) {
                 if (xm0 + RPP * q >= a.r) continue;
-                if (kb + 8 * xkc < K) lds_direct_16(a.A + kb, ao[q], al0 + p * ABUF + q * (RPP * 256));
+                if (kb + 8 * xkc < K) lds_direct_16(A16 + kb, ao[q], al0 + p * ABUF + q * (RPP * 256));
                 else *reinterpret_cast<u32x4 *>(As + p * ABUF + wave * 1024 + q * (RPP * 256) + 16 * lane) = u32x4{0u, 0u, 0u, 0u};
             }
         }
@@ -235,6 +257,42 @@ __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(WN
         for (int rho = 0; rho < R; ++rho) load_group<BITS>(crow[rho] + off, cw[rho]);
     };
 
+    // fp32 A tile of K tile kt: item id = 16 j + kc is columns 8 kc .. +8 of factor row j (columns beyond K: zero)
+    constexpr int AF = F32 ? ((RP / 3) * 16 + NT - 1) / NT : 0;
+    f32x4 af[AF + 1][2];
+    auto load_A32 = [&](int kt) {
+#pragma unroll
+        for (int q = 0; q < AF; ++q) {
+            const int id = tid + NT * q, j = id >> 4, k = kt * 128 + 8 * (id & 15);
+            af[q][0] = af[q][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (j < a.rf && k < K) {
+                const f32x4 *src = reinterpret_cast<const f32x4 *>(reinterpret_cast<const float *>(a.A) + (size_t)j * K + k);
+                af[q][0] = src[0];
+                af[q][1] = src[1];
+            }
+        }
+    };
+    auto store_A32 = [&](int p) {
+#pragma unroll
+        for (int q = 0; q < AF; ++q) {
+            const int id = tid + NT * q, j = id >> 4, kc = id & 15;
+            if (j >= a.rf) continue;
+            u32x4 hi, lo;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float x0 = af[q][e >> 1][2 * (e & 1)], x1 = af[q][e >> 1][2 * (e & 1) + 1];
+                const uint16_t h0 = bf16_bits(x0), h1 = bf16_bits(x1);
+                hi[e] = (uint32_t)h0 | ((uint32_t)h1 << 16);
+                lo[e] = (uint32_t)bf16_bits(x0 - bf16_to_f32(h0)) | ((uint32_t)bf16_bits(x1 - bf16_to_f32(h1)) << 16);
+            }
+#pragma unroll
+            for (int seg = 0; seg < 3; ++seg) {
+                const int row = seg * a.rf + j;
+                *reinterpret_cast<u32x4 *>(As + p * ABUF + row * 256 + ((kc ^ (row & 15)) * 16)) = seg == 1 ? lo : hi;
+            }
+        }
+    };
+
     f32x4 acc[R][MB];
 #pragma unroll
     for (int rho = 0; rho < R; ++rho)
@@ -244,6 +302,7 @@ __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(WN
     uint32_t cw[R][BITS], cwn[R][BITS];
     stage(kt0, 0);
     load_codes(kt0, cw);
+    if constexpr (F32) { load_A32(kt0); store_A32(0); }
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
 
@@ -261,6 +320,7 @@ __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(WN
             // (the main shape issues the loads of a whole next tile one by one from its pipeline steps)
             if (!kPipe || (kt + 2) * 128 > K) stage(kt + 1, p ^ 1);
             load_codes(kt + 1, cwn);
+            if constexpr (F32) load_A32(kt + 1);
         }
         const unsigned char *Xp = Xs + p * XBUF + wm * (16 * MB * 256);
         const unsigned char *Ap = As + p * ABUF;
@@ -363,7 +423,7 @@ __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(WN
                         if (i < XJ) {
                             lds_direct_16(Xtile + kbn, xo[i], xl0 + (p ^ 1) * XBUF + i * (TPP * 256));
                         } else if (xm0 + RPP * (i - XJ) < a.r) {
-                            lds_direct_16(a.A + kbn, ao[i - XJ], al0 + (p ^ 1) * ABUF + (i - XJ) * (RPP * 256));
+                            lds_direct_16(A16 + kbn, ao[i - XJ], al0 + (p ^ 1) * ABUF + (i - XJ) * (RPP * 256));
                         }
                     }
                     if (t + kAhead < 4 * MB) {
@@ -446,6 +506,8 @@ __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(WN
                 }
             }
         }
+        if constexpr (F32)
+            if (kt + 1 < kt1) store_A32(p ^ 1);
         __builtin_amdgcn_s_waitcnt(0);          // the next tile has landed in LDS, the next codes in registers
         __syncthreads();
 #pragma unroll
@@ -545,7 +607,9 @@ static int pf_ss(int r)
     return rp <= 1 ? 1 : rp <= 2 ? 2 : rp <= 4 ? 4 : 0;
 }
 
-bool prefill_fast_supported(const MatmulProblem &p) { return !p.f32fact && pf_ss(p.r) != 0; }
+static int pf_contraction(const MatmulProblem &p) { return p.f32fact ? 3 * p.r : p.r; }   // (fp32 factors: hi/lo parts)
+
+bool prefill_fast_supported(const MatmulProblem &p) { return pf_ss(pf_contraction(p)) != 0 && !(p.f32fact && p.tiled); }
 
 // Tile shape and the cut of the work.  Tile shapes: 256 tokens x 256 rows (8 waves of 32 rows x 256
 // tokens), 256 x 128 (8 waves), and for at most 128 tokens 128 x 256 (8 waves side by side) and
@@ -569,7 +633,7 @@ constexpr int kPfCUs = 256;
 static PfPlan pf_plan(const MatmulProblem &p, size_t avail)
 {
     PfPlan d;
-    d.ss = pf_ss(p.r);
+    d.ss = pf_ss(pf_contraction(p));
     const int ntiles_k = (p.K + 127) / 128;
     // Candidates (tokens x rows of a tile) with the measured time of one K tile of one workgroup at
     // 4 bits and rank 32, all CUs busy, clocks settled:
@@ -580,6 +644,7 @@ static PfPlan pf_plan(const MatmulProblem &p, size_t avail)
     struct Cand { int wm, R, wn, mb; double t; };
     const double rank_cost = d.ss == 1 ? 1.0 : d.ss == 2 ? 1.4 : 2.0;
     const Cand small_rank[4] = {{1, 2, 8, 16, 3.45}, {2, 2, 4, 8, 2.4}, {1, 2, 8, 8, 2.15}, {1, 2, 4, 8, 1.75}};
+    // fp32 factors (contraction 3 r) take them at any rank: the A tile of a 256-token tile has no registers to pass through.
     const Cand large_rank[2] = {{1, 2, 8, 8, 2.15 * rank_cost}, {1, 2, 4, 8, 1.75 * rank_cost}};
     const Cand *cands = d.ss == 1 ? small_rank : large_rank;
     const int ncands = d.ss == 1 ? 4 : 2;
@@ -588,7 +653,8 @@ static PfPlan pf_plan(const MatmulProblem &p, size_t avail)
     for (int i = 0; i < ncands; ++i) {
         const Cand &c = cands[i];
         const int tokens = 16 * c.mb * c.wm, rows = 16 * c.R * c.wn;
-        if (d.ss == 1 && (tokens == 128) != (p.M <= 128)) continue;
+        if (p.f32fact && d.ss == 4 && rows == 256) continue;     // (eight waves: 70 registers over, spilled)
+        if (p.f32fact ? tokens != 128 : d.ss == 1 && (tokens == 128) != (p.M <= 128)) continue;
         const long tiles = (long)((p.N + rows - 1) / rows) * ((p.M + tokens - 1) / tokens);
         const long units = tiles * ntiles_k;
         const size_t tile_bytes = (size_t)tokens * rows * sizeof(float);
@@ -630,16 +696,16 @@ size_t prefill_fast_workspace_bytes(const MatmulProblem &p, size_t limit)
     return pf_plan(p, limit).part_bytes;
 }
 
-template <int BITS, int SS, int WM, int R, int WN = 4, int MB = 8>
+template <int BITS, int SS, int WM, int R, int WN = 4, int MB = 8, bool F32 = false>
 static hipError_t launch_pf_t(const PrefillArgs &a, dim3 grid, hipStream_t st)
 {
     const size_t smem = (size_t)2 * (16 * MB * WM) * 256 + (size_t)2 * (32 * SS) * 256 + (size_t)(1 << (2 * BITS)) * kPfCopies * 4;
     static LdsOptIn lds_opt_in;
     {
-        const hipError_t e = allow_dynamic_lds(lds_opt_in, reinterpret_cast<const void *>(&prefill_kernel<BITS, SS, WM, R, WN, MB>), smem);
+        const hipError_t e = allow_dynamic_lds(lds_opt_in, reinterpret_cast<const void *>(&prefill_kernel<BITS, SS, WM, R, WN, MB, F32>), smem);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((prefill_kernel<BITS, SS, WM, R, WN, MB>), grid, dim3(64 * WN * WM), smem, st, a);
+    hipLaunchKernelGGL((prefill_kernel<BITS, SS, WM, R, WN, MB, F32>), grid, dim3(64 * WN * WM), smem, st, a);
     return hipGetLastError();
 }
 
@@ -653,10 +719,10 @@ hipError_t launch_prefill_fast(const MatmulProblem &p, void *part, size_t part_b
     a.X = (const uint16_t *)p.X;
     a.codes = (const uint8_t *)p.codes;
     a.codebook = p.codebook;
-    a.B = (const uint16_t *)p.B;
-    a.A = (const uint16_t *)p.A;
+    a.B = p.B;
+    a.A = p.A;
     a.Y = p.Y;
-    a.M = p.M; a.N = p.N; a.K = p.K; a.r = p.r;
+    a.M = p.M; a.N = p.N; a.K = p.K; a.r = pf_contraction(p); a.rf = p.r;
     a.y_f32 = p.f32out ? 1 : 0;
     a.row_bytes = p.K / 8 * p.bits;
     a.nt = d.nt;
@@ -670,7 +736,9 @@ hipError_t launch_prefill_fast(const MatmulProblem &p, void *part, size_t part_b
     hipError_t e = hipErrorInvalidValue;
 #define LORDS_PCASE(B_, S_)                                                                     \
     if (p.bits == B_ && ss == S_) {                                                              \
-        if (S_ == 1 && d.mb == 16) e = launch_pf_t<B_, 1, 1, 2, 8, 16>(a, grid, st);               \
+        if (p.f32fact) e = S_ < 4 && wn == 8 ? launch_pf_t<B_, (S_ < 4 ? S_ : 1), 1, 2, 8, 8, true>(a, grid, st)  \
+                                             : launch_pf_t<B_, S_, 1, 2, 4, 8, true>(a, grid, st);                \
+        else if (S_ == 1 && d.mb == 16) e = launch_pf_t<B_, 1, 1, 2, 8, 16>(a, grid, st);               \
         else if (S_ == 1 && wm == 2) e = launch_pf_t<B_, 1, 2, 2>(a, grid, st);                   \
         else if (wn == 8) e = launch_pf_t<B_, S_, 1, 2, 8>(a, grid, st);                         \
         else e = launch_pf_t<B_, S_, 1, 2>(a, grid, st);                                         \
