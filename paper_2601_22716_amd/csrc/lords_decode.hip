@@ -40,8 +40,9 @@ namespace lords {
 //             is then accumulated per lane in fp32 (v_fma_mix_f32) and the lanes are summed in
 //             LDS at the end.  No product MFMA, no bf16 rounding of the weights.
 // M1 = false: 2..16 tokens, product MFMAs as described at the top of the file.
-// BVEC      : bf16 factors with r % 8 == 0, so 8 rank entries of a row of B are one 16-byte load.
-template <int BITS, int SS, int G, bool BVEC, bool M1>
+// FM        : 0 = bf16 factors with r % 8 == 0 (8 rank entries of a row of B are one aligned operand), 1 = bf16 of any
+//             rank, 2 = fp32.
+template <int BITS, int SS, int G, int FM, bool M1>
 __global__ __launch_bounds__(256) void decode_kernel(DecodeArgs a)
 {
     constexpr int KT = 128 * G, AST = KT + 8, NL = 1 << BITS, NE = 1 << (2 * BITS);
@@ -74,18 +75,21 @@ __global__ __launch_bounds__(256) void decode_kernel(DecodeArgs a)
             const int grp = min((kb >> 5) + G * g + v, ngroups - 1);
             load_group<BITS>(a.codes + (size_t)n * a.row_bytes + (size_t)grp * (4 * BITS), cw[i][v]);
         }
-        if (BVEC) {
+        if (FM == 0) {
 #pragma unroll
             for (int s = 0; s < SS; ++s) {
                 const int jj0 = 32 * s + 8 * g;
                 Bop[i][s] = *reinterpret_cast<const bf16x8 *>(
                     reinterpret_cast<const uint16_t *>(a.f.B) + (size_t)n * a.f.r + (jj0 + 8 <= a.f.r ? jj0 : 0));
             }
+        } else if (FM == 1) {
+#pragma unroll
+            for (int s = 0; s < SS; ++s)
+                Bop[i][s] = __builtin_bit_cast(bf16x8, rank8_fetch(reinterpret_cast<const uint16_t *>(a.f.B), a.X, n, 32 * s + 8 * g, N, a.f.r));
         }
     };
-    // Factors that cannot be read as 16-byte operands (fp32, or a rank that is not a multiple of 8): the
-    // rows of B of this workgroup are one contiguous stretch of memory, fetched once with whole-line loads, laid
-    // out in LDS as operands (fp32: the parts [Bhi | Bhi | Blo] of lords_device.h) and read from there slab by slab.
+    // fp32 factors: the rows of B of this workgroup are one contiguous stretch of memory, fetched once with whole-line
+    // loads, laid out in LDS as operands (the parts [Bhi | Bhi | Blo] of lords_device.h) and read from there slab by slab.
     // (Gathered entry by entry at the point of use every slab paid a memory latency; with the A tile below
     // gathered the same way 512 x 256, 4 bits, fp32 rank 4, 4 tokens took 23.0 us, now 7;
     // 4096 x 4096 rank 16, 1 / 4 tokens 69 / 98 -> 17.3 / 25.8 us.)
@@ -99,34 +103,20 @@ __global__ __launch_bounds__(256) void decode_kernel(DecodeArgs a)
         __syncthreads();
         constexpr int FL = 8;                                               // loads in flight per thread
         for (int base = 0; base < total; base += 256 * FL) {
-            if (a.f.f32) {
-                float x[FL];
+            float x[FL];
 #pragma unroll
-                for (int q = 0; q < FL; ++q)
-                    x[q] = reinterpret_cast<const float *>(a.f.B)[(size_t)row0 * r + min(base + tid + 256 * q, total - 1)];
+            for (int q = 0; q < FL; ++q)
+                x[q] = reinterpret_cast<const float *>(a.f.B)[(size_t)row0 * r + min(base + tid + 256 * q, total - 1)];
 #pragma unroll
-                for (int q = 0; q < FL; ++q) {
-                    const int id = base + tid + 256 * q;
-                    if (id >= total) continue;
-                    const int row = (int)((unsigned)id / (unsigned)r), j = id - row * r;
-                    const uint16_t hi = bf16_bits(x[q]);
-                    uint16_t *d = Bs + row * BST + j;
-                    d[0] = hi;
-                    d[r] = hi;
-                    d[2 * r] = bf16_bits(x[q] - bf16_to_f32(hi));
-                }
-            } else {
-                uint16_t x[FL];
-#pragma unroll
-                for (int q = 0; q < FL; ++q)
-                    x[q] = reinterpret_cast<const uint16_t *>(a.f.B)[(size_t)row0 * r + min(base + tid + 256 * q, total - 1)];
-#pragma unroll
-                for (int q = 0; q < FL; ++q) {
-                    const int id = base + tid + 256 * q;
-                    if (id >= total) continue;
-                    const int row = (int)((unsigned)id / (unsigned)r);
-                    Bs[row * BST + (id - row * r)] = x[q];
-                }
+            for (int q = 0; q < FL; ++q) {
+                const int id = base + tid + 256 * q;
+                if (id >= total) continue;
+                const int row = (int)((unsigned)id / (unsigned)r), j = id - row * r;
+                const uint16_t hi = bf16_bits(x[q]);
+                uint16_t *d = Bs + row * BST + j;
+                d[0] = hi;
+                d[r] = hi;
+                d[2 * r] = bf16_bits(x[q] - bf16_to_f32(hi));
             }
         }
     };
@@ -135,13 +125,21 @@ __global__ __launch_bounds__(256) void decode_kernel(DecodeArgs a)
         for (int s = 0; s < SS; ++s)
             Bop[i][s] = *reinterpret_cast<const bf16x8 *>(Bs + (i * 16 + c) * BST + 32 * s + 8 * g);
     };
+    auto fix_B = [&](int i) {
+        const int n = min((slab0 + i) * 16 + c, N - 1);
+        const bool end = (slab0 + i) * 16 + 15 + 8 >= N;
+#pragma unroll
+        for (int s = 0; s < SS; ++s)
+            Bop[i][s] = __builtin_bit_cast(bf16x8, rank8_fix(__builtin_bit_cast(u32x4, Bop[i][s]), reinterpret_cast<const uint16_t *>(a.f.B), n,
+                                                             32 * s + 8 * g, N, a.f.r, end));
+    };
 
     // ---- 0. first loads of the row stream go out before any set-up --------------------------
 #pragma unroll
     for (int i = 0; i < kDepth; ++i) issue(i);
 
     if (tid < NL) cb[tid] = a.codebook[tid];
-    if (!BVEC) stage_B();                          // (visible to all waves after the barriers below)
+    if (FM == 2) stage_B();                          // (visible to all waves after the barriers below)
 
     // ---- 1. A columns of this wave's block -> a-operands of the scale MFMAs ------------------
     bf16x8 Aop[G][SS][8];
@@ -163,7 +161,7 @@ __global__ __launch_bounds__(256) void decode_kernel(DecodeArgs a)
 #pragma unroll
         for (int s = 0; s < SS; ++s) {
             __syncthreads();
-            if (!a.f.f32) {
+            if (FM != 2) {
                 u32x4 tmp[NCH];                       // all loads first, then the stores
 #pragma unroll
                 for (int q = 0; q < NCH; ++q) {
@@ -271,7 +269,8 @@ __global__ __launch_bounds__(256) void decode_kernel(DecodeArgs a)
         if (i < ns) {
             if (i + kDepth < kNS) issue(i + kDepth);
             __builtin_amdgcn_sched_barrier(0);     // keep the prefetch ahead of this slab's arithmetic
-            if (!BVEC) read_B(i);
+            if (FM == 1) fix_B(i);
+            if (FM == 2) read_B(i);
             float p0 = 0.f, p1 = 0.f, p2 = 0.f, p3 = 0.f;
 #pragma unroll
             for (int v = 0; v < G; ++v) {
@@ -442,22 +441,22 @@ size_t decode_fast_workspace_bytes(const MatmulProblem &p)
     return kCounterBytes + (size_t)d.splits * mchunk * p.N * sizeof(float);
 }
 
-template <int BITS, int SS, int G, bool BVEC, bool M1>
+template <int BITS, int SS, int G, int FM, bool M1>
 static hipError_t launch_decode_t(const DecodeArgs &a, dim3 grid, hipStream_t st)
 {
     constexpr int KT = 128 * G, AST = KT + 8;
     constexpr size_t A_BYTES = 4 * 32 * AST * 2, LUT_BYTES = (size_t)(1 << (2 * BITS)) * 256, RED_BYTES = 4 * kNS * 64 * 16;
     constexpr size_t R0 = A_BYTES > LUT_BYTES ? (A_BYTES > RED_BYTES ? A_BYTES : RED_BYTES)
                                               : (LUT_BYTES > RED_BYTES ? LUT_BYTES : RED_BYTES);
-    const size_t smem = R0 + 128 + (BVEC ? 0 : (size_t)a.ns * 16 * (32 * SS + 8) * 2);    // (rows of B that pass through LDS)
+    const size_t smem = R0 + 128 + (FM != 2 ? 0 : (size_t)a.ns * 16 * (32 * SS + 8) * 2);    // (rows of B that pass through LDS)
     static LdsOptIn lds_opt_in;
     if (smem > 48 * 1024) {
         // (asked for once per device: the most any launch of this instantiation takes)
-        const hipError_t e = allow_dynamic_lds(lds_opt_in, reinterpret_cast<const void *>(&decode_kernel<BITS, SS, G, BVEC, M1>),
-                                               R0 + 128 + (BVEC ? 0 : (size_t)kNS * 16 * (32 * SS + 8) * 2));
+        const hipError_t e = allow_dynamic_lds(lds_opt_in, reinterpret_cast<const void *>(&decode_kernel<BITS, SS, G, FM, M1>),
+                                               R0 + 128 + (FM != 2 ? 0 : (size_t)kNS * 16 * (32 * SS + 8) * 2));
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((decode_kernel<BITS, SS, G, BVEC, M1>), grid, dim3(256), smem, st, a);
+    hipLaunchKernelGGL((decode_kernel<BITS, SS, G, FM, M1>), grid, dim3(256), smem, st, a);
     return hipGetLastError();
 }
 
@@ -484,15 +483,14 @@ hipError_t launch_decode_fast(const MatmulProblem &p, void *workspace, hipStream
         a.nslabs = (p.N + 15) / 16;
         a.ns = d.ns;
         a.splits = d.splits;
-        a.b_vec_ok = (!p.f32fact && (p.r % 8) == 0) ? 1 : 0;
         const dim3 grid(d.chunks, 1, d.splits);
         hipError_t e = hipErrorInvalidValue;
-#define LORDS_DCASE(B_, S_, G_) \
-    if (p.bits == B_ && d.ss == S_) \
-        e = a.b_vec_ok ? (a.M == 1 ? launch_decode_t<B_, S_, G_, true, true>(a, grid, st)   \
-                                   : launch_decode_t<B_, S_, G_, true, false>(a, grid, st)) \
-                       : (a.M == 1 ? launch_decode_t<B_, S_, G_, false, true>(a, grid, st)  \
-                                   : launch_decode_t<B_, S_, G_, false, false>(a, grid, st));
+        const int fm = p.f32fact ? 2 : (p.r % 8) == 0 ? 0 : 1;
+#define LORDS_DCASE(B_, S_, G_)                                                                                         \
+    if (p.bits == B_ && d.ss == S_)                                                                                      \
+        e = fm == 0 ? (a.M == 1 ? launch_decode_t<B_, S_, G_, 0, true>(a, grid, st) : launch_decode_t<B_, S_, G_, 0, false>(a, grid, st))  \
+          : fm == 1 ? (a.M == 1 ? launch_decode_t<B_, S_, G_, 1, true>(a, grid, st) : launch_decode_t<B_, S_, G_, 1, false>(a, grid, st))  \
+                    : (a.M == 1 ? launch_decode_t<B_, S_, G_, 2, true>(a, grid, st) : launch_decode_t<B_, S_, G_, 2, false>(a, grid, st));
         LORDS_DCASE(2, 1, 2) LORDS_DCASE(2, 2, 1) LORDS_DCASE(2, 4, 1)
         LORDS_DCASE(3, 1, 2) LORDS_DCASE(3, 2, 1) LORDS_DCASE(3, 4, 1)
         LORDS_DCASE(4, 1, 2) LORDS_DCASE(4, 2, 1) LORDS_DCASE(4, 4, 1)

@@ -23,7 +23,6 @@ struct DecodeArgs {
     int nslabs;            // ceil(N / 16)
     int ns;                // slabs per workgroup, <= kNS
     int splits;            // gridDim.z
-    int b_vec_ok;
 };
 
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4_t;

@@ -115,6 +115,21 @@ __global__ __launch_bounds__(kMxThreads) __attribute__((amdgpu_waves_per_eu(2, 2
         voff[v] = a.tiled ? (uint32_t)(((grp >> 2) * 64 + (grp & 3) * 16 + c) * (4 * BITS)) : (uint32_t)grp * (4 * BITS);
     }
     const size_t slab_bytes = a.tiled ? (size_t)a.nct * 64 * (4 * BITS) : 0;
+    // Ranks that are not a multiple of 8 (BVEC = false): the 16 bytes from the lane's first entry on, at whatever
+    // alignment they have (rank8_* of lords_device.h).  Everything that depends on the slab alone stays in scalar
+    // registers: the load's base (eight entries before the slab's first row, so that no lane's offset is negative) and
+    // the last offset that is still inside B.
+    struct BRange { const uint16_t *base; uint32_t pre, limit; };
+    const bool btiny = !BVEC && rank8_tiny(N, r);
+    auto b_range = [&](int slab) __attribute__((always_inline)) -> BRange {
+        const uint64_t first = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane(slab) * 16u * (uint32_t)r, total = (uint64_t)(uint32_t)N * (uint32_t)r;
+        const uint64_t base = first >= 8 ? first - 8 : 0;
+        if (btiny) return BRange{a.X, 0u, 0u};
+        return BRange{ly.B + base, (uint32_t)(first - base), (uint32_t)min(total - 8 - base, (uint64_t)0x7fffffffu)};
+    };
+    uint32_t crj[SS];                                      // the lane's first entry, counted from the slab's first row
+#pragma unroll
+    for (int s = 0; s < SS; ++s) crj[s] = (uint32_t)(c * r + (32 * s + 8 * g < r ? 32 * s + 8 * g : 0));
     auto issue = [&](int i, int first, int last) __attribute__((always_inline)) {
         const int slab = min(first + i, last);
         const int n = min(slab * 16 + c, N - 1);
@@ -127,21 +142,28 @@ __global__ __launch_bounds__(kMxThreads) __attribute__((amdgpu_waves_per_eu(2, 2
                 const int jj0 = 32 * s + 8 * g;
                 Bop[i][s] = *reinterpret_cast<const bf16x8 *>(ly.B + (size_t)n * r + (jj0 + 8 <= r ? jj0 : 0));
             }
+        } else {
+            const BRange br = b_range(slab);
+#pragma unroll
+            for (int s = 0; s < SS; ++s) {
+                const uint32_t want = crj[s] + (uint32_t)br.pre;
+                const u32x4_any w = *reinterpret_cast<const u32x4_any *>(br.base + min(want, br.limit));
+                Bop[i][s] = __builtin_bit_cast(bf16x8, u32x4{w[0], w[1], w[2], w[3]});
+            }
         }
     };
-    // rank not a multiple of 8: the B operand is gathered entry by entry at the point of use
-    auto gather_B = [&](int i) __attribute__((always_inline)) {
-        const int n = min((slab0 + i) * 16 + c, N - 1);
+    // ... and at the point of use entries of the next row become zero (rows >= N are dropped at the store)
+    auto fix_B = [&](int i) __attribute__((always_inline)) {
+        const int slab = slab0 + i;
 #pragma unroll
         for (int s = 0; s < SS; ++s) {
-            typedef __attribute__((__vector_size__(8 * sizeof(short)))) short s16x8;
-            s16x8 t;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int j = 32 * s + 8 * g + e;
-                t[e] = j < r ? (short)ly.B[(size_t)n * r + j] : (short)0;
+            u32x4 t = __builtin_bit_cast(u32x4, Bop[i][s]);
+            if (slab * 16 + 15 + 8 >= N) {                 // (the same in all lanes: only here may a load have been moved back)
+                const BRange br = b_range(slab);
+                const uint32_t want = crj[s] + br.pre;
+                t = rank8_shift(t, btiny ? 0 : (int)min(want - min(want, br.limit), 7u));
             }
-            Bop[i][s] = __builtin_bit_cast(bf16x8, t);
+            Bop[i][s] = __builtin_bit_cast(bf16x8, rank8_keep(t, r - (32 * s + 8 * g)));
         }
     };
 
@@ -185,6 +207,11 @@ __global__ __launch_bounds__(kMxThreads) __attribute__((amdgpu_waves_per_eu(2, 2
 #pragma unroll
     for (int i = 0; i < kDepth; ++i) issue(i, slab0, max(slab0, min(slab0 + ly.ns, ly.nslabs) - 1));
     __builtin_amdgcn_sched_barrier(0);
+    if (btiny) {                                           // (one slab is all there is: its entries one by one)
+#pragma unroll
+        for (int s = 0; s < SS; ++s)
+            Bop[0][s] = __builtin_bit_cast(bf16x8, rank8_gather(ly.B + (size_t)min(c, N - 1) * r, 32 * s + 8 * g, r));
+    }
 
     // ---- 2. A tile and level table into LDS; scale a-operands back, transposed -----------------
 #pragma unroll
@@ -250,7 +277,7 @@ __global__ __launch_bounds__(kMxThreads) __attribute__((amdgpu_waves_per_eu(2, 2
             if (i < nsw) {
                 if (i + kDepth < kNS) issue(i + kDepth, slab0, slab0 + nsw - 1);
                 __builtin_amdgcn_sched_barrier(0);     // keep the prefetch ahead of this slab's arithmetic
-                if (!BVEC) gather_B(i);
+                if (!BVEC) fix_B(i);
                 f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int v = 0; v < G; ++v) {
@@ -327,15 +354,17 @@ __global__ __launch_bounds__(kMxThreads) __attribute__((amdgpu_waves_per_eu(2, 2
                 s[0] += t[0]; s[1] += t[1]; s[2] += t[2]; s[3] += t[3];
             }
             if (m >= M) continue;
-            if (meet && (N & 3) == 0) {
-                // the lane's four sums are four neighbouring rows of one token: one 16-byte store
-                const int nb = row0 + (hf * ly.ns + i) * 16 + 4 * gl;
-                if (nb < N) store16_agent(ly.partial + ((size_t)blockIdx.z * M + m) * N + nb, s);
+            // the lane's four sums are four neighbouring rows of one token: one 16-byte store, at any multiple of 4
+            // bytes (with scalar stores where N % 4 != 0, 14337 x 4096 at 16 tokens took 24.1 us, now 17.6)
+            const int nb = row0 + (hf * ly.ns + i) * 16 + 4 * gl;
+            if (nb + 3 < N) {
+                if (meet) store16_agent(ly.partial + ((size_t)blockIdx.z * M + m) * N + nb, s);
+                else store_out4(ly.Y, (size_t)m * N + nb, s, a.y_f32);
                 continue;
             }
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int n = row0 + (hf * ly.ns + i) * 16 + 4 * gl + e;
+            for (int e = 0; e < 4; ++e) {                  // (the matrix ends inside the four)
+                const int n = nb + e;
                 if (n >= N) continue;
                 if (meet)
                     __hip_atomic_store(&ly.partial[((size_t)blockIdx.z * M + m) * N + n], s[e], __ATOMIC_RELAXED,
@@ -374,8 +403,7 @@ __global__ __launch_bounds__(kMxThreads) __attribute__((amdgpu_waves_per_eu(2, 2
         const int P = a.parts;
         const int rank = (int)blockIdx.z + ((pair && li == 1) ? a.splits : 0);
         const int mine = rank % P;
-        const bool vec = (N & 3) == 0;
-        const int T = vec ? M * (rows / 4) : M * rows;            // outputs (of four rows, or of one) per chunk
+        const int T = M * (rows / 4);                             // outputs (of four rows each) per chunk
         const int ipp = (T + P - 1) / P;                          // the largest share
         typedef int i32x4 __attribute__((ext_vector_type(4)));
         i32x4 *ent = reinterpret_cast<i32x4 *>(As);               // one entry per ticket of a batch (the sums' region is free now)
@@ -399,10 +427,11 @@ __global__ __launch_bounds__(kMxThreads) __attribute__((amdgpu_waves_per_eu(2, 2
                 __syncthreads();
                 // output q of a chunk whose first row is row0: the column blocks added in order, Y written
                 auto reduce_item = [&](int q, int row0) __attribute__((always_inline)) {
-                    if (vec) {
+                    const int m = q / (rows / 4), n0 = row0 + 4 * (q - m * (rows / 4));
+                    if (n0 >= N) return;
+                    if (n0 + 3 < N) {
                         // four neighbouring rows, 16-byte loads, up to eight column blocks in flight
-                        const int m = q / (rows / 4), n = row0 + 4 * (q - m * (rows / 4));
-                        if (n >= N) return;
+                        const int n = n0;
                         // ZB column blocks in one round trip, added in order.  Straight-line code per count: blocks
                         // beyond the last are not loaded at all (every device-coherent load costs its full price,
                         // also when it repeats an address), and no load's target register is merged with another
@@ -441,19 +470,10 @@ __global__ __launch_bounds__(kMxThreads) __attribute__((amdgpu_waves_per_eu(2, 2
 #pragma unroll
                             for (int e4 = 0; e4 < 4; ++e4) sv[e4] = sv[e4] / (1.0f + __expf(-sv[e4])) * up[e4];
                         }
-                        if (a.y_f32) {
-                            *reinterpret_cast<f32x4 *>(reinterpret_cast<float *>(Yout) + (size_t)m * N + n) = sv;
-                        } else {
-                            typedef __attribute__((__vector_size__(2 * sizeof(uint32_t)))) uint32_t u32x2;
-                            u32x2 o;
-                            o[0] = (uint32_t)bf16_bits(sv[0]) | ((uint32_t)bf16_bits(sv[1]) << 16);
-                            o[1] = (uint32_t)bf16_bits(sv[2]) | ((uint32_t)bf16_bits(sv[3]) << 16);
-                            *reinterpret_cast<u32x2 *>(reinterpret_cast<uint16_t *>(Yout) + (size_t)m * N + n) = o;
-                        }
+                        store_out4(Yout, (size_t)m * N + n, sv, a.y_f32);
                         return;
                     }
-                    const int m = q / rows, n = row0 + (q - m * rows);
-                    if (n >= N) return;
+                    for (int n = n0; n < N; ++n) {         // (the matrix ends inside the four)
                     auto add_blocks = [&](const float *Pp) __attribute__((always_inline)) -> float {
                         float acc = 0.f;
                         for (int z0 = 0; z0 < a.splits; z0 += 8) {
@@ -477,6 +497,7 @@ __global__ __launch_bounds__(kMxThreads) __attribute__((amdgpu_waves_per_eu(2, 2
                     }
                     if (a.y_f32) reinterpret_cast<float *>(Yout)[(size_t)m * N + n] = sc;
                     else reinterpret_cast<uint16_t *>(Yout)[(size_t)m * N + n] = bf16_bits(sc);
+                    }
                 };
                 if (P == 1) {
                     for (int t = 0; t < nt; ++t) {

@@ -89,6 +89,77 @@ __device__ __forceinline__ uint16_t factorB_bits(const Factors &f, int n, int jj
     return seg == 2 ? bf16_bits(x - bf16_to_f32(hi)) : hi;
 }
 
+// Eight rank entries j0 .. j0 + 7 of row n of a bf16 factor with ANY number r of entries per row (row-major, N rows):
+// one 16-byte load at the row's own alignment (2 bytes; global loads need none on gfx950) instead of eight 2-byte
+// gathers, entries of the next row masked off afterwards.  At the array's end the load is moved back so that it stays
+// inside and its entries are shifted into place.  The fetch can be issued far ahead; rank8_fix belongs to the use.
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
+// (A factor of fewer than eight entries in all has no 16 bytes to read: the fetch then reads them from `spare`, any
+// readable 16 bytes, so that it stays one load without a branch, and rank8_fix gathers the entries.)
+__device__ __forceinline__ bool rank8_tiny(int N, int r) { return N < 8 && N * r < 8; }
+__device__ __forceinline__ u32x4 rank8_fetch(const uint16_t *B, const uint16_t *spare, int n, int j0, int N, int r)
+{
+    const uint16_t *base = rank8_tiny(N, r) ? spare : B;                     // (the same in all lanes, as is `last`)
+    const uint64_t last = rank8_tiny(N, r) ? 0 : (uint64_t)N * (uint32_t)r - 8;
+    const uint64_t at = (uint64_t)(uint32_t)n * (uint32_t)r + (uint32_t)(j0 < r ? j0 : 0);
+    const u32x4_any w = *reinterpret_cast<const u32x4_any *>(base + (at < last ? at : last));
+    return u32x4{w[0], w[1], w[2], w[3]};
+}
+// Entries of eight that lie beyond the row's end (v of them belong to it) become zero.
+__device__ __forceinline__ u32x4 rank8_keep(u32x4 t, int v)
+{
+#pragma unroll
+    for (int e = 0; e < 4; ++e) t[e] = v >= 2 * e + 2 ? t[e] : v == 2 * e + 1 ? t[e] & 0xffffu : 0u;
+    return t;
+}
+// The entries of a load that was moved back by `back` (0 .. 7) come to the front.
+__device__ __forceinline__ u32x4 rank8_shift(u32x4 t, int back)
+{
+    uint64_t lo = (uint64_t)t[0] | ((uint64_t)t[1] << 32), hi = (uint64_t)t[2] | ((uint64_t)t[3] << 32);
+    if (back >= 4) { lo = hi; hi = 0; back -= 4; }
+    if (back != 0) { lo = (lo >> (16 * back)) | (hi << (64 - 16 * back)); hi >>= 16 * back; }
+    return u32x4{(uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32)};
+}
+__device__ __forceinline__ u32x4 rank8_gather(const uint16_t *row, int j0, int r)
+{
+    u32x4 t = u32x4{0u, 0u, 0u, 0u};
+#pragma unroll 1
+    for (int e = 0; e < 8; ++e) {
+        const uint32_t w = j0 + e < r ? (uint32_t)row[j0 + e] << (16 * (e & 1)) : 0u;
+        t[0] |= (e >> 1) == 0 ? w : 0u;
+        t[1] |= (e >> 1) == 1 ? w : 0u;
+        t[2] |= (e >> 1) == 2 ? w : 0u;
+        t[3] |= (e >> 1) == 3 ? w : 0u;
+    }
+    return t;
+}
+// `end`: true where a row within eight of the last may be among the lanes' (the shifting is skipped elsewhere).
+__device__ __forceinline__ u32x4 rank8_fix(u32x4 t, const uint16_t *B, int n, int j0, int N, int r, bool end)
+{
+    if (end) {
+        if (rank8_tiny(N, r)) return rank8_gather(B + (size_t)n * r, j0, r);
+        const int rem = min(N - n, 8) * r - j0;              // entries from here to the array's end (or enough of them)
+        t = rank8_shift(t, j0 < r && rem < 8 ? 8 - rem : 0);
+    }
+    return rank8_keep(t, r - j0);
+}
+
+// Four neighbouring outputs of one token, at the alignment their address happens to have (N need not be a multiple of
+// four): one 16- or 8-byte store.
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(2)));
+__device__ __forceinline__ void store_out4(void *Y, size_t at, f32x4 v, int y_f32)
+{
+    if (y_f32) {
+        *reinterpret_cast<f32x4_any *>(reinterpret_cast<float *>(Y) + at) = f32x4_any{v[0], v[1], v[2], v[3]};
+    } else {
+        u32x2_any o;
+        o[0] = (uint32_t)bf16_bits(v[0]) | ((uint32_t)bf16_bits(v[1]) << 16);
+        o[1] = (uint32_t)bf16_bits(v[2]) | ((uint32_t)bf16_bits(v[3]) << 16);
+        *reinterpret_cast<u32x2_any *>(reinterpret_cast<uint16_t *>(Y) + at) = o;
+    }
+}
+
 // fp32 sums that pass from one workgroup to another through memory: 16-byte stores and loads at
 // agent scope (sc1: written through to, and read from, the level all XCDs share), so that the hand-over
 // needs no write-back or invalidation of a whole L2.  Written as assembly because the language

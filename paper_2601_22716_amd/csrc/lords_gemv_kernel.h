@@ -258,14 +258,15 @@ __global__ __launch_bounds__(kGvThreads) __attribute__((amdgpu_waves_per_eu(2, 2
             const u32x4 w = *reinterpret_cast<const u32x4 *>(ly.B + (size_t)n * r + (j0 < r ? j0 : 0));
             if (j0 < r) t = w;
         } else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int j = j0 + e;
-                const uint32_t w = ly.B[(size_t)n * r + (j < r ? j : 0)];
-                if (j < r) t[e >> 1] |= w << (16 * (e & 1));
-            }
+            t = rank8_fetch(ly.B, a.X, n, j0, N, r);
         }
         return t;
+    };
+    // ... and what is left to do with it once it is there (ranks that are not a multiple of 8)
+    auto fix_B = [&](int q, u32x4 t) __attribute__((always_inline)) -> u32x4 {
+        if (BVEC) return t;
+        const int n = min(s0 * 16 + q / BCH, N - 1), j0 = 8 * (q % BCH);
+        return rank8_fix(t, ly.B, n, j0, N, r, n + 8 >= N);
     };
 
     GV_STAMP_DECL;
@@ -283,7 +284,7 @@ __global__ __launch_bounds__(kGvThreads) __attribute__((amdgpu_waves_per_eu(2, 2
     u32x4 Braw[kGvBRounds];
 #pragma unroll
     for (int qq = 0; qq < kGvBRounds; ++qq) Braw[qq] = load_B(min(tid + kGvThreads * qq, nbch - 1));
-    for (int q = tid + kGvThreads * kGvBRounds; q < nbch; q += kGvThreads) *reinterpret_cast<u32x4 *>(Bs + 8 * q) = load_B(q);
+    for (int q = tid + kGvThreads * kGvBRounds; q < nbch; q += kGvThreads) *reinterpret_cast<u32x4 *>(Bs + 8 * q) = fix_B(q, load_B(q));
     __builtin_amdgcn_sched_barrier(0);
     if (wave < kGvBuilders) {
         uint32_t *lut32 = reinterpret_cast<uint32_t *>(smem);
@@ -381,7 +382,7 @@ __global__ __launch_bounds__(kGvThreads) __attribute__((amdgpu_waves_per_eu(2, 2
 #pragma unroll
     for (int qq = 0; qq < kGvBRounds; ++qq) {
         if (kGvThreads * qq < nbch) {
-            if (tid + kGvThreads * qq < nbch) *reinterpret_cast<u32x4 *>(Bs + 8 * (tid + kGvThreads * qq)) = Braw[qq];
+            if (tid + kGvThreads * qq < nbch) *reinterpret_cast<u32x4 *>(Bs + 8 * (tid + kGvThreads * qq)) = fix_B(tid + kGvThreads * qq, Braw[qq]);
             if (lane == 0) __hip_atomic_store(&bflag[qq * kGvWaves + wave], 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
         }
     }

@@ -575,16 +575,8 @@ __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(WN
 #pragma unroll
         for (int rho = 0; rho < R; ++rho) {
             const int n = n_wave + 16 * rho + 4 * g;
-            if (n + 3 < N && (N & 3) == 0) {
-                if (a.y_f32) {
-                    *reinterpret_cast<f32x4 *>(reinterpret_cast<float *>(Yp) + (size_t)m * N + n) = acc[rho][mb];
-                } else {
-                    typedef __attribute__((__vector_size__(2 * sizeof(uint32_t)))) uint32_t u32x2;
-                    u32x2 o;
-                    o[0] = (uint32_t)bf16_bits(acc[rho][mb][0]) | ((uint32_t)bf16_bits(acc[rho][mb][1]) << 16);
-                    o[1] = (uint32_t)bf16_bits(acc[rho][mb][2]) | ((uint32_t)bf16_bits(acc[rho][mb][3]) << 16);
-                    *reinterpret_cast<u32x2 *>(reinterpret_cast<uint16_t *>(Yp) + (size_t)m * N + n) = o;
-                }
+            if (n + 3 < N) {
+                store_out4(Yp, (size_t)m * N + n, acc[rho][mb], a.y_f32);
             } else {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
