@@ -166,7 +166,10 @@ __device__ __forceinline__ void store_out4(void *Y, size_t at, f32x4 v, int y_f3
 // offers agent-scope atomic accesses of at most 8 bytes; the waits are placed by hand.
 __device__ __forceinline__ void store16_agent(float *p, f32x4 v)
 {
-    asm volatile("global_store_dwordx4 %0, %1, off sc1" :: "v"(p), "v"(v) : "memory");
+    // (A store of more than 8 bytes reads its data a cycle late: a vector instruction right behind it must not write those
+    // registers.  The compiler keeps that distance for stores it knows, not for this one: a copy out of an accumulation
+    // register right behind the store changed the first of its four floats.)
+    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" :: "v"(p), "v"(v) : "memory");
 }
 __device__ __forceinline__ f32x4 load16_agent(const float *p)
 {
