@@ -37,6 +37,7 @@
 //
 // Level look-up: two codes index an LDS table of fp16 pairs, 8 copies (address =
 // index*32 + (lane%8)*4); v_fma_mix_f32 multiplies fp16 level by fp32 scale; one rounding to bf16.
+#include <type_traits>
 #include "lords_decode_common.h"
 
 namespace lords {
@@ -521,14 +522,23 @@ __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(WN
     // always the first part of its workgroup, so it waits for nothing); the part that does start there
     // is the last one of its workgroup, collects the others in column order and writes Y.  The sum of a
     // tile is therefore taken in a fixed order whatever the timing.
+    // Of a 128-token tile that holds at most 64 tokens only the first four of the eight token blocks travel (the
+    // buffers keep their size).  14336 x 4096, 4 bits, rank 32, 17 / 40 / 64 tokens: 37.6 / 37.3 / 37.5 -> 30.4 / 30.2 / 30.3 us.
+    // (Exactly the blocks in use, with a branch for each, was no faster there and cost 2-9 % at 100 and 128 tokens; in
+    // 256-token tiles the second form cost registers: 10 % at 2048 tokens.)
     constexpr int kPartFloats = R * MB * NT * 4;
+    const bool few = MB == 8 && M - m_wave <= 64;
     if (kt0 != 0) {
         float *dst = a.part + (size_t)wg * kPartFloats + tid * 4;
         asm volatile("" : "+v"(dst));        // (addresses are made here, not kept in registers over the K loop)
 #pragma unroll
-        for (int rho = 0; rho < R; ++rho)
+        for (int half = 0; half < 2; ++half)
+            if (half == 0 || !few)
 #pragma unroll
-            for (int mb = 0; mb < MB; ++mb) store16_agent(dst + (rho * MB + mb) * (NT * 4), acc[rho][mb]);
+                for (int rho = 0; rho < R; ++rho)
+#pragma unroll
+                    for (int mb = half * (MB / 2); mb < (half + 1) * (MB / 2); ++mb)
+                        store16_agent(dst + (rho * MB + mb) * (NT * 4), acc[rho][mb]);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         if (tid == 0) __hip_atomic_fetch_add(a.arrived + T, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
@@ -545,26 +555,36 @@ __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(WN
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         }
         __syncthreads();
-        for (int j = 1; j <= others; ++j) {
-            const float *src = a.part + (size_t)(wg + j) * kPartFloats + tid * 4;
-            asm volatile("" : "+v"(src));
-            // (sixteen loads in flight: what the registers beside the accumulators hold; each wait is a
-            // round trip to memory)
-            constexpr int kBatch = (R * MB) % 16 == 0 ? 16 : 8;
-            static_assert((R * MB) % kBatch == 0, "whole batches");
+        // (`few` is decided outside the loop: inside, the accumulators changed register files with every part)
+        auto add_parts = [&](auto nr, auto nb) __attribute__((always_inline)) {
+            constexpr int NR = decltype(nr)::value, NBK = decltype(nb)::value;
+            for (int j = 1; j <= others; ++j) {
+                const float *src = a.part + (size_t)(wg + j) * kPartFloats + tid * 4;
+                asm volatile("" : "+v"(src));
+                // sixteen loads in flight (eight for half a tile): what the registers beside the accumulators
+                // hold; each wait is a round trip to memory
 #pragma unroll
-            for (int b0 = 0; b0 < R * MB; b0 += kBatch) {
-                f32x4 t[kBatch];
+                for (int rho0 = 0; rho0 < R; rho0 += NR) {
+                    f32x4 t[NR * NBK];
 #pragma unroll
-                for (int i = 0; i < kBatch; ++i) t[i] = load16_agent(src + (b0 + i) * (NT * 4));
-                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                    for (int q = 0; q < NR * NBK; ++q) t[q] = load16_agent(src + ((rho0 + q / NBK) * MB + q % NBK) * (NT * 4));
+                    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 #pragma unroll
-                for (int i = 0; i < kBatch; ++i) {
-                    asm volatile("" : "+v"(t[i]));               // (not before the wait)
+                    for (int q = 0; q < NR * NBK; ++q) {
+                        asm volatile("" : "+v"(t[q]));                                  // (not before the wait)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) acc[(b0 + i) / MB][(b0 + i) % MB][e] += t[i][e];
+                        for (int e = 0; e < 4; ++e) acc[rho0 + q / NBK][q % NBK][e] += t[q][e];
+                    }
                 }
             }
+        };
+        static_assert(R == 2 && (MB == 8 || MB == 16), "sixteen accumulator blocks a round trip");
+        if constexpr (MB == 16) {
+            add_parts(std::integral_constant<int, 1>{}, std::integral_constant<int, 16>{});
+        } else if (few) {
+            add_parts(std::integral_constant<int, 2>{}, std::integral_constant<int, 4>{});
+        } else {
+            add_parts(std::integral_constant<int, 2>{}, std::integral_constant<int, 8>{});
         }
     }
     void *Yp = a.Y;
@@ -669,7 +689,8 @@ static PfPlan pf_plan(const MatmulProblem &p, size_t avail)
             if (bytes > avail) continue;
             long written = 0;                                                    // parts that start inside a tile
             for (long b = per; b < units; b += per) written += (b % ntiles_k) != 0;
-            const double mb_written = (double)written * tile_bytes / 1048576.0;
+            const double full = p.M <= 64 && tokens == 128 ? 0.5 : 1.0;          // (half a tile travels)
+            const double mb_written = (double)written * tile_bytes * full / 1048576.0;
             const double cost = per >= ntiles_k ? per * c.t * 1.08 + 4.0 + mb_written / 2.4
                                                 : per * c.t + 4.0 + mb_written / 1.2;
             if (cost < best) { best = cost; d.wm = c.wm; d.R = c.R; d.wn = c.wn; d.mb = c.mb; d.per = per; d.part_bytes = bytes; }
