@@ -59,6 +59,7 @@ struct PrefillArgs {
     int tiled;             // codes in the slab-tile layout: tile (slab, K tile) contiguous, chunk = 16 g + c
     int per;               // work units (one K tile of one output tile) per workgroup; units are numbered tile by tile
     uint32_t *arrived;     // per output tile: parts handed over so far (zero before and after a launch)
+    const float *gate;     // M x N fp32 or null: Y = silu(gate) * (the product) instead of the product
     float *part;           // per workgroup: the accumulators of a part that does not start at the tile's first column
 };
 
@@ -588,24 +589,50 @@ __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(WN
         }
     }
     void *Yp = a.Y;
+    auto store_block = [&](int rho, int mb, f32x4 v) __attribute__((always_inline)) {
+        const int m = m_wave + 16 * mb + c, n = n_wave + 16 * rho + 4 * g;
+        if (m >= M) return;
+        if (n + 3 < N) {
+            store_out4(Yp, (size_t)m * N + n, v, a.y_f32);
+        } else {
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb) {
-        const int m = m_wave + 16 * mb + c;
-        if (m >= M) continue;
-#pragma unroll
-        for (int rho = 0; rho < R; ++rho) {
-            const int n = n_wave + 16 * rho + 4 * g;
-            if (n + 3 < N) {
-                store_out4(Yp, (size_t)m * N + n, acc[rho][mb], a.y_f32);
-            } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    if (n + e >= N) continue;
-                    if (a.y_f32) reinterpret_cast<float *>(Yp)[(size_t)m * N + n + e] = acc[rho][mb][e];
-                    else reinterpret_cast<uint16_t *>(Yp)[(size_t)m * N + n + e] = bf16_bits(acc[rho][mb][e]);
-                }
+            for (int e = 0; e < 4; ++e) {
+                if (n + e >= N) continue;
+                if (a.y_f32) reinterpret_cast<float *>(Yp)[(size_t)m * N + n + e] = v[e];
+                else reinterpret_cast<uint16_t *>(Yp)[(size_t)m * N + n + e] = bf16_bits(v[e]);
             }
         }
+    };
+    if (a.gate) {
+        // A gate/up pair: this is the up product, the gate's fp32 sums lie in memory.  Loads of eight token blocks in
+        // flight; addresses are clamped to the matrix's rows, a load of its last columns may reach 12 bytes beyond
+        // them (the buffer is that much longer), and what such loads bring is not stored.
+        constexpr int GB = 8;
+#pragma unroll
+        for (int rho = 0; rho < R; ++rho) {
+            const float *col = a.gate + min(n_wave + 16 * rho + 4 * g, N - 1);
+#pragma unroll
+            for (int b0 = 0; b0 < MB; b0 += GB) {
+                int m0 = m_wave + 16 * b0 + c;
+                asm volatile("" : "+v"(m0));                  // (addresses of one batch at a time: registers)
+                f32x4_any t[GB];
+#pragma unroll
+                for (int i = 0; i < GB; ++i) t[i] = *reinterpret_cast<const f32x4_any *>(col + (size_t)min(m0 + 16 * i, M - 1) * N);
+#pragma unroll
+                for (int i = 0; i < GB; ++i) {
+                    f32x4 v;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[e] = t[i][e] / (1.0f + __expf(-t[i][e])) * acc[rho][b0 + i][e];
+                    store_block(rho, b0 + i, v);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    } else {
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int rho = 0; rho < R; ++rho) store_block(rho, mb, acc[rho][mb]);
     }
     }   // parts of this workgroup
 }
@@ -724,7 +751,7 @@ static hipError_t launch_pf_t(const PrefillArgs &a, dim3 grid, hipStream_t st)
 
 // `part`: part_bytes bytes of scratch (what prefill_fast_workspace_bytes returned for a limit of at most
 // part_bytes), `zeroed`: kZeroBytes of device memory, zero when handed over and left at zero.
-hipError_t launch_prefill_fast(const MatmulProblem &p, void *part, size_t part_bytes, void *zeroed, hipStream_t st)
+hipError_t launch_prefill_fast(const MatmulProblem &p, void *part, size_t part_bytes, void *zeroed, hipStream_t st, const float *gate)
 {
     const PfPlan d = pf_plan(p, (part && zeroed) ? part_bytes : 0);
     const int ss = d.ss, wm = d.wm, wn = d.wn;
@@ -745,6 +772,7 @@ hipError_t launch_prefill_fast(const MatmulProblem &p, void *part, size_t part_b
     a.per = d.per;
     a.arrived = (uint32_t *)zeroed;
     a.part = (float *)part;
+    a.gate = gate;
     const dim3 grid(((d.wgs + 7) / 8) * 8);
     hipError_t e = hipErrorInvalidValue;
 #define LORDS_PCASE(B_, S_)                                                                     \

@@ -80,3 +80,24 @@ def test_gate_up_and_batched(gpu, M, N):
     rms = lambda a: float(np.sqrt(np.mean(a * a)))
     bound = 1.05 * Y_MAX_TOL * (1.1 * rms(G) * np.abs(U) + rms(U) * np.abs(silu)) + 1e-6
     assert np.all(np.abs(H.cpu().numpy() - silu * U) <= bound)
+
+
+@pytest.mark.parametrize("M,N,K,r,bits,fdt", [(17, 1, 288, 8, 4, "bf16"), (40, 131, 544, 32, 2, "bf16"), (130, 257, 416, 48, 3, "f32" ),
+                                              (130, 514, 1056, 13, 3, "f32"), (257, 1027, 416, 32, 4, "bf16"), (2049, 66, 160, 96, 2, "bf16")])
+def test_gate_up_of_many_tokens(gpu, M, N, K, r, bits, fdt):
+    """The up product's large-M kernel reads the gate's sums four columns at a time and multiplies by their silu: last
+    rows and columns, half tiles, a second chunk of one token; fp32 contractions beyond 128 take the element-wise pass."""
+    import torch
+    import paper_2601_22716_amd as L
+    cg = li.make_case("tiny", M=M, N=N, K=K, bits=bits, r=r, factor_dtype=fdt, seed=25)
+    cu = li.make_case("tiny", M=M, N=N, K=K, bits=bits, r=r, factor_dtype=fdt, seed=26)
+    dg, du = gpu.DeviceCase(cg), gpu.DeviceCase(cu)
+    G = onp.matmul(cg.X_f32, cg.codes, cg.codebook, cg.B_f32, cg.A_f32, bits)
+    U = onp.matmul(cg.X_f32, cu.codes, cu.codebook, cu.B_f32, cu.A_f32, bits)
+    H = torch.full((M, N), float("nan"), device="cuda")
+    L.lords_gate_up(dg.X, dg.codes, dg.B, dg.A, du.codes, du.B, du.A, dg.codebook, H, M, N, K, r, bits)
+    torch.cuda.synchronize()
+    silu = G / (1 + np.exp(-G))
+    rms = lambda a: float(np.sqrt(np.mean(a * a)))
+    bound = 1.05 * Y_MAX_TOL * (1.1 * rms(G) * np.abs(U) + rms(U) * np.abs(silu)) + 1e-6
+    assert np.all(np.abs(H.cpu().numpy() - silu * U) <= bound)
