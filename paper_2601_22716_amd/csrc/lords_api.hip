@@ -177,7 +177,17 @@ int run_batched(const lords::BatchedProblem &bp, void *stream)
         if (rc != LORDS_OK) return rc;
         return lords::launch_decode_gemv_batched(bp, ws.zeroed(), (hipStream_t)stream) == hipSuccess ? LORDS_OK : LORDS_ERR_LAUNCH;
     }
-    if (!lords::decode_mx_batched_supported(bp)) return -1;
+    if (!lords::decode_mx_batched_supported(bp)) {
+        // many tokens: the large-M kernel, if every matrix alone would go there (and their scratch is to be had together)
+        for (int l = 0; l < bp.L; ++l) {
+            const lords::MatmulProblem p{bp.X, bp.codes[l], bp.codebook, bp.B[l], bp.A[l], bp.Y[l], bp.M, bp.N[l], bp.K, bp.r, bp.bits, bp.f32fact, bp.f32out};
+            if (is_decode(resolve_path(LORDS_PATH_AUTO, p))) return -1;
+        }
+        if (!lords::prefill_batched_supported(bp)) return -1;
+        WsView ws;
+        if (get_workspace(kFront + lords::prefill_batched_workspace_bytes(bp), stream, &ws) != LORDS_OK) return -1;
+        return lords::launch_prefill_batched(bp, ws.scratch(), ws.zeroed(), (hipStream_t)stream) == hipSuccess ? LORDS_OK : LORDS_ERR_LAUNCH;
+    }
     WsView ws;
     const int rc = get_workspace(lords::kZeroBytes + lords::decode_mx_batched_workspace_bytes(bp), stream, &ws);
     if (rc != LORDS_OK) return rc;
@@ -459,7 +469,7 @@ int lords_matmul_batched(const void *X, const void *const *codes, const float *c
         const int rc = run_batched(bp, stream);
         if (rc >= 0) return rc;
     }
-    // more than one token (or a case the one-launch kernel does not take): matrix by matrix
+    // a case no one-launch kernel takes: matrix by matrix
     for (int l = 0; l < L; ++l) {
         lords::MatmulProblem p{X, codes[l], codebook, B[l], A[l], Y[l], M, N[l], K, r, bits, f32fact, y_dtype == LORDS_F32};
         const int rc = run_matmul(p, LORDS_PATH_AUTO, stream);

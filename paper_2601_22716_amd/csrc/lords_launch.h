@@ -126,6 +126,11 @@ bool prefill_fast_supported(const MatmulProblem &p);
 size_t prefill_fast_workspace_bytes(const MatmulProblem &p, size_t limit);
 // `gate`: null, or M x N fp32 sums of a gate matrix and 12 readable bytes behind them; Y then receives silu(gate) * (the product).
 hipError_t launch_prefill_fast(const MatmulProblem &p, void *part, size_t part_bytes, void *zeroed, hipStream_t st, const float *gate = nullptr);
+// The same for several matrices that read the same X, each summed as it would be alone: `part` holds
+// prefill_batched_workspace_bytes(p) bytes.
+bool prefill_batched_supported(const BatchedProblem &p);
+size_t prefill_batched_workspace_bytes(const BatchedProblem &p);
+hipError_t launch_prefill_batched(const BatchedProblem &p, void *part, void *zeroed, hipStream_t st);
 // ... and the general variant (fp32 factors, any rank; lords_fused.hip).
 hipError_t launch_prefill(const MatmulProblem &p, hipStream_t st);
 

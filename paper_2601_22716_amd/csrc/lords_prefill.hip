@@ -42,25 +42,40 @@
 
 namespace lords {
 
-struct PrefillArgs {
-    const uint16_t *X;
+// One weight matrix of a launch.  Several matrices that read the same X (and are cut into tiles of the same shape) can
+// share a launch: each gets a contiguous range of blockIdx.x, a multiple of eight long, and keeps the cut of the work it
+// would have alone, so its sums are the same bit for bit.  Layers too small to fill the chip run beside each other and
+// the last round of one is filled by the next.  Seven layers of a block (q, k, v in one launch; us before -> after):
+// hidden 4096, 17 / 2048 tokens 228 -> 180 / 1022 -> 987; hidden 1024 (k, v of 256 rows) 115 -> 77 / 253 -> 159 (the gate/up
+// epilogue's share included).
+struct PfLayer {
     const uint8_t *codes;
-    const float *codebook;
     const void *B;         // N x rf, bf16 or fp32
     const void *A;         // rf x K, bf16 or fp32
     void *Y;
-    int M, N, K;
+    const float *gate;     // M x N fp32 or null: Y = silu(gate) * (the product) instead of the product
+    float *part;           // per workgroup: the accumulators of a part that does not start at the tile's first column
+    uint32_t *arrived;     // per output tile: parts handed over so far (zero before and after a launch)
+    int N;
+    int nt;                // tiles along N
+    int per;               // work units (one K tile of one output tile) per workgroup; units are numbered tile by tile
+    int x0, gx;            // first blockIdx.x of this matrix and how many it has (multiples of 8)
+};
+
+template <int NLAYERS>
+struct PrefillArgsT {
+    const uint16_t *X;
+    const float *codebook;
+    int M, K;
     int r;                 // contraction length of the scales: rf, or 3 rf for fp32 factors (hi/lo parts, see the kernel)
     int rf;                // rank of the factors
     int y_f32;
     int row_bytes;
-    int nt, mt;            // tiles along N and M
+    int mt;                // tiles along M
     int ntiles_k;          // ceil(K / 128)
     int tiled;             // codes in the slab-tile layout: tile (slab, K tile) contiguous, chunk = 16 g + c
-    int per;               // work units (one K tile of one output tile) per workgroup; units are numbered tile by tile
-    uint32_t *arrived;     // per output tile: parts handed over so far (zero before and after a launch)
-    const float *gate;     // M x N fp32 or null: Y = silu(gate) * (the product) instead of the product
-    float *part;           // per workgroup: the accumulators of a part that does not start at the tile's first column
+    int L;                 // matrices
+    PfLayer layer[NLAYERS];
 };
 
 constexpr int kPfCopies = 8;
@@ -95,8 +110,10 @@ __device__ __forceinline__ uint32_t pair_index(const uint32_t (&w)[BITS], int p)
 // instructions per thread and K tile at rank 16, no scratch and no launch of its own.
 // 4096 x 4096, 4 bits, rank 16, 500 tokens: 50 us (general kernel of lords_fused.hip: 361); 2048 tokens 100 (728);
 // 14336 x 4096, rank 40, 17 tokens 67 (608).
-template <int BITS, int SS, int WM, int R, int WN = 4, int MB = 8, bool F32 = false>
-__global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(WN * WM / 4, WN * WM / 4))) void prefill_kernel(PrefillArgs a)
+// MULTI: several matrices in the launch (a lone one is read from fixed offsets of a short argument block: through an
+// index it cost 0.3 us a call).
+template <int BITS, int SS, int WM, int R, int WN = 4, int MB = 8, bool F32 = false, bool MULTI = false>
+__global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(WN * WM / 4, WN * WM / 4))) void prefill_kernel(PrefillArgsT<MULTI ? kMaxBatch : 1> a)
 {
     constexpr int BN = 16 * R * WN, BM = 16 * MB * WM, NT = 64 * WN * WM, RP = 32 * SS, NL = 1 << BITS, NE = 1 << (2 * BITS);
     constexpr int RPP = 4 * WN * WM;                           // A tile rows one staging pass of the workgroup covers
@@ -109,19 +126,25 @@ __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(WN
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int c = lane & 15, g = lane >> 4;
-    const int M = a.M, N = a.N, K = a.K;
+    // the matrix this workgroup works on (the same in all lanes)
+    int li = 0;
+    if (MULTI)
+        while (li + 1 < a.L && (int)blockIdx.x >= a.layer[li + 1].x0) ++li;
+    const PfLayer ly = a.layer[MULTI ? li : 0];
+    const int M = a.M, N = ly.N, K = a.K;
 
     // ---- work of this workgroup.  The work is cut into units, one K tile of one output tile each, numbered
     //      tile by tile (n fastest); workgroup w takes units w per .. w per + per - 1, so a workgroup walks a
     //      tail of one output tile, whole tiles, and a head of another.  Workgroups are dealt round-robin to
     //      the 8 XCDs, so each XCD gets a contiguous run of ranges: its workgroups then share X panels in its L2.
-    const int total_units = a.nt * a.mt * a.ntiles_k;
-    const int wg = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
-    int unit = wg * a.per;
-    const int unit_end = min(unit + a.per, total_units);
+    const int total_units = ly.nt * a.mt * a.ntiles_k;
+    const int bx = (int)blockIdx.x - ly.x0;
+    const int wg = (bx & 7) * (ly.gx >> 3) + (bx >> 3);
+    int unit = wg * ly.per;
+    const int unit_end = min(unit + ly.per, total_units);
     if (unit >= unit_end) return;
     const int wn = wave % WN, wm = wave / WN;
-    const uint16_t *A16 = reinterpret_cast<const uint16_t *>(a.A), *B16 = reinterpret_cast<const uint16_t *>(a.B);   // (bf16 factors)
+    const uint16_t *A16 = reinterpret_cast<const uint16_t *>(ly.A), *B16 = reinterpret_cast<const uint16_t *>(ly.B);   // (bf16 factors)
 
     // ---- level table --------------------------------------------------------------------------------
     for (int id = tid; id < NE * kPfCopies; id += NT) {
@@ -142,7 +165,7 @@ __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(WN
     const int T = unit / a.ntiles_k;
     const int kt0 = unit - T * a.ntiles_k, kt1 = min(a.ntiles_k, kt0 + (unit_end - unit));
     unit += kt1 - kt0;
-    const int m_blk = (T / a.nt) * BM, n_blk = (T % a.nt) * BN;
+    const int m_blk = (T / ly.nt) * BM, n_blk = (T % ly.nt) * BN;
     const int n_wave = n_blk + 16 * R * wn;
     const int m_wave = m_blk + 16 * MB * wm;
 
@@ -165,7 +188,7 @@ __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(WN
                         const int jj = jj0 + e;
                         if (jj < a.r) {
                             const int j = jj < a.rf ? jj : jj < 2 * a.rf ? jj - a.rf : jj - 2 * a.rf;
-                            const float x = reinterpret_cast<const float *>(a.B)[(size_t)n * a.rf + j];
+                            const float x = reinterpret_cast<const float *>(ly.B)[(size_t)n * a.rf + j];
                             const uint16_t hi = bf16_bits(x);
                             t[e] = (short)(jj >= 2 * a.rf ? bf16_bits(x - bf16_to_f32(hi)) : hi);
                         }
@@ -247,8 +270,8 @@ __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(WN
 #pragma unroll
     for (int rho = 0; rho < R; ++rho) {
         const int n = min(n_wave + 16 * rho + c, N - 1);
-        crow[rho] = a.tiled ? a.codes + ((size_t)(n >> 4) * a.ntiles_k * 64 + (n & 15)) * (4 * BITS)
-                            : a.codes + (size_t)n * a.row_bytes;
+        crow[rho] = a.tiled ? ly.codes + ((size_t)(n >> 4) * a.ntiles_k * 64 + (n & 15)) * (4 * BITS)
+                            : ly.codes + (size_t)n * a.row_bytes;
     }
     const uint32_t cstep = a.tiled ? 64u * 4 * BITS : 4u * 4 * BITS;
     const uint32_t cgoff = a.tiled ? (uint32_t)g * 16 * 4 * BITS : (uint32_t)g * 4 * BITS;
@@ -268,7 +291,7 @@ __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(WN
             const int id = tid + NT * q, j = id >> 4, k = kt * 128 + 8 * (id & 15);
             af[q][0] = af[q][1] = f32x4{0.f, 0.f, 0.f, 0.f};
             if (j < a.rf && k < K) {
-                const f32x4 *src = reinterpret_cast<const f32x4 *>(reinterpret_cast<const float *>(a.A) + (size_t)j * K + k);
+                const f32x4 *src = reinterpret_cast<const f32x4 *>(reinterpret_cast<const float *>(ly.A) + (size_t)j * K + k);
                 af[q][0] = src[0];
                 af[q][1] = src[1];
             }
@@ -530,7 +553,7 @@ __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(WN
     constexpr int kPartFloats = R * MB * NT * 4;
     const bool few = MB == 8 && M - m_wave <= 64;
     if (kt0 != 0) {
-        float *dst = a.part + (size_t)wg * kPartFloats + tid * 4;
+        float *dst = ly.part + (size_t)wg * kPartFloats + tid * 4;
         asm volatile("" : "+v"(dst));        // (addresses are made here, not kept in registers over the K loop)
 #pragma unroll
         for (int half = 0; half < 2; ++half)
@@ -542,17 +565,17 @@ __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(WN
                         store16_agent(dst + (rho * MB + mb) * (NT * 4), acc[rho][mb]);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
-        if (tid == 0) __hip_atomic_fetch_add(a.arrived + T, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+        if (tid == 0) __hip_atomic_fetch_add(ly.arrived + T, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
         continue;
     }
     if (kt1 != a.ntiles_k) {
-        const int others = (a.ntiles_k - kt1 + a.per - 1) / a.per;       // the workgroups after this one, up to the tile's end
+        const int others = (a.ntiles_k - kt1 + ly.per - 1) / ly.per;       // the workgroups after this one, up to the tile's end
         if (tid == 0) {
             // (bounded: the parts waited for are first parts of their workgroups and never wait themselves)
             int spins = 0;
-            while ((int)__hip_atomic_load(a.arrived + T, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < others && ++spins < (1 << 21))
+            while ((int)__hip_atomic_load(ly.arrived + T, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < others && ++spins < (1 << 21))
                 __builtin_amdgcn_s_sleep(8);
-            __hip_atomic_store(a.arrived + T, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(ly.arrived + T, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         }
         __syncthreads();
@@ -560,7 +583,7 @@ __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(WN
         auto add_parts = [&](auto nr, auto nb) __attribute__((always_inline)) {
             constexpr int NR = decltype(nr)::value, NBK = decltype(nb)::value;
             for (int j = 1; j <= others; ++j) {
-                const float *src = a.part + (size_t)(wg + j) * kPartFloats + tid * 4;
+                const float *src = ly.part + (size_t)(wg + j) * kPartFloats + tid * 4;
                 asm volatile("" : "+v"(src));
                 // sixteen loads in flight (eight for half a tile): what the registers beside the accumulators
                 // hold; each wait is a round trip to memory
@@ -588,7 +611,7 @@ __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(WN
             add_parts(std::integral_constant<int, 2>{}, std::integral_constant<int, 8>{});
         }
     }
-    void *Yp = a.Y;
+    void *Yp = ly.Y;
     auto store_block = [&](int rho, int mb, f32x4 v) __attribute__((always_inline)) {
         const int m = m_wave + 16 * mb + c, n = n_wave + 16 * rho + 4 * g;
         if (m >= M) return;
@@ -603,14 +626,14 @@ __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(WN
             }
         }
     };
-    if (a.gate) {
+    if (ly.gate) {
         // A gate/up pair: this is the up product, the gate's fp32 sums lie in memory.  Loads of eight token blocks in
         // flight; addresses are clamped to the matrix's rows, a load of its last columns may reach 12 bytes beyond
         // them (the buffer is that much longer), and what such loads bring is not stored.
         constexpr int GB = 8;
 #pragma unroll
         for (int rho = 0; rho < R; ++rho) {
-            const float *col = a.gate + min(n_wave + 16 * rho + 4 * g, N - 1);
+            const float *col = ly.gate + min(n_wave + 16 * rho + 4 * g, N - 1);
 #pragma unroll
             for (int b0 = 0; b0 < MB; b0 += GB) {
                 int m0 = m_wave + 16 * b0 + c;
@@ -736,17 +759,69 @@ size_t prefill_fast_workspace_bytes(const MatmulProblem &p, size_t limit)
     return pf_plan(p, limit).part_bytes;
 }
 
-template <int BITS, int SS, int WM, int R, int WN = 4, int MB = 8, bool F32 = false>
-static hipError_t launch_pf_t(const PrefillArgs &a, dim3 grid, hipStream_t st)
+template <int BITS, int SS, int WM, int R, int WN, int MB, bool F32, bool MULTI>
+static hipError_t launch_pf_t(const PrefillArgsT<MULTI ? kMaxBatch : 1> &a, dim3 grid, hipStream_t st)
 {
     const size_t smem = (size_t)2 * (16 * MB * WM) * 256 + (size_t)2 * (32 * SS) * 256 + (size_t)(1 << (2 * BITS)) * kPfCopies * 4;
     static LdsOptIn lds_opt_in;
     {
-        const hipError_t e = allow_dynamic_lds(lds_opt_in, reinterpret_cast<const void *>(&prefill_kernel<BITS, SS, WM, R, WN, MB, F32>), smem);
+        const hipError_t e = allow_dynamic_lds(lds_opt_in, reinterpret_cast<const void *>(&prefill_kernel<BITS, SS, WM, R, WN, MB, F32, MULTI>), smem);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((prefill_kernel<BITS, SS, WM, R, WN, MB, F32>), grid, dim3(64 * WN * WM), smem, st, a);
+    hipLaunchKernelGGL((prefill_kernel<BITS, SS, WM, R, WN, MB, F32, MULTI>), grid, dim3(64 * WN * WM), smem, st, a);
     return hipGetLastError();
+}
+
+// The launch of the matrices in a.layer, all cut into tiles of the shape of `d`.
+template <bool MULTI>
+static hipError_t launch_pf(const PrefillArgsT<MULTI ? kMaxBatch : 1> &a, const PfPlan &d, int bits, bool f32fact, hipStream_t st)
+{
+    const int ss = d.ss, wm = d.wm, wn = d.wn;
+    const dim3 grid(a.layer[a.L - 1].x0 + a.layer[a.L - 1].gx);
+    hipError_t e = hipErrorInvalidValue;
+#define LORDS_PCASE(B_, S_)                                                                                        \
+    if (bits == B_ && ss == S_) {                                                                                   \
+        if (f32fact) e = S_ < 4 && wn == 8 ? launch_pf_t<B_, (S_ < 4 ? S_ : 1), 1, 2, 8, 8, true, MULTI>(a, grid, st) \
+                                           : launch_pf_t<B_, S_, 1, 2, 4, 8, true, MULTI>(a, grid, st);              \
+        else if (S_ == 1 && d.mb == 16) e = launch_pf_t<B_, 1, 1, 2, 8, 16, false, MULTI>(a, grid, st);              \
+        else if (S_ == 1 && wm == 2) e = launch_pf_t<B_, 1, 2, 2, 4, 8, false, MULTI>(a, grid, st);                  \
+        else if (wn == 8) e = launch_pf_t<B_, S_, 1, 2, 8, 8, false, MULTI>(a, grid, st);                            \
+        else e = launch_pf_t<B_, S_, 1, 2, 4, 8, false, MULTI>(a, grid, st);                                         \
+    }
+    LORDS_PCASE(2, 1) LORDS_PCASE(2, 2) LORDS_PCASE(2, 4)
+    LORDS_PCASE(3, 1) LORDS_PCASE(3, 2) LORDS_PCASE(3, 4)
+    LORDS_PCASE(4, 1) LORDS_PCASE(4, 2) LORDS_PCASE(4, 4)
+#undef LORDS_PCASE
+    return e;
+}
+
+template <class Args>
+static void pf_common(Args &a, const MatmulProblem &p, const PfPlan &d)
+{
+    a.X = (const uint16_t *)p.X;
+    a.codebook = p.codebook;
+    a.M = p.M; a.K = p.K; a.r = pf_contraction(p); a.rf = p.r;
+    a.y_f32 = p.f32out ? 1 : 0;
+    a.row_bytes = p.K / 8 * p.bits;
+    a.mt = d.mt;
+    a.ntiles_k = (p.K + 127) / 128;
+    a.tiled = p.tiled ? 1 : 0;
+}
+
+static void pf_layer(PfLayer &ly, const MatmulProblem &p, const PfPlan &d, void *part, void *arrived, int x0)
+{
+    ly.codes = (const uint8_t *)p.codes;
+    ly.B = p.B;
+    ly.A = p.A;
+    ly.Y = p.Y;
+    ly.gate = nullptr;
+    ly.part = (float *)part;
+    ly.arrived = (uint32_t *)arrived;
+    ly.N = p.N;
+    ly.nt = d.nt;
+    ly.per = d.per;
+    ly.x0 = x0;
+    ly.gx = (d.wgs + 7) / 8 * 8;
 }
 
 // `part`: part_bytes bytes of scratch (what prefill_fast_workspace_bytes returned for a limit of at most
@@ -754,41 +829,78 @@ static hipError_t launch_pf_t(const PrefillArgs &a, dim3 grid, hipStream_t st)
 hipError_t launch_prefill_fast(const MatmulProblem &p, void *part, size_t part_bytes, void *zeroed, hipStream_t st, const float *gate)
 {
     const PfPlan d = pf_plan(p, (part && zeroed) ? part_bytes : 0);
-    const int ss = d.ss, wm = d.wm, wn = d.wn;
-    PrefillArgs a;
-    a.X = (const uint16_t *)p.X;
-    a.codes = (const uint8_t *)p.codes;
-    a.codebook = p.codebook;
-    a.B = p.B;
-    a.A = p.A;
-    a.Y = p.Y;
-    a.M = p.M; a.N = p.N; a.K = p.K; a.r = pf_contraction(p); a.rf = p.r;
-    a.y_f32 = p.f32out ? 1 : 0;
-    a.row_bytes = p.K / 8 * p.bits;
-    a.nt = d.nt;
-    a.mt = d.mt;
-    a.ntiles_k = (p.K + 127) / 128;
-    a.tiled = p.tiled ? 1 : 0;
-    a.per = d.per;
-    a.arrived = (uint32_t *)zeroed;
-    a.part = (float *)part;
-    a.gate = gate;
-    const dim3 grid(((d.wgs + 7) / 8) * 8);
-    hipError_t e = hipErrorInvalidValue;
-#define LORDS_PCASE(B_, S_)                                                                     \
-    if (p.bits == B_ && ss == S_) {                                                              \
-        if (p.f32fact) e = S_ < 4 && wn == 8 ? launch_pf_t<B_, (S_ < 4 ? S_ : 1), 1, 2, 8, 8, true>(a, grid, st)  \
-                                             : launch_pf_t<B_, S_, 1, 2, 4, 8, true>(a, grid, st);                \
-        else if (S_ == 1 && d.mb == 16) e = launch_pf_t<B_, 1, 1, 2, 8, 16>(a, grid, st);               \
-        else if (S_ == 1 && wm == 2) e = launch_pf_t<B_, 1, 2, 2>(a, grid, st);                   \
-        else if (wn == 8) e = launch_pf_t<B_, S_, 1, 2, 8>(a, grid, st);                         \
-        else e = launch_pf_t<B_, S_, 1, 2>(a, grid, st);                                         \
+    PrefillArgsT<1> a;
+    pf_common(a, p, d);
+    a.L = 1;
+    pf_layer(a.layer[0], p, d, part, zeroed, 0);
+    a.layer[0].gate = gate;
+    return launch_pf<false>(a, d, p.bits, p.f32fact, st);
+}
+
+// ---- several matrices, the same activations ------------------------------------------------------------------
+static MatmulProblem pf_of(const BatchedProblem &p, int l)
+{
+    MatmulProblem q{p.X, p.codes[l], p.codebook, p.B[l], p.A[l], p.Y[l], p.M, p.N[l], p.K, p.r, p.bits, p.f32fact, p.f32out};
+    q.tiled = p.tiled;
+    return q;
+}
+
+size_t prefill_batched_workspace_bytes(const BatchedProblem &p)
+{
+    size_t sum = 0;
+    for (int l = 0; l < p.L; ++l) sum += (pf_plan(pf_of(p, l), ~(size_t)0).part_bytes + 255) & ~(size_t)255;
+    return sum;
+}
+
+bool prefill_batched_supported(const BatchedProblem &p)
+{
+    if (p.act || p.L < 1 || p.L > kMaxBatch) return false;
+    size_t tiles = 0;
+    for (int l = 0; l < p.L; ++l) {
+        const MatmulProblem q = pf_of(p, l);
+        if (!prefill_fast_supported(q)) return false;
+        const PfPlan d = pf_plan(q, ~(size_t)0);
+        if (d.part_bytes) tiles += (size_t)d.nt * d.mt;
+        if (d.wgs > (1 << 24)) return false;
     }
-    LORDS_PCASE(2, 1) LORDS_PCASE(2, 2) LORDS_PCASE(2, 4)
-    LORDS_PCASE(3, 1) LORDS_PCASE(3, 2) LORDS_PCASE(3, 4)
-    LORDS_PCASE(4, 1) LORDS_PCASE(4, 2) LORDS_PCASE(4, 4)
-#undef LORDS_PCASE
-    return e;
+    return tiles * sizeof(uint32_t) <= kZeroBytes;
+}
+
+// One launch per tile shape that the matrices' plans ask for (usually one).  A part that waits for others cannot wait for
+// ever although not all workgroups fit the chip at once: blocks are dispatched in order, a matrix has at most 256
+// workgroups that share tiles (32 per XCD, one per CU), and those of the matrices before it finish without it.
+hipError_t launch_prefill_batched(const BatchedProblem &p, void *part, void *zeroed, hipStream_t st)
+{
+    PfPlan d[kMaxBatch];
+    unsigned char *parts[kMaxBatch];
+    uint32_t *arrived[kMaxBatch];
+    unsigned char *next_part = (unsigned char *)part;
+    uint32_t *next_arrived = (uint32_t *)zeroed;
+    bool done[kMaxBatch] = {};
+    for (int l = 0; l < p.L; ++l) {
+        d[l] = pf_plan(pf_of(p, l), ~(size_t)0);
+        parts[l] = next_part;
+        arrived[l] = next_arrived;
+        next_part += (d[l].part_bytes + 255) & ~(size_t)255;
+        if (d[l].part_bytes) next_arrived += (size_t)d[l].nt * d[l].mt;      // (whole tiles count no arrivals)
+    }
+    for (int l0 = 0; l0 < p.L; ++l0) {
+        if (done[l0]) continue;
+        PrefillArgsT<kMaxBatch> a;
+        pf_common(a, pf_of(p, l0), d[l0]);
+        a.L = 0;
+        int x0 = 0;
+        for (int l = l0; l < p.L; ++l) {
+            if (done[l] || d[l].wm != d[l0].wm || d[l].wn != d[l0].wn || d[l].mb != d[l0].mb) continue;
+            pf_layer(a.layer[a.L], pf_of(p, l), d[l], parts[l], arrived[l], x0);
+            x0 += a.layer[a.L].gx;
+            ++a.L;
+            done[l] = true;
+        }
+        const hipError_t e = launch_pf<true>(a, d[l0], p.bits, p.f32fact, st);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace lords
