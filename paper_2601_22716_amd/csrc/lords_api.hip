@@ -579,8 +579,7 @@ int lords_backward_input(const void *dY, const void *codes_t, const float *codeb
     const int rc = plan_workspace(p, path, at_bytes + bt_bytes, stream, &ws, &extra);
     if (rc != LORDS_OK) return rc;
     void *At = extra, *Bt = (unsigned char *)extra + at_bytes;
-    if (lords::launch_transpose_factor(A, At, r, K, f32fact, (hipStream_t)stream) != hipSuccess) return LORDS_ERR_LAUNCH;
-    if (lords::launch_transpose_factor(B, Bt, N, r, f32fact, (hipStream_t)stream) != hipSuccess) return LORDS_ERR_LAUNCH;
+    if (lords::launch_transpose_factors(A, At, B, Bt, N, K, r, f32fact, (hipStream_t)stream) != hipSuccess) return LORDS_ERR_LAUNCH;
     p.B = At;
     p.A = Bt;
     return launch_matmul(p, path, ws, stream);

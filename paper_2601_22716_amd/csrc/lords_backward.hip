@@ -25,7 +25,7 @@
 // For dA (contraction over n) the same P values go to LDS as a row-major bf16 tile and come back
 // through the transposing read, with the B tile as the other operand.
 // G and P never reach HBM.  The sums over the other tiles (column tiles for dB, row tiles for dA)
-// are written as fp32 partial results and added in a fixed order by reduce_partials_kernel:
+// are written as fp32 partial results and added in a fixed order by reduce_factor_parts_kernel:
 // results are run-to-run identical.
 #include "lords_decode_common.h"
 
@@ -88,28 +88,38 @@ hipError_t launch_transpose_codes(const void *codes, void *codes_t, int N, int K
     return hipGetLastError();
 }
 
-// out[c][r] = in[r][c] for a small rows x cols factor (bf16 or fp32 elements), through a 32 x 32 tile
+// out[c][r] = in[r][c] for the two small factors (bf16 or fp32 elements) in one launch, through 32 x 32 tiles: blocks
+// below `split` take A (r x K), the others B (N x r).  A launch of this size is all latency (two took 4.9 + 5.4 us on
+// 14336 x 4096 at rank 32, one takes 5.2).
 template <typename T>
-__global__ __launch_bounds__(256) void transpose_factor_kernel(const T *__restrict__ in, T *__restrict__ out, int rows, int cols)
+__global__ __launch_bounds__(256) void transpose_factors_kernel(const T *__restrict__ A, T *__restrict__ At, const T *__restrict__ B,
+                                                                T *__restrict__ Bt, int N, int K, int r, int split)
 {
     __shared__ T tile[32][33];
-    const int r0 = blockIdx.y * 32, c0 = blockIdx.x * 32;
-    for (int id = threadIdx.x; id < 1024; id += 256) {
-        const int rr = id >> 5, cc = id & 31;
+    const bool first = (int)blockIdx.x < split;
+    const T *in = first ? A : B;
+    T *out = first ? At : Bt;
+    const int rows = first ? r : N, cols = first ? K : r;
+    const int id0 = first ? blockIdx.x : blockIdx.x - split, ctiles = (cols + 31) / 32;
+    const int r0 = id0 / ctiles * 32, c0 = id0 % ctiles * 32;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int id = threadIdx.x + 256 * q, rr = id >> 5, cc = id & 31;
         if (r0 + rr < rows && c0 + cc < cols) tile[rr][cc] = in[(size_t)(r0 + rr) * cols + c0 + cc];
     }
     __syncthreads();
-    for (int id = threadIdx.x; id < 1024; id += 256) {
-        const int cc = id >> 5, rr = id & 31;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int id = threadIdx.x + 256 * q, cc = id >> 5, rr = id & 31;
         if (r0 + rr < rows && c0 + cc < cols) out[(size_t)(c0 + cc) * rows + r0 + rr] = tile[rr][cc];
     }
 }
 
-hipError_t launch_transpose_factor(const void *in, void *out, int rows, int cols, bool f32, hipStream_t st)
+hipError_t launch_transpose_factors(const void *A, void *At, const void *B, void *Bt, int N, int K, int r, bool f32, hipStream_t st)
 {
-    const dim3 grid((unsigned)((cols + 31) / 32), (unsigned)((rows + 31) / 32)), block(256);
-    if (f32) hipLaunchKernelGGL(transpose_factor_kernel<float>, grid, block, 0, st, (const float *)in, (float *)out, rows, cols);
-    else hipLaunchKernelGGL(transpose_factor_kernel<uint16_t>, grid, block, 0, st, (const uint16_t *)in, (uint16_t *)out, rows, cols);
+    const unsigned rt = (unsigned)((r + 31) / 32), split = rt * (unsigned)((K + 31) / 32), total = split + rt * (unsigned)((N + 31) / 32);
+    if (f32) hipLaunchKernelGGL(transpose_factors_kernel<float>, dim3(total), dim3(256), 0, st, (const float *)A, (float *)At, (const float *)B, (float *)Bt, N, K, r, (int)split);
+    else hipLaunchKernelGGL(transpose_factors_kernel<uint16_t>, dim3(total), dim3(256), 0, st, (const uint16_t *)A, (uint16_t *)At, (const uint16_t *)B, (uint16_t *)Bt, N, K, r, (int)split);
     return hipGetLastError();
 }
 
@@ -437,14 +447,38 @@ __global__ __launch_bounds__(kFgThreads) __attribute__((amdgpu_waves_per_eu(2, 2
     }
 }
 
-// out[i] = sum over p of part[p][i], p increasing
-__global__ __launch_bounds__(256) void reduce_partials_kernel(const float *__restrict__ part, float *__restrict__ out,
-                                                              long count, int nparts)
+// out[i] = sum over p of part[p][i], p increasing, for dB (blocks below `split`) and dA in one launch.  Bound by memory
+// (87 MB of partial sums on 14336 x 4096 at rank 32): sixteen loads in flight per thread, since the shorter output (dA,
+// 131072 sums of 56 parts there) does not fill the chip with threads; in launches of their own, one load behind the
+// other, the two took 12.0 + 15.2 us, now 14.8 (4096 x 4096 at rank 16 9.0 + 5.3 -> 5.2).
+__global__ __launch_bounds__(256) void reduce_factor_parts_kernel(const float *__restrict__ partB, float *__restrict__ dB, long countB, int npartsB,
+                                                                  const float *__restrict__ partA, float *__restrict__ dA, long countA, int npartsA,
+                                                                  int split)
 {
-    const long i = (long)blockIdx.x * 256 + threadIdx.x;
+    const bool first = (int)blockIdx.x < split;
+    const float *part = first ? partB : partA;
+    float *out = first ? dB : dA;
+    const long count = first ? countB : countA;
+    const int nparts = first ? npartsB : npartsA;
+    const long i = (long)((int)blockIdx.x - (first ? 0 : split)) * 256 + threadIdx.x;
     if (i >= count) return;
     float s = 0.f;
-    for (int p = 0; p < nparts; ++p) s += part[(size_t)p * count + i];
+    int p = 0;
+    for (; p + 16 <= nparts; p += 16) {
+        float t[16];
+#pragma unroll
+        for (int q = 0; q < 16; ++q) t[q] = __builtin_nontemporal_load(part + (size_t)(p + q) * count + i);
+#pragma unroll
+        for (int q = 0; q < 16; ++q) s += t[q];
+    }
+    if (p < nparts) {
+        float t[16];
+#pragma unroll
+        for (int q = 0; q < 16; ++q) t[q] = part[(size_t)min(p + q, nparts - 1) * count + i];
+#pragma unroll
+        for (int q = 0; q < 16; ++q)
+            if (p + q < nparts) s += t[q];
+    }
     out[i] = s;
 }
 
@@ -496,8 +530,9 @@ hipError_t launch_factor_grad(const void *dY, const void *X, const void *codes, 
 #undef LORDS_FGCASE
     if (e != hipSuccess) return e;
     const long cb = (long)N * r, ca = (long)r * K;
-    hipLaunchKernelGGL(reduce_partials_kernel, dim3((unsigned)((cb + 255) / 256)), dim3(256), 0, st, a.partB, dB, cb, 2 * a.ktiles);
-    hipLaunchKernelGGL(reduce_partials_kernel, dim3((unsigned)((ca + 255) / 256)), dim3(256), 0, st, a.partA, dA, ca, a.ntiles);
+    const unsigned split = (unsigned)((cb + 255) / 256), total = split + (unsigned)((ca + 255) / 256);
+    hipLaunchKernelGGL(reduce_factor_parts_kernel, dim3(total), dim3(256), 0, st, (const float *)a.partB, dB, cb, 2 * a.ktiles,
+                       (const float *)a.partA, dA, ca, a.ntiles, (int)split);
     return hipGetLastError();
 }
 

@@ -44,7 +44,8 @@ hipError_t launch_block_init(const void *W, const float *codebook, void *B, void
 // Backward side (lords_backward.hip).  codes_t: the packed codes with the roles of rows and columns
 // swapped (K rows of N codes); N must be a multiple of 32.
 hipError_t launch_transpose_codes(const void *codes, void *codes_t, int N, int K, int bits, hipStream_t st);
-hipError_t launch_transpose_factor(const void *in, void *out, int rows, int cols, bool f32, hipStream_t st);
+// At (K x r) and Bt (r x N) from A (r x K) and B (N x r).
+hipError_t launch_transpose_factors(const void *A, void *At, const void *B, void *Bt, int N, int K, int r, bool f32, hipStream_t st);
 // dB (N x r) and dA (r x K), fp32, from dY (M x N) and X (M x K), both bf16.  `workspace` must hold
 // factor_grad_workspace_bytes(N, K, r) bytes (fp32 partial results per tile, added in a fixed order).
 bool factor_grad_supported(int N, int K, int r);
