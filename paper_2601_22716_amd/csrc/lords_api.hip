@@ -108,6 +108,9 @@ inline lords_path resolve_path(lords_path path, const lords::MatmulProblem &p)
     // (us, few-token / large-M at 4 tokens: 14336 x 4096 rank 16 59.3 / 43.4, rank 40 82 / 67; 4096 x 4096
     // rank 16 25.8 / 31.7, rank 40 34.7 / 41.6; at rank 4 34.5 / 41.3 and 22.7 / 28.7).
     if (p.M >= 2 && p.f32fact && 3 * p.r > 32 && (long)p.N * p.K > (32L << 20) && lords::prefill_fast_supported(p)) return LORDS_PATH_PREFILL;
+    // ... and beyond 128 columns at any token count, where the few-token family is left with its general kernel
+    // (us, general / this: rank 43, one token, 14336 x 4096 473 / 68, 875 x 6496 73 / 43; 40 tokens 1025 / 68, 1676 / 44).
+    if (p.f32fact && 3 * p.r > 128 && lords::prefill_fast_supported(p)) return LORDS_PATH_PREFILL;
     return LORDS_PATH_DECODE;
 }
 

@@ -602,13 +602,13 @@ __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(WN
                 }
             }
         };
-        static_assert(R == 2 && (MB == 8 || MB == 16), "sixteen accumulator blocks a round trip");
+        static_assert(R == 2 && (MB == 4 || MB == 8 || MB == 16), "at most sixteen accumulator blocks a round trip");
         if constexpr (MB == 16) {
             add_parts(std::integral_constant<int, 1>{}, std::integral_constant<int, 16>{});
-        } else if (few) {
+        } else if (MB == 4 || few) {
             add_parts(std::integral_constant<int, 2>{}, std::integral_constant<int, 4>{});
         } else {
-            add_parts(std::integral_constant<int, 2>{}, std::integral_constant<int, 8>{});
+            add_parts(std::integral_constant<int, 2>{}, std::integral_constant<int, MB < 8 ? MB : 8>{});
         }
     }
     void *Yp = ly.Y;
@@ -630,7 +630,7 @@ __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(WN
         // A gate/up pair: this is the up product, the gate's fp32 sums lie in memory.  Loads of eight token blocks in
         // flight; addresses are clamped to the matrix's rows, a load of its last columns may reach 12 bytes beyond
         // them (the buffer is that much longer), and what such loads bring is not stored.
-        constexpr int GB = 8;
+        constexpr int GB = MB < 8 ? MB : 8;
 #pragma unroll
         for (int rho = 0; rho < R; ++rho) {
             const float *col = ly.gate + min(n_wave + 16 * rho + 4 * g, N - 1);
@@ -663,15 +663,17 @@ __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(WN
 // ---------------------------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------------------------
-static int pf_ss(int r)
+// Contraction length of the scales padded to 32 times 1, 2 or 4; six times, of which the A tile leaves LDS for 64 tokens
+// only, with fp32 factors, whose ranks 43 .. 64 come to 129 .. 192 columns.
+static int pf_ss(int contraction, bool f32fact)
 {
-    const int rp = (r + 31) / 32;
-    return rp <= 1 ? 1 : rp <= 2 ? 2 : rp <= 4 ? 4 : 0;
+    const int rp = (contraction + 31) / 32;
+    return rp <= 1 ? 1 : rp <= 2 ? 2 : rp <= 4 ? 4 : rp <= 6 && f32fact ? 6 : 0;
 }
 
 static int pf_contraction(const MatmulProblem &p) { return p.f32fact ? 3 * p.r : p.r; }   // (fp32 factors: hi/lo parts)
 
-bool prefill_fast_supported(const MatmulProblem &p) { return pf_ss(pf_contraction(p)) != 0 && !(p.f32fact && p.tiled); }
+bool prefill_fast_supported(const MatmulProblem &p) { return pf_ss(pf_contraction(p), p.f32fact) != 0 && !(p.f32fact && p.tiled); }
 
 // Tile shape and the cut of the work.  Tile shapes: 256 tokens x 256 rows (8 waves of 32 rows x 256
 // tokens), 256 x 128 (8 waves), and for at most 128 tokens 128 x 256 (8 waves side by side) and
@@ -695,7 +697,7 @@ constexpr int kPfCUs = 256;
 static PfPlan pf_plan(const MatmulProblem &p, size_t avail)
 {
     PfPlan d;
-    d.ss = pf_ss(pf_contraction(p));
+    d.ss = pf_ss(pf_contraction(p), p.f32fact);
     const int ntiles_k = (p.K + 127) / 128;
     // Candidates (tokens x rows of a tile) with the measured time of one K tile of one workgroup at
     // 4 bits and rank 32, all CUs busy, clocks settled:
@@ -704,19 +706,20 @@ static PfPlan pf_plan(const MatmulProblem &p, size_t avail)
     //   128 x 256, eight waves; 128 x 128, four waves          2.15 us, 1.75 us   (up to 128 tokens)
     // Padded ranks of 64 and 128 take the last two shapes at 1.4 and 2 times the cost.
     struct Cand { int wm, R, wn, mb; double t; };
-    const double rank_cost = d.ss == 1 ? 1.0 : d.ss == 2 ? 1.4 : 2.0;
+    const double rank_cost = d.ss == 1 ? 1.0 : d.ss == 2 ? 1.4 : 2.0;      // (six times 32: a shape and a time of its own)
     const Cand small_rank[4] = {{1, 2, 8, 16, 3.45}, {2, 2, 4, 8, 2.4}, {1, 2, 8, 8, 2.15}, {1, 2, 4, 8, 1.75}};
     // fp32 factors (contraction 3 r) take them at any rank: the A tile of a 256-token tile has no registers to pass through.
     const Cand large_rank[2] = {{1, 2, 8, 8, 2.15 * rank_cost}, {1, 2, 4, 8, 1.75 * rank_cost}};
-    const Cand *cands = d.ss == 1 ? small_rank : large_rank;
-    const int ncands = d.ss == 1 ? 4 : 2;
+    const Cand six[1] = {{1, 2, 4, 4, 3.0}};                 // (64 x 128, four waves)
+    const Cand *cands = d.ss == 1 ? small_rank : d.ss == 6 ? six : large_rank;
+    const int ncands = d.ss == 1 ? 4 : d.ss == 6 ? 1 : 2;
     double best = 1e30;
-    d.wm = 1; d.R = 2; d.wn = 4; d.mb = 8; d.per = ntiles_k; d.part_bytes = 0;
+    d.wm = 1; d.R = 2; d.wn = 4; d.mb = d.ss == 6 ? 4 : 8; d.per = ntiles_k; d.part_bytes = 0;
     for (int i = 0; i < ncands; ++i) {
         const Cand &c = cands[i];
         const int tokens = 16 * c.mb * c.wm, rows = 16 * c.R * c.wn;
         if (p.f32fact && d.ss == 4 && rows == 256) continue;     // (eight waves: 70 registers over, spilled)
-        if (p.f32fact ? tokens != 128 : d.ss == 1 && (tokens == 128) != (p.M <= 128)) continue;
+        if (d.ss != 6 && (p.f32fact ? tokens != 128 : d.ss == 1 && (tokens == 128) != (p.M <= 128))) continue;
         const long tiles = (long)((p.N + rows - 1) / rows) * ((p.M + tokens - 1) / tokens);
         const long units = tiles * ntiles_k;
         const size_t tile_bytes = (size_t)tokens * rows * sizeof(float);
@@ -792,6 +795,9 @@ static hipError_t launch_pf(const PrefillArgsT<MULTI ? kMaxBatch : 1> &a, const 
     LORDS_PCASE(3, 1) LORDS_PCASE(3, 2) LORDS_PCASE(3, 4)
     LORDS_PCASE(4, 1) LORDS_PCASE(4, 2) LORDS_PCASE(4, 4)
 #undef LORDS_PCASE
+    if (ss == 6)
+        e = bits == 2 ? launch_pf_t<2, 6, 1, 2, 4, 4, true, MULTI>(a, grid, st)
+          : bits == 3 ? launch_pf_t<3, 6, 1, 2, 4, 4, true, MULTI>(a, grid, st) : launch_pf_t<4, 6, 1, 2, 4, 4, true, MULTI>(a, grid, st);
     return e;
 }
 

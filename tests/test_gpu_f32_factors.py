@@ -1,5 +1,5 @@
 """fp32 factors on the few-token and large-M kernels: the split into bf16 parts at the edges of the contraction
-lengths (3 r = 32, 64, 128), ragged rows and columns, and the calls that have no scratch to share tiles in."""
+lengths (3 r = 32, 64, 128, 192), ragged rows and columns, and the calls that have no scratch to share tiles in."""
 import numpy as np
 import pytest
 
@@ -26,7 +26,7 @@ def check(Y, want, what):
     assert rf <= Y_TOL and mx <= Y_MAX_TOL, (what, rf, mx)
 
 
-@pytest.mark.parametrize("r", [1, 10, 11, 21, 22, 42, 43])
+@pytest.mark.parametrize("r", [1, 10, 11, 21, 22, 42, 43, 64, 65])
 @pytest.mark.parametrize("M,N,K,bits", [(1, 270, 544, 4), (2, 17, 2080, 3), (16, 515, 1312, 2), (17, 129, 288, 4),
                                         (130, 1030, 416, 3), (300, 700, 1184, 2)])
 def test_products_at_the_edges(gpu, M, N, K, bits, r):
@@ -36,7 +36,7 @@ def test_products_at_the_edges(gpu, M, N, K, bits, r):
     check(gpu.DeviceCase(cs).matmul(), want, "product")
 
 
-@pytest.mark.parametrize("r", [4, 16, 40])
+@pytest.mark.parametrize("r", [4, 16, 40, 60])
 def test_low_parts_of_the_factors_are_used(gpu, r):
     """X = the first rows of the identity returns single weights: integer levels and the scale are exact but for the
     dropped Blo * Alo and the rounded low parts (2^-16 of each positive term), the fp32 sums (3 r additions of 2^-24) and
