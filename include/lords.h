@@ -235,8 +235,9 @@ int lords_matmul_repacked(const void *X, const void *codes_tiled, const float *c
  *                            dtype `y_dtype`) and row counts.  The arrays are read before the call
  *                            returns.
  *   K, r, bits, codebook, factor_dtype are shared by all L matrices.  1 <= L <= 8 (LORDS_ERR_SHAPE).
- * With M <= 16 and bf16 factors of rank <= 64 all matrices are served by one kernel launch;
- * other cases run matrix by matrix.  Each Y[l] is the same sum lords_matmul computes for that matrix
+ * With M <= 16 and bf16 factors of rank <= 64 all matrices are served by one kernel launch, and above
+ * 16 tokens (bf16 factors of rank <= 128, fp32 of rank <= 64) by one launch for each tile shape their sizes ask for,
+ * usually one; other cases run matrix by matrix.  Each Y[l] is the same sum lords_matmul computes for that matrix
  * (bit-identical from three tokens on; at one and two tokens the single-matrix call may run another
  * kernel, with another rounding of the same sum).
  */
@@ -251,7 +252,8 @@ int lords_matmul_batched(const void *X, const void *const *codes, const float *c
  *      silu(g) = g / (1 + exp(-g)).
  * G and U are summed in fp32 and never rounded or written out on their own; the product is formed in
  * fp32 and rounded once to `h_dtype`.  With M <= 16 (bf16 factors, rank <= 64) this is one launch; larger
- * M multiplies at most 1024 tokens at a time into an fp32 workspace and combines them in one pass.
+ * M writes the gate's product of at most 2048 tokens at a time to an fp32 workspace and combines it with the up
+ * product where that is stored (ranks beyond the large-M kernel: 1024 tokens of both, combined in one pass).
  *   H   out  M x N
  */
 int lords_gate_up(const void *X, const void *codes_gate, const void *B_gate, const void *A_gate,

@@ -119,7 +119,7 @@ hipError_t launch_decode_fast(const MatmulProblem &p, void *workspace, hipStream
 // by a second kernel.  `workspace` must hold decode_workspace_bytes(p) bytes.
 size_t decode_workspace_bytes(const MatmulProblem &p);
 hipError_t launch_decode(const MatmulProblem &p, void *workspace, hipStream_t st);
-// MFMA GEMM path for large M: bf16 factors up to 128 rank columns (lords_prefill.hip) ...
+// MFMA GEMM path for large M: bf16 factors up to rank 128, fp32 up to rank 64 (lords_prefill.hip) ...
 bool prefill_fast_supported(const MatmulProblem &p);
 // Scratch the kernel would like for the parts of tiles that two or more workgroups share (at most `limit`; with
 // less it plans for less, down to 0 = one whole tile per workgroup), and the launch: `part`/`part_bytes` that
@@ -132,7 +132,7 @@ hipError_t launch_prefill_fast(const MatmulProblem &p, void *part, size_t part_b
 bool prefill_batched_supported(const BatchedProblem &p);
 size_t prefill_batched_workspace_bytes(const BatchedProblem &p);
 hipError_t launch_prefill_batched(const BatchedProblem &p, void *part, void *zeroed, hipStream_t st);
-// ... and the general variant (fp32 factors, any rank; lords_fused.hip).
+// ... and the general variant (any rank; lords_fused.hip).
 hipError_t launch_prefill(const MatmulProblem &p, hipStream_t st);
 
 }  // namespace lords
