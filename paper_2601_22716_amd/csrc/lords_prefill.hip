@@ -39,6 +39,7 @@
 // index*32 + (lane%8)*4); v_fma_mix_f32 multiplies fp16 level by fp32 scale; one rounding to bf16.
 // With fp32 factors the levels stay fp32 too (pairs of 8 bytes, 8 copies): level times scale is then
 // rounded once, to bf16, and no level has to lie within the range of fp16.
+#include <numeric>
 #include <type_traits>
 #include "lords_decode_common.h"
 
@@ -772,8 +773,8 @@ static PfPlan pf_plan(const MatmulProblem &p, size_t avail)
             if (per < 2 || (per % ntiles_k) == 0) continue;                      // (the second: whole tiles again)
             const size_t bytes = (size_t)wgs * tile_bytes;
             if (bytes > avail) continue;
-            long written = 0;                                                    // parts that start inside a tile
-            for (long b = per; b < units; b += per) written += (b % ntiles_k) != 0;
+            // parts that start inside a tile: run boundaries but those that fall on one between tiles
+            const long bounds = (units - 1) / per, written = bounds - bounds / (ntiles_k / std::gcd(per, ntiles_k));
             const double full = p.M <= 64 && tokens == 128 ? 0.5 : 1.0;          // (half a tile travels)
             const double mb_written = (double)written * tile_bytes * full / 1048576.0;
             const double cost = per >= ntiles_k ? per * c.t * 1.08 + 4.0 + mb_written / 2.4
