@@ -19,7 +19,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "liblords.so")
-SOURCES = ["lords_api.hip", "lords_probe.hip", "lords_basic.hip", "lords_quant.hip", "lords_fused.hip", "lords_decode.hip", "lords_gemv.hip", "lords_gemv_b2.hip", "lords_gemv_b2q.hip", "lords_gemv_b3.hip", "lords_gemv_b4.hip", "lords_decode_mx.hip", "lords_prefill.hip", "lords_backward.hip"]
+SOURCES = ["lords_api.hip", "lords_probe.hip", "lords_basic.hip", "lords_quant.hip", "lords_fused.hip", "lords_decode.hip", "lords_gemv.hip", "lords_gemv_b2.hip", "lords_gemv_b2q.hip", "lords_gemv_b3.hip", "lords_gemv_b4.hip", "lords_decode_mx.hip", "lords_prefill.hip", "lords_two_pass.hip", "lords_backward.hip"]
 HEADERS = ["lords_device.h", "lords_scale_f32.h", "lords_launch.h", "lords_decode_common.h", "lords_slab_address.h", "lords_gemv_kernel.h", os.path.join("..", "..", "include", "lords.h")]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -29,6 +29,9 @@ FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-command-line-argument", "-Wno-unknown-warning-option",
 ]
+
+# Results of the matrix instructions that are not kept in the accumulation registers by hand go to vector registers.
+FILE_FLAGS = {"lords_two_pass.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1", "-Wno-inline-asm"]}
 
 
 def _stale(target: str, deps: list[str]) -> bool:
@@ -42,7 +45,7 @@ def _compile(src: str, force: bool, build_dir: str = BUILD, extra: tuple = ()) -
     obj = os.path.join(build_dir, os.path.splitext(src)[0] + ".o")
     deps = [os.path.join(CSRC, src)] + [os.path.normpath(os.path.join(CSRC, h)) for h in HEADERS]
     if force or _stale(obj, deps):
-        cmd = [HIPCC, *FLAGS, *extra, "-c", os.path.join(CSRC, src), "-o", obj]
+        cmd = [HIPCC, *FLAGS, *FILE_FLAGS.get(src, []), *extra, "-c", os.path.join(CSRC, src), "-o", obj]
         r = subprocess.run(cmd, capture_output=True, text=True)
         if r.returncode != 0:
             raise RuntimeError(f"hipcc failed on {src}:\n{r.stderr[-6000:]}")

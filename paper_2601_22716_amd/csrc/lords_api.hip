@@ -27,6 +27,8 @@ struct WsView {
     void *tickets() const { return base ? base + lords::kZeroBytes : nullptr; }    // what the few-token kernels call "workspace"
     void *scratch() const { return base ? base + kFront : nullptr; }
     unsigned char *f32_parts = nullptr;     // kF32Parts bytes, or null (a workspace that is not the library's own)
+    // How a large product uses it: as the large-M kernel plans with what is there; by whole tiles; in two passes.
+    enum Large { kShared, kWhole, kTwoPass } large = kShared;
 };
 
 // Partial sums of a large-M product with fp32 factors, the most its plan ever asks for (256 workgroups x 128 x 256 tiles).
@@ -158,9 +160,56 @@ size_t matmul_need(const lords::MatmulProblem &p, lords_path path, size_t limit 
     return kFront + ((scratch + 255) & ~(size_t)255);
 }
 
-// The large-M kernel, with the scratch its problem has in this workspace.
+lords::BatchedProblem batch_of(const lords::MatmulProblem &p)
+{
+    lords::BatchedProblem bp;
+    bp.X = p.X; bp.codebook = p.codebook; bp.codes[0] = p.codes; bp.B[0] = p.B; bp.A[0] = p.A; bp.Y[0] = p.Y; bp.N[0] = p.N;
+    bp.L = 1; bp.M = p.M; bp.K = p.K; bp.r = p.r; bp.bits = p.bits;
+    bp.f32fact = p.f32fact; bp.f32out = p.f32out; bp.act = false; bp.tiled = p.tiled;
+    return bp;
+}
+
+// The matrices of a batched call for which pick(l) holds.
+template <class Pick>
+lords::BatchedProblem batch_where(const lords::BatchedProblem &bp, Pick pick)
+{
+    lords::BatchedProblem out = bp;
+    out.L = 0;
+    for (int l = 0; l < bp.L; ++l) {
+        if (!pick(l)) continue;
+        out.codes[out.L] = bp.codes[l]; out.B[out.L] = bp.B[l]; out.A[out.L] = bp.A[l]; out.Y[out.L] = bp.Y[l]; out.N[out.L] = bp.N[l];
+        ++out.L;
+    }
+    return out;
+}
+
+lords::MatmulProblem matrix_of(const lords::BatchedProblem &bp, int l)
+{
+    return lords::MatmulProblem{bp.X, bp.codes[l], bp.codebook, bp.B[l], bp.A[l], bp.Y[l], bp.M, bp.N[l], bp.K, bp.r, bp.bits, bp.f32fact, bp.f32out};
+}
+
+// The library's own workspace for a product in two passes, and `extra` bytes behind its scratch.  Where the memory is not to
+// be had (a stream that is being captured, mostly), whole tiles of the large-M kernel give the same result bit for bit.
+int two_pass_workspace(const lords::BatchedProblem &bp, size_t extra, void *stream, WsView *ws, size_t *own)
+{
+    *own = kFront + ((lords::two_pass_workspace_bytes(bp) + 255) & ~(size_t)255);
+    int rc = get_workspace(*own + extra, stream, ws);
+    ws->large = WsView::kTwoPass;
+    if (rc != LORDS_OK) {
+        *own = kFront;
+        rc = get_workspace(*own + extra, stream, ws);
+        ws->large = WsView::kWhole;
+    }
+    return rc;
+}
+
+// The large-M kernel, with the scratch its problem has in this workspace, or both passes.
 int launch_large(const lords::MatmulProblem &p, const WsView &ws, void *stream, const float *gate = nullptr)
 {
+    if (ws.large == WsView::kTwoPass && !gate)
+        return lords::launch_two_pass(batch_of(p), ws.scratch(), (hipStream_t)stream) == hipSuccess ? LORDS_OK : LORDS_ERR_LAUNCH;
+    if (ws.large != WsView::kShared)
+        return lords::launch_prefill_fast(p, nullptr, 0, ws.zeroed(), (hipStream_t)stream, gate) == hipSuccess ? LORDS_OK : LORDS_ERR_LAUNCH;
     void *part = ws.scratch();
     size_t bytes = ws.bytes > kFront ? ws.bytes - kFront : 0;
     if (p.f32fact && ws.f32_parts) {
@@ -189,11 +238,12 @@ int launch_matmul(const lords::MatmulProblem &p, lords_path path, const WsView &
 }
 
 // The library's own workspace for one checked problem on `path` (already resolved), plus `extra` bytes behind it
-// that are left to the caller (*extra_ptr).
-int plan_workspace(const lords::MatmulProblem &p, lords_path path, size_t extra, void *stream, WsView *ws, void **extra_ptr)
+// that are left to the caller (*extra_ptr).  `passes`: whether the product may go in two passes.
+int plan_workspace(const lords::MatmulProblem &p, lords_path path, size_t extra, void *stream, WsView *ws, void **extra_ptr, bool passes = true)
 {
-    const size_t own = p.f32fact && !is_decode(path) ? kFront : matmul_need(p, path);
-    const int rc = get_workspace(own + extra, stream, ws);
+    size_t own = p.f32fact && !is_decode(path) ? kFront : matmul_need(p, path);
+    const int rc = passes && !is_decode(path) && lords::two_pass_faster(batch_of(p)) ? two_pass_workspace(batch_of(p), extra, stream, ws, &own)
+                                                                             : get_workspace(own + extra, stream, ws);
     if (rc == LORDS_OK && extra_ptr) *extra_ptr = ws->base + own;
     return rc;
 }
@@ -205,6 +255,39 @@ int run_matmul(const lords::MatmulProblem &p, lords_path path, void *stream)
     WsView ws;
     const int rc = plan_workspace(p, path, 0, stream, &ws, nullptr);
     return rc != LORDS_OK ? rc : launch_matmul(p, path, ws, stream);
+}
+
+// Several matrices that each go to the large-M kernel or into two passes; a status, or -1 to have them one by one.  Every
+// matrix is summed as it would be alone.  In two passes together: those that alone would take them, and with them those that
+// alone are summed by whole tiles, if that is the faster way for all of these.
+int run_batched_large(const lords::BatchedProblem &bp, void *stream)
+{
+    if (bp.act) return -1;
+    auto alone = [&](int l) { return lords::two_pass_faster(batch_of(matrix_of(bp, l))); };
+    auto whole = [&](int l) { return alone(l) || lords::prefill_fast_workspace_bytes(matrix_of(bp, l), kNoLimit) == 0; };
+    lords::BatchedProblem twice = batch_where(bp, whole), rest = batch_where(bp, [&](int l) { return !whole(l); });
+    if (twice.L == 0 || !lords::two_pass_faster(twice)) {
+        twice = batch_where(bp, alone);
+        rest = batch_where(bp, [&](int l) { return !alone(l); });
+    }
+    WsView ws;
+    if (twice.L > 0) {
+        size_t own;
+        const int rc = two_pass_workspace(twice, 0, stream, &ws, &own);
+        if (rc != LORDS_OK) return rc;
+        if (ws.large == WsView::kTwoPass) {
+            if (lords::launch_two_pass(twice, ws.scratch(), (hipStream_t)stream) != hipSuccess) return LORDS_ERR_LAUNCH;
+        } else {
+            for (int l = 0; l < twice.L; ++l) {
+                const int rcl = launch_large(matrix_of(twice, l), ws, stream);
+                if (rcl != LORDS_OK) return rcl;
+            }
+        }
+    }
+    if (rest.L == 0) return LORDS_OK;
+    if (!lords::prefill_batched_supported(rest)) return -1;
+    if (get_workspace(kFront + lords::prefill_batched_workspace_bytes(rest), stream, &ws) != LORDS_OK) return -1;
+    return lords::launch_prefill_batched(rest, ws.scratch(), ws.zeroed(), (hipStream_t)stream) == hipSuccess ? LORDS_OK : LORDS_ERR_LAUNCH;
 }
 
 // Several matrices in ONE launch, if a kernel takes the case: a status, or -1 if none does.
@@ -222,10 +305,7 @@ int run_batched(const lords::BatchedProblem &bp, void *stream)
             const lords::MatmulProblem p{bp.X, bp.codes[l], bp.codebook, bp.B[l], bp.A[l], bp.Y[l], bp.M, bp.N[l], bp.K, bp.r, bp.bits, bp.f32fact, bp.f32out};
             if (is_decode(resolve_path(LORDS_PATH_AUTO, p))) return -1;
         }
-        if (!lords::prefill_batched_supported(bp)) return -1;
-        WsView ws;
-        if (get_workspace(kFront + lords::prefill_batched_workspace_bytes(bp), stream, &ws) != LORDS_OK) return -1;
-        return lords::launch_prefill_batched(bp, ws.scratch(), ws.zeroed(), (hipStream_t)stream) == hipSuccess ? LORDS_OK : LORDS_ERR_LAUNCH;
+        return run_batched_large(bp, stream);
     }
     WsView ws;
     const int rc = get_workspace(lords::kZeroBytes + lords::decode_mx_batched_workspace_bytes(bp), stream, &ws);
@@ -271,6 +351,32 @@ int gate_up_tokens(lords::BatchedProblem bp, int left)
     return cost(1024) + cost(rest) + 8.0 < 0.95 * cost(left) ? 1024 : left;
 }
 
+// The pair in two passes, all tokens at once: the gate's sums never leave the registers.  Without the scratch: both products by
+// whole tiles, 2048 tokens at a time, the gate's in memory.
+int run_gate_up_two_pass(const lords::BatchedProblem &bp, void *stream)
+{
+    WsView ws;
+    size_t own;
+    const int step = bp.M < 2048 ? bp.M : 2048;
+    const size_t tmp_bytes = (size_t)step * bp.N[0] * sizeof(float) + 16;         // (the gate is read four columns at a time)
+    int rc = two_pass_workspace(bp, 0, stream, &ws, &own);
+    if (rc == LORDS_OK && ws.large == WsView::kTwoPass)
+        return lords::launch_two_pass(bp, ws.scratch(), (hipStream_t)stream) == hipSuccess ? LORDS_OK : LORDS_ERR_LAUNCH;
+    rc = get_workspace(kFront + tmp_bytes, stream, &ws);
+    ws.large = WsView::kWhole;
+    for (int m0 = 0; m0 < bp.M && rc == LORDS_OK; m0 += step) {
+        lords::BatchedProblem part = bp;
+        part.M = bp.M - m0 < step ? bp.M - m0 : step;
+        part.X = (const unsigned char *)bp.X + (size_t)m0 * bp.K * 2;
+        float *G = (float *)ws.scratch();
+        rc = launch_large(gate_up_matrix(part, 0, G, true), ws, stream);
+        if (rc != LORDS_OK) break;
+        void *H = (unsigned char *)bp.Y[0] + (size_t)m0 * bp.N[0] * (bp.f32out ? 4 : 2);
+        rc = launch_large(gate_up_matrix(part, 1, H, bp.f32out), ws, stream, G);
+    }
+    return rc;
+}
+
 // The pair for all bp.M tokens (at most what gate_up_tokens says).  One launch up to 16 tokens where a kernel takes it.
 // Otherwise the gate's product goes to the workspace in fp32.  The large-M kernel multiplies by its silu where it stores the
 // up product; the general kernels write the up product beside it, and an element-wise pass follows.  The arithmetic is the
@@ -287,7 +393,7 @@ int run_gate_up(const lords::BatchedProblem &bp, void *stream)
     const lords_path path = resolve_path(LORDS_PATH_AUTO, pg);
     WsView ws;
     void *tmp = nullptr;
-    int rc = plan_workspace(pg, path, tmp_bytes, stream, &ws, &tmp);
+    int rc = plan_workspace(pg, path, tmp_bytes, stream, &ws, &tmp, false);
     if (rc != LORDS_OK) return rc;
     float *G = (float *)tmp, *U = G + count;
     pg.Y = G;
@@ -607,6 +713,7 @@ int lords_gate_up(const void *X, const void *codes_gate, const void *B_gate, con
     }
     bp.L = 2; bp.M = M; bp.K = K; bp.r = r; bp.bits = bits;
     bp.f32fact = f32fact; bp.f32out = f32out; bp.act = true;
+    if (gate_up_large(bp, M) && lords::two_pass_faster(bp)) return run_gate_up_two_pass(bp, stream);
     for (int m0 = 0, mc; m0 < M; m0 += mc) {
         mc = gate_up_tokens(bp, M - m0);
         bp.M = mc;

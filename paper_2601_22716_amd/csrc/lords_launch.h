@@ -134,6 +134,14 @@ hipError_t launch_prefill_fast(const MatmulProblem &p, void *part, size_t part_b
 bool prefill_batched_supported(const BatchedProblem &p);
 size_t prefill_batched_workspace_bytes(const BatchedProblem &p);
 hipError_t launch_prefill_batched(const BatchedProblem &p, void *part, void *zeroed, hipStream_t st);
+// Many tokens: W dequantised once into scratch, then a product that reads it (lords_two_pass.hip); one matrix, several that
+// read the same X, or (act) a gate/up pair.  Scratch: two_pass_workspace_bytes, at most kTwoPassBytes.
+constexpr size_t kTwoPassBytes = (size_t)128 << 20;
+bool two_pass_supported(const BatchedProblem &p);
+size_t two_pass_workspace_bytes(const BatchedProblem &p);
+// Whether that is the faster way (more than 128 tokens; the large-M kernel must take every matrix).
+bool two_pass_faster(const BatchedProblem &p);
+hipError_t launch_two_pass(const BatchedProblem &p, void *scratch, hipStream_t st);
 // ... and the general variant (any rank; lords_fused.hip).
 hipError_t launch_prefill(const MatmulProblem &p, hipStream_t st);
 

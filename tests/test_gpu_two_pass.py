@@ -1,0 +1,205 @@
+"""Products of many tokens that go in two passes (weights dequantised once into scratch, then a product that reads them),
+through the C ABI: against the fp64 oracle on sampled rows, and bit for bit against the large-M kernel on whole tiles, which
+performs the same operations in the same order.  Gates as for lords_matmul.
+
+Sizes: the smallest at which the planner takes two passes, off the tiles in every direction (tokens and rows not multiples
+of 256, 128, 16 or 4, an odd number of K tiles, a ragged last one), every padded contraction, ranks that are not multiples
+of 4 or 8.
+"""
+import ctypes
+import sys
+
+import numpy as np
+import pytest
+
+import lords_inputs as li
+from oracle import lords_oracle as onp
+
+pytestmark = pytest.mark.gpu
+
+Y_TOL, Y_MAX_TOL = 5e-3, 2e-2
+
+
+def say(*a):
+    print(*a, flush=True)
+    sys.stdout.flush()
+
+
+@pytest.fixture(scope="module")
+def gpu():
+    import torch
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    from tests import gpu_util
+    return gpu_util
+
+
+def takes_two_passes(M, Ns, K, r, bits, f32, act=False):
+    """The planner's choice (lords::two_pass_faster, a host function of the library)."""
+    import paper_2601_22716_amd as L
+    ptr, num, flag = ctypes.c_void_p, ctypes.c_int, ctypes.c_bool
+
+    class Batched(ctypes.Structure):
+        _fields_ = [("X", ptr), ("codebook", ptr), ("codes", ptr * 8), ("B", ptr * 8), ("A", ptr * 8), ("Y", ptr * 8), ("N", num * 8),
+                    ("L", num), ("M", num), ("K", num), ("r", num), ("bits", num),
+                    ("f32fact", flag), ("f32out", flag), ("act", flag), ("tiled", flag)]
+    p = Batched(L=len(Ns), M=M, K=K, r=r, bits=bits, f32fact=f32, f32out=True, act=act)
+    for l, n in enumerate(Ns):
+        p.N[l] = n
+    f = L.library()._ZN5lords15two_pass_fasterERKNS_14BatchedProblemE
+    f.restype = flag
+    return f(ctypes.byref(p))
+
+
+def check_rows(Y, c, X_f32, bits, what, seed=0, count=24):
+    rows = np.unique(np.concatenate([np.random.default_rng(seed).integers(0, c.N, count), [0, c.N - 1]]))
+    want = onp.matmul_rows(X_f32, c.codes, c.codebook, c.B_f32, c.A_f32, bits, rows)
+    rf, mx = onp.rel_fro(Y[:, rows], want), onp.max_abs_over_rms(Y[:, rows], want)
+    say(f"   {what}: rel_fro={rf:.2e} max/rms={mx:.2e}")
+    assert np.isfinite(Y).all(), what
+    assert rf <= Y_TOL and mx <= Y_MAX_TOL, (what, rf, mx)
+
+
+def by_whole_tiles(d, M):
+    """The large-M kernel with a workspace that has no room for parts (its front alone), or None where it asks for more."""
+    import torch
+    import paper_2601_22716_amd as L
+    f32 = d.B.dtype == torch.float32
+    front = L.lords_workspace_zero_bytes()
+    if not f32 and L.lords_workspace_bytes(M, d.N, d.K, d.r, d.bits, L.LORDS_BF16) > front:
+        return None
+    ws = torch.zeros(front, dtype=torch.uint8, device="cuda")
+    Y = torch.full((M, d.N), float("nan"), device="cuda")
+    L.lords_matmul_ws(d.X, d.codes, d.codebook, d.B, d.A, Y, M, d.N, d.K, d.r, d.bits, ws)
+    torch.cuda.synchronize()
+    return Y.cpu().numpy()
+
+
+@pytest.mark.parametrize("M,N,K,r,bits,fdt", [
+    (3000, 777, 544, 64, 4, "f32"), (3001, 1030, 672, 43, 3, "f32"), (4097, 1500, 544, 41, 2, "f32"),
+    (3000, 2999, 1056, 16, 4, "f32"), (4097, 2999, 4128, 10, 3, "f32"),
+    (3000, 2999, 544, 99, 2, "bf16"), (3001, 3002, 672, 128, 4, "bf16"), (3000, 2999, 1056, 45, 3, "bf16"),
+    (3000, 2999, 1056, 64, 2, "bf16"), (3000, 2999, 2208, 31, 4, "bf16"), (3000, 2999, 2208, 8, 3, "bf16")])
+def test_two_pass_product(gpu, M, N, K, r, bits, fdt):
+    say(f"two passes M={M} N={N} K={K} r={r} bits={bits} factors={fdt}")
+    assert takes_two_passes(M, [N], K, r, bits, fdt == "f32")
+    c = li.make_case("tiny", M=M, N=N, K=K, r=r, bits=bits, factor_dtype=fdt, seed=3, signed_factors=True)
+    d = gpu.DeviceCase(c)
+    Y = d.matmul()
+    check_rows(Y, c, c.X_f32, bits, "Y")
+    whole = by_whole_tiles(d, M)
+    if whole is not None:
+        np.testing.assert_array_equal(Y, whole)
+
+
+def test_two_pass_slab_tiles_and_bf16_output(gpu):
+    """Codes in the slab-tile layout give the bits of the canonical rows; bf16 outputs are the rounded fp32 ones."""
+    import torch
+    import paper_2601_22716_amd as L
+    M, N, K, r, bits = 3000, 2999, 544, 99, 3
+    say("two passes, slab tiles")
+    assert takes_two_passes(M, [N], K, r, bits, False)
+    c = li.make_case("tiny", M=M, N=N, K=K, r=r, bits=bits, factor_dtype="bf16", seed=4, signed_factors=True)
+    d = gpu.DeviceCase(c)
+    tiled = torch.empty(L.lords_repack_bytes(N, K, bits), dtype=torch.uint8, device="cuda")
+    L.lords_repack(d.codes, tiled, N, K, bits)
+    Y32 = torch.full((M, N), float("nan"), device="cuda")
+    Y16 = torch.full((M, N), float("nan"), device="cuda", dtype=torch.bfloat16)
+    L.lords_matmul_repacked(d.X, tiled, d.codebook, d.B, d.A, Y32, M, N, K, r, bits)
+    L.lords_matmul(d.X, d.codes, d.codebook, d.B, d.A, Y16, M, N, K, r, bits)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(Y32.cpu().numpy(), d.matmul())
+    assert torch.equal(Y32.bfloat16(), Y16)
+
+
+@pytest.mark.parametrize("N,K", [(19000, 4128), (33000, 2080)])
+def test_two_pass_in_chunks(gpu, N, K):
+    """W larger than the scratch: rows in chunks, the last one ragged."""
+    import torch
+    M, r, bits = 1300, 128, 2
+    say(f"two passes in chunks N={N} K={K}")
+    assert takes_two_passes(M, [N], K, r, bits, False) and ((N + 15) // 16) * ((K + 127) // 128) * 4096 > 128 << 20
+    c = li.make_case("tiny", M=M, N=N, K=K, r=r, bits=bits, factor_dtype="bf16", seed=5, signed_factors=True)
+    d = gpu.DeviceCase(c)
+    Y = d.matmul()
+    check_rows(Y, c, c.X_f32, bits, "Y")
+    whole = by_whole_tiles(d, M)
+    if whole is not None:
+        np.testing.assert_array_equal(Y, whole)
+    del d
+    torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("M,Ns,K,r,bits,fdt", [
+    (3000, [2999, 500, 777], 544, 64, 4, "f32"), (4096, [3000, 40, 3001], 1056, 99, 3, "bf16"), (3000, [2999, 300], 1056, 64, 2, "bf16")])
+def test_two_pass_batched(gpu, M, Ns, K, r, bits, fdt):
+    """Several matrices, some of which alone would not go in two passes: the single calls' bits; from a captured graph too."""
+    import torch
+    import paper_2601_22716_amd as L
+    say(f"two passes batched M={M} Ns={Ns} K={K} r={r} bits={bits} factors={fdt}")
+    assert takes_two_passes(M, [Ns[0]], K, r, bits, fdt == "f32")
+    cases = [li.make_case("tiny", M=M, N=n, K=K, r=r, bits=bits, factor_dtype=fdt, seed=7 + i, signed_factors=True) for i, n in enumerate(Ns)]
+    dev = [gpu.DeviceCase(c) for c in cases]
+    out = [torch.full((M, n), float("nan"), device="cuda") for n in Ns]
+
+    def call():
+        L.lords_matmul_batched(dev[0].X, [d.codes for d in dev], dev[0].codebook, [d.B for d in dev], [d.A for d in dev], out, Ns, M, K, r, bits)
+    call()
+    torch.cuda.synchronize()
+    single = [d.matmul(X=dev[0].X, M=M) for d in dev]
+    for l, (c, o) in enumerate(zip(cases, out)):
+        check_rows(o.cpu().numpy(), c, cases[0].X_f32, bits, f"matrix {l}", seed=l)
+        np.testing.assert_array_equal(o.cpu().numpy(), single[l], err_msg=f"matrix {l}")
+    graph, stream = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    with torch.cuda.graph(graph, stream=stream):
+        call()
+    for rep in range(3):
+        for o in out:
+            o.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        for l, o in enumerate(out):
+            np.testing.assert_array_equal(o.cpu().numpy(), single[l], err_msg=f"replay {rep}, matrix {l}")
+        dev[-1].matmul(X=dev[0].X, M=M)                      # eager work between the replays
+
+
+@pytest.mark.parametrize("M,N,K,r,bits,fdt", [(3000, 2999, 544, 64, 4, "f32"), (3001, 2002, 1056, 99, 3, "bf16"), (3000, 20011, 4128, 64, 2, "bf16")])
+def test_two_pass_gate_up(gpu, M, N, K, r, bits, fdt):
+    """The pair against silu(gate) * up formed from the two single products, whose sums it has: fp32 silu and product, so
+    a few units of 2^-24 and of the exponential's error, relative to the element."""
+    import torch
+    import paper_2601_22716_amd as L
+    say(f"two passes gate/up M={M} N={N} K={K} r={r} bits={bits} factors={fdt}")
+    assert takes_two_passes(M, [N, N], K, r, bits, fdt == "f32", act=True)
+    dev = [gpu.DeviceCase(li.make_case("tiny", M=M, N=N, K=K, r=r, bits=bits, factor_dtype=fdt, seed=11 + i, signed_factors=True)) for i in range(2)]
+    ga, up = dev
+    G, U = (torch.from_numpy(d.matmul(X=ga.X, M=M)).double() for d in dev)
+    H = torch.full((M, N), float("nan"), device="cuda")
+    L.lords_gate_up(ga.X, ga.codes, ga.B, ga.A, up.codes, up.B, up.A, ga.codebook, H, M, N, K, r, bits)
+    torch.cuda.synchronize()
+    want = G * torch.sigmoid(G) * U
+    # (the sums may be cut otherwise where a single product shares tiles: 1e-6 of their rms)
+    bound = 4e-6 * want.abs() + 4e-6 * (G.square().mean().sqrt() * U.abs() + U.square().mean().sqrt() * G.abs()) + 1e-12
+    assert bool(((H.cpu().double() - want).abs() <= bound).all())
+
+
+@pytest.mark.parametrize("fdt,r", [("f32", 64), ("bf16", 99)])
+def test_two_pass_backward_input(gpu, fdt, r):
+    """The gradient of the input is the forward product of the transposed layer."""
+    import torch
+    import paper_2601_22716_amd as L
+    M, N, K, bits = 3000, 544, 2976, 4
+    say(f"two passes backward factors={fdt} r={r}")
+    assert takes_two_passes(M, [K], N, r, bits, fdt == "f32")
+    c = li.make_case("tiny", M=M, N=N, K=K, r=r, bits=bits, factor_dtype=fdt, seed=9, signed_factors=True)
+    d = gpu.DeviceCase(c)
+    codes_t = torch.empty((K, L.lords_row_bytes(N, bits)), dtype=torch.uint8, device="cuda")
+    L.lords_transpose_codes(d.codes, codes_t, N, K, bits)
+    dY = torch.randn((M, N), generator=torch.Generator(device="cuda").manual_seed(1), device="cuda").bfloat16()
+    dX = torch.full((M, K), float("nan"), device="cuda")
+    L.lords_backward_input(dY, codes_t, d.codebook, d.B, d.A, dX, M, N, K, r, bits)
+    torch.cuda.synchronize()
+    Wh = c.codebook.astype(np.float64)[d.unpack()] * (c.B_f32.astype(np.float64) @ c.A_f32.astype(np.float64))
+    want = dY.float().cpu().numpy().astype(np.float64) @ Wh
+    rf, mx = onp.rel_fro(dX.cpu().numpy(), want), onp.max_abs_over_rms(dX.cpu().numpy(), want)
+    say(f"   dX: rel_fro={rf:.2e} max/rms={mx:.2e}")
+    assert rf <= Y_TOL and mx <= Y_MAX_TOL, (rf, mx)
