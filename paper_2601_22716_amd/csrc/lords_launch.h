@@ -125,6 +125,8 @@ bool prefill_fast_supported(const MatmulProblem &p);
 // less it plans for less, down to 0 = one whole tile per workgroup), and the launch: `part`/`part_bytes` that
 // scratch, `zeroed` kZeroBytes of device memory that are zero when handed over and left at zero.
 size_t prefill_fast_workspace_bytes(const MatmulProblem &p, size_t limit);
+// Whether it runs as the form with one wave per SIMD (lords_prefill_wide.hip).
+bool prefill_wide_taken(const MatmulProblem &p, size_t limit);
 // The planner's estimate of the launch, in us, with all the scratch it asks for.
 double prefill_fast_cost(const MatmulProblem &p);
 // `gate`: null, or M x N fp32 sums of a gate matrix and 12 readable bytes behind them; Y then receives silu(gate) * (the product).

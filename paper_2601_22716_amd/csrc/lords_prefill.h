@@ -1,0 +1,58 @@
+// What the two large-M kernels (lords_prefill.hip, lords_prefill_wide.hip) share: the arguments of a launch, code pairs.
+#pragma once
+#include "lords_decode_common.h"
+
+namespace lords {
+
+// One weight matrix of a launch.  Several matrices that read the same X (and are cut into tiles of the same shape) can
+// share a launch: each gets a contiguous range of blockIdx.x, a multiple of eight long, and keeps the cut of the work it
+// would have alone, so its sums are the same bit for bit.  Layers too small to fill the chip run beside each other and
+// the last round of one is filled by the next.  q, k, v (4096 + 1024 + 1024 rows x 4096, 4 bits, rank 32) one by one -> in one
+// launch, us: 17 tokens 78 -> 45, 300 103 -> 70, 1000 122 -> 93, 2048 166 -> 162; 512 + 128 + 128 x 512, 3 bits, 17 tokens
+// 33 -> 12.
+struct PfLayer {
+    const uint8_t *codes;
+    const void *B;         // N x rf, bf16 or fp32
+    const void *A;         // rf x K, bf16 or fp32
+    void *Y;
+    const float *gate;     // M x N fp32 or null: Y = silu(gate) * (the product) instead of the product
+    float *part;           // per workgroup: the accumulators of a part that does not start at the tile's first column
+    uint32_t *arrived;     // per output tile: parts handed over so far (zero before and after a launch)
+    int N;
+    int nt;                // tiles along N
+    int per;               // work units (one K tile of one output tile) per workgroup; units are numbered tile by tile
+    int x0, gx;            // first blockIdx.x of this matrix and how many it has (multiples of 8)
+};
+
+template <int NLAYERS>
+struct PrefillArgsT {
+    const uint16_t *X;
+    const float *codebook;
+    int M, K;
+    int r;                 // contraction length of the scales: rf, or 3 rf for fp32 factors (hi/lo parts, see the kernel)
+    int rf;                // rank of the factors
+    int y_f32;
+    int row_bytes;
+    int mt;                // tiles along M
+    int ntiles_k;          // ceil(K / 128)
+    int tiled;             // codes in the slab-tile layout: tile (slab, K tile) contiguous, chunk = 16 g + c
+    int L;                 // matrices
+    PfLayer layer[NLAYERS];
+};
+
+constexpr int kPfCopies = 8;                               // of the level table
+
+template <int BITS>
+__device__ __forceinline__ uint32_t pair_index(const uint32_t (&w)[BITS], int p)
+{
+    const int o = 2 * BITS * p, d = o >> 5, s = o & 31;
+    uint32_t v = w[d] >> s;
+    if (s + 2 * BITS > 32) v |= w[(d + 1) < BITS ? d + 1 : d] << (32 - s);
+    return v & ((1u << (2 * BITS)) - 1u);
+}
+
+// The form of the kernel with one wave per SIMD: 256 x 256 tiles, bf16 factors of rank 33 .. 64 (lords_prefill_wide.hip).
+hipError_t launch_prefill_wide(const PrefillArgsT<1> &a, dim3 grid, int bits, hipStream_t st);
+hipError_t launch_prefill_wide(const PrefillArgsT<kMaxBatch> &a, dim3 grid, int bits, hipStream_t st);
+
+}  // namespace lords

@@ -41,47 +41,10 @@
 // rounded once, to bf16, and no level has to lie within the range of fp16.
 #include <numeric>
 #include <type_traits>
-#include "lords_decode_common.h"
+#include "lords_prefill.h"
 
 namespace lords {
 
-// One weight matrix of a launch.  Several matrices that read the same X (and are cut into tiles of the same shape) can
-// share a launch: each gets a contiguous range of blockIdx.x, a multiple of eight long, and keeps the cut of the work it
-// would have alone, so its sums are the same bit for bit.  Layers too small to fill the chip run beside each other and
-// the last round of one is filled by the next.  q, k, v (4096 + 1024 + 1024 rows x 4096, 4 bits, rank 32) one by one -> in one
-// launch, us: 17 tokens 78 -> 45, 300 103 -> 70, 1000 122 -> 93, 2048 166 -> 162; 512 + 128 + 128 x 512, 3 bits, 17 tokens
-// 33 -> 12.
-struct PfLayer {
-    const uint8_t *codes;
-    const void *B;         // N x rf, bf16 or fp32
-    const void *A;         // rf x K, bf16 or fp32
-    void *Y;
-    const float *gate;     // M x N fp32 or null: Y = silu(gate) * (the product) instead of the product
-    float *part;           // per workgroup: the accumulators of a part that does not start at the tile's first column
-    uint32_t *arrived;     // per output tile: parts handed over so far (zero before and after a launch)
-    int N;
-    int nt;                // tiles along N
-    int per;               // work units (one K tile of one output tile) per workgroup; units are numbered tile by tile
-    int x0, gx;            // first blockIdx.x of this matrix and how many it has (multiples of 8)
-};
-
-template <int NLAYERS>
-struct PrefillArgsT {
-    const uint16_t *X;
-    const float *codebook;
-    int M, K;
-    int r;                 // contraction length of the scales: rf, or 3 rf for fp32 factors (hi/lo parts, see the kernel)
-    int rf;                // rank of the factors
-    int y_f32;
-    int row_bytes;
-    int mt;                // tiles along M
-    int ntiles_k;          // ceil(K / 128)
-    int tiled;             // codes in the slab-tile layout: tile (slab, K tile) contiguous, chunk = 16 g + c
-    int L;                 // matrices
-    PfLayer layer[NLAYERS];
-};
-
-constexpr int kPfCopies = 8;                               // of the level table
 constexpr int pf_pair_bytes(bool f32fact) { return f32fact ? 8 : 4; }
 typedef float PfLevels __attribute__((ext_vector_type(2)));
 
@@ -97,15 +60,6 @@ __device__ __forceinline__ void lds_direct_16(const void *gbase, uint32_t goff, 
     // these loads itself: s_waitcnt vmcnt(0) and a barrier before a buffer is read.
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                  :: "s"(lds_wave_base), "v"(goff), "s"(gbase) : "memory", "m0");
-}
-
-template <int BITS>
-__device__ __forceinline__ uint32_t pair_index(const uint32_t (&w)[BITS], int p)
-{
-    const int o = 2 * BITS * p, d = o >> 5, s = o & 31;
-    uint32_t v = w[d] >> s;
-    if (s + 2 * BITS > 32) v |= w[(d + 1) < BITS ? d + 1 : d] << (32 - s);
-    return v & ((1u << (2 * BITS)) - 1u);
 }
 
 // F32: fp32 factors.  They are split x = hi + lo (two bf16) and the scale is the contraction of length
@@ -724,6 +678,9 @@ struct PfPlan {
 };
 
 constexpr int kPfCUs = 256;
+// The estimates for 128-token tiles at padded rank 64 read about so much high (1.15 .. 1.3 of what 30 products took), those of the
+// 256 x 256 tiles that they are compared with do not.
+constexpr double kWideScale = 1.22;
 
 static PfPlan pf_plan(const MatmulProblem &p, size_t avail)
 {
@@ -742,10 +699,14 @@ static PfPlan pf_plan(const MatmulProblem &p, size_t avail)
     const double rank_cost = d.ss == 1 ? 1.0 : d.ss == 2 ? 1.4 : 2.0;      // (six times 32: a shape and a time of its own)
     const Cand small_rank[4] = {{1, 2, 8, 16, 3.45}, {2, 2, 4, 8, 2.4}, {1, 2, 8, 8, 2.15}, {1, 2, 4, 8, 1.75}};
     // fp32 factors (contraction 3 r) take them at any rank: the A tile of a 256-token tile has no registers to pass through.
-    const Cand large_rank[2] = {{1, 2, 8, 8, 2.15 * rank_cost}, {1, 2, 4, 8, 1.75 * rank_cost}};
+    // bf16 factors of padded rank 64 have 256 x 256 tiles above 128 tokens in the other form of the kernel (lords_prefill_wide.hip):
+    // 3.3 .. 3.6 us a K tile, which pays where there are tiles for most of the CUs: its parts are twice as large and cost
+    // 27 us to hand over when a tile has two, 38 .. 47 when four, 50 when six (2-bit 28672 x 8192 at 256 tokens, whole / two / three
+    // and more parts 214 / 142 / 148 us, 128-token tiles 177; 3-bit 11008 x 4096 at 333 tokens 115 / 91 / 85 against 66).
+    const Cand large_rank[3] = {{1, 2, 8, 8, 2.15 * rank_cost}, {1, 2, 4, 8, 1.75 * rank_cost}, {1, 4, 4, 16, 3.55}};
     const Cand six[1] = {{1, 2, 4, 4, 3.0}};                 // (64 x 128, four waves: 3.3 us measured)
     const Cand *cands = d.ss == 1 ? small_rank : d.ss == 6 ? six : large_rank;
-    const int ncands = d.ss == 1 ? 4 : d.ss == 6 ? 1 : 2;
+    const int ncands = d.ss == 1 ? 4 : d.ss == 6 ? 1 : d.ss == 2 && !p.f32fact && p.M > 128 ? 3 : 2;
     double best = 1e30;
     d.wm = 1; d.R = 2; d.wn = 4; d.mb = d.ss == 6 ? 4 : 8; d.per = ntiles_k; d.part_bytes = 0;
     for (int i = 0; i < ncands; ++i) {
@@ -758,7 +719,7 @@ static PfPlan pf_plan(const MatmulProblem &p, size_t avail)
         const size_t tile_bytes = (size_t)tokens * rows * sizeof(float);
         // whole tiles, dealt by the hardware in rounds
         {
-            const double cost = (double)((tiles + kPfCUs - 1) / kPfCUs) * ntiles_k * c.t;
+            const double cost = (double)((tiles + kPfCUs - 1) / kPfCUs) * ntiles_k * c.t * (c.R == 4 ? kWideScale : 1.0);
             if (cost < best) { best = cost; d.wm = c.wm; d.R = c.R; d.wn = c.wn; d.mb = c.mb; d.per = ntiles_k; d.part_bytes = 0; }
         }
         // equal runs of units over `wgs` workgroups.  Its price is the hand-over of the parts: measured
@@ -777,7 +738,9 @@ static PfPlan pf_plan(const MatmulProblem &p, size_t avail)
             const long bounds = (units - 1) / per, written = bounds - bounds / (ntiles_k / std::gcd(per, ntiles_k));
             const double full = p.M <= 64 && tokens == 128 ? 0.5 : 1.0;          // (half a tile travels)
             const double mb_written = (double)written * tile_bytes * full / 1048576.0;
-            const double cost = per >= ntiles_k ? per * c.t * 1.08 + 4.0 + mb_written / 2.4
+            const int others = (ntiles_k - 2 + per) / per;                       // parts that the last of a tile's waits for, at most
+            const double cost = c.R == 4 ? kWideScale * (per >= ntiles_k ? per * c.t * 1.08 + 25.0 : per * c.t + 20.0 + 7.0 * (ntiles_k % per ? others : ntiles_k / per - 1))
+                              : per >= ntiles_k ? per * c.t * 1.08 + 4.0 + mb_written / 2.4
                                                 : per * c.t + 4.0 + mb_written / 1.2;
             if (cost < best) { best = cost; d.wm = c.wm; d.R = c.R; d.wn = c.wn; d.mb = c.mb; d.per = per; d.part_bytes = bytes; }
         }
@@ -795,6 +758,8 @@ size_t prefill_fast_workspace_bytes(const MatmulProblem &p, size_t limit)
 {
     return pf_plan(p, limit).part_bytes;
 }
+
+bool prefill_wide_taken(const MatmulProblem &p, size_t limit) { return pf_plan(p, limit).R == 4; }
 
 double prefill_fast_cost(const MatmulProblem &p) { return pf_plan(p, ~(size_t)0).cost; }
 
@@ -822,6 +787,7 @@ static hipError_t launch_pf(const PrefillArgsT<MULTI ? kMaxBatch : 1> &a, const 
     if (bits == B_ && ss == S_) {                                                                                   \
         if (f32fact) e = S_ < 4 && wn == 8 ? launch_pf_t<B_, (S_ < 4 ? S_ : 1), 1, 2, 8, 8, true, MULTI>(a, grid, st) \
                                            : launch_pf_t<B_, S_, 1, 2, 4, 8, true, MULTI>(a, grid, st);              \
+        else if (S_ == 2 && d.mb == 16) e = launch_prefill_wide(a, grid, bits, st);                                  \
         else if (S_ == 1 && d.mb == 16) e = launch_pf_t<B_, 1, 1, 2, 8, 16, false, MULTI>(a, grid, st);              \
         else if (S_ == 1 && wm == 2) e = launch_pf_t<B_, 1, 2, 2, 4, 8, false, MULTI>(a, grid, st);                  \
         else if (wn == 8) e = launch_pf_t<B_, S_, 1, 2, 8, 8, false, MULTI>(a, grid, st);                            \
