@@ -24,6 +24,11 @@
 // v_mfma_f32_16x16x16_bf16 for the contraction over k: dB needs no data movement at all.
 // For dA (contraction over n) the same P values go to LDS as a row-major bf16 tile and come back
 // through the transposing read, with the B tile as the other operand.
+// The tile's end (P, dB, dA) goes in two passes of 128 rows, 32 of each row group, so that all eight waves work in
+// both; the two column halves' dB meet in LDS.  (In passes of 128 columns half the waves stood by, and their dB left as parts
+// of their own: 14336 x 4096, 2048 tokens, 4 bits, rank 32 with its reduction 287 -> 269 us, 3 bits, rank 48 334 -> 287;
+// 4096 x 4096, fp32 rank 16, 500 tokens 41 -> 36.5.)  An order of the tiles by XCD, eight row by four column tiles at a time,
+// changed nothing.
 // G and P never reach HBM.  The sums over the other tiles (column tiles for dB, row tiles for dA)
 // are written as fp32 partial results and added in a fixed order by reduce_factor_parts_kernel:
 // results are run-to-run identical.
@@ -133,7 +138,7 @@ struct FgArgs {
     const float *codebook;
     const void *B;         // N x r
     const void *A;         // r x K
-    float *partB;          // [2*ktiles][N][r]: one part per half tile (128 columns)
+    float *partB;          // [ktiles][N][r]
     float *partA;          // [ntiles][r][K]
     int M, N, K, r;
     int f32fact;
@@ -145,6 +150,7 @@ constexpr int kFgThreads = 512;
 constexpr int kFgBN = 256, kFgBK = 256, kFgMC = 32;
 constexpr int kFgTile = kFgMC * 512;                                      // bytes of one dY or X tile (32 tokens x 256 columns)
 constexpr int kFgLoads = 4;                                               // direct-to-LDS loads per wave and chunk
+constexpr int kFgCopies = 32;                                             // of the level table: lanes of a half-wave read different banks
 constexpr int kFgAST = 520;                                               // bytes per row of the A tile (256 columns + pad)
 
 __device__ __forceinline__ void fg_lds_direct_16(const void *gbase, uint32_t goff, uint32_t lds_wave_base)
@@ -191,14 +197,14 @@ __global__ __launch_bounds__(kFgThreads) __attribute__((amdgpu_waves_per_eu(2, 2
     constexpr int BST = (RP + 4) * 2;                         // bytes per row of the B tile
     constexpr int NB = SS == 1 ? 3 : 2;                       // staging buffers (what LDS leaves room for)
     constexpr int STAGE = NB * 2 * kFgTile;
-    constexpr int CW = 4 * BITS, CST = CW + 1;                // dwords of 128 codes of a row; padded LDS row
+    constexpr int CW = 4 * BITS, CST = 2 * CW + 1;            // dwords of 128 codes of a row; padded LDS row of 256
     extern __shared__ __align__(16) unsigned char smem[];
     unsigned char *As = smem + STAGE;                         // [RP][kFgAST]  bf16
     unsigned char *Bs = As + RP * kFgAST;                     // [256][BST]    bf16
-    float *cb = reinterpret_cast<float *>(Bs + kFgBN * BST);  // [2^BITS]
-    // codes of one half of the tile (256 rows x 128 columns): behind the P tile where the staging
+    float *cb = reinterpret_cast<float *>(Bs + kFgBN * BST);  // [2^BITS][kFgCopies]
+    // codes of half the tile's rows (128 rows x 256 columns): behind the P tile where the staging
     // region is large enough, else in a region of its own
-    uint32_t *ct = SS == 1 ? reinterpret_cast<uint32_t *>(smem + 65536) : reinterpret_cast<uint32_t *>(cb + (1 << BITS));
+    uint32_t *ct = SS == 1 ? reinterpret_cast<uint32_t *>(smem + 65536) : reinterpret_cast<uint32_t *>(cb + (1 << BITS) * kFgCopies);
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int c = lane & 15, g = lane >> 4;
@@ -240,22 +246,29 @@ __global__ __launch_bounds__(kFgThreads) __attribute__((amdgpu_waves_per_eu(2, 2
 #pragma unroll
         for (int i = 0; i < kFgLoads; ++i) stage_one(ch, p, i);
     };
-    // ---- the packed codes of the tile (256 rows x 8*BITS dwords), requested now with coalesced loads and
-    //      parked in registers over the token loop; they go to LDS, half a tile at a time, afterwards ------
-    const int row_dwords = a.row_bytes >> 2;
-    uint32_t ctile[4 * BITS];
-#pragma unroll
-    for (int q = 0; q < 4 * BITS; ++q) {
-        const int id = tid + kFgThreads * q, row = id / (2 * CW), dd = id % (2 * CW);
-        const int gd = (k0 >> 5) * BITS + dd;
-        ctile[q] = 0;
-        if (n0 + row < N && gd < row_dwords)
-            ctile[q] = reinterpret_cast<const uint32_t *>(a.codes + (size_t)(n0 + row) * a.row_bytes)[gd];
-    }
     const int nchunks = (M + kFgMC - 1) / kFgMC;
 #pragma unroll
     for (int d = 0; d < NB - 1; ++d)
         if (d < nchunks) stage(d, d);
+    // ---- the packed codes of the tile (256 rows x 8*BITS dwords), requested now with coalesced loads, 16 bytes each, and
+    //      parked in registers over the token loop; they go to LDS, half a tile at a time, afterwards ------
+    const int row_dwords = a.row_bytes >> 2;
+    const bool inside = n0 + kFgBN <= N && k0 + kFgBK <= K;
+    u32x4 ctile[BITS];
+#pragma unroll
+    for (int q = 0; q < BITS; ++q) {
+        const int id = tid + kFgThreads * q, row = id / (CW / 2), dd = id % (CW / 2) * 4;
+        const int gd = (k0 >> 5) * BITS + dd;
+        const uint32_t *src = reinterpret_cast<const uint32_t *>(a.codes + (size_t)min(n0 + row, N - 1) * a.row_bytes) + gd;
+        if (inside) {
+            typedef uint32_t u32x4_dword __attribute__((ext_vector_type(4), aligned(4)));
+            const u32x4_dword w = *reinterpret_cast<const u32x4_dword *>(src);
+            ctile[q] = u32x4{w[0], w[1], w[2], w[3]};
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) ctile[q][e] = n0 + row < N && gd + e < row_dwords ? src[e] : 0u;
+        }
+    }
 
     // ---- A tile (rank x 256 columns), B tile (256 rows x rank), level table: once per workgroup ------
     typedef __attribute__((__vector_size__(2 * sizeof(uint32_t)))) uint32_t u32x2;
@@ -310,7 +323,7 @@ __global__ __launch_bounds__(kFgThreads) __attribute__((amdgpu_waves_per_eu(2, 2
             *reinterpret_cast<uint16_t *>(Bs + nn * BST + j * 2) = v;
         }
     }
-    if (tid < (1 << BITS)) cb[tid] = a.codebook[tid];
+    for (int id = tid; id < (1 << BITS) * kFgCopies; id += kFgThreads) cb[id] = a.codebook[id / kFgCopies];
 
     // ---- G = dY^T X over the tokens -----------------------------------------------------------------
     f32x4 acc[8][4];
@@ -353,104 +366,135 @@ __global__ __launch_bounds__(kFgThreads) __attribute__((amdgpu_waves_per_eu(2, 2
     }
     __syncthreads();                                       // every wave has left the last chunk: the buffers are free
 
-    // ---- per half of the tile's columns (h = 0: the waves with wk = 0 hold it, then h = 1):
-    //      P = level (.) G; dB = P A^T straight from the registers; P to LDS; dA = B^T P from there ------
-    unsigned char *Ps = smem;                                 // [256][256 bytes], chunk-swizzled
+    // ---- in two passes of 128 rows (pass p: rows 64 wn + 32 p .. + 32 of each row group, so that every wave takes part):
+    //      P = level (.) G; dB = P A^T straight from the registers; P to LDS; dA = B^T P from there; the two column halves'
+    //      contributions to dB are added through LDS ------------------------------------------------------------------
+    unsigned char *Ps = smem;                                 // [128][512 bytes], chunk-swizzled: row 32 wn + (row - 64 wn - 32 p)
     typedef __attribute__((__vector_size__(4 * sizeof(short)))) short s16x4v;
+    f32x4 dAacc[2][JB];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
+    for (int q = 0; q < 2; ++q)
 #pragma unroll
-        for (int q = 0; q < 4 * BITS; ++q) {
-            const int id = tid + kFgThreads * q, row = id / (2 * CW), dd = id % (2 * CW);
-            if (dd / CW == h) ct[row * CST + dd % CW] = ctile[q];
+        for (int jb = 0; jb < JB; ++jb) dAacc[q][jb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int p2 = 0; p2 < 2; ++p2) {
+#pragma unroll
+        for (int q = 0; q < BITS; ++q) {
+            const int id = tid + kFgThreads * q, row = id / (CW / 2), dd = id % (CW / 2) * 4;
+            if (((row >> 5) & 1) == p2)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) ct[(32 * (row >> 6) + (row & 31)) * CST + dd + e] = ctile[q][e];
         }
         __syncthreads();
-        if (wk == h) {
+        f32x4 dBacc[2][JB];
 #pragma unroll
-            for (int nb = 0; nb < 4; ++nb) {
-                const int nl = 64 * wn + 16 * nb + c, n = n0 + nl;    // the row whose four values this lane holds
-                // all LDS reads of a pass are issued before any is used: code words, then levels
-                uint32_t cv[8];
+        for (int q = 0; q < 2; ++q)
 #pragma unroll
-                for (int kb = 0; kb < 8; ++kb) {
-                    const int off = BITS * (16 * kb + 4 * g), d = off >> 5, sh = off & 31;   // within the row's 128 codes of this half
-                    const uint64_t w = (uint64_t)ct[nl * CST + d] | ((uint64_t)ct[nl * CST + min(d + 1, CW - 1)] << 32);
-                    cv[kb] = (uint32_t)(w >> sh);
+            for (int jb = 0; jb < JB; ++jb) dBacc[q][jb] = f32x4{0.f, 0.f, 0.f, 0.f};
+        // all LDS reads of KG column blocks of both row blocks are issued before any is used: code words, then levels.  (Bound by
+        // LDS instructions: the codes of a block come with one read where they lie in one half-word or byte, the A operands serve
+        // both row blocks, the table has a copy per bank.)
+        constexpr int KG = SS == 1 ? 4 : 2;
+#pragma unroll
+        for (int kq = 0; kq < 8; kq += KG) {
+            uint32_t cv[2][KG];
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+#pragma unroll
+                for (int i = 0; i < KG; ++i) {
+                    const uint32_t *row = ct + (32 * wn + 16 * q + c) * CST;
+                    const int off = BITS * (128 * wk + 16 * (kq + i) + 4 * g), d = off >> 5, sh = off & 31;   // within the row's 256 codes
+                    if constexpr (BITS == 4) cv[q][i] = reinterpret_cast<const uint16_t *>(row)[off >> 4];
+                    else if constexpr (BITS == 2) cv[q][i] = reinterpret_cast<const uint8_t *>(row)[off >> 3];
+                    else cv[q][i] = __builtin_amdgcn_alignbit(row[min(d + 1, 2 * CW - 1)], row[d], sh);
                 }
-                float lv[8][4];
+            float lv[2][KG][4];
 #pragma unroll
-                for (int kb = 0; kb < 8; ++kb)
+            for (int q = 0; q < 2; ++q)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) lv[kb][e] = cb[(cv[kb] >> (BITS * e)) & ((1u << BITS) - 1u)];
-                f32x4 dBacc[JB];
+                for (int i = 0; i < KG; ++i)
 #pragma unroll
-                for (int jb = 0; jb < JB; ++jb) dBacc[jb] = f32x4{0.f, 0.f, 0.f, 0.f};
+                    for (int e = 0; e < 4; ++e)
+                        lv[q][i][e] = cb[((cv[q][i] >> (BITS * e)) & ((1u << BITS) - 1u)) * kFgCopies + (lane & (kFgCopies - 1))];
 #pragma unroll
-                for (int kb = 0; kb < 8; ++kb) {
-                    const int kl = 16 * kb + 4 * g, kk = k0 + 128 * h + kl;      // its four columns kk .. kk+3
-                    const bool ok = n < N && kk < K;
+            for (int i = 0; i < KG; ++i) {
+                const int kl = 128 * wk + 16 * (kq + i) + 4 * g, kk = k0 + kl;      // the lane's four columns kk .. kk+3
+                s16x4v aop[JB];
+#pragma unroll
+                for (int jb = 0; jb < JB; ++jb) aop[jb] = *reinterpret_cast<const s16x4v *>(As + (16 * jb + c) * kFgAST + kl * 2);
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    const int nb = 2 * p2 + q, nl = 32 * wn + 16 * q + c;           // the row whose values this lane holds
+                    const bool ok = n0 + 64 * wn + 16 * nb + c < N && kk < K;
                     s16x4v pb;
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
-                        const float pv = ok ? lv[kb][e] * acc[kb][nb][e] : 0.f;
+                        const float pv = ok ? lv[q][i][e] * acc[kq + i][nb][e] : 0.f;
                         pb[e] = (short)bf16_bits(pv);
                     }
                     // dB[n][j] += sum over these four columns of P[n][k] A[j][k]
 #pragma unroll
-                    for (int jb = 0; jb < JB; ++jb) {
-                        const s16x4v aop = *reinterpret_cast<const s16x4v *>(As + (16 * jb + c) * kFgAST + (128 * h + kl) * 2);
-                        dBacc[jb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(pb, aop, dBacc[jb], 0, 0, 0);
-                    }
-                    *reinterpret_cast<s16x4v *>(Ps + nl * 256 + (((kl >> 3) ^ fg_swz(nl)) << 4) + ((kl & 7) << 1)) = pb;
-                }
-                // dB partial of this half tile: lane (c, g) holds rows 4g+e of rank entry 16 jb + c
-#pragma unroll
-                for (int jb = 0; jb < JB; ++jb) {
-                    const int j = 16 * jb + c;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int nn = n0 + 64 * wn + 16 * nb + 4 * g + e;
-                        if (nn < N && j < r) a.partB[((size_t)(2 * kt + h) * N + nn) * r + j] = dBacc[jb][e];
-                    }
+                    for (int jb = 0; jb < JB; ++jb) dBacc[q][jb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(pb, aop[jb], dBacc[q][jb], 0, 0, 0);
+                    *reinterpret_cast<s16x4v *>(Ps + nl * 512 + (((kl >> 3) ^ fg_swz(nl)) << 4) + ((kl & 7) << 1)) = pb;
                 }
             }
         }
         __syncthreads();
 
-        // dA = B^T P over the 256 rows: wave w takes columns 16w .. 16w+15 of the half, all rank blocks
-        f32x4 dAacc[JB];
+        // dA += B^T P over the pass's 128 rows: wave w takes columns 32w .. 32w+31, all rank blocks
 #pragma unroll
-        for (int jb = 0; jb < JB; ++jb) dAacc[jb] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int ns = 0; ns < 8; ++ns) {
-            const bf16x8 Pop = fg_tr_read<256>(Ps, 32 * ns + 8 * g, 16 * wave, c);
+        for (int ns = 0; ns < 4; ++ns) {
+            const bf16x8 P0 = fg_tr_read<512>(Ps, 32 * ns + 8 * g, 32 * wave, c), P1 = fg_tr_read<512>(Ps, 32 * ns + 8 * g, 32 * wave + 16, c);
 #pragma unroll
             for (int jb = 0; jb < JB; ++jb) {
                 typedef __attribute__((__vector_size__(8 * sizeof(short)))) short s16x8;
-                const int ra = 32 * ns + 8 * g + (c >> 2), col = 16 * jb + 4 * (c & 3);
+                const int ra = 64 * ns + 32 * p2 + 8 * g + (c >> 2), col = 16 * jb + 4 * (c & 3);
                 s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t *)(Bs + ra * BST + col * 2));
                 s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t *)(Bs + (ra + 4) * BST + col * 2));
                 const bf16x8 Bop = __builtin_bit_cast(bf16x8, (s16x8)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-                dAacc[jb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Bop, Pop, dAacc[jb], 0, 0, 0);
+                dAacc[0][jb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Bop, P0, dAacc[0][jb], 0, 0, 0);
+                dAacc[1][jb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Bop, P1, dAacc[1][jb], 0, 0, 0);
             }
         }
+        __syncthreads();                                       // (the P tile has been read)
+        // dB of the pass: the waves of columns 128 .. 255 pass theirs on, in the accumulators' own layout
+        f32x4 *xch = reinterpret_cast<f32x4 *>(smem) + (size_t)wn * (2 * JB * 64) + lane;
+        if (wk == 1)
+#pragma unroll
+            for (int i = 0; i < 2 * JB; ++i) xch[i * 64] = dBacc[i / JB][i % JB];
+        __syncthreads();
+        if (wk == 0) {
+            // lane (c, g) holds rows 4g+e of rank entry 16 jb + c
+#pragma unroll
+            for (int i = 0; i < 2 * JB; ++i) {
+                const f32x4 o = xch[i * 64];
+                const int j = 16 * (i % JB) + c;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int nn = n0 + 64 * wn + 16 * (2 * p2 + i / JB) + 4 * g + e;
+                    if (nn < N && j < r) a.partB[((size_t)kt * N + nn) * r + j] = dBacc[i / JB][i % JB][e] + o[e];
+                }
+            }
+        }
+        if (p2 == 0) __syncthreads();                          // the codes, the P tile and the exchanged sums are rewritten
+    }
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
 #pragma unroll
         for (int jb = 0; jb < JB; ++jb) {
-            const int k = k0 + 128 * h + 16 * wave + c;
+            const int k = k0 + 32 * wave + 16 * q + c;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int j = 16 * jb + 4 * g + e;
-                if (j < r && k < K) a.partA[((size_t)nt * r + j) * K + k] = dAacc[jb][e];
+                if (j < r && k < K) a.partA[((size_t)nt * r + j) * K + k] = dAacc[q][jb][e];
             }
         }
-        if (h == 0) __syncthreads();                       // the P tile and the codes are rewritten by the other half
-    }
 }
 
 // out[i] = sum over p of part[p][i], p increasing, for dB (blocks below `split`) and dA in one launch.  Bound by memory
-// (87 MB of partial sums on 14336 x 4096 at rank 32): sixteen loads in flight per thread, since the shorter output (dA,
+// (58 MB of partial sums on 14336 x 4096 at rank 32): sixteen loads in flight per thread, since the shorter output (dA,
 // 131072 sums of 56 parts there) does not fill the chip with threads; in launches of their own, one load behind the
-// other, the two took 12.0 + 15.2 us, now 14.8 (4096 x 4096 at rank 16 9.0 + 5.3 -> 5.2).
+// other, the two took 12.0 + 15.2 us for 87 MB, this 14.8 (4096 x 4096 at rank 16 9.0 + 5.3 -> 5.2); 10.1 for the 58 MB of now.
 __global__ __launch_bounds__(256) void reduce_factor_parts_kernel(const float *__restrict__ partB, float *__restrict__ dB, long countB, int npartsB,
                                                                   const float *__restrict__ partA, float *__restrict__ dA, long countA, int npartsA,
                                                                   int split)
@@ -487,7 +531,7 @@ bool factor_grad_supported(int N, int K, int r) { return r >= 1 && r <= 64 && (N
 size_t factor_grad_workspace_bytes(int N, int K, int r)
 {
     const size_t ntiles = (N + kFgBN - 1) / kFgBN, ktiles = (K + kFgBK - 1) / kFgBK;
-    return (2 * ktiles * (size_t)N * r + ntiles * (size_t)r * K) * sizeof(float);    // dB: one part per half tile of columns
+    return (ktiles * (size_t)N * r + ntiles * (size_t)r * K) * sizeof(float);
 }
 
 template <int BITS, int SS>
@@ -495,7 +539,7 @@ static hipError_t launch_fg_t(const FgArgs &a, hipStream_t st)
 {
     constexpr int RP = 32 * SS;
     const size_t smem = (size_t)(SS == 1 ? 3 : 2) * 2 * kFgTile + (size_t)RP * kFgAST + (size_t)kFgBN * (RP + 4) * 2 +
-                        (size_t)(1 << BITS) * 4 + (SS == 1 ? 0 : (size_t)kFgBN * (4 * BITS + 1) * 4);
+                        (size_t)(1 << BITS) * kFgCopies * 4 + (SS == 1 ? 0 : (size_t)(kFgBN / 2) * (8 * BITS + 1) * 4);
     static LdsOptIn lds_opt_in;
     {
         const hipError_t e = allow_dynamic_lds(lds_opt_in, reinterpret_cast<const void *>(&factor_grad_kernel<BITS, SS>), smem);
@@ -522,7 +566,7 @@ hipError_t launch_factor_grad(const void *dY, const void *X, const void *codes, 
     a.ntiles = (N + kFgBN - 1) / kFgBN;
     a.ktiles = (K + kFgBK - 1) / kFgBK;
     a.partB = (float *)workspace;
-    a.partA = a.partB + (size_t)2 * a.ktiles * N * r;
+    a.partA = a.partB + (size_t)a.ktiles * N * r;
     const int ss = r <= 32 ? 1 : 2;
     hipError_t e = hipErrorInvalidValue;
 #define LORDS_FGCASE(B_, S_) if (bits == B_ && ss == S_) e = launch_fg_t<B_, S_>(a, st);
@@ -531,7 +575,7 @@ hipError_t launch_factor_grad(const void *dY, const void *X, const void *codes, 
     if (e != hipSuccess) return e;
     const long cb = (long)N * r, ca = (long)r * K;
     const unsigned split = (unsigned)((cb + 255) / 256), total = split + (unsigned)((ca + 255) / 256);
-    hipLaunchKernelGGL(reduce_factor_parts_kernel, dim3(total), dim3(256), 0, st, (const float *)a.partB, dB, cb, 2 * a.ktiles,
+    hipLaunchKernelGGL(reduce_factor_parts_kernel, dim3(total), dim3(256), 0, st, (const float *)a.partB, dB, cb, a.ktiles,
                        (const float *)a.partA, dA, ca, a.ntiles, (int)split);
     return hipGetLastError();
 }
