@@ -44,7 +44,9 @@
  *    LORDS_ERR_LAUNCH while `stream` is being captured: warm a shape up once before capturing it.
  *    One product asks for at most 64 MiB of partial sums; lords_matmul_batched above 16 tokens asks for
  *    those of all its matrices together, and runs matrix by matrix, with the same results, where that
- *    much cannot be had.
+ *    much cannot be had.  Products of many tokens (above 128) at ranks above 32 or with fp32 factors may
+ *    instead write their weights once, in bf16, to at most 128 MiB of that workspace and multiply from
+ *    there; where that much cannot be had, they run without it, more slowly and with the same results.
  *    Calls that share one workspace and overlap in time on one device race; issue them from one
  *    stream (or give every stream its own workspace through lords_matmul_ws).  The library keeps no
  *    other state; entry points may be called from several host threads.
@@ -184,9 +186,10 @@ int lords_matmul_ex(const void *X, const void *codes, const float *codebook,
  *   buffer).  `workspace` is a device pointer, 256-byte aligned, of at least
  *   lords_workspace_bytes(...) bytes (LORDS_ERR_WORKSPACE if NULL or smaller; a workspace sized for
  *   the largest problem serves them all).  Two calls that overlap in time must not share one.
- *   One exception: a large-M product with fp32 factors (rank <= 64) takes any workspace from
- *   lords_workspace_zero_bytes() bytes up and uses what there is beyond them.  How much that is decides
- *   how its sums over K are cut, so results are the same bit for bit among workspaces of one size, and of
+ *   Two exceptions: a large-M product with fp32 factors (rank <= 64) takes any workspace from
+ *   lords_workspace_zero_bytes() bytes up and uses what there is beyond them, and one with bf16 factors of
+ *   rank 33 to 64 and more than 128 tokens may take less than the query gives.  How much there is decides
+ *   how the sums over K are cut, so results are the same bit for bit among workspaces of one size, and of
  *   any size the query gives or more; those of a smaller one differ by the order of fp32 sums.
  */
 size_t lords_workspace_bytes(int M, int N, int K, int r, int bits, lords_dtype factor_dtype, lords_path path);

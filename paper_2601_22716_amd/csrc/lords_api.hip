@@ -160,6 +160,13 @@ size_t matmul_need(const lords::MatmulProblem &p, lords_path path, size_t limit 
     return kFront + ((scratch + 255) & ~(size_t)255);
 }
 
+// The least of a workspace that is to be accepted for it.
+size_t matmul_least(const lords::MatmulProblem &p, lords_path path)
+{
+    if (is_decode(path) || !lords::prefill_fast_supported(p)) return matmul_need(p, path);
+    return kFront + ((lords::prefill_least_workspace_bytes(p) + 255) & ~(size_t)255);
+}
+
 lords::BatchedProblem batch_of(const lords::MatmulProblem &p)
 {
     lords::BatchedProblem bp;
@@ -242,8 +249,13 @@ int launch_matmul(const lords::MatmulProblem &p, lords_path path, const WsView &
 int plan_workspace(const lords::MatmulProblem &p, lords_path path, size_t extra, void *stream, WsView *ws, void **extra_ptr, bool passes = true)
 {
     size_t own = p.f32fact && !is_decode(path) ? kFront : matmul_need(p, path);
-    const int rc = passes && !is_decode(path) && lords::two_pass_faster(batch_of(p)) ? two_pass_workspace(batch_of(p), extra, stream, ws, &own)
+    int rc = passes && !is_decode(path) && lords::two_pass_faster(batch_of(p)) ? two_pass_workspace(batch_of(p), extra, stream, ws, &own)
                                                                              : get_workspace(own + extra, stream, ws);
+    if (rc != LORDS_OK && !p.f32fact && matmul_least(p, path) < own) {
+        own = matmul_least(p, path);
+        rc = get_workspace(own + extra, stream, ws);
+        ws->bytes = own;                                   // (the plan is made for this much: `extra` lies behind it)
+    }
     if (rc == LORDS_OK && extra_ptr) *extra_ptr = ws->base + own;
     return rc;
 }
@@ -587,10 +599,11 @@ int matmul_in(const void *X, const void *codes, const float *codebook, const voi
         const bool ok = is_decode(path) ? (use_gemv(p, path) || decode_kind(p) == kFew) : lords::prefill_fast_supported(p);
         if (!ok) return LORDS_ERR_UNSUPPORTED;
     }
-    // (a caller's workspace must have the size the query gives; the static one is used as far as it goes, and so is
-    //  a caller's for a large-M product with fp32 factors, whose whole-tile form needs the front only)
+    // (a caller's workspace must have the size the query gives, or the least that the large-M kernel can do with; the static
+    //  one is used as far as it goes, and so is a caller's for a large-M product with fp32 factors, whose whole-tile form
+    //  needs the front only)
     const bool elastic = !ws_given || (f32fact && !is_decode(path));
-    if (!ws.base || ws.bytes < matmul_need(p, path, elastic ? ws.bytes : kNoLimit)) return LORDS_ERR_WORKSPACE;
+    if (!ws.base || ws.bytes < (elastic ? matmul_need(p, path, ws.bytes) : matmul_least(p, path))) return LORDS_ERR_WORKSPACE;
     return launch_matmul(p, path, ws, stream);
 }
 }  // namespace

@@ -125,6 +125,9 @@ bool prefill_fast_supported(const MatmulProblem &p);
 // less it plans for less, down to 0 = one whole tile per workgroup), and the launch: `part`/`part_bytes` that
 // scratch, `zeroed` kZeroBytes of device memory that are zero when handed over and left at zero.
 size_t prefill_fast_workspace_bytes(const MatmulProblem &p, size_t limit);
+// The least that a caller's workspace must have: what the kernel asks for without its 256-token tiles at ranks 33 .. 64, whose
+// parts are twice as large.  Between this and the figure above, the plan is made for what there is.
+size_t prefill_least_workspace_bytes(const MatmulProblem &p);
 // Whether it runs as the form with one wave per SIMD (lords_prefill_wide.hip).
 bool prefill_wide_taken(const MatmulProblem &p, size_t limit);
 // The planner's estimate of the launch, in us, with all the scratch it asks for.

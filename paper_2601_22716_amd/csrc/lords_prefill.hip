@@ -661,8 +661,9 @@ bool prefill_fast_supported(const MatmulProblem &p)
 
 // Tile shape and the cut of the work.  Tile shapes: 256 tokens x 256 rows (8 waves of 32 rows x 256
 // tokens), 256 x 128 (8 waves), and for at most 128 tokens 128 x 256 (8 waves side by side) and
-// 128 x 128 (4 waves).  Padded ranks above 32 take 128-token tiles only (their B operands need the
-// registers, their A tile the LDS): 256 rows when that still gives every CU a tile, else 128.
+// 128 x 128 (4 waves).  Padded ranks above 32 take 128-token tiles only in this kernel (their B operands
+// need the registers, their A tile the LDS): 256 rows when that still gives every CU a tile, else 128;
+// bf16 factors of padded rank 64 also 256 x 256 in lords_prefill_wide.hip.
 //
 // The work (output tiles x K tiles) is dealt to the CUs in equal contiguous runs of units, so that
 // a tile count that is no multiple of the CU count costs no half-empty last round (448 tiles of the
@@ -682,7 +683,7 @@ constexpr int kPfCUs = 256;
 // 256 x 256 tiles that they are compared with do not.
 constexpr double kWideScale = 1.22;
 
-static PfPlan pf_plan(const MatmulProblem &p, size_t avail)
+static PfPlan pf_plan(const MatmulProblem &p, size_t avail, bool wide = true)
 {
     PfPlan d;
     d.ss = pf_ss(pf_contraction(p), p.f32fact);
@@ -706,7 +707,7 @@ static PfPlan pf_plan(const MatmulProblem &p, size_t avail)
     const Cand large_rank[3] = {{1, 2, 8, 8, 2.15 * rank_cost}, {1, 2, 4, 8, 1.75 * rank_cost}, {1, 4, 4, 16, 3.55}};
     const Cand six[1] = {{1, 2, 4, 4, 3.0}};                 // (64 x 128, four waves: 3.3 us measured)
     const Cand *cands = d.ss == 1 ? small_rank : d.ss == 6 ? six : large_rank;
-    const int ncands = d.ss == 1 ? 4 : d.ss == 6 ? 1 : d.ss == 2 && !p.f32fact && p.M > 128 ? 3 : 2;
+    const int ncands = d.ss == 1 ? 4 : d.ss == 6 ? 1 : d.ss == 2 && !p.f32fact && p.M > 128 && wide ? 3 : 2;
     double best = 1e30;
     d.wm = 1; d.R = 2; d.wn = 4; d.mb = d.ss == 6 ? 4 : 8; d.per = ntiles_k; d.part_bytes = 0;
     for (int i = 0; i < ncands; ++i) {
@@ -757,6 +758,11 @@ static PfPlan pf_plan(const MatmulProblem &p, size_t avail)
 size_t prefill_fast_workspace_bytes(const MatmulProblem &p, size_t limit)
 {
     return pf_plan(p, limit).part_bytes;
+}
+
+size_t prefill_least_workspace_bytes(const MatmulProblem &p)
+{
+    return std::min(pf_plan(p, ~(size_t)0).part_bytes, pf_plan(p, ~(size_t)0, false).part_bytes);
 }
 
 bool prefill_wide_taken(const MatmulProblem &p, size_t limit) { return pf_plan(p, limit).R == 4; }

@@ -33,18 +33,22 @@ def gpu():
     return gpu_util
 
 
-def taken(M, N, K, r, bits, limit=2 ** 62):
-    """The planner's choice (lords::prefill_wide_taken, a host function of the library)."""
+def planner(name, restype, M, N, K, r, bits, *limit):
+    """A host function of the library's planner for this problem."""
     import paper_2601_22716_amd as L
     ptr, num, flag = ctypes.c_void_p, ctypes.c_int, ctypes.c_bool
 
     class Problem(ctypes.Structure):
         _fields_ = [(n, ptr) for n in ("X", "codes", "codebook", "B", "A", "Y")] + [(n, num) for n in ("M", "N", "K", "r", "bits")] + \
                    [(n, flag) for n in ("f32fact", "f32out", "tiled")]
-    f = L.library()._ZN5lords18prefill_wide_takenERKNS_13MatmulProblemEm
-    f.restype, f.argtypes = flag, [ctypes.c_void_p, ctypes.c_size_t]
+    f = getattr(L.library(), f"_ZN5lords{len(name)}{name}ERKNS_13MatmulProblemE" + "m" * len(limit))
+    f.restype, f.argtypes = restype, [ctypes.c_void_p] + [ctypes.c_size_t] * len(limit)
     p = Problem(M=M, N=N, K=K, r=r, bits=bits)
-    return f(ctypes.addressof(p), limit)
+    return f(ctypes.addressof(p), *limit)
+
+
+def taken(M, N, K, r, bits, limit=2 ** 62):
+    return planner("prefill_wide_taken", ctypes.c_bool, M, N, K, r, bits, limit)
 
 
 def check_rows(Y, c, bits, what, seed=0):
@@ -110,3 +114,26 @@ def test_wide_slab_tiles_gate_and_batch(gpu):
     G, U = (s.double() for s in single)
     want = G * torch.sigmoid(G) * U
     assert bool(((H.double() - want).abs() <= 4e-6 * want.abs() + 1e-12).all())
+
+
+@pytest.mark.parametrize("M,N,K,r,bits", [(250, 28672, 8160, 33, 2), (201, 20002, 4192, 64, 2)])
+def test_wide_smaller_workspace(gpu, M, N, K, r, bits):
+    """These tiles' parts are twice as large as those of 128-token tiles.  A workspace that holds the latter is accepted all the
+    same and the cut made for it; a smaller one is refused."""
+    import torch
+    import paper_2601_22716_amd as L
+    least = L.lords_workspace_zero_bytes() + planner("prefill_least_workspace_bytes", ctypes.c_size_t, M, N, K, r, bits)
+    say(f"wide, smaller workspace M={M} N={N} K={K} r={r} bits={bits}: {least}")
+    assert least < L.lords_workspace_bytes(M, N, K, r, bits, L.LORDS_BF16)
+    c = li.make_case("tiny", M=M, N=N, K=K, r=r, bits=bits, factor_dtype="bf16", seed=23, signed_factors=True)
+    d = gpu.DeviceCase(c)
+    room = torch.zeros(least + 4096, dtype=torch.uint8, device="cuda")
+    room[least:] = 77                                          # (nothing behind it is written)
+    Y = torch.full((M, N), float("nan"), device="cuda")
+    with pytest.raises(L.LordsError):
+        L.lords_matmul_ws(d.X, d.codes, d.codebook, d.B, d.A, Y, M, N, K, r, bits, room[:least - 256])
+    for _ in range(2):
+        L.lords_matmul_ws(d.X, d.codes, d.codebook, d.B, d.A, Y, M, N, K, r, bits, room[:least])
+    torch.cuda.synchronize()
+    assert bool((room[least:] == 77).all())
+    check_rows(Y.cpu().numpy(), c, bits, "Y")
