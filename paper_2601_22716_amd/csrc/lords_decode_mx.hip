@@ -19,6 +19,15 @@
 // stores, one arrival ticket per chunk, the last workgroup adds the blocks in increasing order.
 // Results are run-to-run identical.
 //
+// What bounds it: by bytes HBM, in fact the issue of the stream and fixed costs.  At 5 tokens of a 2-bit 28672 x 8192 layer,
+// rank 64, 50 us: without the arithmetic 14, without the second rank block's MFMAs 41, with all loads from cache 47; at 16
+// tokens of a 4-bit 14336 x 4096 one, rank 32, 15.8 us: without the arithmetic and the hand-over 9, without the hand-over 12.
+// The stream's instructions are therefore kept few and in order: slab addresses in scalar registers (as vector arithmetic they
+// were 25 of 110 vector instructions per slab, six of them quarter-rate multiplications) and branches instead of masks around a
+// slab, level pairs read half a group ahead, scale MFMAs that carry the conversion before them (57 -> 54 and 17.9 -> 17.4 us
+// launched one by one, 3-bit 4096 x 14336 rank 48 at 4 tokens 23.4 -> 21.5).  Three slabs in flight instead of two, and scale
+// MFMAs of the next slab under this one's end, gave nothing.
+//
 // Lane mapping (v_mfma_f32_16x16x32_bf16; lane l = (c = l%16, g = l/16)):
 //   scale MFMA t of group v:  D[i][j],  j <-> row n0+j,
 //                             i <-> column kb + 32*(G*(i/4)+v) + 4t + i%4,
@@ -81,7 +90,7 @@ __global__ __launch_bounds__(kMxThreads) __attribute__((amdgpu_waves_per_eu(2, 2
     extern __shared__ __align__(16) unsigned char smem[];
     uint16_t *As = reinterpret_cast<uint16_t *>(smem + LUT_BYTES);        // [SS*32][AST], then X [16][AST], then sums
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // (the slabs' addresses stay scalar)
     const int c = lane & 15, g = lane >> 4;
     const int cb = wave & 3, half = wave >> 2;
     const int kw = blockIdx.z * WK;                            // first column of the workgroup
@@ -105,15 +114,19 @@ __global__ __launch_bounds__(kMxThreads) __attribute__((amdgpu_waves_per_eu(2, 2
     int slab0 = (chunk * 2 + half) * ly.ns;                    // this wave's first slab
     uint32_t cw[kNS][G][BITS];
     bf16x8 Bop[kNS][SS];
-    // Byte offset of the lane's group v inside its row (canonical rows) or inside its slab's run of tiles
-    // (slab-tile layout: tile grp / 4, chunk 16 * (grp % 4) + row); and the step from slab to slab.
+    // Byte offset of the lane's group v inside its slab's 16 rows (canonical rows; below 2^32: at most
+    // 65535 column blocks are taken) or inside
+    // its slab's run of tiles (slab-tile layout: tile grp / 4, chunk 16 * (grp % 4) + row); and the step from slab to slab.
     uint32_t voff[G];
 #pragma unroll
     for (int v = 0; v < G; ++v) {
         const int grp = min((kb >> 5) + G * g + v, ngroups - 1);
-        voff[v] = a.tiled ? (uint32_t)(((grp >> 2) * 64 + (grp & 3) * 16 + c) * (4 * BITS)) : (uint32_t)grp * (4 * BITS);
+        voff[v] = a.tiled ? (uint32_t)(((grp >> 2) * 64 + (grp & 3) * 16 + c) * (4 * BITS)) : (uint32_t)c * (uint32_t)a.row_bytes + (uint32_t)grp * (4 * BITS);
     }
-    const size_t slab_bytes = a.tiled ? (size_t)a.nct * 64 * (4 * BITS) : 0;
+    const size_t slab_bytes = a.tiled ? (size_t)a.nct * 64 * (4 * BITS) : (size_t)a.row_bytes * 16;
+    // Rows that the matrix's last slab does not have read its last row: how far back that is for this lane.
+    const int beyond = max(c - (N - 1 - (ly.nslabs - 1) * 16), 0);
+    const uint32_t back_codes = a.tiled ? 0u : (uint32_t)beyond * (uint32_t)a.row_bytes, back_B = (uint32_t)(beyond * r) * 2u;
     // Ranks that are not a multiple of 8 (BVEC = false): the 16 bytes from the lane's first entry on, at whatever
     // alignment they have (rank8_* of lords_device.h).  Everything that depends on the slab alone stays in scalar
     // registers: the load's base and the last offset that is still inside B (mx_rank_range).
@@ -129,22 +142,23 @@ __global__ __launch_bounds__(kMxThreads) __attribute__((amdgpu_waves_per_eu(2, 2
     for (int s = 0; s < SS; ++s) crj[s] = mx_rank_entry(c, g, s, r);
     auto issue = [&](int i, int first, int last) __attribute__((always_inline)) {
         const int slab = mx_request_slab(first, i, last);
-        const int n = min(slab * 16 + c, N - 1);
-        const uint8_t *rowp = a.tiled ? ly.codes + (size_t)slab * slab_bytes : ly.codes + (size_t)n * a.row_bytes;
+        const uint32_t tail = slab == ly.nslabs - 1 ? ~0u : 0u;
+        const uint8_t *slabp = ly.codes + (size_t)slab * slab_bytes;
 #pragma unroll
-        for (int v = 0; v < G; ++v) load_group<BITS>(rowp + voff[v], cw[i][v]);
+        for (int v = 0; v < G; ++v) load_group<BITS>(slabp + (voff[v] - (back_codes & tail)), cw[i][v]);
         if (BVEC) {
 #pragma unroll
             for (int s = 0; s < SS; ++s) {
                 const int jj0 = 32 * s + 8 * g;
-                Bop[i][s] = *reinterpret_cast<const bf16x8 *>(ly.B + (size_t)n * r + (jj0 + 8 <= r ? jj0 : 0));
+                const uint32_t off = (uint32_t)(c * r + (jj0 + 8 <= r ? jj0 : 0)) * 2u - (back_B & tail);
+                Bop[i][s] = *reinterpret_cast<const bf16x8 *>(reinterpret_cast<const uint8_t *>(ly.B + (size_t)slab * 16 * r) + off);
             }
         } else {
             const BRange br = b_range(slab);
 #pragma unroll
             for (int s = 0; s < SS; ++s) {
                 const uint32_t want = crj[s] + (uint32_t)br.pre;
-                const u32x4_any w = *reinterpret_cast<const u32x4_any *>(br.base + min(want, br.limit));
+                const u32x4_any w = *reinterpret_cast<const u32x4_any *>(reinterpret_cast<const uint8_t *>(br.base) + min(want, br.limit) * 2u);
                 Bop[i][s] = __builtin_bit_cast(bf16x8, u32x4{w[0], w[1], w[2], w[3]});
             }
         }
@@ -170,19 +184,19 @@ __global__ __launch_bounds__(kMxThreads) __attribute__((amdgpu_waves_per_eu(2, 2
     constexpr int NCX = (16 * CPR + kMxThreads - 1) / kMxThreads;
     constexpr int NIT = (NE * 16 + kMxThreads - 1) / kMxThreads;
     const int kc = tid % CPR, k0 = kw + 8 * kc;               // the thread's column chunk is fixed
+    // (rows and columns that are not there read the last ones: a branch per load made the compiler wait for each of them, 3 us)
+    const int kc0 = min(k0, K - 8);
     u32x4 ta[NCA], tx[NCX];
     float lo[NIT], hi[NIT];
 #pragma unroll
     for (int q = 0; q < NCA; ++q) {
         const int jj = (tid + kMxThreads * q) / CPR;
-        ta[q] = u32x4{0u, 0u, 0u, 0u};
-        if (jj < r && k0 < K) ta[q] = *reinterpret_cast<const u32x4 *>(ly.A + (size_t)jj * K + k0);
+        ta[q] = *reinterpret_cast<const u32x4 *>(ly.A + (size_t)min(jj, r - 1) * K + kc0);
     }
 #pragma unroll
     for (int q = 0; q < NCX; ++q) {
         const int m = (tid + kMxThreads * q) / CPR;
-        tx[q] = u32x4{0u, 0u, 0u, 0u};
-        if (m < M && k0 < K) tx[q] = *reinterpret_cast<const u32x4 *>(a.X + (size_t)m * K + k0);
+        tx[q] = *reinterpret_cast<const u32x4 *>(a.X + (size_t)min(m, M - 1) * K + kc0);
     }
 #pragma unroll
     for (int it = 0; it < NIT; ++it) {
@@ -214,7 +228,7 @@ __global__ __launch_bounds__(kMxThreads) __attribute__((amdgpu_waves_per_eu(2, 2
 #pragma unroll
     for (int q = 0; q < NCA; ++q) {
         const int jj = (tid + kMxThreads * q) / CPR;
-        *reinterpret_cast<u32x4 *>(As + jj * AST + 8 * kc) = ta[q];
+        *reinterpret_cast<u32x4 *>(As + jj * AST + 8 * kc) = jj < r && k0 < K ? ta[q] : u32x4{0u, 0u, 0u, 0u};
     }
     {
         uint32_t *lut32 = reinterpret_cast<uint32_t *>(smem);
@@ -252,7 +266,7 @@ __global__ __launch_bounds__(kMxThreads) __attribute__((amdgpu_waves_per_eu(2, 2
 #pragma unroll
     for (int q = 0; q < NCX; ++q) {
         const int m = (tid + kMxThreads * q) / CPR;
-        if (m < 16) *reinterpret_cast<u32x4 *>(As + m * AST + 8 * kc) = tx[q];
+        if (m < 16) *reinterpret_cast<u32x4 *>(As + m * AST + 8 * kc) = m < M && k0 < K ? tx[q] : u32x4{0u, 0u, 0u, 0u};
     }
     __syncthreads();
     bf16x8 Xop[G][4];
@@ -262,6 +276,28 @@ __global__ __launch_bounds__(kMxThreads) __attribute__((amdgpu_waves_per_eu(2, 2
         for (int u = 0; u < 4; ++u)
             Xop[v][u] = *reinterpret_cast<const bf16x8 *>(As + c * AST + cb * KT + 32 * (G * g + v) + 8 * u);
     __syncthreads();                                       // the region now takes the block sums
+
+    // Level pairs of half a group (codes 16 hh .. 16 hh + 15 of the lane's 32), as fp16 pairs.
+    auto read_levels = [&](const uint32_t (&w)[BITS], int hh, uint32_t (&T)[8]) __attribute__((always_inline)) {
+        if constexpr (QUAD) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {                      // bytes 4 hh .. 4 hh + 3 of the group's eight, four codes each
+                const int b = 4 * hh + q;
+                const uint32_t ad = __builtin_amdgcn_perm(w[b >> 2], laneoff, 0x0C0C0000u | ((4u + (b & 3)) << 8));
+                typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+                const u32x2 t = *reinterpret_cast<const __attribute__((address_space(3))) u32x2 *>((uintptr_t)ad);
+                T[2 * q] = t.x;
+                T[2 * q + 1] = t.y;
+            }
+        } else
+#pragma unroll
+        for (int q = 0; q < 8; ++q) T[q] = lds_load_u32(pair_addr<BITS>(w, 8 * hh + q, laneoff));
+    };
+    // Scale MFMA q of half a group: rank block q / 4, columns 4 (4 hh + q % 4) .. of the lane's 32.
+    auto scale_step = [&](f32x4 (&S)[4], int v, int hh, int q, const bf16x8 (&B)[SS]) __attribute__((always_inline)) {
+        const int s = q >> 2, t = q & 3;
+        S[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Aop[v][s][4 * hh + t], B[s], s == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : S[t], 0, 0, 0);
+    };
 
     f32x4 *red = reinterpret_cast<f32x4 *>(As);            // [8 waves][kNS][64 lanes]
 
@@ -276,52 +312,32 @@ __global__ __launch_bounds__(kMxThreads) __attribute__((amdgpu_waves_per_eu(2, 2
                 __builtin_amdgcn_sched_barrier(0);     // keep the prefetch ahead of this slab's arithmetic
                 if (!BVEC) fix_B(i);
                 f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+                // Half groups h = 2 v + hh of 16 columns per lane in turn: the scale MFMAs of the next one carry the conversion of
+                // this one, pair by pair, its level pairs read one half group ahead.  Pinned, because the compiler's own order
+                // reads a level pair right before its use and sets one pair of dependent scale MFMAs behind the other.
+                f32x4 S[2][4];
+                uint32_t T[2][8];
+                bf16x8 W[2];
+                read_levels(cw[i][0], 0, T[0]);
 #pragma unroll
-                for (int v = 0; v < G; ++v) {
+                for (int q = 0; q < 4 * SS; ++q) scale_step(S[0], 0, 0, q, Bop[i]);
+                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                    for (int hh = 0; hh < 2; ++hh) {       // half a group: scale MFMAs 4hh .. 4hh+3
-                        f32x4 S[4];
+                for (int h = 0; h < 2 * G; ++h) {
+                    const int v = h >> 1, hh = h & 1, vn = (h + 1) >> 1, hn = (h + 1) & 1;
+                    const bool more = h + 1 < 2 * G;
+                    if (more) read_levels(cw[i][vn < G ? vn : 0], hn, T[hn]);
 #pragma unroll
-                        for (int s = 0; s < SS; ++s)
-#pragma unroll
-                            for (int t = 0; t < 4; ++t)
-                                S[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Aop[v][s][4 * hh + t], Bop[i][s],
-                                                                               s == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : S[t], 0, 0, 0);
-#pragma unroll
-                        for (int uu = 0; uu < 2; ++uu) {
-                            const int u = 2 * hh + uu;
-                            bf16x8 W;
-                            if constexpr (QUAD) {
-#pragma unroll
-                                for (int q2 = 0; q2 < 2; ++q2) {               // bytes 2u, 2u + 1 of the group's eight: codes 8u .. 8u + 7
-                                    const int b = 2 * u + q2;
-                                    const uint32_t ad = __builtin_amdgcn_perm(cw[i][v][b >> 2], laneoff, 0x0C0C0000u | ((4u + (b & 3)) << 8));
-                                    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-                                    const u32x2 t = *reinterpret_cast<const __attribute__((address_space(3))) u32x2 *>((uintptr_t)ad);
-#pragma unroll
-                                    for (int hq = 0; hq < 2; ++hq) {
-                                        // (the word is picked by name: a bit cast of the subscripted element t[hq]
-                                        // compiled to element 0 for both)
-                                        const f16x2 h = __builtin_bit_cast(f16x2, hq == 0 ? t.x : t.y);
-                                        const int e0 = 4 * q2 + 2 * hq, e1 = e0 + 1;
-                                        const float s0 = S[2 * uu + (e0 >> 2)][e0 & 3], s1 = S[2 * uu + (e1 >> 2)][e1 & 3];
-                                        W[e0] = (__bf16)__builtin_fmaf((float)h[0], s0, 0.0f);
-                                        W[e1] = (__bf16)__builtin_fmaf((float)h[1], s1, 0.0f);
-                                    }
-                                }
-                            } else
-#pragma unroll
-                            for (int pp = 0; pp < 4; ++pp) {
-                                const uint32_t ad = pair_addr<BITS>(cw[i][v], 4 * u + pp, laneoff);
-                                const f16x2 h = __builtin_bit_cast(f16x2, lds_load_u32(ad));
-                                const int e0 = 2 * pp, e1 = 2 * pp + 1;
-                                const float s0 = S[2 * uu + (e0 >> 2)][e0 & 3], s1 = S[2 * uu + (e1 >> 2)][e1 & 3];
-                                W[e0] = (__bf16)__builtin_fmaf((float)h[0], s0, 0.0f);
-                                W[e1] = (__bf16)__builtin_fmaf((float)h[1], s1, 0.0f);
-                            }
-                            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W, Xop[v][u], acc, 0, 0, 0);
-                        }
+                    for (int q = 0; q < 8; ++q) {              // 8 pairs of weights, 4 SS scale MFMAs, 2 product MFMAs
+                        if (more && (SS == 2 || (q & 1) == 0)) scale_step(S[hn], vn < G ? vn : 0, hn, SS == 2 ? q : q >> 1, Bop[i]);
+                        const f16x2 l = __builtin_bit_cast(f16x2, T[hh][q]);
+                        const int t = q >> 1, e = 2 * (q & 1);
+                        W[q >> 2][2 * (q & 3)] = (__bf16)__builtin_fmaf((float)l[0], S[hh][t][e], 0.0f);
+                        W[q >> 2][2 * (q & 3) + 1] = (__bf16)__builtin_fmaf((float)l[1], S[hh][t][e + 1], 0.0f);
+                        if (q == 4) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W[0], Xop[v][2 * hh], acc, 0, 0, 0);
+                        __builtin_amdgcn_sched_barrier(0);
                     }
+                    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W[1], Xop[v][2 * hh + 1], acc, 0, 0, 0);
                 }
                 red[(wave * kNS + i) * 64 + lane] = acc;
                 __builtin_amdgcn_sched_barrier(0);
