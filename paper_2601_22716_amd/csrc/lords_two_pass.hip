@@ -46,7 +46,7 @@ constexpr int kOpCopies = 16;                                  // of the level t
 // A workgroup takes two neighbouring K tiles (waves 0, 1 and 2, 3: the code rows of both lie in the same cache lines) and
 // 2 per_wave slabs.  A wave keeps the A operands of its K tile in registers (up to rank 64; above they are read again
 // from LDS) and walks its slabs, the next one's codes requested before this one's are used.
-// Bound by the writes: 14336 x 4096 at rank 32, 117 MB.
+// Bound by the writes: 14336 x 4096 at rank 32, 117 MB, 28 to 31 us (4.0 TB/s).
 template <int BITS, int SS, bool F32>
 __global__ __launch_bounds__(256) void dequant_operand_kernel(OperandArgs a)
 {
