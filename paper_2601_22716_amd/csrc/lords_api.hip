@@ -283,15 +283,22 @@ int run_batched_large(const lords::BatchedProblem &bp, void *stream)
         rest = batch_where(bp, [&](int l) { return !alone(l); });
     }
     WsView ws;
-    if (twice.L > 0) {
+    for (int first = 0, end; first < twice.L; first = end) {
+        // (as many at a time as the scratch holds a tile of each of: at 36864 columns seven)
+        lords::BatchedProblem group;
+        for (end = twice.L; end > first; --end) {
+            group = batch_where(twice, [&](int l) { return l >= first && l < end; });
+            if (lords::two_pass_supported(group)) break;
+        }
+        if (end == first) return LORDS_ERR_UNSUPPORTED;        // (not reached: each of them alone is supported)
         size_t own;
-        const int rc = two_pass_workspace(twice, 0, stream, &ws, &own);
+        const int rc = two_pass_workspace(group, 0, stream, &ws, &own);
         if (rc != LORDS_OK) return rc;
         if (ws.large == WsView::kTwoPass) {
-            if (lords::launch_two_pass(twice, ws.scratch(), (hipStream_t)stream) != hipSuccess) return LORDS_ERR_LAUNCH;
+            if (lords::launch_two_pass(group, ws.scratch(), (hipStream_t)stream) != hipSuccess) return LORDS_ERR_LAUNCH;
         } else {
-            for (int l = 0; l < twice.L; ++l) {
-                const int rcl = launch_large(matrix_of(twice, l), ws, stream);
+            for (int l = 0; l < group.L; ++l) {
+                const int rcl = launch_large(matrix_of(group, l), ws, stream);
                 if (rcl != LORDS_OK) return rcl;
             }
         }

@@ -508,7 +508,7 @@ static int op_ss(const BatchedProblem &p)
 static size_t op_slab_bytes(const BatchedProblem &p) { return (size_t)((p.K + 127) / 128) * 4096; }
 
 // Rows of each matrix that are taken at once: all of them (0), or whole tiles of them in chunks of about one size that
-// kTwoPassBytes of W hold.
+// kTwoPassBytes of W hold (one tile each where that is too little: more than two_pass_supported lets through).
 static int op_chunk_rows(const BatchedProblem &p)
 {
     size_t slabs = 0;
@@ -517,7 +517,7 @@ static int op_chunk_rows(const BatchedProblem &p)
     if (slabs <= fit) return 0;
     int most = 0;
     for (int l = 0; l < p.L; ++l) most = p.N[l] > most ? p.N[l] : most;
-    const int cap = (int)(fit / p.L / 16 * 256), chunks = (most + cap - 1) / cap;
+    const int cap = (int)std::max<size_t>(fit / p.L / 16, 1) * 256, chunks = (most + cap - 1) / cap;
     return (most + 256 * chunks - 1) / (256 * chunks) * 256;
 }
 
@@ -713,6 +713,7 @@ static hipError_t launch_two_pass_rows(const BatchedProblem &p, int row0, int ro
 
 hipError_t launch_two_pass(const BatchedProblem &p, void *scratch, hipStream_t st)
 {
+    if (!two_pass_supported(p)) return hipErrorInvalidValue;
     const int rows = op_chunk_rows(p);
     if (!rows) return launch_two_pass_rows(p, 0, 0, scratch, st);
     int most = 0;

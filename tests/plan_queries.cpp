@@ -1,0 +1,30 @@
+// The library's planner for tests: problems are put together by the library's own header, so that its structures are never
+// copied by hand.
+#include "../paper_2601_22716_amd/csrc/lords_launch.h"
+
+namespace {
+lords::BatchedProblem batched(const int *N, int L, int M, int K, int r, int bits, int f32, int act)
+{
+    lords::BatchedProblem p{};
+    for (int l = 0; l < L; ++l) p.N[l] = N[l];
+    p.L = L; p.M = M; p.K = K; p.r = r; p.bits = bits;
+    p.f32fact = f32 != 0; p.f32out = true; p.act = act != 0;
+    return p;
+}
+lords::MatmulProblem single(int M, int N, int K, int r, int bits, int f32)
+{
+    lords::MatmulProblem p{};
+    p.M = M; p.N = N; p.K = K; p.r = r; p.bits = bits;
+    p.f32fact = f32 != 0; p.f32out = true;
+    return p;
+}
+}  // namespace
+
+extern "C" {
+int two_pass_faster(const int *N, int L, int M, int K, int r, int bits, int f32, int act) { return lords::two_pass_faster(batched(N, L, M, K, r, bits, f32, act)); }
+int two_pass_supported(const int *N, int L, int M, int K, int r, int bits, int f32, int act) { return lords::two_pass_supported(batched(N, L, M, K, r, bits, f32, act)); }
+size_t two_pass_workspace_bytes(const int *N, int L, int M, int K, int r, int bits, int f32, int act) { return lords::two_pass_workspace_bytes(batched(N, L, M, K, r, bits, f32, act)); }
+size_t prefill_workspace_bytes(int M, int N, int K, int r, int bits, int f32) { return lords::prefill_fast_workspace_bytes(single(M, N, K, r, bits, f32), ~(size_t)0); }
+size_t prefill_least_workspace_bytes(int M, int N, int K, int r, int bits, int f32) { return lords::prefill_least_workspace_bytes(single(M, N, K, r, bits, f32)); }
+int prefill_wide_taken(int M, int N, int K, int r, int bits, int f32) { return lords::prefill_wide_taken(single(M, N, K, r, bits, f32), ~(size_t)0); }
+}

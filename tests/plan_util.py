@@ -1,0 +1,38 @@
+"""The library's planner, asked by tests (plan_queries.cpp, built against the library's own header and linked with it)."""
+from __future__ import annotations
+
+import ctypes
+import functools
+import os
+import subprocess
+import tempfile
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+def compile_queries(out_dir: str, library: str) -> str:
+    out = os.path.join(out_dir, "plan_queries.so")
+    subprocess.run([os.environ.get("CXX", "g++"), "-std=c++17", "-O1", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-isystem", "/opt/rocm/include",
+                    "-o", out, os.path.join(HERE, "plan_queries.cpp"), library], check=True)
+    return out
+
+
+def declare(lib):
+    num, nums = ctypes.c_int, ctypes.POINTER(ctypes.c_int)
+    for name, restype in (("two_pass_faster", num), ("two_pass_supported", num), ("two_pass_workspace_bytes", ctypes.c_size_t)):
+        getattr(lib, name).argtypes, getattr(lib, name).restype = [nums] + [num] * 7, restype
+    for name, restype in (("prefill_workspace_bytes", ctypes.c_size_t), ("prefill_least_workspace_bytes", ctypes.c_size_t), ("prefill_wide_taken", num)):
+        getattr(lib, name).argtypes, getattr(lib, name).restype = [num] * 6, restype
+    return lib
+
+
+@functools.lru_cache(maxsize=None)
+def queries():
+    from paper_2601_22716_amd import binding
+    binding.library()
+    with tempfile.TemporaryDirectory() as d:
+        return declare(ctypes.CDLL(compile_queries(d, binding.library_path())))
+
+
+def takes_two_passes(M, Ns, K, r, bits, f32, act=False, lib=None):
+    return bool((lib or queries()).two_pass_faster((ctypes.c_int * len(Ns))(*Ns), len(Ns), M, K, r, bits, int(f32), int(act)))

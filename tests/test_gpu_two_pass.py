@@ -162,6 +162,22 @@ def test_two_pass_batched(gpu, M, Ns, K, r, bits, fdt):
         dev[-1].matmul(X=dev[0].X, M=M)                      # eager work between the replays
 
 
+def test_two_pass_batched_in_groups(gpu):
+    """Eight matrices of 36864 columns, a tile of each of which is more than the scratch holds: the single calls' bits."""
+    import torch
+    import paper_2601_22716_amd as L
+    M, N, K, r, bits = 2049, 600, 36864, 64, 4
+    say("two passes batched in groups")
+    assert takes_two_passes(M, [N], K, r, bits, True)
+    dev = [gpu.DeviceCase(li.make_case("tiny", M=M if i == 0 else 1, N=N, K=K, r=r, bits=bits, factor_dtype="f32", seed=61 + i, signed_factors=True))
+           for i in range(8)]
+    out = [torch.full((M, N), float("nan"), device="cuda") for _ in dev]
+    L.lords_matmul_batched(dev[0].X, [d.codes for d in dev], dev[0].codebook, [d.B for d in dev], [d.A for d in dev], out, [N] * 8, M, K, r, bits)
+    torch.cuda.synchronize()
+    for l, (d, o) in enumerate(zip(dev, out)):
+        np.testing.assert_array_equal(o.cpu().numpy(), d.matmul(X=dev[0].X, M=M), err_msg=f"matrix {l}")
+
+
 @pytest.mark.parametrize("M,N,K,r,bits,fdt", [(3000, 2999, 544, 64, 4, "f32"), (3001, 2002, 1056, 99, 3, "bf16"), (1025, 20011, 4128, 128, 2, "bf16"), (2049, 2002, 1120, 64, 4, "bf16")])
 def test_two_pass_gate_up(gpu, M, N, K, r, bits, fdt):
     """The pair against silu(gate) * up formed from the two single products, whose sums it has: fp32 silu and product, so

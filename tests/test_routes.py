@@ -1,0 +1,105 @@
+"""Which kernels a call launches and which memory it asks for, through the C ABI on the CPU: the library's host side runs against a
+stand-in for the HIP runtime (hip_double.cpp), each case in a process of its own, so that the library's workspace starts
+unallocated."""
+import ctypes
+import json
+import os
+import subprocess
+import sys
+
+import pytest
+
+from tests import plan_util
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+PREAMBLE = """
+import ctypes, json, sys
+double, library, queries, arg = sys.argv[1], sys.argv[2], sys.argv[3], json.loads(sys.argv[4])
+sys.path.insert(0, sys.argv[5])
+rt = ctypes.CDLL(double, ctypes.RTLD_GLOBAL)
+lib = ctypes.CDLL(library)
+from tests import plan_util
+plan = plan_util.declare(ctypes.CDLL(queries))
+rt.double_launched.restype = ctypes.c_char_p
+rt.double_largest_allocation.argtypes = [ctypes.c_size_t]
+lib.lords_workspace_zero_bytes.restype = ctypes.c_size_t
+vp, front = ctypes.c_void_p, lib.lords_workspace_zero_bytes()
+at = lambda i: (1 << 32) + (i << 24)                       # (addresses: nothing is read)
+each = lambda i, n: (vp * n)(*[at(i + l) for l in range(n)])
+
+
+def launched():
+    # kernels launched since the last call of this, the template's arguments left out
+    names = rt.double_launched().decode().split()
+    rt.double_forget_launches()
+    return [n[n.index("lords") + 5:].lstrip("0123456789").split("_kernel")[0] for n in names]
+
+
+def matmul(M, N, K, r, bits, f32):
+    return lib.lords_matmul(vp(at(0)), vp(at(1)), vp(at(2)), vp(at(3)), vp(at(4)), vp(at(5)), M, N, K, r, bits, int(f32), 1, None)
+
+
+def batched(Ns, M, K, r, bits, f32):
+    n = len(Ns)
+    return lib.lords_matmul_batched(vp(at(0)), each(10, n), vp(at(1)), each(20, n), each(30, n), each(40, n), (ctypes.c_int * n)(*Ns),
+                                    n, M, K, r, bits, int(f32), 1, None)
+
+
+def gate_up(M, N, K, r, bits, f32):
+    return lib.lords_gate_up(vp(at(0)), vp(at(1)), vp(at(2)), vp(at(3)), vp(at(4)), vp(at(5)), vp(at(6)), vp(at(7)), vp(at(8)), M, N, K, r, bits,
+                             int(f32), 1, None)
+"""
+
+
+@pytest.fixture(scope="module")
+def routes(tmp_path_factory):
+    from paper_2601_22716_amd import binding
+    d = str(tmp_path_factory.mktemp("routes"))
+    double = os.path.join(d, "hip_double.so")
+    subprocess.run([os.environ.get("CXX", "g++"), "-std=c++17", "-O1", "-shared", "-fPIC", "-o", double, os.path.join(HERE, "hip_double.cpp")], check=True)
+    queries = plan_util.compile_queries(d, binding.library_path())
+
+    def run(body, arg=None):
+        r = subprocess.run([sys.executable, "-c", PREAMBLE + body, double, binding.library_path(), queries, json.dumps(arg), os.path.dirname(HERE)],
+                           capture_output=True, text=True, timeout=120)
+        assert r.returncode == 0, (r.returncode, r.stderr[-2000:])
+        return json.loads(r.stdout.strip().splitlines()[-1])
+    return run
+
+
+@pytest.mark.parametrize("L,N,M,K,r,f32", [
+    (8, 1024, 2048, 36864, 64, True), (8, 4096, 8192, 36864, 100, False), (4, 1024, 4096, 73728, 64, True), (3, 1024, 4096, 98304, 43, True),
+    (2, 1024, 8192, 147456, 64, True), (7, 1024, 2048, 36864, 64, True), (6, 1000, 3000, 49152, 63, True)])
+def test_batched_two_passes_of_many_columns(routes, L, N, M, K, r, f32):
+    """Matrices of so many columns that a tile of each is more than the scratch for the dequantised weights holds: as many of
+    them at a time as it does hold."""
+    out = routes("""
+Ns, (M, K, r, bits, f32) = [arg["N"]] * arg["L"], arg["rest"]
+alone = plan_util.takes_two_passes(M, Ns[:1], K, r, bits, f32, lib=plan)
+most = max(n for n in range(1, len(Ns) + 1) if plan.two_pass_supported((ctypes.c_int * n)(*Ns[:n]), n, M, K, r, bits, int(f32), 0))
+print(json.dumps([alone, most, batched(Ns, M, K, r, bits, f32), launched()]))
+""", dict(L=L, N=N, rest=[M, K, r, 4, f32]))
+    alone, most, status, kernels = out
+    assert alone and status == 0
+    assert kernels[::2] == ["dequant_operand"] * (len(kernels) // 2) and kernels[1::2] == ["operand_gemm"] * (len(kernels) // 2)
+    assert most < L or (L, K) == (7, 36864)
+    assert len(kernels) >= 2 * -(-L // most)
+
+
+def test_two_pass_scratch_of_any_batch(routes):
+    """The scratch asked for is positive for every batch, and at most what is set aside where the batch is supported."""
+    out = routes("""
+import random
+rng, bad = random.Random(11), []
+for _ in range(4000):
+    L = rng.randint(1, 8)
+    Ns = (ctypes.c_int * L)(*[int(2 ** rng.uniform(0, 15)) for _ in range(L)])
+    K, f32 = 32 * int(2 ** rng.uniform(0, 14.5)), rng.randint(0, 1)
+    a = (Ns, L, int(2 ** rng.uniform(7, 13)), K, rng.randint(1, 42 if f32 else 128), rng.choice([2, 3, 4]), f32, 0)
+    size = plan.two_pass_workspace_bytes(*a)
+    if size <= 0 or plan.two_pass_supported(*a) and size > 128 << 20:
+        bad.append([list(Ns), K, size])
+print(json.dumps(bad))
+""")
+    assert out == []
