@@ -269,8 +269,8 @@ int run_matmul(const lords::MatmulProblem &p, lords_path path, void *stream)
     return rc != LORDS_OK ? rc : launch_matmul(p, path, ws, stream);
 }
 
-// Several matrices that each go to the large-M kernel or into two passes; a status, or -1 to have them one by one.  Every
-// matrix is summed as it would be alone.  In two passes together: those that alone would take them, and with them those that
+// Several matrices that each go to the large-M kernel or into two passes; a status, or -1 (nothing launched) to have them one
+// by one.  Every matrix is summed as it would be alone.  In two passes together: those that alone would take them, and with them those that
 // alone are summed by whole tiles, if that is the faster way for all of these.
 int run_batched_large(const lords::BatchedProblem &bp, void *stream)
 {
@@ -303,10 +303,13 @@ int run_batched_large(const lords::BatchedProblem &bp, void *stream)
             }
         }
     }
-    if (rest.L == 0) return LORDS_OK;
-    if (!lords::prefill_batched_supported(rest)) return -1;
-    if (get_workspace(kFront + lords::prefill_batched_workspace_bytes(rest), stream, &ws) != LORDS_OK) return -1;
-    return lords::launch_prefill_batched(rest, ws.scratch(), ws.zeroed(), (hipStream_t)stream) == hipSuccess ? LORDS_OK : LORDS_ERR_LAUNCH;
+    if (rest.L > 0 && lords::prefill_batched_supported(rest) && get_workspace(kFront + lords::prefill_batched_workspace_bytes(rest), stream, &ws) == LORDS_OK)
+        return lords::launch_prefill_batched(rest, ws.scratch(), ws.zeroed(), (hipStream_t)stream) == hipSuccess ? LORDS_OK : LORDS_ERR_LAUNCH;
+    for (int l = 0; l < rest.L; ++l) {
+        const int rc = run_matmul(matrix_of(rest, l), LORDS_PATH_AUTO, stream);
+        if (rc != LORDS_OK) return rc;
+    }
+    return LORDS_OK;
 }
 
 // Several matrices in ONE launch, if a kernel takes the case: a status, or -1 if none does.

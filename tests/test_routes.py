@@ -103,3 +103,20 @@ for _ in range(4000):
 print(json.dumps(bad))
 """)
     assert out == []
+
+
+def test_batched_call_without_joint_scratch_does_nothing_twice(routes):
+    """One matrix goes in two passes, the others share tiles, whose scratch together is not to be had: each matrix is computed once."""
+    out = routes("""
+Ns, (M, K, r, bits, f32) = [6144] + [3000] * 7, (1000, 4096, 100, 4, 0)
+takes = lambda n: plan_util.takes_two_passes(M, [n], K, r, bits, f32, lib=plan)
+parts = [plan.prefill_workspace_bytes(M, n, K, r, bits, f32) for n in Ns]
+need = plan.two_pass_workspace_bytes((ctypes.c_int * 1)(Ns[0]), 1, M, K, r, bits, f32, 0)
+room = need + front + (33 << 20)                            # (33 MB: what fp32 factors keep beside the first block, and alignment)
+rt.double_largest_allocation(room)
+print(json.dumps([takes(Ns[0]), takes(Ns[1]), min(parts[1:]), max(parts), sum(parts[1:]), room, batched(Ns, M, K, r, bits, f32), launched()]))
+""")
+    first, second, least, most, joint, room, status, kernels = out
+    assert first and not second and 0 < least and most < room < joint and status == 0
+    assert kernels.count("dequant_operand") == 1 and kernels.count("operand_gemm") == 1
+    assert kernels.count("prefill") + kernels.count("prefill_wide") == 7
