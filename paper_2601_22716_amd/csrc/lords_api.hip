@@ -3,6 +3,7 @@
 #include "../../include/lords.h"
 #include "lords_launch.h"
 
+#include <algorithm>
 #include <mutex>
 
 namespace lords {
@@ -41,15 +42,21 @@ constexpr size_t kF32Parts = (size_t)32 << 20;
 // When a call needs more, a new block is allocated (and its front zeroed, which waits for the
 // device); while the stream is being captured that is refused instead.  A refusal leaves no error
 // behind: the caller may go on with less, and the launches that follow report the thread's last error.
+// Where the caller can do with less (`optional`), what the device had no room for is not asked for again at once: two
+// allocations that fail cost more than what they are wanted for gains, on every call beside an allocator that has taken the card.
+// kAskAgain such calls later it is, as memory may have been given back.
 struct OwnWorkspace {
     unsigned char *ptr = nullptr;
     size_t bytes = 0;
     unsigned char *f32_parts = nullptr;
+    size_t refused = ~(size_t)0;        // the least that the device had no room for
+    int without = 0;                    // calls that have done without since
 };
+constexpr int kAskAgain = 1000;
 OwnWorkspace g_ws[kMaxDevices];
 std::mutex g_ws_mutex;
 
-int get_workspace(size_t need, void *stream, WsView *out)
+int get_workspace(size_t need, void *stream, WsView *out, bool optional = false)
 {
     *out = WsView{};
     if (need < kFront) need = kFront;
@@ -64,14 +71,20 @@ int get_workspace(size_t need, void *stream, WsView *out)
             return LORDS_ERR_LAUNCH;
         }
         if (cap != hipStreamCaptureStatusNone) return LORDS_ERR_LAUNCH;
-        size_t want = need < (size_t)(16u << 20) ? (size_t)(16u << 20) : need + need / 2;
         const size_t behind = w.f32_parts ? 0 : kF32Parts;
+        if (optional && need + behind >= w.refused) {
+            if (w.without++ < kAskAgain) return LORDS_ERR_LAUNCH;
+            w.refused = ~(size_t)0;
+        }
+        size_t want = need < (size_t)(16u << 20) ? (size_t)(16u << 20) : need + need / 2;
         unsigned char *fresh = nullptr;
         want = (want + 255) & ~(size_t)255;
         if (hipMalloc((void **)&fresh, want + behind) != hipSuccess) {
             want = (need + 255) & ~(size_t)255;            // (no room for more than was asked for)
             if (hipMalloc((void **)&fresh, want + behind) != hipSuccess) {
                 (void)hipGetLastError();
+                w.refused = std::min(w.refused, need + behind);
+                w.without = 0;
                 return LORDS_ERR_LAUNCH;
             }
             (void)hipGetLastError();
@@ -200,7 +213,7 @@ lords::MatmulProblem matrix_of(const lords::BatchedProblem &bp, int l)
 int two_pass_workspace(const lords::BatchedProblem &bp, size_t extra, void *stream, WsView *ws, size_t *own)
 {
     *own = kFront + ((lords::two_pass_workspace_bytes(bp) + 255) & ~(size_t)255);
-    int rc = get_workspace(*own + extra, stream, ws);
+    int rc = get_workspace(*own + extra, stream, ws, true);
     ws->large = WsView::kTwoPass;
     if (rc != LORDS_OK) {
         *own = kFront;
@@ -249,10 +262,12 @@ int launch_matmul(const lords::MatmulProblem &p, lords_path path, const WsView &
 int plan_workspace(const lords::MatmulProblem &p, lords_path path, size_t extra, void *stream, WsView *ws, void **extra_ptr, bool passes = true)
 {
     size_t own = p.f32fact && !is_decode(path) ? kFront : matmul_need(p, path);
+    // (ranks at which the 256-token tiles of one wave per SIMD ask for more than there need be)
+    const bool elastic = !is_decode(path) && !p.f32fact && p.r > 32 && p.r <= 64 && p.M > 128;
     int rc = passes && !is_decode(path) && lords::two_pass_faster(batch_of(p)) ? two_pass_workspace(batch_of(p), extra, stream, ws, &own)
-                                                                             : get_workspace(own + extra, stream, ws);
-    if (rc != LORDS_OK && !p.f32fact && matmul_least(p, path) < own) {
-        own = matmul_least(p, path);
+                                                                             : get_workspace(own + extra, stream, ws, elastic);
+    if (rc != LORDS_OK && elastic) {
+        own = std::min(own, matmul_least(p, path));
         rc = get_workspace(own + extra, stream, ws);
         ws->bytes = own;                                   // (the plan is made for this much: `extra` lies behind it)
     }
@@ -303,7 +318,7 @@ int run_batched_large(const lords::BatchedProblem &bp, void *stream)
             }
         }
     }
-    if (rest.L > 0 && lords::prefill_batched_supported(rest) && get_workspace(kFront + lords::prefill_batched_workspace_bytes(rest), stream, &ws) == LORDS_OK)
+    if (rest.L > 0 && lords::prefill_batched_supported(rest) && get_workspace(kFront + lords::prefill_batched_workspace_bytes(rest), stream, &ws, true) == LORDS_OK)
         return lords::launch_prefill_batched(rest, ws.scratch(), ws.zeroed(), (hipStream_t)stream) == hipSuccess ? LORDS_OK : LORDS_ERR_LAUNCH;
     for (int l = 0; l < rest.L; ++l) {
         const int rc = run_matmul(matrix_of(rest, l), LORDS_PATH_AUTO, stream);

@@ -120,3 +120,40 @@ print(json.dumps([takes(Ns[0]), takes(Ns[1]), min(parts[1:]), max(parts), sum(pa
     assert first and not second and 0 < least and most < room < joint and status == 0
     assert kernels.count("dequant_operand") == 1 and kernels.count("operand_gemm") == 1
     assert kernels.count("prefill") + kernels.count("prefill_wide") == 7
+
+
+@pytest.mark.parametrize("call", ["matmul(2000, 6144, 4096, 64, 4, True)", "matmul(2000, 6144, 4096, 100, 4, False)", "matmul(1500, 11008, 4096, 48, 4, False)",
+                                  "batched([6144, 3000, 3001], 2000, 4096, 64, 4, True)", "batched([3000] * 4, 1000, 4096, 100, 4, False)"])
+def test_memory_that_is_not_there_is_not_asked_for_on_every_call(routes, call):
+    """Beside an allocator that has left room for little, a call that can do with less asks for more once in a thousand times; once
+    there is room it has it again."""
+    out = routes("""
+matmul(4, 512, 4096, 8, 4, False), launched()               # (the first block)
+rt.double_largest_allocation(front + (40 << 20))
+asked = rt.double_allocations_asked
+call = lambda: eval(arg)
+first = [call(), launched(), asked()]
+status = [call() for _ in range(500)]
+few = [max(status), launched()[-len(first[1]):], asked()]
+rt.double_largest_allocation(1 << 40)
+status = [call() for _ in range(1100)]
+print(json.dumps([first, few, [max(status), launched()[-1], asked()]]))
+""", call)
+    first, few, again = out
+    assert first[0] == few[0] == again[0] == 0
+    assert few[1] == first[1]
+    assert first[2] >= 3 and few[2] == first[2]             # (the first block and two attempts)
+    assert again[2] == few[2] + 1
+    if "True" in call or "matmul(2000" in call:
+        assert "operand_gemm" not in first[1] and again[1] == "operand_gemm"
+
+
+def test_refused_memory_that_a_call_needs_is_asked_for_every_time(routes):
+    """A call that cannot do with less is refused, and served as soon as there is room, whatever was refused before."""
+    out = routes("""
+rt.double_largest_allocation(1 << 20)
+refused = [matmul(100, 8000, 4096, 32, 4, False), matmul(2000, 6144, 4096, 64, 4, True), matmul(1500, 11008, 4096, 48, 4, False)]
+rt.double_largest_allocation(1 << 40)
+print(json.dumps([refused, matmul(100, 8000, 4096, 32, 4, False), matmul(2000, 6144, 4096, 64, 4, True)]))
+""")
+    assert out == [[6, 6, 6], 0, 0]
