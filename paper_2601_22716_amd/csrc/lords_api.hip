@@ -389,17 +389,23 @@ int gate_up_tokens(lords::BatchedProblem bp, int left)
 }
 
 // The pair in two passes, all tokens at once: the gate's sums never leave the registers.  Without the scratch: both products by
-// whole tiles, 2048 tokens at a time, the gate's in memory.
+// whole tiles, the gate's in memory, 2048 tokens at a time or, where there is no room for so many, 1024.
 int run_gate_up_two_pass(const lords::BatchedProblem &bp, void *stream)
 {
     WsView ws;
     size_t own;
-    const int step = bp.M < 2048 ? bp.M : 2048;
-    const size_t tmp_bytes = (size_t)step * bp.N[0] * sizeof(float) + 16;         // (the gate is read four columns at a time)
     int rc = two_pass_workspace(bp, 0, stream, &ws, &own);
     if (rc == LORDS_OK && ws.large == WsView::kTwoPass)
         return lords::launch_two_pass(bp, ws.scratch(), (hipStream_t)stream) == hipSuccess ? LORDS_OK : LORDS_ERR_LAUNCH;
-    rc = get_workspace(kFront + tmp_bytes, stream, &ws);
+    int step = bp.M < 2048 ? bp.M : 2048;
+    auto gate_room = [&](bool optional) {                  // (the gate is read four columns at a time)
+        return get_workspace(kFront + (size_t)step * bp.N[0] * sizeof(float) + 16, stream, &ws, optional);
+    };
+    rc = gate_room(step > 1024);
+    if (rc != LORDS_OK && step > 1024) {
+        step = 1024;
+        rc = gate_room(false);
+    }
     ws.large = WsView::kWhole;
     for (int m0 = 0; m0 < bp.M && rc == LORDS_OK; m0 += step) {
         lords::BatchedProblem part = bp;

@@ -157,3 +157,24 @@ rt.double_largest_allocation(1 << 40)
 print(json.dumps([refused, matmul(100, 8000, 4096, 32, 4, False), matmul(2000, 6144, 4096, 64, 4, True)]))
 """)
     assert out == [[6, 6, 6], 0, 0]
+
+
+@pytest.mark.parametrize("capturing", [0, 1])
+def test_gate_up_with_room_for_1024_tokens(routes, capturing):
+    """Without the scratch for its weights a pair keeps the gate of 2048 tokens in memory, or of 1024: with room for
+    1024 a call of a few more is served, captured too."""
+    out = routes("""
+M, N, K, r = 1112, 6144, 8192, 64
+takes = plan_util.takes_two_passes(M, [N, N], K, r, 4, True, act=True, lib=plan)
+most = front + 1024 * N * 4 + 4096
+matmul(4, 512, 4096, 8, 4, False)                           # (the first block)
+rt.double_largest_allocation(most)
+if arg:
+    gate_up(1024, N, K, 8, 4, True)                        # (grows the block to that)
+    rt.double_capturing(1)
+launched()
+print(json.dumps([takes, gate_up(M, N, K, r, 4, True), launched()]))
+""", capturing)
+    takes, status, kernels = out
+    assert takes and status == 0
+    assert kernels == ["prefill"] * 4
