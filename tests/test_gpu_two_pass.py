@@ -6,7 +6,6 @@ Sizes: the smallest at which the planner takes two passes, off the tiles in ever
 of 256, 128, 16 or 4, an odd number of K tiles, a ragged last one), every padded contraction, ranks that are not multiples
 of 4 or 8.
 """
-import ctypes
 import sys
 
 import numpy as np
@@ -14,6 +13,8 @@ import pytest
 
 import lords_inputs as li
 from oracle import lords_oracle as onp
+from tests import plan_util
+from tests.plan_util import takes_two_passes
 
 pytestmark = pytest.mark.gpu
 
@@ -33,23 +34,6 @@ def gpu():
     return gpu_util
 
 
-def takes_two_passes(M, Ns, K, r, bits, f32, act=False):
-    """The planner's choice (lords::two_pass_faster, a host function of the library)."""
-    import paper_2601_22716_amd as L
-    ptr, num, flag = ctypes.c_void_p, ctypes.c_int, ctypes.c_bool
-
-    class Batched(ctypes.Structure):
-        _fields_ = [("X", ptr), ("codebook", ptr), ("codes", ptr * 8), ("B", ptr * 8), ("A", ptr * 8), ("Y", ptr * 8), ("N", num * 8),
-                    ("L", num), ("M", num), ("K", num), ("r", num), ("bits", num),
-                    ("f32fact", flag), ("f32out", flag), ("act", flag), ("tiled", flag)]
-    p = Batched(L=len(Ns), M=M, K=K, r=r, bits=bits, f32fact=f32, f32out=True, act=act)
-    for l, n in enumerate(Ns):
-        p.N[l] = n
-    f = L.library()._ZN5lords15two_pass_fasterERKNS_14BatchedProblemE
-    f.restype = flag
-    return f(ctypes.byref(p))
-
-
 def check_rows(Y, c, X_f32, bits, what, seed=0, count=24):
     rows = np.unique(np.concatenate([np.random.default_rng(seed).integers(0, c.N, count), [0, c.N - 1]]))
     want = onp.matmul_rows(X_f32, c.codes, c.codebook, c.B_f32, c.A_f32, bits, rows)
@@ -60,13 +44,11 @@ def check_rows(Y, c, X_f32, bits, what, seed=0, count=24):
 
 
 def by_whole_tiles(d, M):
-    """The large-M kernel with a workspace that has no room for parts (its front alone), or None where it asks for more."""
+    """The large-M kernel with a workspace that has no room for parts (its front alone); a bf16 case must need none."""
     import torch
     import paper_2601_22716_amd as L
-    f32 = d.B.dtype == torch.float32
     front = L.lords_workspace_zero_bytes()
-    if not f32 and L.lords_workspace_bytes(M, d.N, d.K, d.r, d.bits, L.LORDS_BF16) > front:
-        return None
+    assert d.B.dtype == torch.float32 or L.lords_workspace_bytes(M, d.N, d.K, d.r, d.bits, L.LORDS_BF16) <= front
     ws = torch.zeros(front, dtype=torch.uint8, device="cuda")
     Y = torch.full((M, d.N), float("nan"), device="cuda")
     L.lords_matmul_ws(d.X, d.codes, d.codebook, d.B, d.A, Y, M, d.N, d.K, d.r, d.bits, ws)
@@ -74,21 +56,55 @@ def by_whole_tiles(d, M):
     return Y.cpu().numpy()
 
 
-@pytest.mark.parametrize("M,N,K,r,bits,fdt", [
-    (3000, 777, 544, 64, 4, "f32"), (3001, 1030, 672, 43, 3, "f32"), (4097, 1500, 544, 41, 2, "f32"),
-    (3000, 2999, 1056, 16, 4, "f32"), (4097, 2999, 4128, 10, 3, "f32"),
-    (3000, 2999, 544, 99, 2, "bf16"), (3001, 3002, 672, 128, 4, "bf16"), (3000, 2999, 2080, 45, 3, "bf16"),
-    (2049, 4001, 2208, 64, 2, "bf16"), (3000, 2999, 2208, 31, 4, "bf16"), (3000, 2999, 2208, 8, 3, "bf16")])
-def test_two_pass_product(gpu, M, N, K, r, bits, fdt):
+def plan_has_whole_tiles(M, N, K, r, bits, fdt):
+    return fdt == "f32" or plan_util.queries().prefill_workspace_bytes(M, N, K, r, bits, 0) == 0
+
+
+# The last column: the large-M kernel's own plan has whole tiles (or, with fp32 factors, makes do with them), so that it can be
+# compared with bit for bit.  Every padded contraction is, and at 128 every code width; one and two K tiles too.
+@pytest.mark.parametrize("M,N,K,r,bits,fdt,compared", [
+    (3000, 777, 544, 64, 4, "f32", True), (3001, 1030, 672, 43, 3, "f32", True), (4097, 1500, 544, 41, 2, "f32", True),
+    (3000, 2999, 1056, 16, 4, "f32", True), (4097, 2999, 4128, 10, 3, "f32", True),
+    (3329, 3622, 96, 64, 4, "f32", True), (4881, 2458, 32, 50, 2, "f32", True), (2456, 5853, 128, 63, 3, "f32", True), (3329, 3622, 160, 62, 4, "f32", True),
+    (3000, 2999, 544, 99, 2, "bf16", False), (3001, 3002, 672, 128, 4, "bf16", False), (3000, 2999, 2080, 45, 3, "bf16", True),
+    (2747, 3331, 544, 99, 2, "bf16", True), (3232, 2361, 672, 128, 4, "bf16", True), (3911, 2361, 544, 70, 3, "bf16", True),
+    (2049, 4001, 2208, 64, 2, "bf16", True), (3000, 2999, 2208, 31, 4, "bf16", True), (3000, 2999, 2208, 8, 3, "bf16", True)])
+def test_two_pass_product(gpu, M, N, K, r, bits, fdt, compared):
     say(f"two passes M={M} N={N} K={K} r={r} bits={bits} factors={fdt}")
     assert takes_two_passes(M, [N], K, r, bits, fdt == "f32")
+    assert plan_has_whole_tiles(M, N, K, r, bits, fdt) == compared
     c = li.make_case("tiny", M=M, N=N, K=K, r=r, bits=bits, factor_dtype=fdt, seed=3, signed_factors=True)
     d = gpu.DeviceCase(c)
     Y = d.matmul()
     check_rows(Y, c, c.X_f32, bits, "Y")
-    whole = by_whole_tiles(d, M)
-    if whole is not None:
-        np.testing.assert_array_equal(Y, whole)
+    if compared:
+        np.testing.assert_array_equal(Y, by_whole_tiles(d, M))
+
+
+@pytest.mark.parametrize("M,N,K,r,bits,fdt", [(3001, 1030, 672, 43, 3, "f32"), (3911, 2361, 544, 70, 3, "bf16"), (2049, 4001, 2208, 64, 2, "bf16")])
+def test_two_pass_infinities_and_nan(gpu, M, N, K, r, bits, fdt):
+    """Infinities and NaN in X and in the factors come out where the large-M kernel has them; the tokens and rows that
+    have none are the finite ones of the oracle."""
+    say(f"two passes, infinities M={M} N={N} K={K} r={r} bits={bits} factors={fdt}")
+    assert takes_two_passes(M, [N], K, r, bits, fdt == "f32")
+    c = li.make_case("tiny", M=M, N=N, K=K, r=r, bits=bits, factor_dtype=fdt, seed=8, signed_factors=True)
+    d = gpu.DeviceCase(c)
+    finite = d.matmul()
+    inf, nan = float("inf"), float("nan")
+    tokens, rows = [0, 255, 256, M // 2, M - 1], [0, 15, 300, N - 1]
+    for m, k, v in zip(tokens, (K - 1, 0, 127, K // 2, K - 9), (inf, -inf, nan, inf, -inf)):
+        d.X[m, k] = v
+    for n, j, v in zip(rows, (0, r - 1, r // 2, r - 1), (nan, inf, -inf, inf)):
+        d.B[n, j] = v
+    Y = d.matmul()
+    np.testing.assert_array_equal(Y, by_whole_tiles(d, M))
+    assert not np.isfinite(Y[tokens]).any() and not np.isfinite(Y[:, rows]).any()
+    keep = np.ix_(np.setdiff1d(np.arange(M), tokens), np.setdiff1d(np.arange(N), rows))
+    np.testing.assert_array_equal(Y[keep], finite[keep])
+    d.A[r - 1, K - 1] = inf                                  # (every weight of the last column)
+    Y = d.matmul()
+    np.testing.assert_array_equal(Y, by_whole_tiles(d, M))
+    assert not np.isfinite(Y).any()
 
 
 def test_two_pass_slab_tiles_and_bf16_output(gpu):
@@ -111,20 +127,20 @@ def test_two_pass_slab_tiles_and_bf16_output(gpu):
     assert torch.equal(Y32.bfloat16(), Y16)
 
 
-@pytest.mark.parametrize("N,K", [(19000, 4128), (33000, 2080)])
-def test_two_pass_in_chunks(gpu, N, K):
+@pytest.mark.parametrize("M,N,K,compared", [(1300, 19000, 4128, False), (1201, 19000, 4128, True), (1300, 33000, 2080, True)])
+def test_two_pass_in_chunks(gpu, M, N, K, compared):
     """W larger than the scratch: rows in chunks, the last one ragged."""
     import torch
-    M, r, bits = 1300, 128, 2
+    r, bits = 128, 2
     say(f"two passes in chunks N={N} K={K}")
     assert takes_two_passes(M, [N], K, r, bits, False) and ((N + 15) // 16) * ((K + 127) // 128) * 4096 > 128 << 20
     c = li.make_case("tiny", M=M, N=N, K=K, r=r, bits=bits, factor_dtype="bf16", seed=5, signed_factors=True)
     d = gpu.DeviceCase(c)
     Y = d.matmul()
     check_rows(Y, c, c.X_f32, bits, "Y")
-    whole = by_whole_tiles(d, M)
-    if whole is not None:
-        np.testing.assert_array_equal(Y, whole)
+    assert plan_has_whole_tiles(M, N, K, r, bits, "bf16") == compared
+    if compared:
+        np.testing.assert_array_equal(Y, by_whole_tiles(d, M))
     del d
     torch.cuda.empty_cache()
 

@@ -6,7 +6,6 @@ Sizes: the planner takes this form at them, and they are off the tiles in every 
 multiples of 256, 64, 16 or 4, K tiles of every raggedness (32, 64 and 96 columns left over), one K tile alone, ranks at both
 ends of the range and odd ones, both code layouts, both output types.
 """
-import ctypes
 import sys
 
 import numpy as np
@@ -14,6 +13,7 @@ import pytest
 
 import lords_inputs as li
 from oracle import lords_oracle as onp
+from tests import plan_util
 
 pytestmark = pytest.mark.gpu
 
@@ -33,22 +33,8 @@ def gpu():
     return gpu_util
 
 
-def planner(name, restype, M, N, K, r, bits, *limit):
-    """A host function of the library's planner for this problem."""
-    import paper_2601_22716_amd as L
-    ptr, num, flag = ctypes.c_void_p, ctypes.c_int, ctypes.c_bool
-
-    class Problem(ctypes.Structure):
-        _fields_ = [(n, ptr) for n in ("X", "codes", "codebook", "B", "A", "Y")] + [(n, num) for n in ("M", "N", "K", "r", "bits")] + \
-                   [(n, flag) for n in ("f32fact", "f32out", "tiled")]
-    f = getattr(L.library(), f"_ZN5lords{len(name)}{name}ERKNS_13MatmulProblemE" + "m" * len(limit))
-    f.restype, f.argtypes = restype, [ctypes.c_void_p] + [ctypes.c_size_t] * len(limit)
-    p = Problem(M=M, N=N, K=K, r=r, bits=bits)
-    return f(ctypes.addressof(p), *limit)
-
-
-def taken(M, N, K, r, bits, limit=2 ** 62):
-    return planner("prefill_wide_taken", ctypes.c_bool, M, N, K, r, bits, limit)
+def taken(*problem):
+    return bool(plan_util.queries().prefill_wide_taken(*problem, 0))
 
 
 def check_rows(Y, c, bits, what, seed=0):
@@ -122,7 +108,7 @@ def test_wide_smaller_workspace(gpu, M, N, K, r, bits):
     same and the cut made for it; a smaller one is refused."""
     import torch
     import paper_2601_22716_amd as L
-    least = L.lords_workspace_zero_bytes() + planner("prefill_least_workspace_bytes", ctypes.c_size_t, M, N, K, r, bits)
+    least = L.lords_workspace_zero_bytes() + plan_util.queries().prefill_least_workspace_bytes(M, N, K, r, bits, 0)
     say(f"wide, smaller workspace M={M} N={N} K={K} r={r} bits={bits}: {least}")
     assert least < L.lords_workspace_bytes(M, N, K, r, bits, L.LORDS_BF16)
     c = li.make_case("tiny", M=M, N=N, K=K, r=r, bits=bits, factor_dtype="bf16", seed=23, signed_factors=True)
@@ -137,3 +123,24 @@ def test_wide_smaller_workspace(gpu, M, N, K, r, bits):
     torch.cuda.synchronize()
     assert bool((room[least:] == 77).all())
     check_rows(Y.cpu().numpy(), c, bits, "Y")
+
+
+@pytest.mark.parametrize("M,N,K,r,bits", [(257, 28001, 544, 63, 4), (1001, 9003, 3072, 50, 4)])
+def test_wide_infinities_and_nan(gpu, M, N, K, r, bits):
+    """Infinities and NaN in X and in the factors stay with their tokens and rows; the others keep their bits."""
+    say(f"wide, infinities M={M} N={N} K={K} r={r} bits={bits}")
+    assert taken(M, N, K, r, bits) and not plan_util.takes_two_passes(M, [N], K, r, bits, 0)
+    d = gpu.DeviceCase(li.make_case("tiny", M=M, N=N, K=K, r=r, bits=bits, factor_dtype="bf16", seed=8, signed_factors=True))
+    finite = d.matmul()
+    inf, nan = float("inf"), float("nan")
+    tokens, rows = [0, 255, 256, M // 2, M - 1], [0, 15, 300, N - 1]
+    for m, k, v in zip(tokens, (K - 1, 0, 127, K // 2, K - 9), (inf, -inf, nan, inf, -inf)):
+        d.X[m, k] = v
+    for n, j, v in zip(rows, (0, r - 1, r // 2, r - 1), (nan, inf, -inf, inf)):
+        d.B[n, j] = v
+    Y = d.matmul()
+    assert not np.isfinite(Y[tokens]).any() and not np.isfinite(Y[:, rows]).any()
+    keep = np.ix_(np.setdiff1d(np.arange(M), tokens), np.setdiff1d(np.arange(N), rows))
+    np.testing.assert_array_equal(Y[keep], finite[keep])
+    d.A[r - 1, K - 1] = inf                                  # (every weight of the last column)
+    assert not np.isfinite(d.matmul()).any()
