@@ -198,14 +198,10 @@ lords::BatchedProblem batch_where(const lords::BatchedProblem &bp, Pick pick)
     for (int l = 0; l < bp.L; ++l) {
         if (!pick(l)) continue;
         out.codes[out.L] = bp.codes[l]; out.B[out.L] = bp.B[l]; out.A[out.L] = bp.A[l]; out.Y[out.L] = bp.Y[l]; out.N[out.L] = bp.N[l];
+        out.whole[out.L] = bp.whole[l];
         ++out.L;
     }
     return out;
-}
-
-lords::MatmulProblem matrix_of(const lords::BatchedProblem &bp, int l)
-{
-    return lords::MatmulProblem{bp.X, bp.codes[l], bp.codebook, bp.B[l], bp.A[l], bp.Y[l], bp.M, bp.N[l], bp.K, bp.r, bp.bits, bp.f32fact, bp.f32out};
 }
 
 // The library's own workspace for a product in two passes, and `extra` bytes behind its scratch.  Where the memory is not to
@@ -285,18 +281,37 @@ int run_matmul(const lords::MatmulProblem &p, lords_path path, void *stream)
 }
 
 // Several matrices that each go to the large-M kernel or into two passes; a status, or -1 (nothing launched) to have them one
-// by one.  Every matrix is summed as it would be alone.  In two passes together: those that alone would take them, and with them those that
-// alone are summed by whole tiles, if that is the faster way for all of these.
-int run_batched_large(const lords::BatchedProblem &bp, void *stream)
+// by one.  Every matrix is summed as it would be alone.  Together in two passes: none of them, those that alone would take
+// them, or with these the ones that alone are summed by whole tiles, whichever the planner expects to be the fastest with one launch of the
+// large-M kernel for the others; a launch of its own is 8 us.  (us, by that kernel all / whichever is faster: 11343 rows of four
+// matrices, 864 columns, rank 38, 516 tokens 50 / 50, three in two passes and one after them 66; 6144 rows of three, 4096 columns,
+// fp32 rank 64, 2048 tokens 701 / 197.)
+int run_batched_large(lords::BatchedProblem bp, void *stream)
 {
     if (bp.act) return -1;
-    auto alone = [&](int l) { return lords::two_pass_faster(batch_of(matrix_of(bp, l))); };
-    auto whole = [&](int l) { return alone(l) || lords::prefill_fast_workspace_bytes(matrix_of(bp, l), kNoLimit) == 0; };
-    lords::BatchedProblem twice = batch_where(bp, whole), rest = batch_where(bp, [&](int l) { return !whole(l); });
-    if (twice.L == 0 || !lords::two_pass_faster(twice)) {
-        twice = batch_where(bp, alone);
-        rest = batch_where(bp, [&](int l) { return !alone(l); });
+    const unsigned all = (1u << bp.L) - 1;
+    unsigned whole = 0, alone = 0, in_two = 0;
+    for (int l = 0; l < bp.L && bp.M > 128; ++l) {
+        const lords::MatmulProblem p = lords::matrix_of(bp, l);
+        if (!lords::two_pass_supported(batch_of(p))) continue;
+        if (lords::two_pass_faster(batch_of(p))) { alone |= 1u << l; bp.whole[l] = true; }
+        else if (lords::prefill_fast_workspace_bytes(p, kNoLimit) == 0) whole |= 1u << l;
     }
+    whole |= alone;
+    auto pick = [&](unsigned set) { return batch_where(bp, [&](int l) { return (set >> l & 1) != 0; }); };
+    if (whole) {
+        auto cost = [&](unsigned set) {
+            const double two = set ? lords::two_pass_cost(pick(set)) : 0.0;
+            return set == all ? two : two + lords::large_cost(pick(all & ~set)) + (set ? 8.0 : 0.0);
+        };
+        double best = 0.95 * cost(0);
+        for (unsigned set : {alone, whole}) {
+            if (!set || set == in_two) continue;
+            const double us = cost(set);
+            if (us < best) { best = us; in_two = set; }
+        }
+    }
+    const lords::BatchedProblem twice = pick(in_two), rest = pick(all & ~in_two);
     WsView ws;
     for (int first = 0, end; first < twice.L; first = end) {
         // (as many at a time as the scratch holds a tile of each of: at 36864 columns seven)
@@ -313,7 +328,7 @@ int run_batched_large(const lords::BatchedProblem &bp, void *stream)
             if (lords::launch_two_pass(group, ws.scratch(), (hipStream_t)stream) != hipSuccess) return LORDS_ERR_LAUNCH;
         } else {
             for (int l = 0; l < group.L; ++l) {
-                const int rcl = launch_large(matrix_of(group, l), ws, stream);
+                const int rcl = launch_large(lords::matrix_of(group, l), ws, stream);
                 if (rcl != LORDS_OK) return rcl;
             }
         }
@@ -321,7 +336,7 @@ int run_batched_large(const lords::BatchedProblem &bp, void *stream)
     if (rest.L > 0 && lords::prefill_batched_supported(rest) && get_workspace(kFront + lords::prefill_batched_workspace_bytes(rest), stream, &ws, true) == LORDS_OK)
         return lords::launch_prefill_batched(rest, ws.scratch(), ws.zeroed(), (hipStream_t)stream) == hipSuccess ? LORDS_OK : LORDS_ERR_LAUNCH;
     for (int l = 0; l < rest.L; ++l) {
-        const int rc = run_matmul(matrix_of(rest, l), LORDS_PATH_AUTO, stream);
+        const int rc = run_matmul(lords::matrix_of(rest, l), LORDS_PATH_AUTO, stream);
         if (rc != LORDS_OK) return rc;
     }
     return LORDS_OK;
@@ -339,8 +354,7 @@ int run_batched(const lords::BatchedProblem &bp, void *stream)
     if (!lords::decode_mx_batched_supported(bp)) {
         // many tokens: the large-M kernel, if every matrix alone would go there (and their scratch is to be had together)
         for (int l = 0; l < bp.L; ++l) {
-            const lords::MatmulProblem p{bp.X, bp.codes[l], bp.codebook, bp.B[l], bp.A[l], bp.Y[l], bp.M, bp.N[l], bp.K, bp.r, bp.bits, bp.f32fact, bp.f32out};
-            if (is_decode(resolve_path(LORDS_PATH_AUTO, p))) return -1;
+            if (is_decode(resolve_path(LORDS_PATH_AUTO, lords::matrix_of(bp, l)))) return -1;
         }
         return run_batched_large(bp, stream);
     }

@@ -94,7 +94,14 @@ struct BatchedProblem {
     int L, M, K, r, bits;
     bool f32fact, f32out, act;
     bool tiled = false;     // every codes[l] is in the slab-tile layout (see MatmulProblem)
+    bool whole[kMaxBatch] = {};     // large-M kernel: this matrix by whole tiles (the bits of a product in two passes)
 };
+inline MatmulProblem matrix_of(const BatchedProblem &p, int l)
+{
+    MatmulProblem q{p.X, p.codes[l], p.codebook, p.B[l], p.A[l], p.Y[l], p.M, p.N[l], p.K, p.r, p.bits, p.f32fact, p.f32out};
+    q.tiled = p.tiled;
+    return q;
+}
 // One and two tokens, bf16 factors (lords_gemv.hip): all matrices in one launch; `zeroed` as for the single matrix.
 bool decode_gemv_batched_supported(const BatchedProblem &p);
 hipError_t launch_decode_gemv_batched(const BatchedProblem &p, void *zeroed, hipStream_t st);
@@ -138,13 +145,19 @@ hipError_t launch_prefill_fast(const MatmulProblem &p, void *part, size_t part_b
 // prefill_batched_workspace_bytes(p) bytes.
 bool prefill_batched_supported(const BatchedProblem &p);
 size_t prefill_batched_workspace_bytes(const BatchedProblem &p);
+// The planner's estimate of that launch, in us (what one matrix leaves idle of the chip is the next one's).
+double prefill_batched_cost(const BatchedProblem &p);
 hipError_t launch_prefill_batched(const BatchedProblem &p, void *part, void *zeroed, hipStream_t st);
 // Many tokens: W dequantised once into scratch, then a product that reads it (lords_two_pass.hip); one matrix, several that
 // read the same X, or (act) a gate/up pair.  Scratch: two_pass_workspace_bytes, at most kTwoPassBytes.
 constexpr size_t kTwoPassBytes = (size_t)128 << 20;
 bool two_pass_supported(const BatchedProblem &p);
 size_t two_pass_workspace_bytes(const BatchedProblem &p);
-// Whether that is the faster way (more than 128 tokens; the large-M kernel must take every matrix).
+// The planner's estimates of both ways, in us on one scale: this one, and the large-M kernel (a pair: its two products one after
+// the other; several matrices: together, as marked).
+double two_pass_cost(const BatchedProblem &p);
+double large_cost(const BatchedProblem &p);
+// Whether this is the faster way for one matrix or a pair (more than 128 tokens; the large-M kernel must take it too).
 bool two_pass_faster(const BatchedProblem &p);
 hipError_t launch_two_pass(const BatchedProblem &p, void *scratch, hipStream_t st);
 // ... and the general variant (any rank; lords_fused.hip).

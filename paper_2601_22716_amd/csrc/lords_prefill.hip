@@ -39,6 +39,7 @@
 // index*32 + (lane%8)*4); v_fma_mix_f32 multiplies fp16 level by fp32 scale; one rounding to bf16.
 // With fp32 factors the levels stay fp32 too (pairs of 8 bytes, 8 copies): level times scale is then
 // rounded once, to bf16, and no level has to lie within the range of fp16.
+#include <algorithm>
 #include <numeric>
 #include <type_traits>
 #include "lords_prefill.h"
@@ -852,17 +853,12 @@ hipError_t launch_prefill_fast(const MatmulProblem &p, void *part, size_t part_b
 }
 
 // ---- several matrices, the same activations ------------------------------------------------------------------
-static MatmulProblem pf_of(const BatchedProblem &p, int l)
-{
-    MatmulProblem q{p.X, p.codes[l], p.codebook, p.B[l], p.A[l], p.Y[l], p.M, p.N[l], p.K, p.r, p.bits, p.f32fact, p.f32out};
-    q.tiled = p.tiled;
-    return q;
-}
+static PfPlan batched_plan(const BatchedProblem &p, int l) { return pf_plan(matrix_of(p, l), p.whole[l] ? 0 : ~(size_t)0); }
 
 size_t prefill_batched_workspace_bytes(const BatchedProblem &p)
 {
     size_t sum = 0;
-    for (int l = 0; l < p.L; ++l) sum += (pf_plan(pf_of(p, l), ~(size_t)0).part_bytes + 255) & ~(size_t)255;
+    for (int l = 0; l < p.L; ++l) sum += (batched_plan(p, l).part_bytes + 255) & ~(size_t)255;
     return sum;
 }
 
@@ -871,13 +867,50 @@ bool prefill_batched_supported(const BatchedProblem &p)
     if (p.act || p.L < 1 || p.L > kMaxBatch) return false;
     size_t tiles = 0;
     for (int l = 0; l < p.L; ++l) {
-        const MatmulProblem q = pf_of(p, l);
-        if (!prefill_fast_supported(q)) return false;
-        const PfPlan d = pf_plan(q, ~(size_t)0);
+        if (!prefill_fast_supported(matrix_of(p, l))) return false;
+        const PfPlan d = batched_plan(p, l);
         if (d.part_bytes) tiles += (size_t)d.nt * d.mt;
         if (d.wgs > (1 << 24)) return false;
     }
     return tiles * sizeof(uint32_t) <= kZeroBytes;
+}
+
+static bool same_shape(const PfPlan &a, const PfPlan &b) { return a.wm == b.wm && a.wn == b.wn && a.mb == b.mb; }
+
+// The matrices' workgroups in order, each to the CU that is free first; the launches of other tile shapes behind it.  A workgroup's
+// start and end (8 us), which a planner that weighs one tile shape against another can leave out, make several short rounds
+// longer than one: of 250 calls of two to six matrices, measured / estimated lies within 0.72 .. 1.05 for nine in ten of each
+// padded contraction (1.05 .. 1.3 at six times 32), 0.8 .. 1.8 without them.
+constexpr double kPfStartEnd = 8.0;
+double prefill_batched_cost(const BatchedProblem &p)
+{
+    PfPlan d[kMaxBatch];
+    bool done[kMaxBatch] = {};
+    for (int l = 0; l < p.L; ++l) d[l] = batched_plan(p, l);
+    double us = 0;
+    for (int l0 = 0; l0 < p.L; ++l0) {
+        if (done[l0]) continue;
+        struct Free { double at; long cus; } free[kMaxBatch + 1] = {{0.0, kPfCUs}};     // in order of time
+        int n = 1;
+        double end = 0;
+        for (int l = l0; l < p.L; ++l) {
+            if (done[l] || !same_shape(d[l], d[l0])) continue;
+            done[l] = true;
+            const double each = d[l].cost / ((d[l].wgs + kPfCUs - 1) / kPfCUs) + kPfStartEnd;
+            for (long left = d[l].wgs; left > 0;) {
+                const Free next{free[0].at + each, std::min(left, free[0].cus)};
+                left -= next.cus;
+                free[0].cus -= next.cus;
+                if (free[0].cus == 0) std::copy(free + 1, free + n--, free);
+                int at = n++;
+                for (; at > 0 && free[at - 1].at > next.at; --at) free[at] = free[at - 1];
+                free[at] = next;
+                end = std::max(end, next.at);
+            }
+        }
+        us += end;
+    }
+    return us;
 }
 
 // One launch per tile shape that the matrices' plans ask for (usually one).  A part that waits for others cannot wait for
@@ -892,7 +925,7 @@ hipError_t launch_prefill_batched(const BatchedProblem &p, void *part, void *zer
     uint32_t *next_arrived = (uint32_t *)zeroed;
     bool done[kMaxBatch] = {};
     for (int l = 0; l < p.L; ++l) {
-        d[l] = pf_plan(pf_of(p, l), ~(size_t)0);
+        d[l] = batched_plan(p, l);
         parts[l] = next_part;
         arrived[l] = next_arrived;
         next_part += (d[l].part_bytes + 255) & ~(size_t)255;
@@ -901,12 +934,12 @@ hipError_t launch_prefill_batched(const BatchedProblem &p, void *part, void *zer
     for (int l0 = 0; l0 < p.L; ++l0) {
         if (done[l0]) continue;
         PrefillArgsT<kMaxBatch> a;
-        pf_common(a, pf_of(p, l0), d[l0]);
+        pf_common(a, matrix_of(p, l0), d[l0]);
         a.L = 0;
         int x0 = 0;
         for (int l = l0; l < p.L; ++l) {
-            if (done[l] || d[l].wm != d[l0].wm || d[l].wn != d[l0].wn || d[l].mb != d[l0].mb) continue;
-            pf_layer(a.layer[a.L], pf_of(p, l), d[l], parts[l], arrived[l], x0);
+            if (done[l] || !same_shape(d[l], d[l0])) continue;
+            pf_layer(a.layer[a.L], matrix_of(p, l), d[l], parts[l], arrived[l], x0);
             x0 += a.layer[a.L].gx;
             ++a.L;
             done[l] = true;

@@ -601,8 +601,7 @@ static long op_tiles(const BatchedProblem &p, int row0, int rows, int R)
     return t * ((p.M + 255) / 256);
 }
 
-// The planner's estimate of both passes, in us.
-static double two_pass_cost(const BatchedProblem &p)
+double two_pass_cost(const BatchedProblem &p)
 {
     const int rows = op_chunk_rows(p), ntk = (p.K + 127) / 128;
     int most = 0;
@@ -619,10 +618,19 @@ static double two_pass_cost(const BatchedProblem &p)
     return us + op_dequant_us(p, weights);
 }
 
-// Whether the weights are dequantised once, in a pass of their own, or for every tile of tokens again (several matrices: all of
-// them by the large-M kernel).  Decided by the two planners' estimates, not by what has been allocated.  The large-M
-// kernel's reads high or low by the padded contraction (measured / estimated, the middle of 10 to 40 products each: bf16
-// factors 32 columns 1.0, 64 0.85, 128 0.82; fp32 factors 0.95, 0.92, 0.9, six times 32 1.15); the last twentieth is the margin.
+// The large-M kernel's estimate reads high or low by the padded contraction (measured / estimated, the middle of 10 to 40
+// products each: bf16 factors 32 columns 1.0, 64 0.85, 128 0.82; fp32 factors 0.95, 0.92, 0.9, six times 32 1.15).
+double large_cost(const BatchedProblem &p)
+{
+    const int ss = op_ss(p);
+    const double scale = p.f32fact ? (ss == 1 ? 0.95 : ss == 2 ? 0.92 : ss == 4 ? 0.9 : 1.15) : (ss == 1 ? 1.0 : ss == 2 ? 0.85 : 0.82);
+    double us = 0;
+    for (int l = 0; l < p.L; ++l) us += prefill_fast_cost(matrix_of(p, l));
+    return scale * (p.act || p.L == 1 ? us : std::min(us, prefill_batched_cost(p)));
+}
+
+// Whether the weights are dequantised once, in a pass of their own, or for every tile of tokens again.  Decided by the
+// two planners' estimates, not by what has been allocated; the last twentieth is the margin.
 //   us, large-M kernel / two passes:   1024 tokens   2048          4096
 //   14336 x 4096 bf16 rank 32          115 / 128     230 / 227     430 / 416
 //                bf16 rank 48          169 / 125     307 / 227     620 / 413
@@ -634,16 +642,9 @@ static double two_pass_cost(const BatchedProblem &p)
 bool two_pass_faster(const BatchedProblem &p)
 {
     if (p.M <= 128 || !two_pass_supported(p)) return false;
-    const int ss = op_ss(p);
-    const double scale = p.f32fact ? (ss == 1 ? 0.95 : ss == 2 ? 0.92 : ss == 4 ? 0.9 : 1.15) : (ss == 1 ? 1.0 : ss == 2 ? 0.85 : 0.82);
-    double fused = 0;
-    for (int l = 0; l < p.L; ++l) {
-        MatmulProblem q{p.X, p.codes[l], p.codebook, p.B[l], p.A[l], p.Y[l], p.M, p.N[l], p.K, p.r, p.bits, p.f32fact, p.f32out};
-        q.tiled = p.tiled;
-        if (!prefill_fast_supported(q)) return false;
-        fused += prefill_fast_cost(q);
-    }
-    return two_pass_cost(p) < 0.95 * scale * fused;
+    for (int l = 0; l < p.L; ++l)
+        if (!prefill_fast_supported(matrix_of(p, l))) return false;
+    return two_pass_cost(p) < 0.95 * large_cost(p);
 }
 
 static hipError_t launch_two_pass_rows(const BatchedProblem &p, int row0, int rows, void *scratch, hipStream_t st)

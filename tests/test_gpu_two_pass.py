@@ -146,9 +146,11 @@ def test_two_pass_in_chunks(gpu, M, N, K, compared):
 
 
 @pytest.mark.parametrize("M,Ns,K,r,bits,fdt", [
-    (3000, [2999, 500, 777], 544, 64, 4, "f32"), (4096, [3000, 40, 3001], 1056, 99, 3, "bf16"), (3000, [2999, 300], 2208, 64, 2, "bf16")])
+    (3000, [2999, 500, 777], 544, 64, 4, "f32"), (4096, [3000, 40, 3001], 1056, 99, 3, "bf16"), (3000, [2999, 300], 2208, 64, 2, "bf16"),
+    (2296, [2452, 1975], 704, 22, 3, "f32")])
 def test_two_pass_batched(gpu, M, Ns, K, r, bits, fdt):
-    """Several matrices, some of which alone would not go in two passes: the single calls' bits; from a captured graph too."""
+    """Several matrices, some of which alone would not go in two passes (of the last ones none does together): the single
+    calls' bits; from a captured graph too."""
     import torch
     import paper_2601_22716_amd as L
     say(f"two passes batched M={M} Ns={Ns} K={K} r={r} bits={bits} factors={fdt}")

@@ -178,3 +178,28 @@ print(json.dumps([takes, gate_up(M, N, K, r, 4, True), launched()]))
     takes, status, kernels = out
     assert takes and status == 0
     assert kernels == ["prefill"] * 4
+
+
+@pytest.mark.parametrize("Ns,rest,first", [
+    ([2305, 1545, 5312, 658, 1443, 480], [143, 640, 5, 2, 1], False), ([3722, 2776, 4485, 354], [516, 864, 38, 4, 0], False),
+    ([3129, 1837, 2122, 649], [647, 864, 18, 2, 1], False), ([2452, 1975], [2296, 704, 22, 3, 1], True)])
+def test_batched_matrices_stay_in_one_launch_where_that_is_faster(routes, Ns, rest, first):
+    """Matrices that alone leave much of the chip idle are one launch of the large-M kernel, beside each other: two passes are
+    to beat that launch, not the sum of launches that each idle; also where one alone would go in two passes."""
+    out = routes("""
+Ns, (M, K, r, bits, f32) = arg
+print(json.dumps([[plan_util.takes_two_passes(M, [n], K, r, bits, f32, lib=plan) for n in Ns], batched(Ns, M, K, r, bits, f32), launched()]))
+""", [Ns, rest])
+    alone, status, kernels = out
+    assert alone == [first] + [False] * (len(Ns) - 1) and status == 0
+    assert set(kernels) <= {"prefill", "prefill_wide"} and len(kernels) <= 2
+
+
+def test_batched_matrices_go_in_two_passes_together(routes):
+    """... and two passes where they are the faster way, with them matrices that alone would not take them."""
+    out = routes("""
+Ns, (M, K, r, bits, f32) = [4096, 1024, 1024], (2048, 4096, 64, 4, 1)
+print(json.dumps([[plan_util.takes_two_passes(M, [n], K, r, bits, f32, lib=plan) for n in Ns], batched(Ns, M, K, r, bits, f32), launched()]))
+""")
+    alone, status, kernels = out
+    assert status == 0 and kernels == ["dequant_operand", "operand_gemm"]
