@@ -7,8 +7,9 @@
  * where Q holds one k-bit level index per element (k = 2, 3 or 4), C is the
  * 2^k-entry look-up table of the target data type (Alg. 1, "Require"), and the
  * element-wise scale S is the product of the rank-r factors B (N x r) and
- * A (r x K).  S and W_hat are regenerated per tile inside the kernels and are
- * never written to device memory by lords_matmul.
+ * A (r x K).  S and W_hat are regenerated per tile inside the kernels.  S is never
+ * written to device memory; of W_hat some products of many tokens write a bf16 copy
+ * to the library's own workspace (see Workspace below).
  *
  * Conventions common to every entry point
  *  - Every data pointer is a DEVICE pointer owned by the caller, at least 16-byte
@@ -42,11 +43,16 @@
  *    device once) and the old one is kept, so that work already queued and HIP graphs captured
  *    earlier stay valid; it is released when the process ends.  Such a growth is refused with
  *    LORDS_ERR_LAUNCH while `stream` is being captured: warm a shape up once before capturing it.
+ *    A block is half as large again as the call asks for, 16 MiB at least, where the device has that much,
+ *    so that few are ever allocated; 32 MiB for the parts of products with fp32 factors lie beside the first.
  *    One product asks for at most 64 MiB of partial sums; lords_matmul_batched above 16 tokens asks for
- *    those of all its matrices together, and runs matrix by matrix, with the same results, where that
- *    much cannot be had.  Products of many tokens (above 128) at ranks above 32 or with fp32 factors may
- *    instead write their weights once, in bf16, to at most 128 MiB of that workspace and multiply from
- *    there; where that much cannot be had, they run without it, more slowly and with the same results.
+ *    those of all its matrices together, and runs matrix by matrix where that much cannot be had.  Products
+ *    of many tokens (above 128; which ones, a cost model decides) may instead write their weights once, in
+ *    bf16, to at most 128 MiB of that workspace and multiply from there; where that much cannot be had,
+ *    they run without it, more slowly.  Both with the same results, except that bf16 factors of rank
+ *    33 to 64 above 128 tokens also run with the smaller partial sums of 128-token tiles, and the order of
+ *    their fp32 sums then follows from what there is.  Memory that the device refused
+ *    is asked for again only after a thousand calls that could do without it.
  *    Calls that share one workspace and overlap in time on one device race; issue them from one
  *    stream (or give every stream its own workspace through lords_matmul_ws).  The library keeps no
  *    other state; entry points may be called from several host threads.
@@ -191,6 +197,9 @@ int lords_matmul_ex(const void *X, const void *codes, const float *codebook,
  *   rank 33 to 64 and more than 128 tokens may take less than the query gives.  How much there is decides
  *   how the sums over K are cut, so results are the same bit for bit among workspaces of one size, and of
  *   any size the query gives or more; those of a smaller one differ by the order of fp32 sums.
+ *   Weights are never written to a caller's workspace: where lords_matmul would do that (see Workspace
+ *   above), this call is the slower one, up to several times at high ranks, and may take its fp32 sums in
+ *   another order.
  */
 size_t lords_workspace_bytes(int M, int N, int K, int r, int bits, lords_dtype factor_dtype, lords_path path);
 size_t lords_workspace_zero_bytes(void);
@@ -208,7 +217,8 @@ int lords_matmul_ws(const void *X, const void *codes, const float *codebook,
  * (every decode shape of the Llama-3-8B/70B layers fits; large prefill shapes whose K range is cut
  * may not).  All calls on one GPU share the array: calls that overlap in time on one GPU race.  Its
  * front (slots and tickets) starts at zero and every call leaves it at zero.  (The array's size bounds the
- * partial sums of a large-M product, which may therefore be cut in another order than lords_matmul's.)
+ * partial sums of a large-M product, which may therefore be cut in another order than lords_matmul's; weights
+ * are never written to it, as with lords_matmul_ws.)
  */
 size_t lords_noalloc_limit(void);
 int lords_matmul_noalloc(const void *X, const void *codes, const float *codebook,
@@ -249,8 +259,8 @@ int lords_matmul_repacked(const void *X, const void *codes_tiled, const float *c
  *   K, r, bits, codebook, factor_dtype are shared by all L matrices.  1 <= L <= 8 (LORDS_ERR_SHAPE).
  * With M <= 16 and bf16 factors of rank <= 64 all matrices are served by one kernel launch, and where each
  * alone would go to the MFMA GEMM (above 16 tokens bf16 factors of rank <= 128 and fp32 of rank <= 64; at few tokens
- * see lords_matmul) by one launch for each tile shape their sizes ask for, usually one; other cases run matrix
- * by matrix.  Each Y[l] is the same sum lords_matmul computes for that matrix
+ * see lords_matmul) by one launch for each tile shape their sizes ask for, usually one, or those of them for
+ * which that is faster together in two passes (see Workspace above); other cases run matrix by matrix.  Each Y[l] is the same sum lords_matmul computes for that matrix
  * (bit-identical from three tokens on; at one and two tokens the single-matrix call may run another
  * kernel, with another rounding of the same sum).
  */

@@ -3,7 +3,7 @@
 // the eight waves of 128 registers for operands have room for 128 tokens only, so every weight was dequantised again for
 // every 128 tokens; a wave that has a SIMD and its 512 registers to itself holds the sums of 256 tokens in its 256 accumulation
 // registers and everything else in the other half.  (At ranks up to 32, where eight waves of 32 rows x 256 tokens do the
-// same work per weight, this form is no faster: 2048 x 14336 x 4096 227 against 230 us; the chip's power bounds both.)
+// same work per weight, this form is no faster: 2048 x 14336 x 4096 227 against 230 us.)
 //
 // Work division, hand-over of parts and the lane mapping are those of lords_prefill.hip; so is a K tile of four stages
 // u = 0 .. 3.  The whole K range is one software pipeline, also across K tiles: under the 64 product MFMAs of a stage

@@ -2,9 +2,9 @@
 //
 // The large-M kernel (lords_prefill.hip) dequantises a tile's weights again for every 256 tokens.  That is the larger part
 // of what it does besides the product: on 16384 x 16384, 2048 tokens, a K tile of 256 x 256 takes 3.4 us, the same loop
-// without table reads, scales and roundings 2.0 us, and the chip runs at 1.85 GHz instead of 2.3, because the large-M kernel is
-// bound by the power that its work draws, not by latency or issue (a second form of it with half the LDS reads and
-// one wave per SIMD took the same time).  With enough tokens it is cheaper to write W out once as bf16 and to read it
+// without table reads, scales and roundings (a timing-only build) 2.0 us.  Its matrix pipes are busy for 52 % of its cycles, those
+// of pass 2 for 59 % (14336 x 4096, 2048 tokens, both at 2.0 to 2.2 GHz by the counters); a second form of it with half the LDS
+// reads and one wave per SIMD took the same time.  With enough tokens it is cheaper to write W out once as bf16 and to read it
 // back as MFMA operands:
 //
 //   pass 1  dequant_operand_kernel: codes, B, A -> W in scratch, in the order in which pass 2 wants it in its registers
@@ -46,7 +46,8 @@ constexpr int kOpCopies = 16;                                  // of the level t
 // A workgroup takes two neighbouring K tiles (waves 0, 1 and 2, 3: the code rows of both lie in the same cache lines) and
 // 2 per_wave slabs.  A wave keeps the A operands of its K tile in registers (up to rank 64; above they are read again
 // from LDS) and walks its slabs, the next one's codes requested before this one's are used.
-// Bound by the writes: 14336 x 4096 at rank 32, 117 MB, 28 to 31 us (4.0 TB/s).
+// Bound by the writes: 14336 x 4096 at rank 32, 117 MB, 28 to 31 us (4.0 TB/s); at padded contraction 128 by the conversion as
+// well (44 to 53 us), at six times 32 by the scale contraction (159).
 template <int BITS, int SS, bool F32>
 __global__ __launch_bounds__(256) void dequant_operand_kernel(OperandArgs a)
 {
@@ -632,13 +633,16 @@ double large_cost(const BatchedProblem &p)
 // Whether the weights are dequantised once, in a pass of their own, or for every tile of tokens again.  Decided by the
 // two planners' estimates, not by what has been allocated; the last twentieth is the margin.
 //   us, large-M kernel / two passes:   1024 tokens   2048          4096
-//   14336 x 4096 bf16 rank 32          115 / 128     230 / 227     430 / 416
-//                bf16 rank 48          169 / 125     307 / 227     620 / 413
-//                bf16 rank 100         228 / 148     424 / 239     849 / 422
-//                fp32 rank 16          190 / 138     337 / 232     697 / 426
-//                fp32 rank 64          812 / 253     1622 / 357    3246 / 555
-//   4096 x 4096  bf16 rank 48          63 / 77       92 / 82       180 / 114
-//   3000 x 2048  fp32 rank 64          110 / 72      199 / 86      392 / 92
+//   14336 x 4096 bf16 rank 32          120 / 122     231 / 223     455 / 427
+//                bf16 rank 48          133 / 125     253 / 230     513 / 437
+//                bf16 rank 100         241 / 137     434 / 232     878 / 445
+//                fp32 rank 16          194 / 130     361 / 233     706 / 445
+//                fp32 rank 64          814 / 248     1627 / 342    3249 / 572
+//   4096 x 14336 bf16 rank 48          147 / 216     248 / 286     428 / 399
+//   4096 x 4096  bf16 rank 48          63 / 76       93 / 97       136 / 117
+//   3000 x 2048  fp32 rank 64          109 / 73      199 / 86      394 / 90
+// A pair at rank 32 stays with the large-M kernel up to 4096 tokens (14336 rows, 2048 tokens: 506 against 437 us), because the
+// estimate of its two products leaves out that the gate is written and read.
 bool two_pass_faster(const BatchedProblem &p)
 {
     if (p.M <= 128 || !two_pass_supported(p)) return false;
