@@ -110,31 +110,52 @@ def bf16_from_bits(bits_u16, device="cuda"):
     return torch.from_numpy(a.view(np.int16).copy()).to(device).view(torch.bfloat16)
 
 
+# A call of the smallest layers takes the GPU about as long as the host needs to ask for it, so what every call does here is
+# kept to a few attribute look-ups: modules imported and functions found once, the current stream as a raw handle instead of
+# through a torch.cuda.Stream object (one token of 4096 x 4096, back to back: 8.6 us a call before, 6.5 now, which is what the
+# kernel takes; the host side of it 9.4 -> 6.4).
+_BF16 = _F32 = None                     # torch's dtypes, once torch is imported
+_device_of = _stream_of = None          # current device, its current stream as an int; once CUDA is initialised
+
+
 def _ptr(t):
     """Device pointer of a torch tensor (or a raw int / None passed through)."""
-    if t is None:
-        return None
-    if isinstance(t, int):
+    if t is None or isinstance(t, int):
         return t
     if not t.is_contiguous():
         raise ValueError("tensors handed to the library must be contiguous")
     return t.data_ptr()
 
 
+def _current_stream():
+    global _device_of, _stream_of
+    if _stream_of is not None:
+        return _stream_of(_device_of())
+    import torch
+    stream = torch.cuda.current_stream().cuda_stream           # (initialises CUDA where that has not been done)
+    raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+    if raw is not None and device is not None:
+        _device_of, _stream_of = device, raw
+    return stream
+
+
 def _stream(stream):
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        return _current_stream()
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
 
 
 def _dtype_code(t) -> int:
-    import torch
-    if t.dtype == torch.bfloat16:
+    global _BF16, _F32
+    if _BF16 is None:
+        import torch
+        _BF16, _F32 = torch.bfloat16, torch.float32
+    dtype = t.dtype
+    if dtype == _BF16:
         return LORDS_BF16
-    if t.dtype == torch.float32:
+    if dtype == _F32:
         return LORDS_F32
     raise TypeError(f"unsupported dtype {t.dtype}: the library takes bfloat16 or float32")
 
