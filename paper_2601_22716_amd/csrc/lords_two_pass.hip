@@ -621,12 +621,27 @@ double two_pass_cost(const BatchedProblem &p)
 
 // The large-M kernel's estimate reads high or low by the padded contraction (measured / estimated, the middle of 10 to 40
 // products each: bf16 factors 32 columns 1.0, 64 0.85, 128 0.82; fp32 factors 0.95, 0.92, 0.9, six times 32 1.15).
+constexpr double kGateMost = 64.0 * (1 << 30);
 double large_cost(const BatchedProblem &p)
 {
     const int ss = op_ss(p);
     const double scale = p.f32fact ? (ss == 1 ? 0.95 : ss == 2 ? 0.92 : ss == 4 ? 0.9 : 1.15) : (ss == 1 ? 1.0 : ss == 2 ? 0.85 : 0.82);
-    double us = 0;
-    for (int l = 0; l < p.L; ++l) us += prefill_fast_cost(matrix_of(p, l));
+    auto products = [&](int M) {
+        double us = 0;
+        for (int l = 0; l < p.L; ++l) {
+            MatmulProblem m = matrix_of(p, l);
+            m.M = M;
+            us += prefill_fast_cost(m);
+        }
+        return us;
+    };
+    // A pair: 2048 tokens at a time; the gate's fp32 sums go through memory (14336 rows, 2048 tokens, 235 MB in about 62 us).
+    // Not beyond kGateMost of them, which the large-M kernel's way has no memory for: such a pair is refused there, and stays so.
+    if (p.act && (double)std::min(p.M, 2048) * p.N[0] * 4.0 <= kGateMost) {
+        const int pieces = p.M / 2048, rest = p.M % 2048;
+        return scale * (pieces * products(2048) + (rest ? products(rest) : 0.0)) + (double)p.M * p.N[0] * 8.0 / 3.8e6;
+    }
+    const double us = products(p.M);
     return scale * (p.act || p.L == 1 ? us : std::min(us, prefill_batched_cost(p)));
 }
 
@@ -641,8 +656,11 @@ double large_cost(const BatchedProblem &p)
 //   4096 x 14336 bf16 rank 48          147 / 216     248 / 286     428 / 399
 //   4096 x 4096  bf16 rank 48          63 / 76       93 / 97       136 / 117
 //   3000 x 2048  fp32 rank 64          109 / 73      199 / 86      394 / 90
-// A pair at rank 32 stays with the large-M kernel up to 4096 tokens (14336 rows, 2048 tokens: 506 against 437 us), because the
-// estimate of its two products leaves out that the gate is written and read.
+// A pair (us, two products by the large-M kernel with the gate through memory / two passes; of 36 drawn pairs that go here
+// since the estimate counts the gate's way, 0.28 .. 0.87 of the time, none slower):
+//   14336 x 4096 bf16 rank 32          2048 tokens 507 / 445, 4096 1014 / 814
+//   4096 x 4096                        4096 tokens 370 / 215;  8192 x 2048, 2048 tokens 163 / 131;  28672 x 8192, 2048 1737 / 1581
+//   19771 x 1664, 2 bits, rank 26, 1217 tokens 259 / 209;  1264 x 416, fp32 rank 11, 3887 tokens 79 / 34
 bool two_pass_faster(const BatchedProblem &p)
 {
     if (p.M <= 128 || !two_pass_supported(p)) return false;

@@ -196,7 +196,8 @@ def test_two_pass_batched_in_groups(gpu):
         np.testing.assert_array_equal(o.cpu().numpy(), d.matmul(X=dev[0].X, M=M), err_msg=f"matrix {l}")
 
 
-@pytest.mark.parametrize("M,N,K,r,bits,fdt", [(3000, 2999, 544, 64, 4, "f32"), (3001, 2002, 1056, 99, 3, "bf16"), (1025, 20011, 4128, 128, 2, "bf16"), (2049, 2002, 1120, 64, 4, "bf16")])
+@pytest.mark.parametrize("M,N,K,r,bits,fdt", [(3000, 2999, 544, 64, 4, "f32"), (3001, 2002, 1056, 99, 3, "bf16"), (1025, 20011, 4128, 128, 2, "bf16"), (2049, 2002, 1120, 64, 4, "bf16"),
+                                                (2243, 617, 288, 21, 2, "bf16"), (2049, 1990, 416, 32, 3, "bf16"), (4100, 1031, 320, 7, 4, "bf16"), (2557, 2003, 1696, 9, 3, "f32")])
 def test_two_pass_gate_up(gpu, M, N, K, r, bits, fdt):
     """The pair against silu(gate) * up formed from the two single products, whose sums it has: fp32 silu and product, so
     a few units of 2^-24 and of the exponential's error, relative to the element."""

@@ -180,6 +180,16 @@ print(json.dumps([takes, gate_up(M, N, K, r, 4, True), launched()]))
     assert kernels == ["prefill"] * 4
 
 
+def test_a_pair_whose_gate_is_not_to_be_had_stays_refused(routes):
+    """Two passes need no gate in memory, but a pair that the large-M kernel's way has no memory for is not to be accepted for it."""
+    out = routes("""
+rt.double_largest_allocation(1 << 38)
+takes = [plan_util.takes_two_passes(2048, [n, n], 32, 8, 4, False, act=True, lib=plan) for n in (1 << 20, 1 << 26)]
+print(json.dumps([takes, gate_up(2048, 1 << 26, 32, 8, 4, False), launched()]))
+""")
+    assert out == [[True, False], 6, []]
+
+
 @pytest.mark.parametrize("Ns,rest,first", [
     ([2305, 1545, 5312, 658, 1443, 480], [143, 640, 5, 2, 1], False), ([3722, 2776, 4485, 354], [516, 864, 38, 4, 0], False),
     ([3129, 1837, 2122, 649], [647, 864, 18, 2, 1], False), ([2452, 1975], [2296, 704, 22, 3, 1], True)])
