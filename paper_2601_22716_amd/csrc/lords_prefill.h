@@ -1,4 +1,4 @@
-// What the two large-M kernels (lords_prefill.hip, lords_prefill_wide.hip) share: the arguments of a launch, code pairs.
+// What the two large-M kernels (lords_prefill_kernel.h, lords_prefill_wide.hip) share: the arguments of a launch, code pairs.
 #pragma once
 #include "lords_decode_common.h"
 
@@ -51,6 +51,17 @@ __device__ __forceinline__ uint32_t pair_index(const uint32_t (&w)[BITS], int p)
     return v & ((1u << (2 * BITS)) - 1u);
 }
 
+// Tile shape: padded contraction / 32, waves along the tokens and the rows, token blocks per wave.
+struct PfShape {
+    int ss, wm, wn, mb;
+    bool f32fact;
+};
+hipError_t launch_prefill_2bit(const PrefillArgsT<1> &a, const PfShape &d, dim3 grid, hipStream_t st);
+hipError_t launch_prefill_2bit(const PrefillArgsT<kMaxBatch> &a, const PfShape &d, dim3 grid, hipStream_t st);
+hipError_t launch_prefill_3bit(const PrefillArgsT<1> &a, const PfShape &d, dim3 grid, hipStream_t st);
+hipError_t launch_prefill_3bit(const PrefillArgsT<kMaxBatch> &a, const PfShape &d, dim3 grid, hipStream_t st);
+hipError_t launch_prefill_4bit(const PrefillArgsT<1> &a, const PfShape &d, dim3 grid, hipStream_t st);
+hipError_t launch_prefill_4bit(const PrefillArgsT<kMaxBatch> &a, const PfShape &d, dim3 grid, hipStream_t st);
 // The form of the kernel with one wave per SIMD: 256 x 256 tiles, bf16 factors of rank 33 .. 64 (lords_prefill_wide.hip).
 hipError_t launch_prefill_wide(const PrefillArgsT<1> &a, dim3 grid, int bits, hipStream_t st);
 hipError_t launch_prefill_wide(const PrefillArgsT<kMaxBatch> &a, dim3 grid, int bits, hipStream_t st);

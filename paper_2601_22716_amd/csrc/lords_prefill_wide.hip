@@ -1,11 +1,11 @@
-// The large-M kernel of lords_prefill.hip in the form for bf16 factors of rank 33 .. 64: 256 x 256 tiles, four waves of 64 rows x
+// The large-M kernel of lords_prefill_kernel.h in the form for bf16 factors of rank 33 .. 64: 256 x 256 tiles, four waves of 64 rows x
 // 256 tokens, one per SIMD.  At these ranks the scales cost two matrix instructions where rank 32 costs one, and
 // the eight waves of 128 registers for operands have room for 128 tokens only, so every weight was dequantised again for
 // every 128 tokens; a wave that has a SIMD and its 512 registers to itself holds the sums of 256 tokens in its 256 accumulation
 // registers and everything else in the other half.  (At ranks up to 32, where eight waves of 32 rows x 256 tokens do the
 // same work per weight, this form is no faster: 2048 x 14336 x 4096 227 against 230 us.)
 //
-// Work division, hand-over of parts and the lane mapping are those of lords_prefill.hip; so is a K tile of four stages
+// Work division, hand-over of parts and the lane mapping are those of lords_prefill_kernel.h; so is a K tile of four stages
 // u = 0 .. 3.  The whole K range is one software pipeline, also across K tiles: under the 64 product MFMAs of a stage
 // (16 token blocks x 4 slabs) ride the conversion of the next stage's weights (one pair per token block), the table reads
 // five blocks ahead of it, and the scale MFMAs of the stage after it.  Instructions follow an MFMA two by two at most, LDS and
@@ -77,7 +77,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     }
 
     // ---- tile loads.  Through buffer descriptors whose bounds end with the matrix: rows beyond it read as zeros.
-    // X tile: as in lords_prefill.hip.  Half h of an A tile holds the columns 32 gg + 16 h .. + 16 of each rank row (stages
+    // X tile: as in lords_prefill_kernel.h.  Half h of an A tile holds the columns 32 gg + 16 h .. + 16 of each rank row (stages
     // 2 h and 2 h + 1), 128 bytes: the 16-byte chunk 2 gg + uu in slot (2 gg + uu) ^ ((row >> 1) & 1), so that the rows of
     // a transposing read spread over the banks.
     constexpr int XJ = 16, AQ = 2;                             // loads of an X tile, of half an A tile, per wave
@@ -105,7 +105,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     auto shift_X = [&](int kt) __attribute__((always_inline)) -> uint32_t { return (uint32_t)min(2 * (K - 8 - xkcol - kt * 128), 0); };
     auto shift_A = [&](int kt, int h) __attribute__((always_inline)) -> uint32_t { return kt * 128 + acol + 16 * h < K ? 32u * (uint32_t)h : 0x80000000u; };
 
-    // Codes of K tile kt, slab rho, of the lane's row and group (layouts: lords_prefill.hip); rows beyond the matrix read as code 0,
+    // Codes of K tile kt, slab rho, of the lane's row and group (layouts: lords_prefill_kernel.h); rows beyond the matrix read as code 0,
     // groups beyond K as any code (their scales are zero).
     const uint32_t crho = a.tiled ? (uint32_t)a.ntiles_k * 64u * 4 * BITS : 16u * (uint32_t)a.row_bytes;     // a slab's codes
     const uint32_t cstep = a.tiled ? 64u * 4 * BITS : 4u * 4 * BITS;
@@ -298,7 +298,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     }
     asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");            // (results of the last matrix instructions)
 
-    // ---- epilogue: lane (c, g) holds token 16 mb + c, rows 16 rho + 4 g + {0..3}; hand-over as in lords_prefill.hip
+    // ---- epilogue: lane (c, g) holds token 16 mb + c, rows 16 rho + 4 g + {0..3}; hand-over as in lords_prefill_kernel.h
     constexpr int kPartFloats = R * MB * NT * 4;
     if (kt0 != 0) {
         float *dst = ly.part + (size_t)wg * kPartFloats + tid * 4;

@@ -1,6 +1,6 @@
 // Large products in two passes:  Y = X W^T  with  W = C[Q] (.) (B A)  dequantised once.
 //
-// The large-M kernel (lords_prefill.hip) dequantises a tile's weights again for every 256 tokens.  That is the larger part
+// The large-M kernel (lords_prefill_kernel.h) dequantises a tile's weights again for every 256 tokens.  That is the larger part
 // of what it does besides the product: on 16384 x 16384, 2048 tokens, a K tile of 256 x 256 takes 3.4 us, the same loop
 // without table reads, scales and roundings (a timing-only build) 2.0 us.  Its matrix pipes are busy for 52 % of its cycles, those
 // of pass 2 for 59 % (14336 x 4096, 2048 tokens, both at 2.0 to 2.2 GHz by the counters); a second form of it with half the LDS
@@ -140,7 +140,7 @@ __global__ __launch_bounds__(256) void dequant_operand_kernel(OperandArgs a)
 #pragma unroll
             for (int s = 0; s < SS; ++s) Aop[t][s] = read_Aop(s, t);
     }
-    // Codes of a lane (row n, group g of this K tile), see lords_prefill.hip; groups beyond K: the row's last one (their
+    // Codes of a lane (row n, group g of this K tile), see lords_prefill_kernel.h; groups beyond K: the row's last one (their
     // weights are zeros).
     auto load_codes = [&](int s, uint32_t (&w)[BITS]) __attribute__((always_inline)) {
         const int n = min(16 * s + c, N - 1);
@@ -311,7 +311,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     int T = first + ((int)blockIdx.x >> 3);
     if (T >= last) return;
 
-    // ---- staging of X (layout as in lords_prefill.hip)
+    // ---- staging of X (layout as in lords_prefill_kernel.h)
     constexpr int XJ = 16;
     const int xt0 = 4 * wave + ((lane >> 3) & 3);
     const int xv = (lane & 7) ^ (xt0 & 7);
