@@ -20,7 +20,8 @@ struct PfLayer {
     uint32_t *arrived;     // per output tile: parts handed over so far (zero before and after a launch)
     int N;
     int nt;                // tiles along N
-    int per;               // work units (one K tile of one output tile) per workgroup; units are numbered tile by tile
+    int per;               // work units (one K tile of one output tile) per workgroup, or per 2^meet; units are numbered tile by tile
+    int meet;              // 0, or 1 .. 3: each tile is cut into 2^meet parts, one workgroup each, that finish it together
     int x0, gx;            // first blockIdx.x of this matrix and how many it has (multiples of 8)
 };
 

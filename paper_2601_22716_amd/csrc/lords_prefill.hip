@@ -40,6 +40,7 @@ struct PfPlan {
     int ss, wm, R, wn, mb, nt, mt;
     int per, wgs;          // units per workgroup, workgroups that get any
     size_t part_bytes;     // 0: whole tiles
+    int meet;              // 0, or the parts of a tile that finish it together: 2, 4 or 8
     double cost;           // modelled time, us
 };
 
@@ -49,6 +50,13 @@ constexpr int kPfCUs = 256;
 // columns) for which the planner took the latter, they took 0.84 of the former's time in the middle, up to 0.96 for nine in ten, and
 // longer for four, 1.04 and 1.07 at worst, those with one and two K tiles.
 constexpr double kWideScale = 1.22;
+
+// Whether every tile may be cut into `parts` that meet (see PfLayer::meet): one workgroup per CU at most.  (Not in
+// lords_prefill_wide.hip, where it made no difference: two parts of 28672 x 8192, 2 bits, rank 64, 256 tokens 140 us either way.)
+static bool pf_may_meet(long tiles, int parts, int ntiles_k, int R, int mb)
+{
+    return R != 4 && parts <= (mb < 8 ? 4 : 8) && ntiles_k >= 2 * parts && tiles * parts <= kPfCUs;
+}
 
 static PfPlan pf_plan(const MatmulProblem &p, size_t avail, bool wide = true)
 {
@@ -76,7 +84,7 @@ static PfPlan pf_plan(const MatmulProblem &p, size_t avail, bool wide = true)
     const Cand *cands = d.ss == 1 ? small_rank : d.ss == 6 ? six : large_rank;
     const int ncands = d.ss == 1 ? 4 : d.ss == 6 ? 1 : d.ss == 2 && !p.f32fact && p.M > 128 && wide ? 3 : 2;
     double best = 1e30;
-    d.wm = 1; d.R = 2; d.wn = 4; d.mb = d.ss == 6 ? 4 : 8; d.per = ntiles_k; d.part_bytes = 0;
+    d.wm = 1; d.R = 2; d.wn = 4; d.mb = d.ss == 6 ? 4 : 8; d.per = ntiles_k; d.part_bytes = 0; d.meet = 0;
     for (int i = 0; i < ncands; ++i) {
         const Cand &c = cands[i];
         const int tokens = 16 * c.mb * c.wm, rows = 16 * c.R * c.wn;
@@ -88,7 +96,7 @@ static PfPlan pf_plan(const MatmulProblem &p, size_t avail, bool wide = true)
         // whole tiles, dealt by the hardware in rounds
         {
             const double cost = (double)((tiles + kPfCUs - 1) / kPfCUs) * ntiles_k * c.t * (c.R == 4 ? kWideScale : 1.0);
-            if (cost < best) { best = cost; d.wm = c.wm; d.R = c.R; d.wn = c.wn; d.mb = c.mb; d.per = ntiles_k; d.part_bytes = 0; }
+            if (cost < best) { best = cost; d.wm = c.wm; d.R = c.R; d.wn = c.wn; d.mb = c.mb; d.per = ntiles_k; d.part_bytes = 0; d.meet = 0; }
         }
         // equal runs of units over `wgs` workgroups.  Its price is the hand-over of the parts: measured
         // 4 us + 1 us per 1.2 MB of parts written when the runs are shorter than a tile (every part is
@@ -97,11 +105,11 @@ static PfPlan pf_plan(const MatmulProblem &p, size_t avail, bool wide = true)
         // dealt in rounds do.
         if (tiles * sizeof(uint32_t) > kZeroBytes || units > (1L << 30)) continue;
         static const int kWgs[] = {256, 224, 192, 160, 128, 112, 96, 80, 64, 48, 32, 16, 8};
-        for (int wgs : kWgs) {
+        auto consider = [&](int wgs) {
             const int per = (int)((units + wgs - 1) / wgs);
-            if (per < 2 || (per % ntiles_k) == 0) continue;                      // (the second: whole tiles again)
+            if (per < 2 || (per % ntiles_k) == 0) return;                        // (the second: whole tiles again)
             const size_t bytes = (size_t)wgs * tile_bytes;
-            if (bytes > avail) continue;
+            if (bytes > avail) return;
             // parts that start inside a tile: run boundaries but those that fall on one between tiles
             const long bounds = (units - 1) / per, written = bounds - bounds / (ntiles_k / std::gcd(per, ntiles_k));
             const double full = p.M <= 64 && tokens == 128 ? 0.5 : 1.0;          // (half a tile travels)
@@ -110,14 +118,25 @@ static PfPlan pf_plan(const MatmulProblem &p, size_t avail, bool wide = true)
             const double cost = c.R == 4 ? kWideScale * (per >= ntiles_k ? per * c.t * 1.08 + 25.0 : per * c.t + 20.0 + 7.0 * (ntiles_k % per ? others : ntiles_k / per - 1))
                               : per >= ntiles_k ? per * c.t * 1.08 + 4.0 + mb_written / 2.4
                                                 : per * c.t + 4.0 + mb_written / 1.2;
-            if (cost < best) { best = cost; d.wm = c.wm; d.R = c.R; d.wn = c.wn; d.mb = c.mb; d.per = per; d.part_bytes = bytes; }
+            if (cost < best) { best = cost; d.wm = c.wm; d.R = c.R; d.wn = c.wn; d.mb = c.mb; d.per = per; d.part_bytes = bytes; d.meet = 0; }
+        };
+        for (int wgs : kWgs) consider(wgs);
+        // Two, four or eight parts of every tile, which their workgroups finish together: 7 us + 1 us per 2.4 MB, of blocks with
+        // tokens in them.
+        const double live_mb = (double)((p.M + 15) / 16 * 16) * ((p.N + 15) / 16 * 16) * sizeof(float) / 1048576.0;
+        for (int parts : {2, 4, 8}) {
+            const size_t bytes = (size_t)tiles * parts * tile_bytes;
+            if (!pf_may_meet(tiles, parts, ntiles_k, c.R, c.mb) || bytes > avail) continue;
+            const int per = (ntiles_k + parts - 1) / parts;
+            const double cost = per * c.t + 7.0 + (parts - 1) * live_mb / 2.4;
+            if (cost < best) { best = cost; d.wm = c.wm; d.R = c.R; d.wn = c.wn; d.mb = c.mb; d.per = per; d.part_bytes = bytes; d.meet = parts; }
         }
     }
     const int tokens = 16 * d.mb * d.wm, rows = 16 * d.R * d.wn;
     d.nt = (p.N + rows - 1) / rows;
     d.mt = (p.M + tokens - 1) / tokens;
     const long units = (long)d.nt * d.mt * ntiles_k;
-    d.wgs = (int)((units + d.per - 1) / d.per);
+    d.wgs = d.meet ? d.nt * d.mt * d.meet : (int)((units + d.per - 1) / d.per);
     d.cost = best;
     return d;
 }
@@ -170,9 +189,11 @@ static void pf_layer(PfLayer &ly, const MatmulProblem &p, const PfPlan &d, void 
     ly.arrived = (uint32_t *)arrived;
     ly.N = p.N;
     ly.nt = d.nt;
-    ly.per = d.per;
+    ly.per = d.meet ? (p.K + 127) / 128 : d.per;
     ly.x0 = x0;
-    ly.gx = (d.wgs + 7) / 8 * 8;
+    ly.meet = d.meet == 8 ? 3 : d.meet / 2;
+    const int at_once = 8 * (d.meet ? d.meet : 1);             // (the workgroups of a tile on one XCD)
+    ly.gx = (d.wgs + at_once - 1) / at_once * at_once;
 }
 
 // `part`: part_bytes bytes of scratch (what prefill_fast_workspace_bytes returned for a limit of at most

@@ -72,7 +72,10 @@ __device__ __forceinline__ void lds_direct_16(const void *gbase, uint32_t goff, 
 // 14336 x 4096, rank 40, 17 tokens 69 (602).
 // MULTI: several matrices in the launch (a lone one is read from fixed offsets of a short argument block: through an
 // index it cost 0.3 us a call).
-template <int BITS, int SS, int WM, int R, int WN = 4, int MB = 8, bool F32 = false, bool MULTI = false>
+// FORM: of a lone matrix, parts that meet (kMeet) or any other cut of the work (kRuns), a kernel each: in one, the code of the
+// former cost the latter up to 2.5 % (333 tokens of 11008 x 4096, 3 bits, rank 48 61.5 -> 62.3 us).  kEither: several matrices.
+enum PfForm { kRuns, kMeet, kEither };
+template <int BITS, int SS, int WM, int R, int WN = 4, int MB = 8, bool F32 = false, bool MULTI = false, PfForm FORM = kRuns>
 __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(WN * WM / 4, WN * WM / 4))) void prefill_kernel(PrefillArgsT<MULTI ? kMaxBatch : 1> a)
 {
     constexpr int BN = 16 * R * WN, BM = 16 * MB * WM, NT = 64 * WN * WM, RP = 32 * SS, NL = 1 << BITS, NE = 1 << (2 * BITS);
@@ -100,8 +103,10 @@ __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(WN
     const int total_units = ly.nt * a.mt * a.ntiles_k;
     const int bx = (int)blockIdx.x - ly.x0;
     const int wg = (bx & 7) * (ly.gx >> 3) + (bx >> 3);
-    int unit = wg * ly.per;
-    const int unit_end = min(unit + ly.per, total_units);
+    // Parts that meet (see the epilogue): 2^meet workgroups share the `per` units of a tile, a unit more or less each.
+    const int meet_log = FORM == kRuns ? 0 : ly.meet, meet_part = wg & ((1 << meet_log) - 1);
+    const int unit0 = (wg >> meet_log) * ly.per, unit_end = min(unit0 + ((meet_part + 1) * ly.per >> meet_log), total_units);
+    int unit = unit0 + (meet_part * ly.per >> meet_log);
     if (unit >= unit_end) return;
     const int wn = wave % WN, wm = wave / WN;
     const uint16_t *A16 = reinterpret_cast<const uint16_t *>(ly.A), *B16 = reinterpret_cast<const uint16_t *>(ly.B);   // (bf16 factors)
@@ -532,6 +537,133 @@ __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(WN
     // (Exactly the blocks in use, with a branch for each, was no faster there and cost 2-9 % at 100 and 128 tokens; in
     // 256-token tiles the second form cost registers: 10 % at 2048 tokens.)
     constexpr int kPartFloats = R * MB * NT * 4;
+    void *Yp = ly.Y;
+    auto store_at = [&](int m, int n, f32x4 v) __attribute__((always_inline)) {          // rows n .. n + 3 of token m
+        if (m >= M) return;
+        if (n + 3 < N) {
+            store_out4(Yp, (size_t)m * N + n, v, a.y_f32);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if (n + e >= N) continue;
+                if (a.y_f32) reinterpret_cast<float *>(Yp)[(size_t)m * N + n + e] = v[e];
+                else reinterpret_cast<uint16_t *>(Yp)[(size_t)m * N + n + e] = bf16_bits(v[e]);
+            }
+        }
+    };
+    auto store_block = [&](int rho, int mb, f32x4 v) __attribute__((always_inline)) { store_at(m_wave + 16 * mb + c, n_wave + 16 * rho + 4 * g, v); };
+    // A tile that G workgroups share in equal parts, one each: every one of them finishes a slice of MB / G token blocks.  It
+    // writes the other slices for their owners, counts itself in, waits for the others and adds what they have written of its
+    // own, in column order (the sums are those of the form below).  All CUs then write, read and store Y, 1 / G of a tile each,
+    // and only blocks with tokens in them travel.  us, before (one of them collected the tile) / this, 4 bits, rank 32 where
+    // nothing else is said:
+    //   4096 x 4096    32 tokens 24.2 / 18.9, 128 28.7 / 21.7, 300 39.6 / 33.9, 512 40.3 / 34.2, 2048 82.7 / 75.5; 500 tokens,
+    //                  rank 48 42.5 / 36.6, fp32 rank 16 51.0 / 46.9
+    //   1024 x 4096    300 tokens 31.4 / 19.9, 2048 40.2 / 34.4;   4096 x 14336 512 85.8 / 78.4, 2048 213.5 / 207.9
+    // Nothing waits for what may never start: the workgroups of a tile are neighbours in the order of dispatch (blockIdx.x in
+    // steps of 8), so that whatever else runs, only the last few of a launch's running workgroups, at most 8 (G - 1), wait for
+    // one that has no CU yet, and the others end and make room.  The counter goes through 2 G values back to zero: each counts in
+    // once before it waits and once after.
+    // Parts and counter are agent-scope accesses (sc1: they pass the XCD's L2 by), the part's stores have been acknowledged by
+    // all waves before the count, and nothing else is handed over, so neither a write-back nor an invalidation of an L2 is
+    // wanted: with a release and an acquire at agent scope around the count, G of each per tile, 3 to 7 us more.
+    if constexpr (FORM != kRuns) if (FORM == kMeet || __builtin_expect(ly.meet != 0, 0)) {       // (behind the other form in the code)
+        // (what this wants of its thread is worked out again: registers of the K loop)
+        int t_out = tid;
+        asm volatile("" : "+v"(t_out));
+        const int c_out = t_out & 15, g_out = (t_out >> 4) & 3, w_out = __builtin_amdgcn_readfirstlane(t_out >> 6);
+        const int n_out = n_blk + 16 * R * (w_out % WN), m_out = m_blk + 16 * MB * (w_out / WN);
+        // (... and of its workgroup: 150 to 200 instructions that the compiler would otherwise place in front of the first part,
+        // 0.5 us of every launch)
+        int own = meet_part, wg_first = wg - own, tokens = M;
+        uint64_t part_base = (uint64_t)(uintptr_t)ly.part;
+        uint32_t *counter = ly.arrived;
+        asm volatile("" : "+s"(own), "+s"(wg_first), "+s"(tokens), "+s"(part_base), "+s"(counter));
+        float *const parts_of_tile = (float *)(uintptr_t)part_base + (size_t)wg_first * kPartFloats;
+        counter += T;
+        auto meet = [&](auto parts) __attribute__((always_inline)) {
+            constexpr int G = decltype(parts)::value, MS = MB / G;
+            float *dst = parts_of_tile + own * kPartFloats + t_out * 4;
+            asm volatile("" : "+v"(dst));        // (addresses are made here, not kept in registers over the K loop)
+#pragma unroll
+            for (int s = 0; s < G; ++s) {
+                if (s == own || m_out + 16 * s * MS >= tokens) continue;       // (tokens beyond M do not travel)
+#pragma unroll
+                for (int q = 0; q < MS; ++q) {
+#pragma unroll
+                    for (int rho = 0; rho < R; ++rho) store16_agent(dst + (rho * MB + s * MS + q) * (NT * 4), acc[rho][s * MS + q]);
+                    asm volatile("" : "+v"(dst));                       // (addresses one by one: registers)
+                }
+            }
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+            if (t_out == 0) {
+                __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                int spins = 0;
+                while (__hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < (uint32_t)G && ++spins < (1 << 21))
+                    __builtin_amdgcn_s_sleep(2);
+                atomicInc(counter, 2 * G - 1);
+            }
+            __syncthreads();
+            if (m_out + 16 * own * MS >= tokens) return;
+            // (accumulators are only read, where they are: blocks per round trip by the registers beside them)
+            constexpr int TB = std::min(MS * R, G == 2 ? 16 : G == 4 ? 4 : 2);
+#pragma unroll
+            for (int b0 = 0; b0 < MS * R; b0 += TB) {
+                f32x4 t[G - 1][TB];
+#pragma unroll
+                for (int i = 0; i < G - 1; ++i) {
+                    const float *src = parts_of_tile + (i + (i >= own)) * kPartFloats + own * (MS * NT * 4) + t_out * 4;
+                    asm volatile("" : "+v"(src));
+#pragma unroll
+                    for (int b = 0; b < TB; ++b) {
+                        t[i][b] = load16_agent(src + ((b0 + b) % R * MB + (b0 + b) / R) * (NT * 4));
+                        asm volatile("" : "+v"(src));
+                    }
+                }
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#pragma unroll
+                for (int i = 0; i < G - 1; ++i)
+#pragma unroll
+                    for (int b = 0; b < TB; ++b) asm volatile("" : "+v"(t[i][b]));       // (not before the wait)
+#pragma unroll
+                for (int s = 0; s < G; ++s) {
+                    if (s != own) continue;
+                    asm volatile("" ::: "memory");          // (a branch, not a choice between slices: registers)
+#pragma unroll
+                    for (int b = 0; b < TB; ++b) {
+                        const f32x4 mine = acc[(b0 + b) % R][s * MS + (b0 + b) / R];
+                        f32x4 v = s == 0 ? mine : t[0][b];
+#pragma unroll
+                        for (int i = 1; i < G; ++i) {
+                            const f32x4 next = i < s ? t[i < G - 1 ? i : 0][b] : i == s ? mine : t[i - 1][b];
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) v[e] += next[e];
+                        }
+                        asm volatile("" : "+v"(v));
+                        t[0][b] = v;
+                    }
+                }
+#pragma unroll
+                for (int b = 0; b < TB; ++b) {
+                    int m = m_out + 16 * (own * MS + (b0 + b) / R) + c_out, n = n_out + 16 * ((b0 + b) % R) + 4 * g_out;
+                    asm volatile("" : "+v"(m), "+v"(n));
+                    if (ly.gate) {
+                        const f32x4_any ga = *reinterpret_cast<const f32x4_any *>(ly.gate + (size_t)min(m, tokens - 1) * N + min(n, N - 1));
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) t[0][b][e] = ga[e] / (1.0f + __expf(-ga[e])) * t[0][b][e];
+                    }
+                    store_at(m, n, t[0][b]);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        if (ly.meet == 1) meet(std::integral_constant<int, 2>{});
+        else if (MB < 8 || ly.meet == 2) meet(std::integral_constant<int, 4>{});
+        else meet(std::integral_constant<int, MB < 8 ? 4 : 8>{});
+        return;
+    }
+    if constexpr (FORM != kMeet) {
     const bool few = MB == 8 && M - m_wave <= 64;
     if (kt0 != 0) {
         float *dst = ly.part + (size_t)wg * kPartFloats + tid * 4;
@@ -592,21 +724,6 @@ __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(WN
             add_parts(std::integral_constant<int, 2>{}, std::integral_constant<int, MB < 8 ? MB : 8>{});
         }
     }
-    void *Yp = ly.Y;
-    auto store_block = [&](int rho, int mb, f32x4 v) __attribute__((always_inline)) {
-        const int m = m_wave + 16 * mb + c, n = n_wave + 16 * rho + 4 * g;
-        if (m >= M) return;
-        if (n + 3 < N) {
-            store_out4(Yp, (size_t)m * N + n, v, a.y_f32);
-        } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                if (n + e >= N) continue;
-                if (a.y_f32) reinterpret_cast<float *>(Yp)[(size_t)m * N + n + e] = v[e];
-                else reinterpret_cast<uint16_t *>(Yp)[(size_t)m * N + n + e] = bf16_bits(v[e]);
-            }
-        }
-    };
     if (ly.gate) {
         // A gate/up pair: this is the up product, the gate's fp32 sums lie in memory.  Loads of eight token blocks in
         // flight; addresses are clamped to the matrix's rows, a load of its last columns may reach 12 bytes beyond
@@ -638,19 +755,22 @@ __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(WN
 #pragma unroll
             for (int rho = 0; rho < R; ++rho) store_block(rho, mb, acc[rho][mb]);
     }
+    }
     }   // parts of this workgroup
 }
 
-template <int BITS, int SS, int WM, int R, int WN, int MB, bool F32, bool MULTI>
+template <int BITS, int SS, int WM, int R, int WN, int MB, bool F32, bool MULTI, PfForm FORM = MULTI ? kEither : kRuns>
 static hipError_t launch_pf_t(const PrefillArgsT<MULTI ? kMaxBatch : 1> &a, dim3 grid, hipStream_t st)
 {
+    if constexpr (FORM == kRuns)
+        if (a.layer[0].meet) return launch_pf_t<BITS, SS, WM, R, WN, MB, F32, MULTI, kMeet>(a, grid, st);
     const size_t smem = (size_t)2 * (16 * MB * WM) * 256 + (size_t)2 * (32 * SS) * 256 + (size_t)(1 << (2 * BITS)) * kPfCopies * pf_pair_bytes(F32);
     static LdsOptIn lds_opt_in;
     {
-        const hipError_t e = allow_dynamic_lds(lds_opt_in, reinterpret_cast<const void *>(&prefill_kernel<BITS, SS, WM, R, WN, MB, F32, MULTI>), smem);
+        const hipError_t e = allow_dynamic_lds(lds_opt_in, reinterpret_cast<const void *>(&prefill_kernel<BITS, SS, WM, R, WN, MB, F32, MULTI, FORM>), smem);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((prefill_kernel<BITS, SS, WM, R, WN, MB, F32, MULTI>), grid, dim3(64 * WN * WM), smem, st, a);
+    hipLaunchKernelGGL((prefill_kernel<BITS, SS, WM, R, WN, MB, F32, MULTI, FORM>), grid, dim3(64 * WN * WM), smem, st, a);
     return hipGetLastError();
 }
 

@@ -1,0 +1,60 @@
+"""Products of many tokens whose tiles are cut into two, four or eight parts that several workgroups finish together, through
+the C ABI: against the fp64 oracle, and run to run bit for bit.  Gates as for lords_matmul.
+
+Sizes: every number of parts and tile shape, K tiles that the parts do not divide (a unit more or less each), ragged last K
+tiles, token counts at which the last slices of a tile have no tokens (17, 33, 65, 129 ...), rows off the tiles.
+"""
+import sys
+
+import numpy as np
+import pytest
+
+import lords_inputs as li
+from oracle import lords_oracle as onp
+
+pytestmark = pytest.mark.gpu
+
+Y_TOL, Y_MAX_TOL = 5e-3, 2e-2
+
+
+@pytest.fixture(scope="module")
+def gpu():
+    import torch
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    from tests import gpu_util
+    return gpu_util
+
+
+@pytest.mark.parametrize("M,N,K,r,bits,fdt", [
+    (17, 4096, 4096, 32, 4, "bf16"), (33, 1000, 4000, 7, 3, "bf16"), (65, 4099, 3104, 32, 2, "bf16"), (128, 4096, 4096, 20, 4, "bf16"),
+    (129, 1003, 2016, 10, 3, "bf16"), (300, 1024, 4096, 32, 4, "bf16"), (445, 1882, 2016, 10, 4, "bf16"), (1795, 1765, 2176, 10, 2, "bf16"),
+    (2048, 1021, 1120, 31, 4, "bf16"), (100, 1999, 2592, 48, 3, "bf16"), (500, 4096, 1056, 48, 4, "bf16"), (237, 3699, 1568, 87, 4, "bf16"),
+    (3, 2000, 4096, 100, 2, "bf16"), (100, 4096, 4096, 10, 4, "f32"), (705, 2284, 2624, 7, 2, "f32"), (86, 3869, 2304, 64, 4, "f32"),
+    (500, 4096, 1056, 16, 3, "f32"), (250, 16000, 4128, 60, 2, "bf16")])
+def test_parts_that_meet(gpu, M, N, K, r, bits, fdt):
+    print(f"parts that meet M={M} N={N} K={K} r={r} bits={bits} factors={fdt}", flush=True)
+    sys.stdout.flush()
+    c = li.make_case("tiny", M=M, N=N, K=K, r=r, bits=bits, factor_dtype=fdt, seed=81, signed_factors=True)
+    d = gpu.DeviceCase(c)
+    Y = d.matmul()
+    rows = np.unique(np.r_[np.random.default_rng(1).integers(0, N, 24), 0, N - 1])
+    want = onp.matmul_rows(c.X_f32, c.codes, c.codebook, c.B_f32, c.A_f32, bits, rows)
+    assert np.isfinite(Y).all()
+    rf, mx = onp.rel_fro(Y[:, rows], want), onp.max_abs_over_rms(Y[:, rows], want)
+    assert rf <= Y_TOL and mx <= Y_MAX_TOL, (rf, mx)
+    for _ in range(3):
+        np.testing.assert_array_equal(d.matmul(), Y)
+
+
+def test_parts_that_meet_in_one_launch_of_several_matrices(gpu):
+    """... and each matrix of a batched call has the bits of its single call."""
+    import torch
+    import paper_2601_22716_amd as L
+    M, K, r, bits, Ns = 300, 4000, 32, 4, [4096, 1024, 1000]
+    dev = [gpu.DeviceCase(li.make_case("tiny", M=M, N=N, K=K, bits=bits, r=r, factor_dtype="bf16", seed=85 + i)) for i, N in enumerate(Ns)]
+    want = [d.matmul(X=dev[0].X, M=M) for d in dev]
+    Ys = [torch.full((M, N), float("nan"), device="cuda") for N in Ns]
+    L.lords_matmul_batched(dev[0].X, [d.codes for d in dev], dev[0].codebook, [d.B for d in dev], [d.A for d in dev], Ys, Ns, M, K, r, bits)
+    torch.cuda.synchronize()
+    for Y, w in zip(Ys, want):
+        np.testing.assert_array_equal(Y.cpu().numpy(), w)
