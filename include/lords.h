@@ -275,7 +275,8 @@ int lords_matmul_batched(const void *X, const void *const *codes, const float *c
  *      silu(g) = g / (1 + exp(-g)).
  * G and U are summed in fp32 and never rounded or written out on their own; the product is formed in
  * fp32 and rounded once to `h_dtype`.  With M <= 16 (bf16 factors, rank <= 64) this is one launch; larger
- * M writes the gate's product of at most 2048 tokens at a time to an fp32 workspace and combines it with the up
+ * M goes in two passes, where that is faster, with both products in registers (see Workspace above), or
+ * writes the gate's product of at most 2048 tokens at a time to an fp32 workspace and combines it with the up
  * product where that is stored (ranks beyond the large-M kernel: 1024 tokens of both, combined in one pass); the
  * last few tokens of a call may be served as a call of that many tokens would be.
  *   H   out  M x N

@@ -121,14 +121,14 @@ static PfPlan pf_plan(const MatmulProblem &p, size_t avail, bool wide = true)
             if (cost < best) { best = cost; d.wm = c.wm; d.R = c.R; d.wn = c.wn; d.mb = c.mb; d.per = per; d.part_bytes = bytes; d.meet = 0; }
         };
         for (int wgs : kWgs) consider(wgs);
-        // Two, four or eight parts of every tile, which their workgroups finish together: 7 us + 1 us per 2.4 MB, of blocks with
+        // Two, four or eight parts of every tile, which their workgroups finish together: 7 us + 1 us per 3 MB, of blocks with
         // tokens in them.
         const double live_mb = (double)((p.M + 15) / 16 * 16) * ((p.N + 15) / 16 * 16) * sizeof(float) / 1048576.0;
         for (int parts : {2, 4, 8}) {
             const size_t bytes = (size_t)tiles * parts * tile_bytes;
             if (!pf_may_meet(tiles, parts, ntiles_k, c.R, c.mb) || bytes > avail) continue;
             const int per = (ntiles_k + parts - 1) / parts;
-            const double cost = per * c.t + 7.0 + (parts - 1) * live_mb / 2.4;
+            const double cost = per * c.t + 7.0 + (parts - 1) * live_mb / 3.0;
             if (cost < best) { best = cost; d.wm = c.wm; d.R = c.R; d.wn = c.wn; d.mb = c.mb; d.per = per; d.part_bytes = bytes; d.meet = parts; }
         }
     }

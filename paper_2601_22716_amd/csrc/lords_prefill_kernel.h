@@ -557,9 +557,9 @@ __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(WN
     // own, in column order (the sums are those of the form below).  All CUs then write, read and store Y, 1 / G of a tile each,
     // and only blocks with tokens in them travel.  us, before (one of them collected the tile) / this, 4 bits, rank 32 where
     // nothing else is said:
-    //   4096 x 4096    32 tokens 24.2 / 18.9, 128 28.7 / 21.7, 300 39.6 / 33.9, 512 40.3 / 34.2, 2048 82.7 / 75.5; 500 tokens,
-    //                  rank 48 42.5 / 36.6, fp32 rank 16 51.0 / 46.9
-    //   1024 x 4096    300 tokens 31.4 / 19.9, 2048 40.2 / 34.4;   4096 x 14336 512 85.8 / 78.4, 2048 213.5 / 207.9
+    //   4096 x 4096    32 tokens 24.3 / 18.0, 64 23.9 / 18.6, 128 29.0 / 20.3, 300 37.2 / 31.4, 512 39.5 / 33.2, 2048 80.8 / 74.2;
+    //                  500 tokens, rank 48 41.8 / 35.9, fp32 rank 16 49.9 / 44.7
+    //   1024 x 4096    300 tokens 31.4 / 19.4, 2048 39.8 / 33.9;   4096 x 14336 512 83.4 / 75.8, 2048 210.6 / 207.0
     // Nothing waits for what may never start: the workgroups of a tile are neighbours in the order of dispatch (blockIdx.x in
     // steps of 8), so that whatever else runs, only the last few of a launch's running workgroups, at most 8 (G - 1), wait for
     // one that has no CU yet, and the others end and make room.  The counter goes through 2 G values back to zero: each counts in
