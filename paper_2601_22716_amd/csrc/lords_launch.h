@@ -135,19 +135,26 @@ size_t prefill_fast_workspace_bytes(const MatmulProblem &p, size_t limit);
 // The least that a caller's workspace must have: what the kernel asks for without its 256-token tiles at ranks 33 .. 64, whose
 // parts are twice as large.  Between this and the figure above, the plan is made for what there is.
 size_t prefill_least_workspace_bytes(const MatmulProblem &p);
+// Its tiles, and into how many parts that meet each is cut (0: whole tiles, or runs of any length).
+struct PrefillCut { int tokens, rows, meet; };
+PrefillCut prefill_cut(const MatmulProblem &p, size_t limit);
 // Whether it runs as the form with one wave per SIMD (lords_prefill_wide.hip).
 bool prefill_wide_taken(const MatmulProblem &p, size_t limit);
 // The planner's estimate of the launch, in us, with all the scratch it asks for.
 double prefill_fast_cost(const MatmulProblem &p);
 // `gate`: null, or M x N fp32 sums of a gate matrix and 12 readable bytes behind them; Y then receives silu(gate) * (the product).
-hipError_t launch_prefill_fast(const MatmulProblem &p, void *part, size_t part_bytes, void *zeroed, hipStream_t st, const float *gate = nullptr);
+// `polls`: how often a workgroup looks for the parts of others that it is to finish its share of a tile with (0.6 us each); it
+// then leaves the share to another.  The time of a launch depends on it, the result does not.
+constexpr int kMeetPolls = 64;
+hipError_t launch_prefill_fast(const MatmulProblem &p, void *part, size_t part_bytes, void *zeroed, hipStream_t st, const float *gate = nullptr,
+                               int polls = kMeetPolls);
 // The same for several matrices that read the same X, each summed as it would be alone: `part` holds
 // prefill_batched_workspace_bytes(p) bytes.
 bool prefill_batched_supported(const BatchedProblem &p);
 size_t prefill_batched_workspace_bytes(const BatchedProblem &p);
 // The planner's estimate of that launch, in us (what one matrix leaves idle of the chip is the next one's).
 double prefill_batched_cost(const BatchedProblem &p);
-hipError_t launch_prefill_batched(const BatchedProblem &p, void *part, void *zeroed, hipStream_t st);
+hipError_t launch_prefill_batched(const BatchedProblem &p, void *part, void *zeroed, hipStream_t st, int polls = kMeetPolls);
 // Many tokens: W dequantised once into scratch, then a product that reads it (lords_two_pass.hip); one matrix, several that
 // read the same X, or (act) a gate/up pair.  Scratch: two_pass_workspace_bytes, at most kTwoPassBytes.
 constexpr size_t kTwoPassBytes = (size_t)128 << 20;

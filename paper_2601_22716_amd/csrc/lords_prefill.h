@@ -17,7 +17,7 @@ struct PfLayer {
     void *Y;
     const float *gate;     // M x N fp32 or null: Y = silu(gate) * (the product) instead of the product
     float *part;           // per workgroup: the accumulators of a part that does not start at the tile's first column
-    uint32_t *arrived;     // per output tile: parts handed over so far (zero before and after a launch)
+    uint32_t *arrived;     // per output tile: parts handed over so far, or lords_meet.h's count (zero before and after a launch)
     int N;
     int nt;                // tiles along N
     int per;               // work units (one K tile of one output tile) per workgroup, or per 2^meet; units are numbered tile by tile
@@ -38,6 +38,7 @@ struct PrefillArgsT {
     int ntiles_k;          // ceil(K / 128)
     int tiled;             // codes in the slab-tile layout: tile (slab, K tile) contiguous, chunk = 16 g + c
     int L;                 // matrices
+    int polls;             // how often a workgroup of a tile that meets looks for the others' parts before it leaves
     PfLayer layer[NLAYERS];
 };
 

@@ -151,6 +151,12 @@ size_t prefill_least_workspace_bytes(const MatmulProblem &p)
     return std::min(pf_plan(p, ~(size_t)0).part_bytes, pf_plan(p, ~(size_t)0, false).part_bytes);
 }
 
+PrefillCut prefill_cut(const MatmulProblem &p, size_t limit)
+{
+    const PfPlan d = pf_plan(p, limit);
+    return PrefillCut{16 * d.mb * d.wm, 16 * d.R * d.wn, d.meet};
+}
+
 bool prefill_wide_taken(const MatmulProblem &p, size_t limit) { return pf_plan(p, limit).R == 4; }
 
 double prefill_fast_cost(const MatmulProblem &p) { return pf_plan(p, ~(size_t)0).cost; }
@@ -166,7 +172,7 @@ static hipError_t launch_pf(const PrefillArgsT<MULTI ? kMaxBatch : 1> &a, const 
 }
 
 template <class Args>
-static void pf_common(Args &a, const MatmulProblem &p, const PfPlan &d)
+static void pf_common(Args &a, const MatmulProblem &p, const PfPlan &d, int polls)
 {
     a.X = (const uint16_t *)p.X;
     a.codebook = p.codebook;
@@ -176,6 +182,7 @@ static void pf_common(Args &a, const MatmulProblem &p, const PfPlan &d)
     a.mt = d.mt;
     a.ntiles_k = (p.K + 127) / 128;
     a.tiled = p.tiled ? 1 : 0;
+    a.polls = polls;
 }
 
 static void pf_layer(PfLayer &ly, const MatmulProblem &p, const PfPlan &d, void *part, void *arrived, int x0)
@@ -198,11 +205,11 @@ static void pf_layer(PfLayer &ly, const MatmulProblem &p, const PfPlan &d, void 
 
 // `part`: part_bytes bytes of scratch (what prefill_fast_workspace_bytes returned for a limit of at most
 // part_bytes), `zeroed`: kZeroBytes of device memory, zero when handed over and left at zero.
-hipError_t launch_prefill_fast(const MatmulProblem &p, void *part, size_t part_bytes, void *zeroed, hipStream_t st, const float *gate)
+hipError_t launch_prefill_fast(const MatmulProblem &p, void *part, size_t part_bytes, void *zeroed, hipStream_t st, const float *gate, int polls)
 {
     const PfPlan d = pf_plan(p, (part && zeroed) ? part_bytes : 0);
     PrefillArgsT<1> a;
-    pf_common(a, p, d);
+    pf_common(a, p, d, polls);
     a.L = 1;
     pf_layer(a.layer[0], p, d, part, zeroed, 0);
     a.layer[0].gate = gate;
@@ -270,10 +277,10 @@ double prefill_batched_cost(const BatchedProblem &p)
     return us;
 }
 
-// One launch per tile shape that the matrices' plans ask for (usually one).  A part that waits for others cannot wait for
-// ever although not all workgroups fit the chip at once: blocks are dispatched in order, a matrix has at most 256
-// workgroups that share tiles (32 per XCD, one per CU), and those of the matrices before it finish without it.
-hipError_t launch_prefill_batched(const BatchedProblem &p, void *part, void *zeroed, hipStream_t st)
+// One launch per tile shape that the matrices' plans ask for (usually one).  Not all workgroups fit the chip at once.  In runs a
+// workgroup waits for first parts of later ones, which wait for nothing and are dispatched as soon as any CU of the XCD is free; one
+// whose tile meets waits for a while and then leaves its share to the others (lords_meet.h).
+hipError_t launch_prefill_batched(const BatchedProblem &p, void *part, void *zeroed, hipStream_t st, int polls)
 {
     PfPlan d[kMaxBatch];
     unsigned char *parts[kMaxBatch];
@@ -291,7 +298,7 @@ hipError_t launch_prefill_batched(const BatchedProblem &p, void *part, void *zer
     for (int l0 = 0; l0 < p.L; ++l0) {
         if (done[l0]) continue;
         PrefillArgsT<kMaxBatch> a;
-        pf_common(a, matrix_of(p, l0), d[l0]);
+        pf_common(a, matrix_of(p, l0), d[l0], polls);
         a.L = 0;
         int x0 = 0;
         for (int l = l0; l < p.L; ++l) {

@@ -43,6 +43,7 @@
 #include <algorithm>
 #include <type_traits>
 #include "lords_prefill.h"
+#include "lords_meet.h"
 
 namespace lords {
 
@@ -557,13 +558,14 @@ __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(WN
     // own, in column order (the sums are those of the form below).  All CUs then write, read and store Y, 1 / G of a tile each,
     // and only blocks with tokens in them travel.  us, before (one of them collected the tile) / this, 4 bits, rank 32 where
     // nothing else is said:
-    //   4096 x 4096    32 tokens 24.3 / 18.0, 64 23.9 / 18.6, 128 29.0 / 20.3, 300 37.2 / 31.4, 512 39.5 / 33.2, 2048 80.8 / 74.2;
-    //                  500 tokens, rank 48 41.8 / 35.9, fp32 rank 16 49.9 / 44.7
-    //   1024 x 4096    300 tokens 31.4 / 19.4, 2048 39.8 / 33.9;   4096 x 14336 512 83.4 / 75.8, 2048 210.6 / 207.0
-    // Nothing waits for what may never start: the workgroups of a tile are neighbours in the order of dispatch (blockIdx.x in
-    // steps of 8), so that whatever else runs, only the last few of a launch's running workgroups, at most 8 (G - 1), wait for
-    // one that has no CU yet, and the others end and make room.  The counter goes through 2 G values back to zero: each counts in
-    // once before it waits and once after.
+    //   4096 x 4096    32 tokens 24.1 / 19.1, 64 23.7 / 19.7, 128 28.5 / 21.6, 300 37.3 / 31.7, 512 39.4 / 33.1, 2048 80.2 / 73.0;
+    //                  500 tokens, fp32 rank 16 49.2 / 42.3
+    //   1024 x 4096    300 tokens 30.7 / 19.2;   4096 x 14336 2048 209.6 / 203.7
+    // (of these 1 us where eight meet, and less where fewer do, is the first thread's word to the others in LDS.)
+    // The wait is bounded (a.polls), and giving it up costs no more than time: the workgroup then also writes its own slice and
+    // goes, and another finishes it (lords_meet.h).  So a tile needs no two of its workgroups to run at the same time.
+    // That they do is what makes it fast: they are neighbours in the order of dispatch (blockIdx.x in steps of 8), so on an
+    // idle chip all but the last few of a launch are resident together.
     // Parts and counter are agent-scope accesses (sc1: they pass the XCD's L2 by), the part's stores have been acknowledged by
     // all waves before the count, and nothing else is handed over, so neither a write-back nor an invalidation of an L2 is
     // wanted: with a release and an acquire at agent scope around the count, G of each per tile, 3 to 7 us more.
@@ -581,8 +583,16 @@ __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(WN
         asm volatile("" : "+s"(own), "+s"(wg_first), "+s"(tokens), "+s"(part_base), "+s"(counter));
         float *const parts_of_tile = (float *)(uintptr_t)part_base + (size_t)wg_first * kPartFloats;
         counter += T;
+        auto finish_at = [&](int m, int n, f32x4 v) __attribute__((always_inline)) {
+            if (ly.gate) {
+                const f32x4_any ga = *reinterpret_cast<const f32x4_any *>(ly.gate + (size_t)min(m, tokens - 1) * N + min(n, N - 1));
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = ga[e] / (1.0f + __expf(-ga[e])) * v[e];
+            }
+            store_at(m, n, v);
+        };
         auto meet = [&](auto parts) __attribute__((always_inline)) {
-            constexpr int G = decltype(parts)::value, MS = MB / G;
+            constexpr int G = decltype(parts)::value, MS = MB / G, kLog = G == 2 ? 1 : G == 4 ? 2 : 3;
             float *dst = parts_of_tile + own * kPartFloats + t_out * 4;
             asm volatile("" : "+v"(dst));        // (addresses are made here, not kept in registers over the K loop)
 #pragma unroll
@@ -597,14 +607,78 @@ __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(WN
             }
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();
+            // (of the workgroup's first thread: its slice to finish, nothing, or slices that lie in memory; the tiles in LDS are done with)
+            uint32_t *const verdict = reinterpret_cast<uint32_t *>(smem);
             if (t_out == 0) {
-                __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                int spins = 0;
-                while (__hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < (uint32_t)G && ++spins < (1 << 21))
+                __hip_atomic_fetch_add(counter, meet_unit(kLog), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                uint32_t now, taken = 0;
+                for (int polls = a.polls;; --polls) {
+                    now = __hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if ((now & kMeetAllThere) || polls <= 0) break;
                     __builtin_amdgcn_s_sleep(2);
-                atomicInc(counter, 2 * G - 1);
+                }
+                if (now & kMeetAllThere) {
+                    if (__builtin_expect((now & kMeetSlices) != 0, 0))
+                        taken = __hip_atomic_fetch_and(counter, ~kMeetSlices, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kMeetSlices;
+                    __hip_atomic_fetch_add(counter, meet_leave(kLog, taken, true), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                } else {
+                    taken = kMeetAllThere;
+                }
+                *verdict = taken;
             }
             __syncthreads();
+            uint32_t mine = __builtin_amdgcn_readfirstlane(*verdict);
+            if (__builtin_expect(mine != 0, 0)) {
+                const bool gave_up = mine == kMeetAllThere;
+                if (gave_up) {
+                    // waited long enough: the own slice goes to memory too
+#pragma unroll
+                    for (int s = 0; s < G; ++s) {
+                        if (s != own || m_out + 16 * s * MS >= tokens) continue;
+#pragma unroll
+                        for (int q = 0; q < MS; ++q) {
+#pragma unroll
+                            for (int rho = 0; rho < R; ++rho) store16_agent(dst + (rho * MB + s * MS + q) * (NT * 4), acc[rho][s * MS + q]);
+                            asm volatile("" : "+v"(dst));
+                        }
+                    }
+                    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                    __syncthreads();
+                    if (t_out == 0) {
+                        uint32_t taken = 0;
+                        if (__hip_atomic_fetch_add(counter, 1u << own, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kMeetAllThere) {
+                            taken = __hip_atomic_fetch_and(counter, ~kMeetSlices, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kMeetSlices;
+                            __hip_atomic_fetch_add(counter, meet_leave(kLog, taken, false), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        }
+                        *verdict = taken;
+                    }
+                    __syncthreads();
+                    mine = __builtin_amdgcn_readfirstlane(*verdict);
+                }
+                // slices of which all parts lie in memory, a block at a time
+                for (uint32_t left = mine; left != 0; left &= left - 1) {
+                    const int b0 = __builtin_ctz(left) * MS;
+                    if (m_out + 16 * b0 >= tokens) continue;
+#pragma nounroll
+                    for (int b = 0; b < MS * R; ++b) {
+                        const int rho = b % R, mb = b0 + b / R;
+                        f32x4 v = {0.f, 0.f, 0.f, 0.f};
+#pragma nounroll
+                        for (int i = 0; i < G; ++i) {
+                            uint64_t *src = reinterpret_cast<uint64_t *>(parts_of_tile + (size_t)i * kPartFloats + (rho * MB + mb) * (NT * 4) + t_out * 4);
+                            const uint64_t lo = __hip_atomic_load(src, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                            const uint64_t hi = __hip_atomic_load(src + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                            const f32x4 t = {__builtin_bit_cast(float, (uint32_t)lo), __builtin_bit_cast(float, (uint32_t)(lo >> 32)),
+                                             __builtin_bit_cast(float, (uint32_t)hi), __builtin_bit_cast(float, (uint32_t)(hi >> 32))};
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) v[e] = i == 0 ? t[e] : v[e] + t[e];
+                        }
+                        const int m = m_out + 16 * mb + c_out, n = n_out + 16 * rho + 4 * g_out;
+                        finish_at(m, n, v);
+                    }
+                }
+                if (gave_up) return;
+            }
             if (m_out + 16 * own * MS >= tokens) return;
             // (accumulators are only read, where they are: blocks per round trip by the registers beside them)
             constexpr int TB = std::min(MS * R, G == 2 ? 16 : G == 4 ? 4 : 2);
@@ -648,12 +722,7 @@ __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(WN
                 for (int b = 0; b < TB; ++b) {
                     int m = m_out + 16 * (own * MS + (b0 + b) / R) + c_out, n = n_out + 16 * ((b0 + b) % R) + 4 * g_out;
                     asm volatile("" : "+v"(m), "+v"(n));
-                    if (ly.gate) {
-                        const f32x4_any ga = *reinterpret_cast<const f32x4_any *>(ly.gate + (size_t)min(m, tokens - 1) * N + min(n, N - 1));
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) t[0][b][e] = ga[e] / (1.0f + __expf(-ga[e])) * t[0][b][e];
-                    }
-                    store_at(m, n, t[0][b]);
+                    finish_at(m, n, t[0][b]);
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -684,7 +753,9 @@ __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(WN
     if (kt1 != a.ntiles_k) {
         const int others = (a.ntiles_k - kt1 + ly.per - 1) / ly.per;       // the workgroups after this one, up to the tile's end
         if (tid == 0) {
-            // (bounded: the parts waited for are first parts of their workgroups and never wait themselves)
+            // (The parts waited for are first parts of their workgroups and never wait themselves, so one free CU an XCD is enough for the
+            // wait to end, whatever else waits.  The bound, some two seconds, is there so that every wave ends; a launch whose next
+            // workgroup gets no CU for that long would have a wrong sum.)
             int spins = 0;
             while ((int)__hip_atomic_load(ly.arrived + T, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < others && ++spins < (1 << 21))
                 __builtin_amdgcn_s_sleep(8);

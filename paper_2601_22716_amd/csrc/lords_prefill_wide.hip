@@ -316,7 +316,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     if (kt1 != a.ntiles_k) {
         others = (a.ntiles_k - kt1 + ly.per - 1) / ly.per;                 // the workgroups after this one, up to the tile's end
         if (tid == 0) {
-            // (bounded: the parts waited for are first parts of their workgroups and never wait themselves)
+            // (bounded as in lords_prefill_kernel.h: the parts waited for are first parts of their workgroups and never wait themselves)
             int spins = 0;
             while ((int)__hip_atomic_load(ly.arrived + T, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < others && ++spins < (1 << 21))
                 __builtin_amdgcn_s_sleep(8);

@@ -26,5 +26,18 @@ int two_pass_supported(const int *N, int L, int M, int K, int r, int bits, int f
 size_t two_pass_workspace_bytes(const int *N, int L, int M, int K, int r, int bits, int f32, int act) { return lords::two_pass_workspace_bytes(batched(N, L, M, K, r, bits, f32, act)); }
 size_t prefill_workspace_bytes(int M, int N, int K, int r, int bits, int f32) { return lords::prefill_fast_workspace_bytes(single(M, N, K, r, bits, f32), ~(size_t)0); }
 size_t prefill_least_workspace_bytes(int M, int N, int K, int r, int bits, int f32) { return lords::prefill_least_workspace_bytes(single(M, N, K, r, bits, f32)); }
+void prefill_cut(int M, int N, int K, int r, int bits, int f32, int *tokens_rows_parts)
+{
+    const lords::PrefillCut cut = lords::prefill_cut(single(M, N, K, r, bits, f32), ~(size_t)0);
+    tokens_rows_parts[0] = cut.tokens; tokens_rows_parts[1] = cut.rows; tokens_rows_parts[2] = cut.meet;
+}
 int prefill_wide_taken(int M, int N, int K, int r, int bits, int f32) { return lords::prefill_wide_taken(single(M, N, K, r, bits, f32), ~(size_t)0); }
+// The large-M kernel itself, with a say in how long a workgroup waits for the parts of others; scratch of the size above.
+int launch_large(const void *X, const void *codes, const float *codebook, const void *B, const void *A, void *Y, const float *gate, int M, int N, int K,
+                 int r, int bits, int f32, int f32out, void *part, size_t part_bytes, void *zeroed, void *stream, int polls)
+{
+    lords::MatmulProblem p = single(M, N, K, r, bits, f32);
+    p.X = X; p.codes = codes; p.codebook = codebook; p.B = B; p.A = A; p.Y = Y; p.f32out = f32out != 0;
+    return (int)lords::launch_prefill_fast(p, part, part_bytes, zeroed, (hipStream_t)stream, gate, polls);
+}
 }

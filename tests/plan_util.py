@@ -23,6 +23,9 @@ def declare(lib):
         getattr(lib, name).argtypes, getattr(lib, name).restype = [nums] + [num] * 7, restype
     for name, restype in (("prefill_workspace_bytes", ctypes.c_size_t), ("prefill_least_workspace_bytes", ctypes.c_size_t), ("prefill_wide_taken", num)):
         getattr(lib, name).argtypes, getattr(lib, name).restype = [num] * 6, restype
+    ptr = ctypes.c_void_p
+    lib.prefill_cut.argtypes, lib.prefill_cut.restype = [num] * 6 + [ctypes.POINTER(num)], None
+    lib.launch_large.argtypes, lib.launch_large.restype = [ptr] * 7 + [num] * 7 + [ptr, ctypes.c_size_t, ptr, ptr, num], num
     return lib
 
 
@@ -36,3 +39,10 @@ def queries():
 
 def takes_two_passes(M, Ns, K, r, bits, f32, act=False, lib=None):
     return bool((lib or queries()).two_pass_faster((ctypes.c_int * len(Ns))(*Ns), len(Ns), M, K, r, bits, int(f32), int(act)))
+
+
+def cut(M, N, K, r, bits, f32, lib=None):
+    """The large-M kernel's tiles and the number of parts that meet in each: (tokens, rows, parts)."""
+    out = (ctypes.c_int * 3)()
+    (lib or queries()).prefill_cut(M, N, K, r, bits, int(f32), out)
+    return tuple(out)

@@ -58,3 +58,42 @@ def test_parts_that_meet_in_one_launch_of_several_matrices(gpu):
     torch.cuda.synchronize()
     for Y, w in zip(Ys, want):
         np.testing.assert_array_equal(Y.cpu().numpy(), w)
+
+
+@pytest.mark.parametrize("M,N,K,r,bits,fdt,cut", [
+    (1700, 4099, 4128, 9, 2, "bf16", (256, 256, 2)), (250, 5123, 4128, 20, 4, "bf16", (256, 128, 4)), (205, 5122, 4096, 16, 3, "bf16", (256, 128, 4)),
+    (256, 5119, 5120, 32, 4, "bf16", (256, 256, 8)), (100, 4093, 4096, 20, 4, "bf16", (128, 128, 8)), (70, 4097, 4096, 20, 4, "bf16", (128, 256, 8)),
+    (17, 14337, 4096, 7, 3, "bf16", (128, 256, 4)),
+    (500, 4095, 1056, 48, 4, "bf16", (128, 128, 2)), (705, 2282, 2624, 7, 2, "f32", (128, 256, 4)), (86, 3869, 2304, 64, 4, "f32", (64, 128, 4))])
+def test_parts_left_to_others(gpu, M, N, K, r, bits, fdt, cut):
+    """Workgroups that do not wait, or hardly, leave their shares of a tile to others: the same bits, with and without a gate, in
+    both output types, and the counts back at zero."""
+    import torch
+    import paper_2601_22716_amd as L
+    from tests import plan_util
+    print(f"parts left to others M={M} N={N} K={K} r={r} bits={bits} factors={fdt}", flush=True)
+    q, f32 = plan_util.queries(), fdt == "f32"
+    assert plan_util.cut(M, N, K, r, bits, f32) == cut
+    d = gpu.DeviceCase(li.make_case("tiny", M=M, N=N, K=K, r=r, bits=bits, factor_dtype=fdt, seed=91, signed_factors=True))
+    front, part = L.lords_workspace_zero_bytes(), q.prefill_workspace_bytes(M, N, K, r, bits, int(f32))
+    ws = torch.zeros(front + part, dtype=torch.uint8, device="cuda")
+    gate = torch.randn(M * N + 4, device="cuda")                # (read four columns at a time)
+    stream = torch.cuda.current_stream().cuda_stream
+
+    def launch(dtype, gate_at, polls):
+        Y = torch.full((M, N), float("nan"), dtype=dtype, device="cuda")
+        ws[front:] = 255                                        # (not a number: a part that is read before it is written shows)
+        assert q.launch_large(d.X.data_ptr(), d.codes.data_ptr(), d.codebook.data_ptr(), d.B.data_ptr(), d.A.data_ptr(), Y.data_ptr(), gate_at, M, N, K, r,
+                              bits, int(f32), int(dtype == torch.float32), ws.data_ptr() + front, part, ws.data_ptr(), stream, polls) == 0
+        torch.cuda.synchronize()
+        assert not ws[:front].any()
+        return Y
+
+    for gate_at in (None, gate.data_ptr()):
+        for dtype in (torch.float32, torch.bfloat16):
+            want = launch(dtype, gate_at, 1 << 20)
+            assert torch.isfinite(want).all()
+            for polls in (0, 1, 3):
+                assert torch.equal(launch(dtype, gate_at, polls), want), (gate_at is not None, dtype, polls)
+    ref = torch.from_numpy(d.matmul()).cuda()
+    assert torch.equal(launch(torch.float32, None, 0), ref)

@@ -1,0 +1,28 @@
+"""Tiles that several workgroups finish together: whatever order their events come in, and whichever of them give up waiting, every
+slice is finished once, from parts that are all there, and the count is back at zero.  The kernel's own count
+(lords_meet.h), compiled for the host."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+@pytest.fixture(scope="module")
+def orders(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("meet") / "meet_count.so")
+    subprocess.run([os.environ.get("CXX", "g++"), "-std=c++17", "-O2", "-shared", "-fPIC", "-o", out, os.path.join(HERE, "meet_count.cpp")], check=True)
+    return ctypes.CDLL(out).meet_orders
+
+
+@pytest.mark.parametrize("log", [1, 2])
+@pytest.mark.parametrize("may_give_up", [0, 1])
+def test_every_order_of_two_and_four(orders, log, may_give_up):
+    assert orders(log, may_give_up, 0) == 0
+
+
+@pytest.mark.parametrize("may_give_up", [0, 1])
+def test_drawn_orders_of_eight(orders, may_give_up):
+    assert orders(3, may_give_up, 200000) == 0
