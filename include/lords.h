@@ -49,8 +49,8 @@
  *    those of all its matrices together, and runs matrix by matrix where that much cannot be had.  Products
  *    of many tokens (above 128; which ones, a cost model decides) may instead write their weights once, in
  *    bf16, to at most 128 MiB of that workspace and multiply from there; where that much cannot be had,
- *    they run without it, more slowly.  Both with the same results, except that bf16 factors of rank
- *    33 to 64 above 128 tokens also run with the smaller partial sums of 128-token tiles, and the order of
+ *    they run without it, more slowly.  Both with the same results.  Products with bf16 factors above 16 tokens (ranks
+ *    above 64: above one) also run with smaller partial sums than they ask for first, more slowly, and the order of
  *    their fp32 sums then follows from what there is.  Memory that the device refused
  *    is asked for again only after a thousand calls that could do without it.
  *    Calls that share one workspace and overlap in time on one device race; issue them from one
@@ -193,8 +193,8 @@ int lords_matmul_ex(const void *X, const void *codes, const float *codebook,
  *   lords_workspace_bytes(...) bytes (LORDS_ERR_WORKSPACE if NULL or smaller; a workspace sized for
  *   the largest problem serves them all).  Two calls that overlap in time must not share one.
  *   Two exceptions: a large-M product with fp32 factors (rank <= 64) takes any workspace from
- *   lords_workspace_zero_bytes() bytes up and uses what there is beyond them, and one with bf16 factors of
- *   rank 33 to 64 and more than 128 tokens may take less than the query gives.  How much there is decides
+ *   lords_workspace_zero_bytes() bytes up and uses what there is beyond them, and one with bf16 factors
+ *   may take less than the query gives, where the work can be cut to need less.  How much there is decides
  *   how the sums over K are cut, so results are the same bit for bit among workspaces of one size, and of
  *   any size the query gives or more; those of a smaller one differ by the order of fp32 sums.
  *   Weights are never written to a caller's workspace: where lords_matmul would do that (see Workspace

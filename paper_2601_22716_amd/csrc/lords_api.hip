@@ -258,8 +258,8 @@ int launch_matmul(const lords::MatmulProblem &p, lords_path path, const WsView &
 int plan_workspace(const lords::MatmulProblem &p, lords_path path, size_t extra, void *stream, WsView *ws, void **extra_ptr, bool passes = true)
 {
     size_t own = p.f32fact && !is_decode(path) ? kFront : matmul_need(p, path);
-    // (ranks at which the 256-token tiles of one wave per SIMD ask for more than there need be)
-    const bool elastic = !is_decode(path) && !p.f32fact && p.r > 32 && p.r <= 64 && p.M > 128;
+    // (bf16 factors: 256-token tiles of one wave per SIMD, and parts that meet, ask for more than there need be)
+    const bool elastic = !is_decode(path) && !p.f32fact && own > kFront;
     int rc = passes && !is_decode(path) && lords::two_pass_faster(batch_of(p)) ? two_pass_workspace(batch_of(p), extra, stream, ws, &own)
                                                                              : get_workspace(own + extra, stream, ws, elastic);
     if (rc != LORDS_OK && elastic) {

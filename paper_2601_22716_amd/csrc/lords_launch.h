@@ -133,7 +133,8 @@ bool prefill_fast_supported(const MatmulProblem &p);
 // scratch, `zeroed` kZeroBytes of device memory that are zero when handed over and left at zero.
 size_t prefill_fast_workspace_bytes(const MatmulProblem &p, size_t limit);
 // The least that a caller's workspace must have: what the kernel asks for without its 256-token tiles at ranks 33 .. 64, whose
-// parts are twice as large.  Between this and the figure above, the plan is made for what there is.
+// parts are twice as large, or without parts that meet, of which there are more.  Between this and the figure above, the plan is
+// made for what there is.
 size_t prefill_least_workspace_bytes(const MatmulProblem &p);
 // Its tiles, and into how many parts that meet each is cut (0: whole tiles, or runs of any length).
 struct PrefillCut { int tokens, rows, meet; };

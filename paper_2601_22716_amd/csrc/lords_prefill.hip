@@ -58,7 +58,7 @@ static bool pf_may_meet(long tiles, int parts, int ntiles_k, int R, int mb)
     return R != 4 && parts <= (mb < 8 ? 4 : 8) && ntiles_k >= 2 * parts && tiles * parts <= kPfCUs;
 }
 
-static PfPlan pf_plan(const MatmulProblem &p, size_t avail, bool wide = true)
+static PfPlan pf_plan(const MatmulProblem &p, size_t avail, bool wide = true, bool meet = true)
 {
     PfPlan d;
     d.ss = pf_ss(pf_contraction(p), p.f32fact);
@@ -125,6 +125,7 @@ static PfPlan pf_plan(const MatmulProblem &p, size_t avail, bool wide = true)
         // tokens in them.
         const double live_mb = (double)((p.M + 15) / 16 * 16) * ((p.N + 15) / 16 * 16) * sizeof(float) / 1048576.0;
         for (int parts : {2, 4, 8}) {
+            if (!meet) break;
             const size_t bytes = (size_t)tiles * parts * tile_bytes;
             if (!pf_may_meet(tiles, parts, ntiles_k, c.R, c.mb) || bytes > avail) continue;
             const int per = (ntiles_k + parts - 1) / parts;
@@ -148,7 +149,10 @@ size_t prefill_fast_workspace_bytes(const MatmulProblem &p, size_t limit)
 
 size_t prefill_least_workspace_bytes(const MatmulProblem &p)
 {
-    return std::min(pf_plan(p, ~(size_t)0).part_bytes, pf_plan(p, ~(size_t)0, false).part_bytes);
+    size_t least = ~(size_t)0;
+    for (bool wide : {true, false})
+        for (bool meet : {true, false}) least = std::min(least, pf_plan(p, ~(size_t)0, wide, meet).part_bytes);
+    return least;
 }
 
 PrefillCut prefill_cut(const MatmulProblem &p, size_t limit)

@@ -97,3 +97,17 @@ def test_parts_left_to_others(gpu, M, N, K, r, bits, fdt, cut):
                 assert torch.equal(launch(dtype, gate_at, polls), want), (gate_at is not None, dtype, polls)
     ref = torch.from_numpy(d.matmul()).cuda()
     assert torch.equal(launch(torch.float32, None, 0), ref)
+
+
+@pytest.mark.parametrize("M,N,K,r,bits", [(411, 7402, 1376, 4, 4), (83, 22668, 2336, 27, 3)])
+def test_without_room_for_parts_that_meet(gpu, M, N, K, r, bits):
+    """A caller's workspace of the front alone: whole tiles.  Their sums of K fp32 additions are taken in another order (about
+    sqrt(K) 2^-24 of their rms)."""
+    import torch
+    import paper_2601_22716_amd as L
+    d = gpu.DeviceCase(li.make_case("tiny", M=M, N=N, K=K, r=r, bits=bits, factor_dtype="bf16", seed=97, signed_factors=True))
+    ws = torch.zeros(L.lords_workspace_zero_bytes(), dtype=torch.uint8, device="cuda")
+    Y = torch.full((M, N), float("nan"), device="cuda")
+    L.lords_matmul_ws(d.X, d.codes, d.codebook, d.B, d.A, Y, M, N, K, r, bits, ws)
+    torch.cuda.synchronize()
+    assert not ws.any() and onp.rel_fro(Y.cpu().numpy(), d.matmul()) <= 1e-5

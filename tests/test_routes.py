@@ -159,6 +159,24 @@ print(json.dumps([refused, matmul(100, 8000, 4096, 32, 4, False), matmul(2000, 6
     assert out == [[6, 6, 6], 0, 0]
 
 
+@pytest.mark.parametrize("M,N,K,r,bits", [(411, 7402, 1376, 4, 4), (83, 22668, 2336, 27, 3), (411, 14000, 4096, 20, 4)])
+def test_parts_that_meet_are_optional(routes, M, N, K, r, bits):
+    """Tiles that several workgroups finish together ask for more memory than other cuts of the work: where it is not to be had a
+    call runs with less, also in a caller's workspace of what the other cuts need and while the stream is captured."""
+    out = routes("""
+M, N, K, r, bits = arg
+asks = front + plan.prefill_workspace_bytes(M, N, K, r, bits, 0)
+in_ws = lambda size: lib.lords_matmul_ws(vp(at(0)), vp(at(1)), vp(at(2)), vp(at(3)), vp(at(4)), vp(at(5)), M, N, K, r, bits, 0, 1, None, 0, vp(at(9)),
+                                         ctypes.c_size_t(size))
+rt.double_largest_allocation(50 << 20)                      # (32 MiB of it for products with fp32 factors)
+short = [matmul(M, N, K, r, bits, False), launched()]
+caller = [in_ws(front), in_ws(asks), launched()]
+rt.double_capturing(1)
+print(json.dumps([asks > front + (20 << 20), short, caller, matmul(M, N, K, r, bits, False), launched()]))
+""", [M, N, K, r, bits])
+    assert out == [True, [0, ["prefill"]], [0, 0, ["prefill"] * 2], 0, ["prefill"]]
+
+
 @pytest.mark.parametrize("capturing", [0, 1])
 def test_gate_up_with_room_for_1024_tokens(routes, capturing):
     """Without the scratch for its weights a pair keeps the gate of 2048 tokens in memory, or of 1024: with room for
