@@ -136,8 +136,8 @@ size_t prefill_fast_workspace_bytes(const MatmulProblem &p, size_t limit);
 // parts are twice as large, or without parts that meet, of which there are more.  Between this and the figure above, the plan is
 // made for what there is.
 size_t prefill_least_workspace_bytes(const MatmulProblem &p);
-// Its tiles, and into how many parts that meet each is cut (0: whole tiles, or runs of any length).
-struct PrefillCut { int tokens, rows, meet; };
+// Its tiles, into how many parts that meet each is cut (0: whole tiles, or runs of any length), and how many of them are one workgroup's.
+struct PrefillCut { int tokens, rows, meet, walk; };
 PrefillCut prefill_cut(const MatmulProblem &p, size_t limit);
 // Whether it runs as the form with one wave per SIMD (lords_prefill_wide.hip).
 bool prefill_wide_taken(const MatmulProblem &p, size_t limit);
@@ -152,6 +152,7 @@ hipError_t launch_prefill_fast(const MatmulProblem &p, void *part, size_t part_b
 // The same for several matrices that read the same X, each summed as it would be alone: `part` holds
 // prefill_batched_workspace_bytes(p) bytes.
 bool prefill_batched_supported(const BatchedProblem &p);
+PrefillCut prefill_batched_cut(const BatchedProblem &p, int l);
 size_t prefill_batched_workspace_bytes(const BatchedProblem &p);
 // The planner's estimate of that launch, in us (what one matrix leaves idle of the chip is the next one's).
 double prefill_batched_cost(const BatchedProblem &p);

@@ -27,4 +27,14 @@ LORDS_MEET_HD uint32_t meet_unit(int log) { return kMeetAllThere >> log; }
 // What a workgroup adds to leave: a unit for itself (not if it gave up: who takes its slice counts for it) and for each slice taken.
 LORDS_MEET_HD uint32_t meet_leave(int log, uint32_t taken, bool itself) { return meet_unit(log) * ((uint32_t)__builtin_popcount(taken) + (itself ? 1u : 0u)); }
 
+// Where workgroup bx of 8 * (workgroups of a tile) * ceil(tiles / 8) works: a tile's workgroups are on one XCD (bx mod 8), and tiles go to
+// the XCDs as evenly as they can, one more to the first ones from `xcd` on.  False: nowhere.
+LORDS_MEET_HD bool meet_place(int bx, int xcd, int tiles, int log, int &tile, int &part)
+{
+    const int slot = bx >> 3, y = (bx - xcd) & 7, more = tiles & 7;
+    tile = y * (tiles >> 3) + (y < more ? y : more) + (slot >> log);
+    part = slot & ((1 << log) - 1);
+    return slot >> log < (tiles >> 3) + (y < more ? 1 : 0);
+}
+
 }  // namespace lords

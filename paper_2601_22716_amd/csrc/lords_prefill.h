@@ -5,11 +5,12 @@
 namespace lords {
 
 // One weight matrix of a launch.  Several matrices that read the same X (and are cut into tiles of the same shape) can
-// share a launch: each gets a contiguous range of blockIdx.x, a multiple of eight long, and keeps the cut of the work it
-// would have alone, so its sums are the same bit for bit.  Layers too small to fill the chip run beside each other and
-// the last round of one is filled by the next.  q, k, v (4096 + 1024 + 1024 rows x 4096, 4 bits, rank 32) one by one -> in one
-// launch, us: 17 tokens 78 -> 45, 300 103 -> 70, 1000 122 -> 93, 2048 166 -> 162; 512 + 128 + 128 x 512, 3 bits, 17 tokens
-// 33 -> 12.
+// share a launch: each gets a contiguous range of blockIdx.x, a multiple of eight long, and keeps the cut of the sums over K that it
+// would have alone, so they are the same bit for bit.  Layers too small to fill the chip run beside each other and
+// the last round of one is filled by the next; where a tile is cut into parts to fill the chip alone, one workgroup may take several
+// of them.  q, k, v (4096 + 1024 + 1024 rows x 4096, 4 bits, rank 32) in one launch, us, no tiles in parts / in parts as alone / parts by
+// workgroup and tiles chosen for the launch: 64 tokens 46 / 45 / 42, 256 40 / 48 / 33, 512 77 / 63 / 58, 1024 91 / 111 / 84,
+// 2048 160 / 148 / 129; three of 1088 x 1088, 1360 tokens 31 / 63 / 38.
 struct PfLayer {
     const uint8_t *codes;
     const void *B;         // N x rf, bf16 or fp32
@@ -22,6 +23,8 @@ struct PfLayer {
     int nt;                // tiles along N
     int per;               // work units (one K tile of one output tile) per workgroup, or per 2^meet; units are numbered tile by tile
     int meet;              // 0, or 1 .. 3: each tile is cut into 2^meet parts, one workgroup each, that finish it together
+    int walk;              // 0, or 1 .. 3: each tile is cut into 2^(meet + walk) parts, 2^walk of them one workgroup's
+    int xcd;               // tiles in parts: where those that do not go round evenly begin
     int x0, gx;            // first blockIdx.x of this matrix and how many it has (multiples of 8)
 };
 

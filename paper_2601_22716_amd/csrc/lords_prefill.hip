@@ -41,7 +41,9 @@ struct PfPlan {
     int per, wgs;          // units per workgroup, workgroups that get any
     size_t part_bytes;     // 0: whole tiles
     int meet;              // 0, or the parts of a tile that finish it together: 2, 4 or 8
-    double cost;           // modelled time, us
+    int walk;              // of these parts, how many one workgroup takes one after the other (1: none waits in memory for the next)
+    double t;              // modelled time of a K tile, us
+    double cost;           // ... and of the launch
 };
 
 constexpr int kPfCUs = 256;
@@ -57,6 +59,12 @@ static bool pf_may_meet(long tiles, int parts, int ntiles_k, int R, int mb)
 {
     return R != 4 && parts <= (mb < 8 ? 4 : 8) && ntiles_k >= 2 * parts && tiles * parts <= kPfCUs;
 }
+
+// Sums of a product in fp32, of blocks of 16 x 16 with tokens in them.
+static double pf_live_mb(const MatmulProblem &p) { return (double)((p.M + 15) / 16 * 16) * ((p.N + 15) / 16 * 16) * sizeof(float) / 1048576.0; }
+
+// What it takes beside the K tiles that `parts` of a tile meet (fitted to 16 products of 32 to 2048 tokens, within 2 us of 14).
+static double pf_meet_us(int parts, double live_mb) { return (parts == 2 ? 7.5 : parts == 4 ? 8.0 : 10.5) + (parts - 1) * live_mb / 2.5; }
 
 static PfPlan pf_plan(const MatmulProblem &p, size_t avail, bool wide = true, bool meet = true)
 {
@@ -84,7 +92,7 @@ static PfPlan pf_plan(const MatmulProblem &p, size_t avail, bool wide = true, bo
     const Cand *cands = d.ss == 1 ? small_rank : d.ss == 6 ? six : large_rank;
     const int ncands = d.ss == 1 ? 4 : d.ss == 6 ? 1 : d.ss == 2 && !p.f32fact && p.M > 128 && wide ? 3 : 2;
     double best = 1e30;
-    d.wm = 1; d.R = 2; d.wn = 4; d.mb = d.ss == 6 ? 4 : 8; d.per = ntiles_k; d.part_bytes = 0; d.meet = 0;
+    d.wm = 1; d.R = 2; d.wn = 4; d.mb = d.ss == 6 ? 4 : 8; d.per = ntiles_k; d.part_bytes = 0; d.meet = 0; d.walk = 1; d.t = 0.0;
     for (int i = 0; i < ncands; ++i) {
         const Cand &c = cands[i];
         const int tokens = 16 * c.mb * c.wm, rows = 16 * c.R * c.wn;
@@ -96,7 +104,7 @@ static PfPlan pf_plan(const MatmulProblem &p, size_t avail, bool wide = true, bo
         // whole tiles, dealt by the hardware in rounds
         {
             const double cost = (double)((tiles + kPfCUs - 1) / kPfCUs) * ntiles_k * c.t * (c.R == 4 ? kWideScale : 1.0);
-            if (cost < best) { best = cost; d.wm = c.wm; d.R = c.R; d.wn = c.wn; d.mb = c.mb; d.per = ntiles_k; d.part_bytes = 0; d.meet = 0; }
+            if (cost < best) { best = cost; d.t = c.t; d.wm = c.wm; d.R = c.R; d.wn = c.wn; d.mb = c.mb; d.per = ntiles_k; d.part_bytes = 0; d.meet = 0; }
         }
         // equal runs of units over `wgs` workgroups.  Its price is the hand-over of the parts: measured
         // 4 us + 1 us per 1.2 MB of parts written when the runs are shorter than a tile (every part is
@@ -118,20 +126,30 @@ static PfPlan pf_plan(const MatmulProblem &p, size_t avail, bool wide = true, bo
             const double cost = c.R == 4 ? kWideScale * (per >= ntiles_k ? per * c.t * 1.08 + 25.0 : per * c.t + 20.0 + 7.0 * (ntiles_k % per ? others : ntiles_k / per - 1))
                               : per >= ntiles_k ? per * c.t * 1.08 + 4.0 + mb_written / 2.4
                                                 : per * c.t + 4.0 + mb_written / 1.2;
-            if (cost < best) { best = cost; d.wm = c.wm; d.R = c.R; d.wn = c.wn; d.mb = c.mb; d.per = per; d.part_bytes = bytes; d.meet = 0; }
+            if (cost < best) { best = cost; d.t = c.t; d.wm = c.wm; d.R = c.R; d.wn = c.wn; d.mb = c.mb; d.per = per; d.part_bytes = bytes; d.meet = 0; }
         };
         for (int wgs : kWgs) consider(wgs);
         // Two, four or eight parts of every tile, which their workgroups finish together: 7 us + 1 us per 3 MB, of blocks with
-        // tokens in them.
-        const double live_mb = (double)((p.M + 15) / 16 * 16) * ((p.N + 15) / 16 * 16) * sizeof(float) / 1048576.0;
-        for (int parts : {2, 4, 8}) {
-            if (!meet) break;
-            const size_t bytes = (size_t)tiles * parts * tile_bytes;
-            if (!pf_may_meet(tiles, parts, ntiles_k, c.R, c.mb) || bytes > avail) continue;
-            const int per = (ntiles_k + parts - 1) / parts;
-            const double cost = per * c.t + 7.0 + (parts - 1) * live_mb / 3.0;
-            if (cost < best) { best = cost; d.wm = c.wm; d.R = c.R; d.wn = c.wn; d.mb = c.mb; d.per = per; d.part_bytes = bytes; d.meet = parts; }
+        // tokens in them.  More parts only where they gain a tenth: beside other matrices (batched_plans) each part is a start, a store and
+        // a load more.  Two / four parts, us: 1360 tokens of 1088 x 1088 23.1 / 22.7 alone, three of them 37.8 / 59; 1024 tokens of
+        // 2048 x 2048 28.5 / 26.8, with two of 512 x 2048 30.8 / 41.9; 943 tokens of 1216 x 1216 21.9 / 20.2, three 28.0 / 41.6.
+        const double live_mb = pf_live_mb(p);
+        double cost = 1e30;
+        int most = 0;
+        for (size_t room : {~(size_t)0, avail}) {              // (room for the parts chosen is all that it takes to choose them)
+            if (!meet || (most && most * tiles * tile_bytes <= avail)) break;
+            double fewer = cost = 1e30;
+            most = 0;
+            for (int parts : {2, 4, 8}) {
+                if (!pf_may_meet(tiles, parts, ntiles_k, c.R, c.mb) || parts * tiles * tile_bytes > room) continue;
+                const double units = (ntiles_k + parts - 1) / parts * c.t, each = units + pf_meet_us(parts, live_mb);
+                cost = std::min(cost, units + 7.0 + (parts - 1) * live_mb / 3.0);
+                if (each > 0.9 * fewer) continue;
+                fewer = each;
+                most = parts;
+            }
         }
+        if (cost < best) { best = cost; d.t = c.t; d.wm = c.wm; d.R = c.R; d.wn = c.wn; d.mb = c.mb; d.per = (ntiles_k + most - 1) / most; d.part_bytes = (size_t)tiles * most * tile_bytes; d.meet = most; }
     }
     const int tokens = 16 * d.mb * d.wm, rows = 16 * d.R * d.wn;
     d.nt = (p.N + rows - 1) / rows;
@@ -158,7 +176,7 @@ size_t prefill_least_workspace_bytes(const MatmulProblem &p)
 PrefillCut prefill_cut(const MatmulProblem &p, size_t limit)
 {
     const PfPlan d = pf_plan(p, limit);
-    return PrefillCut{16 * d.mb * d.wm, 16 * d.R * d.wn, d.meet};
+    return PrefillCut{16 * d.mb * d.wm, 16 * d.R * d.wn, d.meet, d.walk};
 }
 
 bool prefill_wide_taken(const MatmulProblem &p, size_t limit) { return pf_plan(p, limit).R == 4; }
@@ -189,7 +207,10 @@ static void pf_common(Args &a, const MatmulProblem &p, const PfPlan &d, int poll
     a.polls = polls;
 }
 
-static void pf_layer(PfLayer &ly, const MatmulProblem &p, const PfPlan &d, void *part, void *arrived, int x0)
+// Workgroups of a tile in parts; 0: tiles in runs, or whole and each by the workgroup of its number.
+static int share(const PfPlan &d) { return d.meet / d.walk; }
+
+static void pf_layer(PfLayer &ly, const MatmulProblem &p, const PfPlan &d, void *part, void *arrived, int x0, int xcd)
 {
     ly.codes = (const uint8_t *)p.codes;
     ly.B = p.B;
@@ -202,9 +223,11 @@ static void pf_layer(PfLayer &ly, const MatmulProblem &p, const PfPlan &d, void 
     ly.nt = d.nt;
     ly.per = d.meet ? (p.K + 127) / 128 : d.per;
     ly.x0 = x0;
-    ly.meet = d.meet == 8 ? 3 : d.meet / 2;
-    const int at_once = 8 * (d.meet ? d.meet : 1);             // (the workgroups of a tile on one XCD)
+    ly.meet = share(d) == 8 ? 3 : share(d) / 2;
+    ly.walk = d.walk == 8 ? 3 : d.walk / 2;
+    const int at_once = 8 * std::max(share(d), 1);
     ly.gx = (d.wgs + at_once - 1) / at_once * at_once;
+    ly.xcd = xcd;
 }
 
 // `part`: part_bytes bytes of scratch (what prefill_fast_workspace_bytes returned for a limit of at most
@@ -215,58 +238,47 @@ hipError_t launch_prefill_fast(const MatmulProblem &p, void *part, size_t part_b
     PrefillArgsT<1> a;
     pf_common(a, p, d, polls);
     a.L = 1;
-    pf_layer(a.layer[0], p, d, part, zeroed, 0);
+    pf_layer(a.layer[0], p, d, part, zeroed, 0, 0);
     a.layer[0].gate = gate;
     return launch_pf<false>(a, d, p.bits, p.f32fact, st);
 }
 
 // ---- several matrices, the same activations ------------------------------------------------------------------
-static PfPlan batched_plan(const BatchedProblem &p, int l) { return pf_plan(matrix_of(p, l), p.whole[l] ? 0 : ~(size_t)0); }
+static bool same_shape(const PfPlan &a, const PfPlan &b) { return a.R == b.R && a.wm == b.wm && a.wn == b.wn && a.mb == b.mb; }
 
-size_t prefill_batched_workspace_bytes(const BatchedProblem &p)
-{
-    size_t sum = 0;
-    for (int l = 0; l < p.L; ++l) sum += (batched_plan(p, l).part_bytes + 255) & ~(size_t)255;
-    return sum;
-}
-
-bool prefill_batched_supported(const BatchedProblem &p)
-{
-    if (p.act || p.L < 1 || p.L > kMaxBatch) return false;
-    size_t tiles = 0;
-    for (int l = 0; l < p.L; ++l) {
-        if (!prefill_fast_supported(matrix_of(p, l))) return false;
-        const PfPlan d = batched_plan(p, l);
-        if (d.part_bytes) tiles += (size_t)d.nt * d.mt;
-        if (d.wgs > (1 << 24)) return false;
-    }
-    return tiles * sizeof(uint32_t) <= kZeroBytes;
-}
-
-static bool same_shape(const PfPlan &a, const PfPlan &b) { return a.wm == b.wm && a.wn == b.wn && a.mb == b.mb; }
-
-// The matrices' workgroups in order, each to the CU that is free first; the launches of other tile shapes behind it.  A workgroup's
-// start and end (8 us), which a planner that weighs one tile shape against another can leave out, make several short rounds
-// longer than one: of 250 calls of two to six matrices, measured / estimated lies within 0.72 .. 1.05 for nine in ten of each
-// padded contraction (1.05 .. 1.3 at six times 32), 0.8 .. 1.8 without them.
+// The matrices' workgroups in order on the XCD that has most to do, each to the CU that is free first; the launches of other tile
+// shapes behind it.  A workgroup's start and end (8 us), which a planner that weighs one tile shape against another can leave out, make
+// several short rounds longer than one: of 250 calls of two to six matrices, measured / estimated lies within 0.72 .. 1.05 for nine in
+// ten of each padded contraction (1.05 .. 1.3 at six times 32), 0.8 .. 1.8 without them.
 constexpr double kPfStartEnd = 8.0;
-double prefill_batched_cost(const BatchedProblem &p)
+static double batched_cost(const PfPlan *d, int L)
 {
-    PfPlan d[kMaxBatch];
+    constexpr int kXCDs = 8;
     bool done[kMaxBatch] = {};
-    for (int l = 0; l < p.L; ++l) d[l] = batched_plan(p, l);
     double us = 0;
-    for (int l0 = 0; l0 < p.L; ++l0) {
+    for (int l0 = 0; l0 < L; ++l0) {
         if (done[l0]) continue;
-        struct Free { double at; long cus; } free[kMaxBatch + 1] = {{0.0, kPfCUs}};     // in order of time
-        int n = 1;
-        double end = 0;
-        for (int l = l0; l < p.L; ++l) {
+        long on[kXCDs][kMaxBatch] = {};
+        double each[kMaxBatch], all[kXCDs] = {};
+        int xcd = 0;
+        for (int l = l0; l < L; ++l) {
             if (done[l] || !same_shape(d[l], d[l0])) continue;
             done[l] = true;
-            const double each = d[l].cost / ((d[l].wgs + kPfCUs - 1) / kPfCUs) + kPfStartEnd;
-            for (long left = d[l].wgs; left > 0;) {
-                const Free next{free[0].at + each, std::min(left, free[0].cus)};
+            each[l] = d[l].cost / ((d[l].wgs + kPfCUs - 1) / kPfCUs) + kPfStartEnd;
+            const int tiles = d[l].nt * d[l].mt, most = (d[l].wgs + kXCDs - 1) / kXCDs;
+            for (int x = 0; x < kXCDs; ++x) {
+                on[x][l] = share(d[l]) ? (long)share(d[l]) * (tiles / kXCDs + (((x - xcd) & 7) < tiles % kXCDs ? 1 : 0)) : std::max(0, std::min(most, d[l].wgs - x * most));
+                all[x] += on[x][l] * each[l];
+            }
+            if (share(d[l])) xcd = (xcd + tiles) & 7;
+        }
+        const int x = (int)(std::max_element(all, all + kXCDs) - all);
+        struct Free { double at; long cus; } free[kMaxBatch + 1] = {{0.0, kPfCUs / kXCDs}};     // in order of time
+        int n = 1;
+        double end = 0;
+        for (int l = l0; l < L; ++l) {
+            for (long left = on[x][l]; left > 0;) {
+                const Free next{free[0].at + each[l], std::min(left, free[0].cus)};
                 left -= next.cus;
                 free[0].cus -= next.cus;
                 if (free[0].cus == 0) std::copy(free + 1, free + n--, free);
@@ -281,6 +293,112 @@ double prefill_batched_cost(const BatchedProblem &p)
     return us;
 }
 
+// A plan of whole tiles or of tiles in parts, on tiles of another shape and with several parts to a workgroup.  The cut of K, and
+// with it every sum, stays.
+static PfPlan recut(const PfPlan &d, const MatmulProblem &p, const PfPlan &shape, int walk)
+{
+    if (d.R == 4 || shape.R == 4 || (d.meet == 0 && d.part_bytes != 0)) return d;       // (runs: cut by the tiles' numbering)
+    PfPlan e = d;
+    e.wm = shape.wm; e.wn = shape.wn; e.mb = shape.mb; e.t = shape.t;
+    const int tokens = 16 * e.mb * e.wm, rows = 16 * e.R * e.wn, ntiles_k = (p.K + 127) / 128;
+    e.nt = (p.N + rows - 1) / rows;
+    e.mt = (p.M + tokens - 1) / tokens;
+    const int tiles = e.nt * e.mt;
+    if (d.meet == 0) {
+        e.wgs = tiles;
+        e.cost = (double)((tiles + kPfCUs - 1) / kPfCUs) * ntiles_k * e.t;
+        return e;
+    }
+    e.walk = std::min(walk, e.meet);
+    e.wgs = tiles * share(e);
+    e.part_bytes = (size_t)tiles * e.meet * tokens * rows * sizeof(float);
+    const double mb = (e.meet - 1) * pf_live_mb(p);
+    e.cost = (double)((e.wgs + kPfCUs - 1) / kPfCUs) * ((ntiles_k + share(e) - 1) / share(e) * e.t + (share(e) > 1 ? 7.0 : 0.0) + 2.0 * (e.walk - 1)) + mb / 3.0;
+    return e;
+}
+
+// Each matrix's cut is the one that it has alone, which fixes its sums.  How many parts of a tile one workgroup takes, and the
+// tiles' shape, are chosen for the launch, by the estimate: of 12 choices timed for each of 48 sets of three matrices, those it
+// prefers were within 3 % of the fastest for all but one set (7 %).
+static double batched_plans(const BatchedProblem &p, PfPlan (&d)[kMaxBatch])
+{
+    bool cut = false, one_shape = true;
+    long wgs = 0;
+    for (int l = 0; l < p.L; ++l) {
+        d[l] = pf_plan(matrix_of(p, l), p.whole[l] ? 0 : ~(size_t)0);
+        cut |= d[l].meet != 0;
+        one_shape &= same_shape(d[l], d[0]);
+        wgs += d[l].wgs;
+    }
+    double best = batched_cost(d, p.L);
+    if (p.L == 1 || !cut || (one_shape && wgs <= kPfCUs)) return best;
+    PfPlan alone[kMaxBatch], e[kMaxBatch];
+    std::copy(d, d + p.L, alone);
+    for (int j = -1; j < p.L; ++j) {                           // tiles as alone, or as the j-th matrix has them
+        if (j == 0 && one_shape) break;
+        bool seen = false;
+        for (int i = 0; i < j; ++i) seen |= same_shape(alone[i], alone[j]);
+        if (seen) continue;
+        auto take = [&](int l, int walk) { return j < 0 && walk == 1 ? alone[l] : recut(alone[l], matrix_of(p, l), j < 0 ? alone[l] : alone[j], walk); };
+        int most = 1;
+        for (int walk = 1; walk <= most; walk *= 2) {
+            for (int l = 0; l < p.L; ++l) {
+                most = std::max(most, alone[l].meet);
+                e[l] = take(l, walk);
+            }
+            double cost = batched_cost(e, p.L);
+            // ... one matrix more or less
+            for (int l = p.L - 1; l >= 0; --l) {
+                if (e[l].walk < 2) continue;
+                const PfPlan now = e[l];
+                e[l] = take(l, now.walk / 2);
+                const double other = batched_cost(e, p.L);
+                if (other < 0.97 * cost) cost = other;
+                else e[l] = now;
+            }
+            if (cost < best) { best = cost; std::copy(e, e + p.L, d); }
+        }
+    }
+    return best;
+}
+
+size_t prefill_batched_workspace_bytes(const BatchedProblem &p)
+{
+    PfPlan d[kMaxBatch];
+    batched_plans(p, d);
+    size_t sum = 0;
+    for (int l = 0; l < p.L; ++l) sum += (d[l].part_bytes + 255) & ~(size_t)255;
+    return sum;
+}
+
+bool prefill_batched_supported(const BatchedProblem &p)
+{
+    if (p.act || p.L < 1 || p.L > kMaxBatch) return false;
+    for (int l = 0; l < p.L; ++l)
+        if (!prefill_fast_supported(matrix_of(p, l))) return false;
+    PfPlan d[kMaxBatch];
+    batched_plans(p, d);
+    size_t tiles = 0;
+    for (int l = 0; l < p.L; ++l) {
+        if (d[l].part_bytes) tiles += (size_t)d[l].nt * d[l].mt;
+        if (d[l].wgs > (1 << 24)) return false;
+    }
+    return tiles * sizeof(uint32_t) <= kZeroBytes;
+}
+
+PrefillCut prefill_batched_cut(const BatchedProblem &p, int l)
+{
+    PfPlan d[kMaxBatch];
+    batched_plans(p, d);
+    return PrefillCut{16 * d[l].mb * d[l].wm, 16 * d[l].R * d[l].wn, d[l].meet, d[l].walk};
+}
+
+double prefill_batched_cost(const BatchedProblem &p)
+{
+    PfPlan d[kMaxBatch];
+    return batched_plans(p, d);
+}
+
 // One launch per tile shape that the matrices' plans ask for (usually one).  Not all workgroups fit the chip at once.  In runs a
 // workgroup waits for first parts of later ones, which wait for nothing and are dispatched as soon as any CU of the XCD is free; one
 // whose tile meets waits for a while and then leaves its share to the others (lords_meet.h).
@@ -292,8 +410,8 @@ hipError_t launch_prefill_batched(const BatchedProblem &p, void *part, void *zer
     unsigned char *next_part = (unsigned char *)part;
     uint32_t *next_arrived = (uint32_t *)zeroed;
     bool done[kMaxBatch] = {};
+    batched_plans(p, d);
     for (int l = 0; l < p.L; ++l) {
-        d[l] = batched_plan(p, l);
         parts[l] = next_part;
         arrived[l] = next_arrived;
         next_part += (d[l].part_bytes + 255) & ~(size_t)255;
@@ -304,11 +422,12 @@ hipError_t launch_prefill_batched(const BatchedProblem &p, void *part, void *zer
         PrefillArgsT<kMaxBatch> a;
         pf_common(a, matrix_of(p, l0), d[l0], polls);
         a.L = 0;
-        int x0 = 0;
+        int x0 = 0, xcd = 0;
         for (int l = l0; l < p.L; ++l) {
             if (done[l] || !same_shape(d[l], d[l0])) continue;
-            pf_layer(a.layer[a.L], matrix_of(p, l), d[l], parts[l], arrived[l], x0);
+            pf_layer(a.layer[a.L], matrix_of(p, l), d[l], parts[l], arrived[l], x0, xcd);
             x0 += a.layer[a.L].gx;
+            if (share(d[l])) xcd = (xcd + d[l].nt * d[l].mt) & 7;
             ++a.L;
             done[l] = true;
         }

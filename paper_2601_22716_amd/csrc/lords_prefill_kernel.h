@@ -73,9 +73,11 @@ __device__ __forceinline__ void lds_direct_16(const void *gbase, uint32_t goff, 
 // 14336 x 4096, rank 40, 17 tokens 69 (602).
 // MULTI: several matrices in the launch (a lone one is read from fixed offsets of a short argument block: through an
 // index it cost 0.3 us a call).
-// FORM: of a lone matrix, parts that meet (kMeet) or any other cut of the work (kRuns), a kernel each: in one, the code of the
-// former cost the latter up to 2.5 % (333 tokens of 11008 x 4096, 3 bits, rank 48 61.5 -> 62.3 us).  kEither: several matrices.
-enum PfForm { kRuns, kMeet, kEither };
+// FORM: parts that meet (kMeet) or any other cut of the work (kRuns), a kernel each: in one, the code of the
+// former cost the latter up to 2.5 % (333 tokens of 11008 x 4096, 3 bits, rank 48 61.5 -> 62.3 us).  Several matrices: kEither where
+// those of some meet, kWalk where a workgroup takes several parts of a tile (PfLayer::walk; in one kernel the two cost launches without
+// walk up to 1 us of 22).
+enum PfForm { kRuns, kMeet, kEither, kWalk };
 template <int BITS, int SS, int WM, int R, int WN = 4, int MB = 8, bool F32 = false, bool MULTI = false, PfForm FORM = kRuns>
 __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(WN * WM / 4, WN * WM / 4))) void prefill_kernel(PrefillArgsT<MULTI ? kMaxBatch : 1> a)
 {
@@ -103,11 +105,21 @@ __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(WN
     //      the 8 XCDs, so each XCD gets a contiguous run of ranges: its workgroups then share X panels in its L2.
     const int total_units = ly.nt * a.mt * a.ntiles_k;
     const int bx = (int)blockIdx.x - ly.x0;
-    const int wg = (bx & 7) * (ly.gx >> 3) + (bx >> 3);
-    // Parts that meet (see the epilogue): 2^meet workgroups share the `per` units of a tile, a unit more or less each.
-    const int meet_log = FORM == kRuns ? 0 : ly.meet, meet_part = wg & ((1 << meet_log) - 1);
-    const int unit0 = (wg >> meet_log) * ly.per, unit_end = min(unit0 + ((meet_part + 1) * ly.per >> meet_log), total_units);
-    int unit = unit0 + (meet_part * ly.per >> meet_log);
+    // Parts that meet (see the epilogue): 2^meet workgroups share the `per` units of a tile, a unit more or less each.  With
+    // walk, 2^(meet + walk) parts of a tile are shared in the same way by 2^meet workgroups, 2^walk parts each, one after the other.
+    // A tile's workgroups are on one XCD, and tiles are dealt to the XCDs as evenly as they go, one more on the first ones from ly.xcd
+    // on.  (Rounded up on all but the last, those of several matrices piled up on the first XCDs, and as workgroups are dispatched in
+    // order the others then wait too.  Q/k/v of 4096 + 1024 + 1024 rows x 4096, 256 tokens: 42.4 us so, 33.4 now.)
+    const int meet_log = FORM == kRuns ? 0 : ly.meet, walk = FORM == kWalk ? ly.walk : 0, cut_log = meet_log + walk;
+    int wg = (bx & 7) * (ly.gx >> 3) + (bx >> 3), meet_part = 0;
+    if (FORM == kMeet || (FORM >= kEither && cut_log)) {
+        int tile;
+        if (!meet_place(bx, ly.xcd, ly.nt * a.mt, meet_log, tile, meet_part)) return;
+        wg = (tile << meet_log) + meet_part;
+    }
+    const int unit0 = (wg >> meet_log) * ly.per, unit_end = min(unit0 + (((meet_part + 1) << walk) * ly.per >> cut_log), total_units);
+    int unit = unit0 + ((meet_part << walk) * ly.per >> cut_log);
+    int walked = 0;
     if (unit >= unit_end) return;
     const int wn = wave % WN, wm = wave / WN;
     const uint16_t *A16 = reinterpret_cast<const uint16_t *>(ly.A), *B16 = reinterpret_cast<const uint16_t *>(ly.B);   // (bf16 factors)
@@ -134,7 +146,9 @@ __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(WN
     while (unit < unit_end) {
     // ---- this part: K tiles kt0 .. kt1 - 1 of output tile T ------------------------------------------------
     const int T = unit / a.ntiles_k;
-    const int kt0 = unit - T * a.ntiles_k, kt1 = min(a.ntiles_k, kt0 + (unit_end - unit));
+    const int kt0 = unit - T * a.ntiles_k;
+    int kt1 = min(a.ntiles_k, kt0 + (unit_end - unit));
+    if (FORM == kWalk && walk) kt1 = ((meet_part << walk) + ++walked) * ly.per >> cut_log;
     unit += kt1 - kt0;
     const int m_blk = (T / ly.nt) * BM, n_blk = (T % ly.nt) * BN;
     const int n_wave = n_blk + 16 * R * wn;
@@ -569,7 +583,7 @@ __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(WN
     // Parts and counter are agent-scope accesses (sc1: they pass the XCD's L2 by), the part's stores have been acknowledged by
     // all waves before the count, and nothing else is handed over, so neither a write-back nor an invalidation of an L2 is
     // wanted: with a release and an acquire at agent scope around the count, G of each per tile, 3 to 7 us more.
-    if constexpr (FORM != kRuns) if (FORM == kMeet || __builtin_expect(ly.meet != 0, 0)) {       // (behind the other form in the code)
+    if constexpr (FORM != kRuns) if (FORM == kMeet || __builtin_expect((ly.meet | walk) != 0, 0)) {       // (behind the other form in the code)
         // (what this wants of its thread is worked out again: registers of the K loop)
         int t_out = tid;
         asm volatile("" : "+v"(t_out));
@@ -581,7 +595,7 @@ __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(WN
         uint64_t part_base = (uint64_t)(uintptr_t)ly.part;
         uint32_t *counter = ly.arrived;
         asm volatile("" : "+s"(own), "+s"(wg_first), "+s"(tokens), "+s"(part_base), "+s"(counter));
-        float *const parts_of_tile = (float *)(uintptr_t)part_base + (size_t)wg_first * kPartFloats;
+        float *const parts_of_tile = (float *)(uintptr_t)part_base + ((size_t)wg_first << walk) * kPartFloats;
         counter += T;
         auto finish_at = [&](int m, int n, f32x4 v) __attribute__((always_inline)) {
             if (ly.gate) {
@@ -591,6 +605,111 @@ __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(WN
             }
             store_at(m, n, v);
         };
+        if constexpr (FORM == kWalk) if (walk) {
+            // Several of a tile's parts by one workgroup, one after the other: each is summed from zero and goes to memory, so that the
+            // tile has the sum that it has where each part is a workgroup's own.  (In registers there is room for one part.)
+            // (Added into the accumulators of the next part, which a K loop follows, they cost 900 to 1200 spilled registers.)
+            if (!ly.meet) {
+                // the tile is this workgroup's alone: the sum so far, which a thread reads back where it wrote it
+                float *sum = parts_of_tile + t_out * 4;
+                constexpr int TB = std::min(8, MB * R);
+#pragma unroll
+                for (int b0 = 0; b0 < MB * R; b0 += TB) {
+                    if (m_out + 16 * (b0 / R) >= tokens) continue;
+                    asm volatile("" : "+v"(sum));
+                    f32x4 v[TB];
+#pragma unroll
+                    for (int b = 0; b < TB; ++b) v[b] = walked > 1 ? *reinterpret_cast<const f32x4 *>(sum + ((b0 + b) % R * MB + (b0 + b) / R) * (NT * 4)) : f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int b = 0; b < TB; ++b) {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) v[b][e] = walked > 1 ? v[b][e] + acc[(b0 + b) % R][(b0 + b) / R][e] : acc[(b0 + b) % R][(b0 + b) / R][e];
+                        if (walked == 1 << walk) {
+                            int m = m_out + 16 * ((b0 + b) / R) + c_out, n = n_out + 16 * ((b0 + b) % R) + 4 * g_out;
+                            asm volatile("" : "+v"(m), "+v"(n));
+                            finish_at(m, n, v[b]);
+                        } else {
+                            *reinterpret_cast<f32x4 *>(sum + ((b0 + b) % R * MB + (b0 + b) / R) * (NT * 4)) = v[b];
+                        }
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                if (walked == 1 << walk) return;
+                continue;
+            }
+            // All parts to memory, and a slice of the tile added from there by each workgroup; who does not wait leaves its own, as below.
+            float *dst = parts_of_tile + own * (kPartFloats << walk) + (walked - 1) * kPartFloats + t_out * 4;
+            asm volatile("" : "+v"(dst));
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb) {
+                if (m_out + 16 * mb >= tokens) continue;
+#pragma unroll
+                for (int rho = 0; rho < R; ++rho) store16_agent(dst + (rho * MB + mb) * (NT * 4), acc[rho][mb]);
+                asm volatile("" : "+v"(dst));
+            }
+            if (walked != 1 << walk) continue;
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+            uint32_t *const verdict = reinterpret_cast<uint32_t *>(smem);
+            const int log = ly.meet;
+            if (t_out == 0) {
+                __hip_atomic_fetch_add(counter, meet_unit(log), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                uint32_t now, mine = 0;
+                for (int polls = a.polls;; --polls) {
+                    now = __hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if ((now & kMeetAllThere) || polls <= 0) break;
+                    __builtin_amdgcn_s_sleep(2);
+                }
+                const bool stays = (now & kMeetAllThere) != 0;
+                if (!stays) now = __hip_atomic_fetch_add(counter, 1u << own, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (now & kMeetAllThere) {
+                    if (!stays || (now & kMeetSlices)) mine = __hip_atomic_fetch_and(counter, ~kMeetSlices, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kMeetSlices;
+                    __hip_atomic_fetch_add(counter, meet_leave(log, mine, stays), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+                *verdict = stays ? mine | 1u << own : mine;
+            }
+            __syncthreads();
+            const int blocks = MB * R >> log;                  // of a slice
+            auto add_up = [&](auto parts) __attribute__((always_inline)) {
+                // (16 loads in flight)
+                constexpr int G = decltype(parts)::value, TB = std::min(16, 2 * MB * R) / G;
+                for (uint32_t left = __builtin_amdgcn_readfirstlane(*verdict); left != 0; left &= left - 1) {
+                    const int b0 = __builtin_ctz(left) * blocks;
+#pragma nounroll
+                    for (int b = b0; b < b0 + blocks; b += TB) {
+                        if (m_out + 16 * (b / R) >= tokens) break;
+                        f32x4 t[G][TB];
+#pragma unroll
+                        for (int i = 0; i < G; ++i) {
+                            const float *src = parts_of_tile + i * kPartFloats + b / R * (NT * 4) + t_out * 4;
+                            asm volatile("" : "+v"(src));
+#pragma unroll
+                            for (int q = 0; q < TB; ++q) {
+                                t[i][q] = load16_agent(src + (q % R * MB + q / R) * (NT * 4));
+                                asm volatile("" : "+v"(src));
+                            }
+                        }
+                        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#pragma unroll
+                        for (int q = 0; q < TB; ++q) {
+#pragma unroll
+                            for (int i = 0; i < G; ++i) {
+                                asm volatile("" : "+v"(t[i][q]));                       // (not before the wait)
+#pragma unroll
+                                for (int e = 0; e < 4; ++e)
+                                    if (i) t[0][q][e] += t[i][q][e];
+                            }
+                            int m = m_out + 16 * (b / R + q / R) + c_out, n = n_out + 16 * (q % R) + 4 * g_out;
+                            asm volatile("" : "+v"(m), "+v"(n), "+v"(t[0][q]));
+                            finish_at(m, n, t[0][q]);
+                        }
+                    }
+                }
+            };
+            if (MB < 8 || cut_log == 2) add_up(std::integral_constant<int, 4>{});
+            else add_up(std::integral_constant<int, MB < 8 ? 4 : 8>{});
+            return;
+        }
         auto meet = [&](auto parts) __attribute__((always_inline)) {
             constexpr int G = decltype(parts)::value, MS = MB / G, kLog = G == 2 ? 1 : G == 4 ? 2 : 3;
             float *dst = parts_of_tile + own * kPartFloats + t_out * 4;
@@ -830,11 +949,15 @@ __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(WN
     }   // parts of this workgroup
 }
 
-template <int BITS, int SS, int WM, int R, int WN, int MB, bool F32, bool MULTI, PfForm FORM = MULTI ? kEither : kRuns>
+template <int BITS, int SS, int WM, int R, int WN, int MB, bool F32, bool MULTI, PfForm FORM = kRuns>
 static hipError_t launch_pf_t(const PrefillArgsT<MULTI ? kMaxBatch : 1> &a, dim3 grid, hipStream_t st)
 {
-    if constexpr (FORM == kRuns)
-        if (a.layer[0].meet) return launch_pf_t<BITS, SS, WM, R, WN, MB, F32, MULTI, kMeet>(a, grid, st);
+    if constexpr (FORM == kRuns) {
+        int meet = 0, walk = 0;
+        for (int l = 0; l < a.L; ++l) meet |= a.layer[l].meet, walk |= a.layer[l].walk;
+        if (MULTI && walk) return launch_pf_t<BITS, SS, WM, R, WN, MB, F32, MULTI, MULTI ? kWalk : kMeet>(a, grid, st);
+        if (meet) return launch_pf_t<BITS, SS, WM, R, WN, MB, F32, MULTI, MULTI ? kEither : kMeet>(a, grid, st);
+    }
     const size_t smem = (size_t)2 * (16 * MB * WM) * 256 + (size_t)2 * (32 * SS) * 256 + (size_t)(1 << (2 * BITS)) * kPfCopies * pf_pair_bytes(F32);
     static LdsOptIn lds_opt_in;
     {

@@ -85,3 +85,20 @@ extern "C" int meet_orders(int log, int may_give_up, int walks)
     }
     return 0;
 }
+
+// Workgroups of a launch that are given no tile's part, one that is another's, or a tile's parts on two XCDs: 0 if every part has one.
+extern "C" int meet_places_wrong(int xcd, int tiles, int log)
+{
+    std::vector<int> seen((size_t)tiles << log, 0), on(tiles, -1);
+    int wrong = 0;
+    for (int bx = 0; bx < (8 * ((tiles + 7) / 8)) << log; ++bx) {
+        int tile, part;
+        if (!lords::meet_place(bx, xcd, tiles, log, tile, part)) continue;
+        if (tile < 0 || tile >= tiles || part < 0 || part >> log) { ++wrong; continue; }
+        wrong += seen[((size_t)tile << log) + part]++ != 0;
+        wrong += on[tile] >= 0 && on[tile] != (bx & 7);
+        on[tile] = bx & 7;
+    }
+    for (int s : seen) wrong += s != 1;
+    return wrong;
+}

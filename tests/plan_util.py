@@ -24,7 +24,12 @@ def declare(lib):
     for name, restype in (("prefill_workspace_bytes", ctypes.c_size_t), ("prefill_least_workspace_bytes", ctypes.c_size_t), ("prefill_wide_taken", num)):
         getattr(lib, name).argtypes, getattr(lib, name).restype = [num] * 6, restype
     ptr = ctypes.c_void_p
-    lib.prefill_cut.argtypes, lib.prefill_cut.restype = [num] * 6 + [ctypes.POINTER(num)], None
+    lib.prefill_cut.argtypes, lib.prefill_cut.restype = [num] * 6 + [nums], None
+    lib.prefill_batched_cut.argtypes, lib.prefill_batched_cut.restype = [nums] + [num] * 7 + [nums], None
+    lib.prefill_batched_cost.argtypes, lib.prefill_batched_cost.restype = [nums] + [num] * 6, ctypes.c_double
+    lib.prefill_batched_workspace_bytes.argtypes, lib.prefill_batched_workspace_bytes.restype = [nums] + [num] * 6, ctypes.c_size_t
+    ptrs = ctypes.POINTER(ptr)
+    lib.launch_large_batched.argtypes, lib.launch_large_batched.restype = [ptr, ptrs, ptr, ptrs, ptrs, ptrs, nums] + [num] * 7 + [ptr] * 3 + [num], num
     lib.launch_large.argtypes, lib.launch_large.restype = [ptr] * 7 + [num] * 7 + [ptr, ctypes.c_size_t, ptr, ptr, num], num
     return lib
 
@@ -46,3 +51,18 @@ def cut(M, N, K, r, bits, f32, lib=None):
     out = (ctypes.c_int * 3)()
     (lib or queries()).prefill_cut(M, N, K, r, bits, int(f32), out)
     return tuple(out)
+
+
+def batched_cuts(M, Ns, K, r, bits, f32, lib=None):
+    """... of the matrices of one launch, and how many of the parts one workgroup takes: [(tokens, rows, parts, walk), ..]."""
+    lib, cuts = lib or queries(), []
+    for l in range(len(Ns)):
+        out = (ctypes.c_int * 4)()
+        lib.prefill_batched_cut((ctypes.c_int * len(Ns))(*Ns), len(Ns), M, K, r, bits, int(f32), l, out)
+        cuts.append(tuple(out))
+    return cuts
+
+
+def batched_cost(M, Ns, K, r, bits, f32, lib=None):
+    """The planner's estimate of that launch, us."""
+    return (lib or queries()).prefill_batched_cost((ctypes.c_int * len(Ns))(*Ns), len(Ns), M, K, r, bits, int(f32))

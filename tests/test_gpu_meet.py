@@ -62,7 +62,7 @@ def test_parts_that_meet_in_one_launch_of_several_matrices(gpu):
 
 @pytest.mark.parametrize("M,N,K,r,bits,fdt,cut", [
     (1700, 4099, 4128, 9, 2, "bf16", (256, 256, 2)), (250, 5123, 4128, 20, 4, "bf16", (256, 128, 4)), (205, 5122, 4096, 16, 3, "bf16", (256, 128, 4)),
-    (256, 5119, 5120, 32, 4, "bf16", (256, 256, 8)), (100, 4093, 4096, 20, 4, "bf16", (128, 128, 8)), (70, 4097, 4096, 20, 4, "bf16", (128, 256, 8)),
+    (256, 5119, 5120, 32, 4, "bf16", (256, 256, 8)), (30, 4093, 4096, 20, 4, "bf16", (128, 128, 8)), (70, 4097, 4096, 20, 4, "bf16", (128, 256, 8)),
     (17, 14337, 4096, 7, 3, "bf16", (128, 256, 4)),
     (500, 4095, 1056, 48, 4, "bf16", (128, 128, 2)), (705, 2282, 2624, 7, 2, "f32", (128, 256, 4)), (86, 3869, 2304, 64, 4, "f32", (64, 128, 4))])
 def test_parts_left_to_others(gpu, M, N, K, r, bits, fdt, cut):

@@ -231,3 +231,17 @@ print(json.dumps([[plan_util.takes_two_passes(M, [n], K, r, bits, f32, lib=plan)
 """)
     alone, status, kernels = out
     assert status == 0 and kernels == ["dequant_operand", "operand_gemm"]
+
+
+@pytest.mark.parametrize("Ns,rest,most", [
+    ([4096, 1024, 1024], [256, 4096, 32, 4, 0], 41), ([4096, 1024, 1024], [1024, 4096, 32, 4, 0], 105), ([2048, 512, 512], [1024, 2048, 32, 4, 0], 38),
+    ([1600, 400, 400], [651, 1600, 11, 4, 0], 34), ([1216] * 3, [943, 1216, 16, 4, 0], 28), ([1088] * 3, [1360, 1088, 9, 4, 0], 30)])
+def test_matrices_cut_into_parts_do_not_queue_for_the_chip(routes, Ns, rest, most):
+    """Tiles that fill the chip in parts where their matrix is alone are taken with fewer workgroups beside others: at most an
+    eighth over the estimates of the launches without parts (us), and one launch."""
+    out = routes("""
+Ns, (M, K, r, bits, f32) = arg
+print(json.dumps([plan_util.batched_cost(M, Ns, K, r, bits, f32, lib=plan), batched(Ns, M, K, r, bits, f32), launched()]))
+""", [Ns, rest])
+    cost, status, kernels = out
+    assert cost <= 1.125 * most and status == 0 and kernels == ["prefill"]
