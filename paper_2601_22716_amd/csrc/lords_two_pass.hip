@@ -619,9 +619,16 @@ double two_pass_cost(const BatchedProblem &p)
     return us + op_dequant_us(p, weights);
 }
 
+// A cut-off of the planner, not a limit of the device: a gate of more bytes than this is not counted in the large-M kernel's way (its
+// output alone would be 32 GB in bf16), so that such a pair is served or refused as that way has the memory for it.
+constexpr double kGateMost = 64.0 * (1 << 30);
+// What the estimate of tiles that meet leaves out of each product of a pair, us.  Of 80 pairs (137 .. 539 tokens) that it had drawn
+// from the two passes to the large-M kernel, 52 were up to 17 % slower for it; of 70 others (185 .. 2390 tokens) that this term sends the
+// other way, two passes are faster for 53, by 7 % in the middle and 25 % at most, and slower for the rest, by 9 % at most.  6528 x 2496,
+// rank 15, 330 tokens: 74.5 in two passes, 82.3 by the large-M kernel.
+constexpr double kPairMeets = 2.5;
 // The large-M kernel's estimate reads high or low by the padded contraction (measured / estimated, the middle of 10 to 40
 // products each: bf16 factors 32 columns 1.0, 64 0.85, 128 0.82; fp32 factors 0.95, 0.92, 0.9, six times 32 1.15).
-constexpr double kGateMost = 64.0 * (1 << 30);
 double large_cost(const BatchedProblem &p)
 {
     const int ss = op_ss(p);
@@ -631,12 +638,12 @@ double large_cost(const BatchedProblem &p)
         for (int l = 0; l < p.L; ++l) {
             MatmulProblem m = matrix_of(p, l);
             m.M = M;
-            us += prefill_fast_cost(m);
+            us += prefill_fast_cost(m) + (p.act && prefill_cut(m, ~(size_t)0).meet ? kPairMeets : 0.0);
         }
         return us;
     };
     // A pair: 2048 tokens at a time; the gate's fp32 sums go through memory (14336 rows, 2048 tokens, 235 MB in about 62 us).
-    // Not beyond kGateMost of them, which the large-M kernel's way has no memory for: such a pair is refused there, and stays so.
+    // (up to kGateMost)
     if (p.act && (double)std::min(p.M, 2048) * p.N[0] * 4.0 <= kGateMost) {
         const int pieces = p.M / 2048, rest = p.M % 2048;
         return scale * (pieces * products(2048) + (rest ? products(rest) : 0.0)) + (double)p.M * p.N[0] * 8.0 / 3.8e6;

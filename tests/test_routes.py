@@ -245,3 +245,14 @@ print(json.dumps([plan_util.batched_cost(M, Ns, K, r, bits, f32, lib=plan), batc
 """, [Ns, rest])
     cost, status, kernels = out
     assert cost <= 1.125 * most and status == 0 and kernels == ["prefill"]
+
+
+@pytest.mark.parametrize("M,N,K,r,bits", [(330, 6528, 2496, 15, 4), (362, 3008, 1216, 23, 4), (385, 2464, 1088, 29, 3), (282, 3456, 1216, 12, 4), (260, 7264, 1920, 8, 2)])
+def test_pairs_that_two_passes_serve_faster_go_there(routes, M, N, K, r, bits):
+    """Pairs of which the large-M kernel's tiles would meet in parts, 10 to 18 % slower than two passes."""
+    out = routes("""
+M, N, K, r, bits = arg
+status = lib.lords_gate_up(*[vp(at(i)) for i in range(9)], M, N, K, r, bits, 0, 1, None)
+print(json.dumps([plan_util.cut(M, N, K, r, bits, 0, lib=plan)[2] > 0, status, launched()]))
+""", [M, N, K, r, bits])
+    assert out == [True, 0, ["dequant_operand", "operand_gemm"]]
