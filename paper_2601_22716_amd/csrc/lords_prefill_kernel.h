@@ -548,7 +548,8 @@ __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(WN
     // is the last one of its workgroup, collects the others in column order and writes Y.  The sum of a
     // tile is therefore taken in a fixed order whatever the timing.
     // Of a 128-token tile that holds at most 64 tokens only the first four of the eight token blocks travel (the
-    // buffers keep their size).  14336 x 4096, 4 bits, rank 32, 17 / 40 / 64 tokens: 37.6 / 37.3 / 37.5 -> 30.4 / 30.2 / 30.3 us.
+    // buffers keep their size).  14336 x 4096, 4 bits, rank 32, 17 / 40 / 64 tokens, when these went in runs: 37.6 / 37.3 / 37.5 -> 30.4 / 30.2 /
+    // 30.3 us (their parts meet now; 28672 x 8192 goes in runs at 17 to 64 tokens, 76 .. 79 us).
     // (Exactly the blocks in use, with a branch for each, was no faster there and cost 2-9 % at 100 and 128 tokens; in
     // 256-token tiles the second form cost registers: 10 % at 2048 tokens.)
     constexpr int kPartFloats = R * MB * NT * 4;

@@ -628,7 +628,7 @@ constexpr double kGateMost = 64.0 * (1 << 30);
 // rank 15, 330 tokens: 74.5 in two passes, 82.3 by the large-M kernel.
 constexpr double kPairMeets = 2.5;
 // The large-M kernel's estimate reads high or low by the padded contraction (measured / estimated, the middle of 10 to 40
-// products each: bf16 factors 32 columns 1.0, 64 0.85, 128 0.82; fp32 factors 0.95, 0.92, 0.9, six times 32 1.15).
+// products each, whole tiles and runs: bf16 factors 32 columns 1.0, 64 0.85, 128 0.82; fp32 factors 0.95, 0.92, 0.9, six times 32 1.15).
 double large_cost(const BatchedProblem &p)
 {
     const int ss = op_ss(p);
@@ -661,7 +661,7 @@ double large_cost(const BatchedProblem &p)
 //                fp32 rank 16          194 / 130     361 / 233     706 / 445
 //                fp32 rank 64          814 / 248     1627 / 342    3249 / 572
 //   4096 x 14336 bf16 rank 48          147 / 216     248 / 286     428 / 399
-//   4096 x 4096  bf16 rank 48          63 / 76       93 / 97       136 / 117
+//   4096 x 4096  bf16 rank 48          56 / 76       93 / 97       136 / 117      (1024: in two parts that meet)
 //   3000 x 2048  fp32 rank 64          109 / 73      199 / 86      394 / 90
 // A pair (us, two products by the large-M kernel with the gate through memory / two passes; of 36 drawn pairs that go here
 // since the estimate counts the gate's way, 0.28 .. 0.87 of the time, none slower):

@@ -1,7 +1,8 @@
 """Products of many tokens whose tiles are cut into two, four or eight parts that several workgroups finish together, through
 the C ABI: against the fp64 oracle, and run to run bit for bit.  Gates as for lords_matmul.
 
-Sizes: every number of parts and tile shape, K tiles that the parts do not divide (a unit more or less each), ragged last K
+Sizes: every tile shape, each with the numbers of parts that its plans have (the tokens and rows of a tile and the parts stand beside
+each case and are asked of the planner), K tiles that the parts do not divide (a unit more or less each), ragged last K
 tiles, token counts at which the last slices of a tile have no tokens (17, 33, 65, 129 ...), rows off the tiles.
 """
 import sys
@@ -25,13 +26,20 @@ def gpu():
     return gpu_util
 
 
-@pytest.mark.parametrize("M,N,K,r,bits,fdt", [
-    (17, 4096, 4096, 32, 4, "bf16"), (33, 1000, 4000, 7, 3, "bf16"), (65, 4099, 3104, 32, 2, "bf16"), (128, 4096, 4096, 20, 4, "bf16"),
-    (129, 1003, 2016, 10, 3, "bf16"), (300, 1024, 4096, 32, 4, "bf16"), (445, 1882, 2016, 10, 4, "bf16"), (1795, 1765, 2176, 10, 2, "bf16"),
-    (2048, 1021, 1120, 31, 4, "bf16"), (100, 1999, 2592, 48, 3, "bf16"), (500, 4096, 1056, 48, 4, "bf16"), (237, 3699, 1568, 87, 4, "bf16"),
-    (3, 2000, 4096, 100, 2, "bf16"), (100, 4096, 4096, 10, 4, "f32"), (705, 2284, 2624, 7, 2, "f32"), (86, 3869, 2304, 64, 4, "f32"),
-    (500, 4096, 1056, 16, 3, "f32"), (250, 16000, 4128, 60, 2, "bf16")])
-def test_parts_that_meet(gpu, M, N, K, r, bits, fdt):
+@pytest.mark.parametrize("M,N,K,r,bits,fdt,cut", [
+    (17, 4096, 4096, 32, 4, "bf16", (128, 128, 8)), (33, 3001, 4000, 7, 3, "bf16", (128, 128, 8)), (65, 4099, 3104, 32, 2, "bf16", (128, 256, 4)),
+    (128, 4096, 4096, 20, 4, "bf16", (128, 128, 4)), (129, 1003, 2016, 10, 3, "bf16", (256, 128, 4)),
+    (300, 1024, 4096, 32, 4, "bf16", (256, 128, 8)), (445, 1882, 2016, 10, 4, "bf16", (256, 128, 4)),
+    (1795, 1765, 2176, 10, 2, "bf16", (256, 128, 2)), (2047, 1021, 2080, 31, 4, "bf16", (256, 128, 2)),
+    (261, 8714, 1984, 20, 4, "bf16", (256, 256, 2)), (262, 4165, 1344, 8, 4, "bf16", (256, 256, 4)), (264, 2174, 2720, 8, 4, "bf16", (256, 256, 8)),
+    (37, 14251, 1024, 8, 2, "bf16", (128, 256, 2)), (17, 8379, 960, 60, 3, "bf16", (128, 256, 4)), (100, 1999, 2592, 48, 3, "bf16", (128, 128, 8)),
+    (500, 4096, 1056, 48, 4, "bf16", (128, 128, 2)), (237, 3699, 1568, 87, 4, "bf16", (128, 128, 4)), (18, 4495, 1952, 96, 4, "bf16", (128, 256, 8)),
+    (100, 4096, 4096, 10, 4, "f32", (128, 128, 4)), (19, 3045, 2048, 40, 3, "f32", (128, 128, 8)), (705, 2284, 2624, 7, 2, "f32", (128, 256, 4)),
+    (133, 4782, 1024, 8, 3, "f32", (128, 256, 2)), (26, 4453, 1952, 20, 4, "f32", (128, 256, 8)), (86, 3869, 2304, 64, 4, "f32", (64, 128, 4)),
+    (17, 14575, 1088, 60, 4, "f32", (64, 128, 2)), (500, 4096, 1056, 16, 3, "f32", (128, 128, 2)), (250, 16000, 4128, 60, 2, "bf16", (128, 256, 2))])
+def test_parts_that_meet(gpu, M, N, K, r, bits, fdt, cut):
+    from tests import plan_util
+    assert plan_util.cut(M, N, K, r, bits, fdt == "f32") == cut and not plan_util.takes_two_passes(M, [N], K, r, bits, fdt == "f32")
     print(f"parts that meet M={M} N={N} K={K} r={r} bits={bits} factors={fdt}", flush=True)
     sys.stdout.flush()
     c = li.make_case("tiny", M=M, N=N, K=K, r=r, bits=bits, factor_dtype=fdt, seed=81, signed_factors=True)
@@ -97,6 +105,36 @@ def test_parts_left_to_others(gpu, M, N, K, r, bits, fdt, cut):
                 assert torch.equal(launch(dtype, gate_at, polls), want), (gate_at is not None, dtype, polls)
     ref = torch.from_numpy(d.matmul()).cuda()
     assert torch.equal(launch(torch.float32, None, 0), ref)
+
+
+@pytest.mark.parametrize("M,N,K,r,bits,fdt,hdt,cut", [
+    (28, 14595, 800, 96, 4, "bf16", "f32", (128, 128, 2)), (19, 2626, 1952, 20, 3, "bf16", "bf16", (128, 128, 4)), (18, 2699, 2016, 60, 2, "bf16", "f32", (128, 128, 8)),
+    (37, 14251, 1024, 8, 2, "bf16", "bf16", (128, 256, 2)), (17, 8379, 960, 60, 3, "bf16", "f32", (128, 256, 4)), (128, 4099, 4096, 16, 4, "bf16", "f32", (128, 256, 8)),
+    (148, 4635, 1056, 8, 3, "bf16", "f32", (256, 128, 2)), (297, 298, 1984, 8, 3, "bf16", "bf16", (256, 128, 4)), (258, 278, 2624, 8, 3, "bf16", "f32", (256, 128, 8)),
+    (140, 8490, 1440, 32, 2, "bf16", "f32", (256, 256, 4)), (269, 2053, 2624, 32, 2, "bf16", "bf16", (256, 256, 8)), (559, 10975, 512, 20, 3, "bf16", "f32", (256, 256, 0)),
+    (18, 14345, 800, 32, 4, "f32", "f32", (128, 128, 2)), (19, 3045, 2048, 40, 3, "f32", "bf16", (128, 128, 8)), (133, 4782, 1024, 8, 3, "f32", "f32", (128, 256, 2)),
+    (26, 4453, 1952, 20, 4, "f32", "bf16", (128, 256, 8)), (25, 6481, 928, 60, 3, "f32", "f32", (64, 128, 4))])
+def test_gate_up_whose_products_meet(gpu, M, N, K, r, bits, fdt, hdt, cut):
+    """The up product's workgroups multiply their slices by the gate's silu: sampled rows of the matrices, the last ones among them,
+    against the oracle, with the bound that the gates of the two products carry through (|silu'| <= 1.1, |silu(g)| <= |g|)."""
+    import torch
+    import paper_2601_22716_amd as L
+    from tests import plan_util
+    print(f"pair M={M} N={N} K={K} r={r} bits={bits} factors={fdt} out={hdt}", flush=True)
+    f32 = fdt == "f32"
+    assert plan_util.cut(M, N, K, r, bits, f32) == cut and not plan_util.takes_two_passes(M, [N, N], K, r, bits, f32, act=True)
+    cg, cu = (li.make_case("tiny", M=M, N=N, K=K, r=r, bits=bits, factor_dtype=fdt, seed=101 + i, signed_factors=True) for i in range(2))
+    dg, du = gpu.DeviceCase(cg), gpu.DeviceCase(cu)
+    H = torch.full((M, N), float("nan"), dtype=torch.float32 if hdt == "f32" else torch.bfloat16, device="cuda")
+    L.lords_gate_up(dg.X, dg.codes, dg.B, dg.A, du.codes, du.B, du.A, dg.codebook, H, M, N, K, r, bits)
+    torch.cuda.synchronize()
+    rows = np.unique(np.r_[np.random.default_rng(2).integers(0, N, 40), 0, N - 3, N - 2, N - 1])
+    G, U = (onp.matmul_rows(cg.X_f32, c.codes, c.codebook, c.B_f32, c.A_f32, bits, rows) for c in (cg, cu))
+    silu = G / (1 + np.exp(-G))
+    rms = lambda a: float(np.sqrt(np.mean(a * a)))
+    want = silu * U
+    bound = 1.05 * Y_MAX_TOL * (1.1 * rms(G) * np.abs(U) + rms(U) * np.abs(silu)) + 1e-6 + (0.0 if hdt == "f32" else 2.0 ** -8) * np.abs(want)
+    assert torch.isfinite(H).all() and np.all(np.abs(H.float().cpu().numpy()[:, rows] - want) <= bound)
 
 
 @pytest.mark.parametrize("M,N,K,r,bits", [(411, 7402, 1376, 4, 4), (83, 22668, 2336, 27, 3)])

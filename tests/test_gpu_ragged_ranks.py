@@ -83,15 +83,18 @@ def test_gate_up_and_batched(gpu, M, N):
 
 
 @pytest.mark.parametrize("M,N,K,r,bits,fdt", [(17, 1, 288, 8, 4, "bf16"), (40, 131, 544, 32, 2, "bf16"), (130, 257, 416, 48, 3, "f32" ),
-                                              (130, 514, 1056, 13, 3, "f32"), (257, 1027, 416, 32, 4, "bf16"), (2049, 66, 160, 96, 2, "bf16"),
-                                              # a last piece of a few tokens, at an odd offset of H
+                                              (130, 514, 1056, 13, 3, "f32"), (257, 1027, 416, 32, 4, "bf16"),
                                               (1025, 67, 160, 32, 4, "bf16"), (1039, 33, 1184, 20, 3, "bf16"), (1030, 35, 160, 10, 4, "f32"),
-                                              (2050, 131, 288, 40, 2, "bf16"), (1056, 14337, 1184, 8, 4, "bf16"), (1040, 2051, 2080, 24, 4, "bf16"),
+                                              # several pieces, at an odd offset of H: 2048 and a few, 2048 and some, 1024 and a few
+                                              (2049, 67, 160, 20, 2, "bf16"), (2073, 65, 160, 20, 2, "bf16"), (2098, 65, 160, 20, 4, "f32"), (1028, 943, 4480, 20, 3, "bf16"),
                                               # ranks beyond the large-M kernel: both products, then the element-wise pass, 1024 tokens at a time
                                               (40, 131, 288, 136, 4, "bf16"), (1100, 67, 160, 136, 3, "bf16"), (40, 35, 288, 65, 2, "f32"), (1100, 66, 160, 65, 4, "f32")])
 def test_gate_up_of_many_tokens(gpu, M, N, K, r, bits, fdt):
     """The up product's large-M kernel reads the gate's sums four columns at a time and multiplies by their silu: last
-    rows and columns, half tiles, pieces of a call."""
+    rows and columns, half tiles, pieces of a call (how many: test_routes.py).  Pairs in two passes are test_gpu_two_pass.py's, those
+    whose tiles meet test_gpu_meet.py's."""
+    from tests import plan_util
+    assert not plan_util.takes_two_passes(M, [N, N], K, r, bits, fdt == "f32", act=True)
     import torch
     import paper_2601_22716_amd as L
     cg = li.make_case("tiny", M=M, N=N, K=K, bits=bits, r=r, factor_dtype=fdt, seed=25)

@@ -256,3 +256,13 @@ status = lib.lords_gate_up(*[vp(at(i)) for i in range(9)], M, N, K, r, bits, 0, 
 print(json.dumps([plan_util.cut(M, N, K, r, bits, 0, lib=plan)[2] > 0, status, launched()]))
 """, [M, N, K, r, bits])
     assert out == [True, 0, ["dequant_operand", "operand_gemm"]]
+
+
+@pytest.mark.parametrize("M,N,K,r,bits,f32,pieces", [
+    (2049, 67, 160, 20, 2, 0, [2048, 1]), (2073, 65, 160, 20, 2, 0, [2048, 25]), (2098, 65, 160, 20, 4, 1, [2048, 50]), (1028, 943, 4480, 20, 3, 0, [1024, 4]),
+    (1114, 3866, 8608, 8, 2, 0, [1024, 90]), (1025, 67, 160, 32, 4, 0, [1025]), (4101, 72, 4704, 60, 2, 0, [2048, 2048, 5])])
+def test_pieces_of_a_pair(routes, M, N, K, r, bits, f32, pieces):
+    """The pieces that a pair of many tokens goes in: two launches of the large-M kernel each, one of a few-token kernel for a few."""
+    status, kernels = routes("print(json.dumps([gate_up(*arg), launched()]))", [M, N, K, r, bits, f32])
+    assert status == 0 and kernels.count("prefill") == 2 * sum(p > 16 for p in pieces)
+    assert len([k for k in kernels if k.startswith(("decode", "gemv"))]) == sum(p <= 16 for p in pieces)
