@@ -356,7 +356,9 @@ static double batched_plans(const BatchedProblem &p, PfPlan (&d)[kMaxBatch])
                 if (other < 0.97 * cost) cost = other;
                 else e[l] = now;
             }
-            if (cost < best) { best = cost; std::copy(e, e + p.L, d); }
+            // (Fewer workgroups only for a gain: CUs that idle raise the clock where the call is timed alone, but not among others that load
+            // the chip.  q, k, v of 2048 tokens between gate/up pairs, one workgroup a part / two parts each 139 / 155 us; alone 126 / 126.)
+            if (cost < 0.97 * best) { best = cost; std::copy(e, e + p.L, d); }
         }
     }
     return best;
