@@ -63,8 +63,12 @@ static bool pf_may_meet(long tiles, int parts, int ntiles_k, int R, int mb)
 // Sums of a product in fp32, of blocks of 16 x 16 with tokens in them.
 static double pf_live_mb(const MatmulProblem &p) { return (double)((p.M + 15) / 16 * 16) * ((p.N + 15) / 16 * 16) * sizeof(float) / 1048576.0; }
 
-// What it takes beside the K tiles that `parts` of a tile meet (fitted to 16 products of 32 to 2048 tokens, within 2 us of 14).
-static double pf_meet_us(int parts, double live_mb) { return (parts == 2 ? 7.5 : parts == 4 ? 8.0 : 10.5) + (parts - 1) * live_mb / 2.5; }
+// What it takes beside the K tiles that `parts` of each of `tiles` tiles meet: parts travel at the rate above if all CUs are at it (to
+// weigh one number of parts against another: the ratio of the times of 16 products of 32 to 2048 tokens to 0.06).
+static double pf_meet_us(int parts, long tiles, double live_mb, int M)
+{
+    return (parts == 2 ? 7.5 : parts == 4 ? 8.0 : 10.0) + (parts - 1) * live_mb / (M <= 128 ? 3.0 : 2.5) * (tiles * parts) / kPfCUs;
+}
 
 static PfPlan pf_plan(const MatmulProblem &p, size_t avail, bool wide = true, bool meet = true)
 {
@@ -132,7 +136,9 @@ static PfPlan pf_plan(const MatmulProblem &p, size_t avail, bool wide = true, bo
         // Two, four or eight parts of every tile, which their workgroups finish together: 7 us + 1 us per 3 MB, of blocks with
         // tokens in them.  More parts only where they gain a tenth: beside other matrices (batched_plans) each part is a start, a store and
         // a load more.  Two / four parts, us: 1360 tokens of 1088 x 1088 23.1 / 22.7 alone, three of them 37.8 / 59; 1024 tokens of
-        // 2048 x 2048 28.5 / 26.8, with two of 512 x 2048 30.8 / 41.9; 943 tokens of 1216 x 1216 21.9 / 20.2, three 28.0 / 41.6.
+        // 2048 x 2048 28.5 / 26.8, with two of 512 x 2048 30.8 / 41.9; 943 tokens of 1216 x 1216 21.9 / 20.2, three 28.0 / 41.6.  (At
+        // 7.5 % three of 1216 x 1216 took four parts.)  Up to 128 tokens, whose parts are small, 3 % is enough (84 tokens of 7861 x 5152, four /
+        // eight parts 34.6 / 31.6; q, k and v of 4096 + 1024 + 1024 x 4096 38 with either).
         const double live_mb = pf_live_mb(p);
         double cost = 1e30;
         int most = 0;
@@ -142,9 +148,9 @@ static PfPlan pf_plan(const MatmulProblem &p, size_t avail, bool wide = true, bo
             most = 0;
             for (int parts : {2, 4, 8}) {
                 if (!pf_may_meet(tiles, parts, ntiles_k, c.R, c.mb) || parts * tiles * tile_bytes > room) continue;
-                const double units = (ntiles_k + parts - 1) / parts * c.t, each = units + pf_meet_us(parts, live_mb);
+                const double units = (ntiles_k + parts - 1) / parts * c.t, each = units + pf_meet_us(parts, tiles, live_mb, p.M);
                 cost = std::min(cost, units + 7.0 + (parts - 1) * live_mb / 3.0);
-                if (each > 0.9 * fewer) continue;
+                if (each > (p.M <= 128 ? 0.97 : 0.9) * fewer) continue;
                 fewer = each;
                 most = parts;
             }
@@ -320,7 +326,7 @@ static PfPlan recut(const PfPlan &d, const MatmulProblem &p, const PfPlan &shape
 // Each matrix's cut is the one that it has alone, which fixes its sums.  How many parts of a tile one workgroup takes, and the
 // tiles' shape, are chosen for the launch, by the estimate: of 12 choices timed for each of 48 sets of three matrices, those it
 // prefers were within 3 % of the fastest for all but one set (7 %).
-static double batched_plans(const BatchedProblem &p, PfPlan (&d)[kMaxBatch])
+static void batched_plans(const BatchedProblem &p, PfPlan (&d)[kMaxBatch])
 {
     bool cut = false, one_shape = true;
     long wgs = 0;
@@ -330,8 +336,8 @@ static double batched_plans(const BatchedProblem &p, PfPlan (&d)[kMaxBatch])
         one_shape &= same_shape(d[l], d[0]);
         wgs += d[l].wgs;
     }
+    if (p.L == 1 || !cut || (one_shape && wgs <= kPfCUs)) return;
     double best = batched_cost(d, p.L);
-    if (p.L == 1 || !cut || (one_shape && wgs <= kPfCUs)) return best;
     PfPlan alone[kMaxBatch], e[kMaxBatch];
     std::copy(d, d + p.L, alone);
     for (int j = -1; j < p.L; ++j) {                           // tiles as alone, or as the j-th matrix has them
@@ -361,7 +367,6 @@ static double batched_plans(const BatchedProblem &p, PfPlan (&d)[kMaxBatch])
             if (cost < 0.97 * best) { best = cost; std::copy(e, e + p.L, d); }
         }
     }
-    return best;
 }
 
 size_t prefill_batched_workspace_bytes(const BatchedProblem &p)
@@ -398,7 +403,8 @@ PrefillCut prefill_batched_cut(const BatchedProblem &p, int l)
 double prefill_batched_cost(const BatchedProblem &p)
 {
     PfPlan d[kMaxBatch];
-    return batched_plans(p, d);
+    batched_plans(p, d);
+    return batched_cost(d, p.L);
 }
 
 // One launch per tile shape that the matrices' plans ask for (usually one).  Not all workgroups fit the chip at once.  In runs a

@@ -27,15 +27,15 @@ def gpu():
 
 
 @pytest.mark.parametrize("M,N,K,r,bits,fdt,cut", [
-    (17, 4096, 4096, 32, 4, "bf16", (128, 128, 8)), (33, 3001, 4000, 7, 3, "bf16", (128, 128, 8)), (65, 4099, 3104, 32, 2, "bf16", (128, 256, 4)),
-    (128, 4096, 4096, 20, 4, "bf16", (128, 128, 4)), (129, 1003, 2016, 10, 3, "bf16", (256, 128, 4)),
+    (17, 4096, 4096, 32, 4, "bf16", (128, 128, 8)), (33, 3001, 4000, 7, 3, "bf16", (128, 128, 8)), (65, 4099, 3104, 32, 2, "bf16", (128, 256, 8)),
+    (128, 4096, 4096, 20, 4, "bf16", (128, 128, 8)), (129, 1003, 2016, 10, 3, "bf16", (256, 128, 8)),
     (300, 1024, 4096, 32, 4, "bf16", (256, 128, 8)), (445, 1882, 2016, 10, 4, "bf16", (256, 128, 4)),
     (1795, 1765, 2176, 10, 2, "bf16", (256, 128, 2)), (2047, 1021, 2080, 31, 4, "bf16", (256, 128, 2)),
     (261, 8714, 1984, 20, 4, "bf16", (256, 256, 2)), (262, 4165, 1344, 8, 4, "bf16", (256, 256, 4)), (264, 2174, 2720, 8, 4, "bf16", (256, 256, 8)),
-    (37, 14251, 1024, 8, 2, "bf16", (128, 256, 2)), (17, 8379, 960, 60, 3, "bf16", (128, 256, 4)), (100, 1999, 2592, 48, 3, "bf16", (128, 128, 8)),
+    (18, 16643, 1696, 8, 3, "bf16", (128, 256, 2)), (17, 6325, 928, 8, 3, "bf16", (128, 128, 4)), (17, 8379, 960, 60, 3, "bf16", (128, 256, 4)), (100, 1999, 2592, 48, 3, "bf16", (128, 128, 8)),
     (500, 4096, 1056, 48, 4, "bf16", (128, 128, 2)), (237, 3699, 1568, 87, 4, "bf16", (128, 128, 4)), (18, 4495, 1952, 96, 4, "bf16", (128, 256, 8)),
-    (100, 4096, 4096, 10, 4, "f32", (128, 128, 4)), (19, 3045, 2048, 40, 3, "f32", (128, 128, 8)), (705, 2284, 2624, 7, 2, "f32", (128, 256, 4)),
-    (133, 4782, 1024, 8, 3, "f32", (128, 256, 2)), (26, 4453, 1952, 20, 4, "f32", (128, 256, 8)), (86, 3869, 2304, 64, 4, "f32", (64, 128, 4)),
+    (100, 4096, 4096, 10, 4, "f32", (128, 128, 8)), (19, 3045, 2048, 40, 3, "f32", (128, 128, 8)), (705, 2284, 2624, 7, 2, "f32", (128, 256, 4)),
+    (135, 5466, 1184, 8, 3, "f32", (128, 256, 2)), (26, 4453, 1952, 20, 4, "f32", (128, 256, 8)), (86, 3869, 2304, 64, 4, "f32", (64, 128, 4)),
     (17, 14575, 1088, 60, 4, "f32", (64, 128, 2)), (500, 4096, 1056, 16, 3, "f32", (128, 128, 2)), (250, 16000, 4128, 60, 2, "bf16", (128, 256, 2))])
 def test_parts_that_meet(gpu, M, N, K, r, bits, fdt, cut):
     from tests import plan_util
@@ -108,11 +108,11 @@ def test_parts_left_to_others(gpu, M, N, K, r, bits, fdt, cut):
 
 
 @pytest.mark.parametrize("M,N,K,r,bits,fdt,hdt,cut", [
-    (28, 14595, 800, 96, 4, "bf16", "f32", (128, 128, 2)), (19, 2626, 1952, 20, 3, "bf16", "bf16", (128, 128, 4)), (18, 2699, 2016, 60, 2, "bf16", "f32", (128, 128, 8)),
-    (37, 14251, 1024, 8, 2, "bf16", "bf16", (128, 256, 2)), (17, 8379, 960, 60, 3, "bf16", "f32", (128, 256, 4)), (128, 4099, 4096, 16, 4, "bf16", "f32", (128, 256, 8)),
-    (148, 4635, 1056, 8, 3, "bf16", "f32", (256, 128, 2)), (297, 298, 1984, 8, 3, "bf16", "bf16", (256, 128, 4)), (258, 278, 2624, 8, 3, "bf16", "f32", (256, 128, 8)),
+    (28, 14595, 800, 96, 4, "bf16", "f32", (128, 128, 2)), (19, 2626, 1952, 20, 3, "bf16", "bf16", (128, 128, 8)), (18, 2699, 2016, 60, 2, "bf16", "f32", (128, 128, 8)),
+    (18, 16643, 1696, 8, 3, "bf16", "bf16", (128, 256, 2)), (17, 6325, 928, 8, 3, "bf16", "f32", (128, 128, 4)), (17, 8379, 960, 60, 3, "bf16", "f32", (128, 256, 4)), (128, 4099, 4096, 16, 4, "bf16", "f32", (128, 256, 8)),
+    (129, 6927, 928, 20, 3, "bf16", "f32", (256, 128, 2)), (257, 682, 928, 20, 3, "bf16", "bf16", (256, 128, 4)), (258, 278, 2624, 8, 3, "bf16", "f32", (256, 128, 8)),
     (140, 8490, 1440, 32, 2, "bf16", "f32", (256, 256, 4)), (269, 2053, 2624, 32, 2, "bf16", "bf16", (256, 256, 8)), (559, 10975, 512, 20, 3, "bf16", "f32", (256, 256, 0)),
-    (18, 14345, 800, 32, 4, "f32", "f32", (128, 128, 2)), (19, 3045, 2048, 40, 3, "f32", "bf16", (128, 128, 8)), (133, 4782, 1024, 8, 3, "f32", "f32", (128, 256, 2)),
+    (18, 14345, 800, 32, 4, "f32", "f32", (128, 128, 2)), (19, 3045, 2048, 40, 3, "f32", "bf16", (128, 128, 8)), (135, 5466, 1184, 8, 3, "f32", "f32", (128, 256, 2)),
     (26, 4453, 1952, 20, 4, "f32", "bf16", (128, 256, 8)), (25, 6481, 928, 60, 3, "f32", "f32", (64, 128, 4))])
 def test_gate_up_whose_products_meet(gpu, M, N, K, r, bits, fdt, hdt, cut):
     """The up product's workgroups multiply their slices by the gate's silu: sampled rows of the matrices, the last ones among them,
