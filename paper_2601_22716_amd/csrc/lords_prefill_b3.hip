@@ -1,10 +1,9 @@
-// The large-M kernel for 3-bit codes (the kernel template lives in lords_prefill_kernel.h; one translation unit per code
-// width keeps the build parallel).
+// The large-M kernel for 3-bit codes, one matrix (the kernel template lives in lords_prefill_kernel.h; a translation unit for
+// each code width, and one for several matrices, keep the build parallel).
 #include "lords_prefill_kernel.h"
 
 namespace lords {
 
 hipError_t launch_prefill_3bit(const PrefillArgsT<1> &a, const PfShape &d, dim3 grid, hipStream_t st) { return launch_pf_bits<3, false>(a, d, grid, st); }
-hipError_t launch_prefill_3bit(const PrefillArgsT<kMaxBatch> &a, const PfShape &d, dim3 grid, hipStream_t st) { return launch_pf_bits<3, true>(a, d, grid, st); }
 
 }  // namespace lords
